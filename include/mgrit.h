@@ -441,9 +441,10 @@ int mgrit_measure_event_bracket(double* us, void* stream);
 /* Test hook: route GEMMs (first flag) / attention (second flag) to the generic kernels. */
 void mgrit_debug_force_simple_kernels(int gemm, int attn);
 
-/* Tuning hook: tile configuration of the MFMA grouped GEMM (0 = chosen by shape, the default;
- * 1 = 256x256x64 and 3 = 256x192x64, one block per CU; 4 = 128x128x64 and 2 = 256x128x32, two
- * blocks per CU).  A configuration that does not fit a shape falls back to configuration 2. */
+/* Tuning hook: tile configuration of the MFMA grouped GEMM (0 = chosen by shape, the default; k-tiles
+ * of 64: 1 = 256x256 and 3 = 256x192, one block per CU; 4 = 128x128, two blocks per CU; 6 = 128x128, four
+ * stages, one block per CU; 8 and 9 = 64x64 with four and two stages, two and four blocks per CU).
+ * 3 falls back to 4 where the shape is no multiple of it. */
 void mgrit_debug_gemm_tile_config(int cfg);
 
 /* Tuning hook: which attention kernels use 256-row blocks.  Bits 0-2: forward, dQ pass, dK/dV

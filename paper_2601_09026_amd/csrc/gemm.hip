@@ -173,7 +173,7 @@ constexpr int ce_gcd(int a, int b) { return b == 0 ? a : ce_gcd(b, a % b); }
 // Whole-tile epilogue of one wavefront of the MFMA kernel.  All operand pointers are
 // restrict-qualified parameters of this one function, so that the compiler may hoist the
 // loads of later rows above the stores of earlier ones (outputs never alias inputs).
-template <int EPI, typename TO, int TM, int TN, bool STAGED>
+template <int EPI, typename TO, int TM, int TN, bool STAGED, bool RAGGED>
 __device__ __forceinline__ void tile_epilogue(
     f32x16 (&acc)[TM][TN], unsigned char* ep, const float* __restrict__ bias, TO* __restrict__ out_op,
     float* __restrict__ out_f32, TO* __restrict__ z_out, const TO* __restrict__ z_in, TO* __restrict__ g_out,
@@ -202,7 +202,9 @@ __device__ __forceinline__ void tile_epilogue(
 #pragma unroll
       for (int h = 0; h < CW / 4; ++h) {
         const f32x4 z = {0.f, 0.f, 0.f, 0.f};
-        bv[p][h] = bias ? *reinterpret_cast<const f32x4*>(bias + ncol0 + CW * ((p * 64 + lane) % CI) + 4 * h) : z;
+        int n = ncol0 + CW * ((p * 64 + lane) % CI) + 4 * h;
+        if (RAGGED) n = n < N ? n : 0;
+        bv[p][h] = bias ? *reinterpret_cast<const f32x4*>(bias + n) : z;
       }
     // The bias vectors have landed before the first item uses them; saying so once, outside the
     // row guards below, keeps the per-item waits on them from also waiting for every earlier
@@ -228,14 +230,16 @@ __device__ __forceinline__ void tile_epilogue(
         const unsigned char* src = ep + row * EP_LD + ci * CW * 4;
         const f32x4 v0 = *reinterpret_cast<const f32x4*>(src) + bv[it % NB][0];
         const int m = mrow0 + 32 * i + row;
-        const long idx = (long)m * N + ncol0 + CW * ci;
+        const int n = ncol0 + CW * ci;
+        const long idx = (long)m * N + n;
+        const bool inside = !GUARD || (m < M && (!RAGGED || n < N));   // N is a multiple of 8
         if constexpr (WIDE) {
           const f32x4 v1 = *reinterpret_cast<const f32x4*>(src + 16) + bv[it % NB][1];
-          if (!GUARD || m < M)
+          if (inside)
             apply8<EPI, OPT>(reinterpret_cast<bf16*>(out_op), reinterpret_cast<bf16*>(z_out),
                              reinterpret_cast<const bf16*>(z_in), reinterpret_cast<bf16*>(g_out), idx, v0, v1);
         } else {
-          if (!GUARD || m < M)
+          if (inside)
             apply4<EPI, TO, OPT>(out_op, out_f32, z_out, z_in, g_out, base, X, ybar, RHS, OUT, hstep, sgn, idx, v0);
         }
       }
@@ -252,7 +256,7 @@ __device__ __forceinline__ void tile_epilogue(
 #pragma unroll
       for (int i = 0; i < TM; ++i) rows32(guard_tag, opt_tag, i);
     };
-    if (mrow0 + 32 * TM <= M) {                            // wave-uniform
+    if (mrow0 + 32 * TM <= M && (!RAGGED || ncol0 + WTN <= N)) {   // wave-uniform
       if (opt == 0) all_rows(std::false_type{}, std::integral_constant<int, 0>{});
       else if (opt == 1) all_rows(std::false_type{}, std::integral_constant<int, NOPT >= 2 ? 1 : 0>{});
       else if (opt == 2) all_rows(std::false_type{}, std::integral_constant<int, NOPT == 4 ? 2 : 0>{});
@@ -291,36 +295,41 @@ __device__ __forceinline__ void tile_epilogue(
 // ---------------------------------------------------------------------------
 // MFMA kernel.  WM x WN wavefronts, each owning a (BM/WM) x (BN/WN) tile of the output.
 //  * Operands go from global memory straight into LDS (global_load_lds, 16 bytes per lane,
-//    no register staging) through a ring of STAGES k-tiles of depth BK (32 or 64).
-//  * An LDS row holds the BK bf16 of one matrix row (64 or 128 bytes) unpadded; its 16-byte
-//    chunks are XOR-swizzled by the row number so that the 16-byte fragment reads of 32
-//    consecutive rows are bank-conflict free.  A load instruction of a wavefront fills 1 KB
-//    = 8 (or 16) consecutive rows; the lane that will land at position p of row r fetches
-//    logical chunk p ^ f(r) of that row.
-//  * MFMA fragments are double-buffered in registers (LDS reads of k-step s+1 overlap the
-//    MFMAs of s) and the next tile's load instructions are issued one at a time between
-//    MFMA groups, so their issue time overlaps matrix work.
+//    no register staging) through a ring of STAGES k-tiles of depth BK.
+//  * An LDS row holds the BK bf16 of one matrix row unpadded; its 16-byte chunks are XOR-swizzled by
+//    the row number so that the 16-byte fragment reads of 32 consecutive rows are bank-conflict free.
+//    A load instruction of a wavefront fills 1 KB = 8 (or 16) consecutive rows; the lane that will
+//    land at position p of row r fetches logical chunk p ^ f(r) of that row.
+//  * MFMA fragments are double-buffered in registers: the LDS reads of k-step s+1 are spread between
+//    the MFMAs of s, across the boundary of two k-tiles as well, and so are the loads that refill a stage.
+//  * The barriers are bare: loads stay in flight across them, and each tile is waited for by count.
+//    (__syncthreads() drains every outstanding load first, so that a deeper ring gains nothing: with it a
+//    4096 x 768 product of reduction 3072 took 49 us with two, three or four stages of 128x128x64 tiles;
+//    with counted waits 45, 41 and 38 us.)
 //  * The weight fragment is the first MFMA operand: a lane then holds 4 consecutive output
 //    columns per register quad.
-//  * Epilogue, STAGED: each wavefront transposes 32 rows at a time through a private padded
-//    LDS region and walks them row-major (32 lanes per row), so every global access of the
-//    epilogue covers whole contiguous rows.  Otherwise: straight from the MFMA layout.
+//  * Epilogue: each wavefront transposes 32 rows at a time through a private padded LDS region and
+//    walks them row-major, so every global access of the epilogue covers whole contiguous rows.
+//  * RAGGED: N no multiple of BN or K no multiple of BK (both multiples of 8): weight rows are clamped,
+//    columns guarded, and the chunks of the last k-tile that lie past K come from a zero chunk.
+// What bounds it: large launches the matrix cores at the clock the power limit leaves (the k loop of the
+// 256x256 tile runs at 1220 TFLOP/s on random operands, 1340-1500 without its loads) and then the epilogue,
+// which moves 4 to 16 bytes per output element with the matrix cores idle; launches of up to one tile per
+// CU the latency of first touches past the L2, which the deep ring covers.
 // ---------------------------------------------------------------------------
 typedef __attribute__((address_space(1))) const void* gas_ptr;
 typedef __attribute__((address_space(3))) void* las_ptr;
 
 template <int N> __device__ __forceinline__ void wait_vmcnt() {
   static_assert(N >= 0 && N < 64, "vmcnt range");
-  if constexpr (N == 0) asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
-  else if constexpr (N == 4) asm volatile("s_waitcnt vmcnt(4)" ::: "memory");
-  else if constexpr (N == 6) asm volatile("s_waitcnt vmcnt(6)" ::: "memory");
-  else if constexpr (N == 8) asm volatile("s_waitcnt vmcnt(8)" ::: "memory");
-  else if constexpr (N == 12) asm volatile("s_waitcnt vmcnt(12)" ::: "memory");
-  else if constexpr (N == 16) asm volatile("s_waitcnt vmcnt(16)" ::: "memory");
-  else if constexpr (N == 18) asm volatile("s_waitcnt vmcnt(18)" ::: "memory");
-  else if constexpr (N == 24) asm volatile("s_waitcnt vmcnt(24)" ::: "memory");
-  else if constexpr (N == 32) asm volatile("s_waitcnt vmcnt(32)" ::: "memory");
-  else asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+  asm volatile("s_waitcnt vmcnt(%0)" ::"n"(N) : "memory");
+}
+// Block barrier that waits for nothing else.  __syncthreads() would first wait for every outstanding
+// vector-memory operation of the wavefront, i.e. drain the whole ring of k-tiles in flight.
+__device__ __forceinline__ void bare_barrier() {
+  __builtin_amdgcn_sched_barrier(0);
+  asm volatile("s_barrier" ::: "memory");
+  __builtin_amdgcn_sched_barrier(0);
 }
 
 // LDS has 64 four-byte banks (256 bytes per clock); a 16-byte read is served 16 lanes at a
@@ -331,8 +340,11 @@ template <int BK> __device__ __forceinline__ int swz(int row) {
   return BK == 64 ? ((row >> 1) & 7) : ((row >> 2) & 3);
 }
 
-template <int BM, int BN, int BK, int STAGES, int OCC, bool STAGED, int EPI, typename TO, int WM = 2, int WN = 2>
-__global__ void __launch_bounds__(64 * WM * WN, OCC)
+// Source of the chunks of a last k-tile that lie past K.
+__device__ const __attribute__((aligned(16))) unsigned char g_zero_chunk[16] = {};
+
+template <int BM, int BN, int BK, int STAGES, int OCC, bool RAGGED, int EPI, typename TO, int WM, int WN>
+__global__ void __launch_bounds__(64 * WM * WN, OCC * WM * WN / 4)
 gemm_mfma_kernel(const GemmArgs a, int tiles_m, int tiles_n, int total_tiles, int per_xcd, int pm, int pn) {
   constexpr int NW = WM * WN;                            // wavefronts per block
   constexpr int WTM = BM / WM, WTN = BN / WN;
@@ -345,8 +357,6 @@ gemm_mfma_kernel(const GemmArgs a, int tiles_m, int tiles_n, int total_tiles, in
   constexpr int A_LD = BM / RPL / NW, B_LD = BN / RPL / NW; // load instructions per wave per k-tile
   static_assert(A_LD >= 1 && B_LD >= 1 && A_LD * RPL * NW == BM && B_LD * RPL * NW == BN, "tile/wave split");
   constexpr int PER_TILE = A_LD + B_LD;
-  constexpr int SLOTS = KS * TM;                         // MFMA groups per k-tile
-  constexpr int PER_SLOT = (PER_TILE + SLOTS - 1) / SLOTS;
   extern __shared__ __attribute__((aligned(1024))) unsigned char smem2[];
 
   // XCD-aware tile order: workgroup ids are dealt round-robin to the 8 XCDs, so give each
@@ -376,7 +386,7 @@ gemm_mfma_kernel(const GemmArgs a, int tiles_m, int tiles_n, int total_tiles, in
   const bf16* A = reinterpret_cast<const bf16*>(a.A) + a.a_slots.of(g) * a.a_slot_stride;
   const char* pblock = a.B.at(g);
   const bf16* B = reinterpret_cast<const bf16*>(pblock + a.b_off);
-  const int K = a.K, M = a.M;
+  const int K = a.K, M = a.M, N = a.N;
 
   const int tid = threadIdx.x;
   const int wave = tid >> 6, lane = tid & 63;
@@ -396,17 +406,22 @@ gemm_mfma_kernel(const GemmArgs a, int tiles_m, int tiles_n, int total_tiles, in
 #pragma unroll
   for (int j = 0; j < B_LD; ++j) {
     const int row = (wave * B_LD + j) * RPL + lrow;
-    boff[j] = (unsigned)(n0 + row) * (unsigned)K + (lpos ^ swz<BK>(row)) * 8;
+    int gn = n0 + row;
+    if (RAGGED) gn = gn < N ? gn : N - 1;
+    boff[j] = (unsigned)gn * (unsigned)K + (lpos ^ swz<BK>(row)) * 8;
   }
 
   auto issue_one = [&](int stage, int k0, int idx) {
     unsigned char* sa = smem2 + stage * STAGE;
-    if (idx < A_LD)
-      __builtin_amdgcn_global_load_lds((gas_ptr)(A + aoff[idx] + k0), (las_ptr)(sa + (wave * A_LD + idx) * 1024),
-                                       16, 0, 0);
-    else
-      __builtin_amdgcn_global_load_lds((gas_ptr)(B + boff[idx - A_LD] + k0),
-                                       (las_ptr)(sa + A_BYTES + (wave * B_LD + idx - A_LD) * 1024), 16, 0, 0);
+    const bool is_a = idx < A_LD;
+    const bf16* src = is_a ? A + aoff[idx < A_LD ? idx : 0] + k0 : B + boff[idx < A_LD ? 0 : idx - A_LD] + k0;
+    unsigned char* dst = is_a ? sa + (wave * A_LD + idx) * 1024 : sa + A_BYTES + (wave * B_LD + idx - A_LD) * 1024;
+    if constexpr (RAGGED) {
+      // the last k-tile reaches past K: its 16-byte chunks from K on are zeros (K is a multiple of 8)
+      const int row = is_a ? (wave * A_LD + idx) * RPL + lrow : (wave * B_LD + idx - A_LD) * RPL + lrow;
+      if (k0 + (lpos ^ swz<BK>(row)) * 8 >= K) src = reinterpret_cast<const bf16*>(g_zero_chunk);
+    }
+    __builtin_amdgcn_global_load_lds((gas_ptr)src, (las_ptr)dst, 16, 0, 0);
   };
   auto issue = [&](int stage, int k0) {
 #pragma unroll
@@ -426,57 +441,79 @@ gemm_mfma_kernel(const GemmArgs a, int tiles_m, int tiles_n, int total_tiles, in
 #pragma unroll
       for (int r = 0; r < 16; ++r) acc[i][j][r] = 0.f;
 
-  const int KT = K / BK;
+  // Ring: tile kt lives in stage kt % STAGES.  The fragments of the first k-step of tile kt+1 are read
+  // during the last k-step of tile kt, so that step begins by making sure tile kt+1 has landed (own loads:
+  // vmcnt, the others': barrier); from that barrier on nobody reads tile kt any more (its last fragments
+  // are in registers), and its stage is refilled with tile kt+STAGES.
+  const int KT = RAGGED ? (K + BK - 1) / BK : K / BK;
 #pragma unroll
-  for (int s = 0; s < STAGES - 1; ++s)
+  for (int s = 0; s < STAGES; ++s)
     if (s < KT) issue(s, s * BK);
-  if (KT > STAGES - 2) wait_vmcnt<(STAGES - 2) * PER_TILE>(); else wait_vmcnt<0>();
-  __syncthreads();
-
+  auto wait_tile = [&](int kt, int issued) {               // own loads of tile kt have landed (issued: tiles so far)
+    const int behind = issued - 1 - kt;
+    if constexpr (STAGES >= 5) if (behind >= 4) { wait_vmcnt<4 * PER_TILE>(); return; }
+    if constexpr (STAGES >= 4) if (behind >= 3) { wait_vmcnt<3 * PER_TILE>(); return; }
+    if constexpr (STAGES >= 3) if (behind >= 2) { wait_vmcnt<2 * PER_TILE>(); return; }
+    if (behind >= 1) { wait_vmcnt<PER_TILE>(); return; }
+    wait_vmcnt<0>();
+  };
+  bf16x8 fa[2][TM], fb[2][TN];
+  wait_tile(0, STAGES < KT ? STAGES : KT);
+  bare_barrier();
+#pragma unroll
+  for (int j = 0; j < TN; ++j) fb[0][j] = *reinterpret_cast<const bf16x8*>(smem2 + A_BYTES + (wn0 + j * 32) * RB + foff[0]);
+#pragma unroll
+  for (int i = 0; i < TM; ++i) fa[0][i] = *reinterpret_cast<const bf16x8*>(smem2 + (wm0 + i * 32) * RB + foff[0]);
+  int cur = 0;
   for (int kt = 0; kt < KT; ++kt) {
-    const int cur = kt % STAGES;
-    const bool pf = kt + STAGES - 1 < KT;
-    const int pstage = (kt + STAGES - 1) % STAGES, pk0 = (kt + STAGES - 1) * BK;
-    const unsigned char* sA = smem2 + cur * STAGE + wm0 * RB;
-    const unsigned char* sB = smem2 + cur * STAGE + A_BYTES + wn0 * RB;
-    bf16x8 fa[2][TM], fb[2][TN];
-#pragma unroll
-    for (int i = 0; i < TM; ++i) fa[0][i] = *reinterpret_cast<const bf16x8*>(sA + i * 32 * RB + foff[0]);
-#pragma unroll
-    for (int j = 0; j < TN; ++j) fb[0][j] = *reinterpret_cast<const bf16x8*>(sB + j * 32 * RB + foff[0]);
+    const int nxt = cur + 1 == STAGES ? 0 : cur + 1;
+    const bool pf = kt + STAGES < KT;
+    const int pk0 = (kt + STAGES) * BK;
 #pragma unroll
     for (int ks = 0; ks < KS; ++ks) {
       const int cb = ks & 1, nb = cb ^ 1;
-      if (ks + 1 < KS) {
-#pragma unroll
-        for (int i = 0; i < TM; ++i)
-          fa[nb][i] = *reinterpret_cast<const bf16x8*>(sA + i * 32 * RB + foff[ks + 1 < KS ? ks + 1 : 0]);
-#pragma unroll
-        for (int j = 0; j < TN; ++j)
-          fb[nb][j] = *reinterpret_cast<const bf16x8*>(sB + j * 32 * RB + foff[ks + 1 < KS ? ks + 1 : 0]);
+      const bool last = ks == KS - 1;
+      if (last) {
+        asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
+        wait_tile(kt + 1, kt + STAGES < KT ? kt + STAGES : KT);
+        bare_barrier();
       }
+      const int rst = last ? nxt : cur, rks = last ? 0 : ks + 1;
+      const unsigned char* sA = smem2 + rst * STAGE + wm0 * RB;
+      const unsigned char* sB = smem2 + rst * STAGE + A_BYTES + wn0 * RB;
+      // The fragment reads of the next k-step and the loads of the refilled stage are spread between
+      // the matrix instructions, fenced so that the scheduler keeps them apart: a wavefront that has to
+      // wait for its turn at the LDS or the load unit has matrix work queued meanwhile.
+      constexpr int NM = TM * TN, RD = TM + TN;
 #pragma unroll
-      for (int i = 0; i < TM; ++i) {
+      for (int q = 0; q < NM; ++q) {
+        const int i = q / TN, j = q % TN;
+        acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(fb[cb][j], fa[cb][i], acc[i][j], 0, 0, 0);
+        const int r0 = (q * RD * 4 / 3 + NM - 1) / NM, r1 = ((q + 1) * RD * 4 / 3 + NM - 1) / NM;
 #pragma unroll
-        for (int j = 0; j < TN; ++j)
-          acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(fb[cb][j], fa[cb][i], acc[i][j], 0, 0, 0);
+        for (int u = 0; u < RD; ++u)
+          if (u >= r0 && (u < r1 || q == NM - 1)) {
+            if (u < TN) fb[nb][u] = *reinterpret_cast<const bf16x8*>(sB + u * 32 * RB + foff[rks]);
+            else fa[nb][u - TN] = *reinterpret_cast<const bf16x8*>(sA + (u - TN) * 32 * RB + foff[rks]);
+          }
+        if (last) {
+          const int l0 = (q * PER_TILE + NM - 1) / NM, l1 = ((q + 1) * PER_TILE + NM - 1) / NM;
 #pragma unroll
-        for (int u = 0; u < PER_SLOT; ++u) {
-          const int idx = (ks * TM + i) * PER_SLOT + u;
-          if (idx < PER_TILE && pf) issue_one(pstage, pk0, idx);
+          for (int u = 0; u < PER_TILE; ++u)
+            if (u >= l0 && u < l1 && pf) issue_one(cur, pk0, u);
         }
+        __builtin_amdgcn_sched_barrier(0);
       }
     }
-    // tile kt+1 must have landed (later tiles may still be in flight), and every wave must be
-    // done reading this stage before it is refilled
-    if (kt + STAGES - 1 < KT) wait_vmcnt<(STAGES - 2) * PER_TILE>(); else wait_vmcnt<0>();
-    __syncthreads();
+    cur = nxt;
   }
+  asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");       // (the reads ahead of a tile that does not exist)
+  bare_barrier();
 
   // the staging regions reuse the (now idle) k-tile ring; the launcher sizes LDS for both
   constexpr int EP_BYTES = (32 * (WTN * 4 + 16) + 1023) / 1024 * 1024;
   const EpiPtrs P = resolve_epi<TO>(a, g, EPI);
-  tile_epilogue<EPI, TO, TM, TN, STAGED>(acc, smem2 + wave * EP_BYTES, P.bias, static_cast<TO*>(P.out),
+  tile_epilogue<EPI, TO, TM, TN, true, RAGGED>(acc, smem2 + wave * EP_BYTES, P.bias, static_cast<TO*>(P.out),
                                          static_cast<float*>(P.out), static_cast<TO*>(P.aux),
                                          static_cast<const TO*>(P.aux), static_cast<TO*>(P.aux2), P.base, P.X,
                                          static_cast<const float*>(P.aux), P.RHS, P.OUT, a.hstep, a.rhs_sign, a.N,
@@ -528,7 +565,7 @@ gemm_f32_mfma_kernel(const GemmArgs a, int tiles_m, int tiles_n) {
                                                       acc[0][0], 0, 0, 0);
   }
   const EpiPtrs P = resolve_epi<float>(a, g, EPI);
-  tile_epilogue<EPI, float, 1, 1, false>(acc, nullptr, P.bias, static_cast<float*>(P.out), static_cast<float*>(P.out),
+  tile_epilogue<EPI, float, 1, 1, false, false>(acc, nullptr, P.bias, static_cast<float*>(P.out), static_cast<float*>(P.out),
                                          static_cast<float*>(P.aux), static_cast<const float*>(P.aux),
                                          static_cast<float*>(P.aux2), P.base, P.X,
                                          static_cast<const float*>(P.aux), P.RHS, P.OUT, a.hstep, a.rhs_sign, a.N, M,
@@ -608,13 +645,13 @@ static int compute_units() {
   return n;
 }
 
-template <int BM, int BN, int BK, int STAGES, int OCC, bool STAGED, int EPI, int WM = 2, int WN = 2>
+template <int BM, int BN, int BK, int STAGES, int OCC, bool RAGGED, int EPI, int WM, int WN>
 static hipError_t launch_mfma(const GemmArgs& a, hipStream_t st) {
-  const int tiles_m = (a.M + BM - 1) / BM, tiles_n = a.N / BN;
+  const int tiles_m = (a.M + BM - 1) / BM, tiles_n = (a.N + BN - 1) / BN;
   const int total = tiles_m * tiles_n * a.n_groups;
   const int per_xcd = (total + 7) / 8;
   const size_t ring = (size_t)STAGES * (BM + BN) * BK * 2;
-  const size_t staging = STAGED ? (size_t)WM * WN * ((32 * (BN / WN * 4 + 16) + 1023) / 1024 * 1024) : 0;
+  const size_t staging = (size_t)WM * WN * ((32 * (BN / WN * 4 + 16) + 1023) / 1024 * 1024);
   const size_t smem = ring > staging ? ring : staging;
   // patch shape of the tile order: 4 tiles wide, half of what one XCD runs at a time (two patches next
   // to each other are resident together; measured against whole-resident-set patches: the bias+GELU
@@ -625,7 +662,7 @@ static hipError_t launch_mfma(const GemmArgs& a, hipStream_t st) {
     pn = 4;
     pm = resident / 8;
   }
-  auto kern = gemm_mfma_kernel<BM, BN, BK, STAGES, OCC, STAGED, EPI, bf16, WM, WN>;
+  auto kern = gemm_mfma_kernel<BM, BN, BK, STAGES, OCC, RAGGED, EPI, bf16, WM, WN>;
   static bool attr_done = false;
   if (!attr_done) {
     hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(kern),
@@ -669,50 +706,69 @@ static double gemm_bytes(const GemmArgs& a, double esz) {
   return b;
 }
 
-// Tile configurations of the MFMA kernel (BK = 64, two stages, unless noted):
-//  1: 256x256, 8 wavefronts 2x4 (128x64 each, two per SIMD), one block per CU;
-//  3: 256x192, 8 wavefronts 4x2 (64x96 each), one block per CU;
-//  4: 128x128, 4 wavefronts (64x64 each), two blocks per CU;
-//  2: 256x128x32, three stages, 4 wavefronts (128x64 each), two blocks per CU: any N % 128 == 0.
-// A launch runs in rounds of (CUs x blocks per CU) tiles.  Measured on MI355X at 768..3072 wide
-// operands, the time of a round hardly depends on how full it is, and relative to a round of
-// 256x256 tiles a round of 256x192 tiles takes 0.9 and a (double) round of 128x128 tiles 0.62:
-// pick the configuration with the cheapest sum of rounds.
-static int choose_tile_config(int n_groups, int M, int N, double* cost_out = nullptr) {
-  struct Cand { int cfg, bm, bn, occ; double round_cost; };
-  static const Cand cands[] = {{1, 256, 256, 1, 1.0}, {3, 256, 192, 1, 0.9}, {4, 128, 128, 2, 0.62}};
+// Tile configurations of the MFMA kernel (k-tiles of 64) and what a round of each takes on MI355X, in
+// microseconds: fixed + per_ktile * (k-tiles).  A launch runs in rounds of (CUs x resident blocks) tiles
+// whose time hardly depends on how full the round is; measured with launches of 9 to 3840 tiles and
+// reductions of 384 to 4096 (model within 10 % of the measured time for the better configurations):
+//  1: 256x256, 8 wavefronts of 128x64, two stages: most reuse, what large launches run on;
+//  3: 256x192, 8 wavefronts of 64x96, two stages: where 256 columns leave a round much emptier;
+//  4: 128x128, two stages, two blocks per CU (one block's epilogue under the other's k loop);
+//  6: 128x128, four stages, one block per CU: launches of up to one tile per CU, which wait for memory
+//     latency and not for bandwidth (4096 x 768, reduction 3072: 49 us with two stages, 38 with four);
+//  8: 64x64, four stages, two blocks per CU, and 9: two stages, four blocks per CU: few rows or columns
+//     (768 x 768, reduction 4096: 43 us as 128x128 tiles, 24 as 64x64).
+struct TileCfg { int id, bm, bn, per_cu; double fixed, per_ktile; };
+static const TileCfg kTileCfgs[] = {{1, 256, 256, 1, 7.0, 1.60}, {3, 256, 192, 1, 5.5, 1.33}, {4, 128, 128, 2, 2.7, 1.07},
+                                    {6, 128, 128, 1, 2.5, 0.55}, {8, 64, 64, 2, 2.5, 0.375}, {9, 64, 64, 4, 2.5, 0.75}};
+static int choose_tile_config(int n_groups, int M, int N, int K, double* cost_out = nullptr) {
   const long cus = compute_units();
-  int best = 2;
+  const int ktiles = (K + 63) / 64;
+  int best = 4;
   double best_cost = 1e30;
-  for (const Cand& c : cands) {
-    if (N % c.bn != 0) continue;
-    const long tiles = (long)((M + c.bm - 1) / c.bm) * (N / c.bn) * n_groups;
-    const long rounds = (tiles + cus * c.occ - 1) / (cus * c.occ);
-    const double cost = rounds * c.round_cost;
-    if (cost < best_cost) { best_cost = cost; best = c.cfg; }
-  }
-  if (best == 2) {                                       // 256x128x32, two blocks per CU
-    const long tiles = (long)((M + 255) / 256) * ((N + 127) / 128) * n_groups;
-    best_cost = (double)((tiles + cus * 2 - 1) / (cus * 2));
+  for (const TileCfg& c : kTileCfgs) {
+    if (c.id == 3 && (N % 192 != 0 || K % 64 != 0)) continue;            // no ragged form
+    const long tiles = (long)((M + c.bm - 1) / c.bm) * ((N + c.bn - 1) / c.bn) * n_groups;
+    const long rounds = (tiles + cus * c.per_cu - 1) / (cus * c.per_cu);
+    const double cost = rounds * (c.fixed + c.per_ktile * ktiles);
+    if (cost < best_cost) { best_cost = cost; best = c.id; }
   }
   if (cost_out) *cost_out = best_cost;
   return best;
 }
 
-// Modelled time of one grouped launch, in rounds of 256x256 tiles per 64 of reduction length (the
-// driver sizes its launch chunks with it).
+// Modelled time of one grouped launch (the driver sizes its launch chunks with it).
 double gemm_model_cost(int n_groups, int M, int N, int K) {
   double c = 0.0;
-  choose_tile_config(n_groups, M, N, &c);
-  return c * K / 64.0;
+  choose_tile_config(n_groups, M, N, K, &c);
+  return c;
+}
+
+// RAGGED: N or K is no multiple of the tile (columns are clamped and guarded, the last k-tile's chunks
+// past K read as zeros).
+template <int EPI, bool RAGGED>
+static hipError_t launch_cfg(int cfg, const GemmArgs& a, hipStream_t st) {
+  switch (cfg) {
+    case 1: return launch_mfma<256, 256, 64, 2, 1, RAGGED, EPI, 2, 4>(a, st);
+    case 3:
+      if constexpr (!RAGGED) return launch_mfma<256, 192, 64, 2, 1, false, EPI, 4, 2>(a, st);
+      break;
+    case 6: return launch_mfma<128, 128, 64, 4, 1, RAGGED, EPI, 4, 2>(a, st);
+    case 8: return launch_mfma<64, 64, 64, 4, 2, RAGGED, EPI, 2, 2>(a, st);
+    case 9: return launch_mfma<64, 64, 64, 2, 4, RAGGED, EPI, 2, 2>(a, st);
+    default: break;
+  }
+  // two blocks per CU; long reductions: 8 wavefronts of 32x64 (four per SIMD) hide the k-loop's latencies
+  // better than 4 of 64x64; short ones are all epilogue, where 4 do better
+  if (RAGGED || a.K >= 512) return launch_mfma<128, 128, 64, 2, 2, RAGGED, EPI, 4, 2>(a, st);
+  return launch_mfma<128, 128, 64, 2, 2, false, EPI, 2, 2>(a, st);
 }
 
 template <int EPI>
 static hipError_t launch_epi(const GemmArgs& a, bool is_bf16, hipStream_t st) {
   if (a.n_groups <= 0 || a.M <= 0) return hipSuccess;
   const double flops = 2.0 * a.n_groups * a.M * (double)a.N * a.K;
-  // the MFMA kernel needs whole 64-deep k-tiles and 128-wide column tiles, and 32-bit element offsets
-  const bool mfma_ok = is_bf16 && !g_force_simple && (a.K % 64 == 0) && (a.N % 128 == 0) &&
+  // the MFMA kernel moves 16-byte chunks and needs 32-bit element offsets
+  const bool mfma_ok = is_bf16 && !g_force_simple && (a.K % 8 == 0) && (a.N % 8 == 0) &&
                        (double)a.M * a.K < 4e9 && (double)a.N * a.K < 4e9;
   const int cls = mfma_ok ? (a.n_groups > 1 ? PC_GEMM_MFMA : PC_GEMM_MFMA_SINGLE) + EPI : PC_GEMM_SIMPLE;
   ProfScope ps(cls, flops, gemm_bytes<EPI>(a, is_bf16 ? 2 : 4), st);
@@ -722,20 +778,11 @@ static hipError_t launch_epi(const GemmArgs& a, bool is_bf16, hipStream_t st) {
     return launch_simple<float, EPI>(a, st);
   }
   if (!mfma_ok) return launch_simple<bf16, EPI>(a, st);
-  int cfg = g_tile_cfg;
-  if (cfg == 0) cfg = choose_tile_config(a.n_groups, a.M, a.N);
-  switch (cfg) {
-    case 1: if (a.N % 256 == 0) return launch_mfma<256, 256, 64, 2, 1, true, EPI, 2, 4>(a, st); break;
-    case 2: return launch_mfma<256, 128, 32, 3, 2, true, EPI>(a, st);
-    case 3: if (a.N % 192 == 0) return launch_mfma<256, 192, 64, 2, 1, true, EPI, 4, 2>(a, st); break;
-    case 4:
-      // long reductions: 8 wavefronts of 32x64 (four per SIMD with two blocks resident) hide the
-      // k-loop's latencies better than 4 of 64x64; short ones are all epilogue, where 4 do better
-      if (a.K >= 512) return launch_mfma<128, 128, 64, 2, 2, true, EPI, 4, 2>(a, st);
-      return launch_mfma<128, 128, 64, 2, 2, true, EPI>(a, st);
-    default: break;
-  }
-  return launch_mfma<256, 128, 32, 3, 2, true, EPI>(a, st);
+  const int cfg = g_tile_cfg ? g_tile_cfg : choose_tile_config(a.n_groups, a.M, a.N, a.K);
+  const int bn = cfg == 1 ? 256 : cfg == 3 ? 192 : cfg == 8 || cfg == 9 ? 64 : 128;
+  const bool ragged = a.N % bn != 0 || a.K % 64 != 0;
+  if (ragged && cfg == 3) return launch_cfg<EPI, true>(4, a, st);
+  return ragged ? launch_cfg<EPI, true>(cfg, a, st) : launch_cfg<EPI, false>(cfg, a, st);
 }
 
 hipError_t launch_gemm(const GemmArgs& a, int epi, bool is_bf16, hipStream_t st) {
