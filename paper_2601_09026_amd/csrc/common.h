@@ -119,6 +119,34 @@ template <typename V> __device__ __forceinline__ V ld_stream(const V* p) {
   return __builtin_nontemporal_load((gptr)p);
 }
 
+// ---------------------------------------------------------------------------
+// Transposed fragments from row-major LDS tiles (ds_read_b64_tr_b16, bf16): in each group of 16 lanes, lane l
+// addresses the 8 bytes at columns 4*(l%4).. of row l/4 of a 4 x 16 block and receives column l%16 of its 4 rows.
+// The reads are inline assembly because the compiler's wait-count pass puts a wait for every outstanding
+// global-to-LDS load before the builtin; their results are there after wait_lgkm() and pass through tr_value().
+// ---------------------------------------------------------------------------
+typedef __attribute__((__vector_size__(4 * sizeof(short)))) short s16x4;
+typedef __attribute__((__vector_size__(8 * sizeof(short)))) short s16x8;
+struct TrFrag { s16x4 lo, hi; };           // 4 + 4 consecutive reduction indices of this lane's column
+__device__ __forceinline__ unsigned lds_offset(const void* p) {
+  return (unsigned)(size_t)(__attribute__((address_space(3))) const void*)p;
+}
+template <int LO, int HI> __device__ __forceinline__ void tr_read(TrFrag& f, unsigned addr) {
+  static_assert(LO >= 0 && HI >= 0 && LO < 65536 && HI < 65536, "16-bit immediate offsets");
+  asm volatile("ds_read_b64_tr_b16 %0, %1 offset:%2" : "=v"(f.lo) : "v"(addr), "n"(LO));
+  asm volatile("ds_read_b64_tr_b16 %0, %1 offset:%2" : "=v"(f.hi) : "v"(addr), "n"(HI));
+}
+__device__ __forceinline__ void wait_lgkm() {
+  asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
+  __builtin_amdgcn_sched_barrier(0);
+}
+// the fragment as an MFMA operand; ties the values to this point (after the wait) for the compiler
+__device__ __forceinline__ bf16x8 tr_value(TrFrag& f) {
+  asm volatile("" : "+v"(f.lo), "+v"(f.hi));
+  const s16x8 v = {f.lo[0], f.lo[1], f.lo[2], f.lo[3], f.hi[0], f.hi[1], f.hi[2], f.hi[3]};
+  return __builtin_bit_cast(bf16x8, v);
+}
+
 // load / store 4 consecutive elements as floats
 template <typename T> __device__ __forceinline__ f32x4 load4(const T* p);
 template <> __device__ __forceinline__ f32x4 load4<float>(const float* p) {
@@ -143,15 +171,15 @@ template <> __device__ __forceinline__ void store4<bf16>(bf16* p, f32x4 v) {
 // ---------------------------------------------------------------------------
 enum Epi : int {
   EPI_STORE = 0,        // out = acc + bias                               (packed, operand type)
-  EPI_GELU = 1,         // out = gelu(acc + bias); optionally z = acc + bias kept for the adjoint
+  EPI_GELU = 1,         // out = gelu(acc + bias)
   EPI_RESID_INNER = 2,  // ybar[m,n] (fp32, packed) = [base +] acc + bias      (sum of attention sublayers)
   EPI_RESID_OUTER = 3,  // OUT[m,n] = X + h*(ybar + acc + bias) + rhs          (the Euler update)
   EPI_DGELU = 4,        // out = acc * g[m,n], g = the cached gelu'(z)          (adjoint of the activation)
   EPI_STORE_F32 = 5,    // out (fp32, packed or inside the group's output block) = hstep * (acc + bias)
-  EPI_GELU_PRIME = 6,   // out = gelu'(acc + bias) (operand type); optionally z = acc + bias kept as well:
-                        // the linearisation cache holds the derivative, evaluated once per layer
-  EPI_GELU_BOTH = 7     // out = gelu(acc + bias) and aux2 = gelu'(acc + bias); optionally z kept as well:
-                        // a forward step that also leaves its layer's entry of the linearisation cache
+  EPI_GELU_PRIME = 6,   // out = gelu'(acc + bias) (operand type): the linearisation cache holds the derivative,
+                        // evaluated once per layer
+  EPI_GELU_BOTH = 7     // out = gelu(acc + bias) and aux2 = gelu'(acc + bias): a forward step that also leaves its
+                        // layer's entry of the linearisation cache
 };
 
 struct GemmArgs {
@@ -165,8 +193,7 @@ struct GemmArgs {
   Params bias;
   // outputs / epilogue operands
   void* out; long out_slot_stride; Slots out_slots;      // packed output (operand type or fp32)
-  void* aux; long aux_slot_stride; Slots aux_slots;      // EPI_GELU, EPI_GELU_PRIME: z out (may be null); EPI_DGELU: g in;
-                                                         // EPI_RESID_OUTER: ybar (fp32 packed)
+  void* aux; long aux_slot_stride; Slots aux_slots;      // EPI_DGELU: g in; EPI_RESID_OUTER: ybar (fp32 packed)
   void* aux2; long aux2_slot_stride; Slots aux2_slots;   // EPI_GELU_BOTH: gelu'(z) out (operand type)
   Rows X;                      // EPI_RESID_OUTER: the step's input state
   const float* base; long base_slot_stride; Slots base_slots;   // EPI_RESID_INNER: optional packed fp32 addend
@@ -176,6 +203,19 @@ struct GemmArgs {
   float rhs_sign;              // EPI_RESID_OUTER with RHS: OUT = RHS + rhs_sign * (X + h*(..)); +1 the step, -1 the
                                // coarse right-hand side g' = R - Phi'(w) formed in the step that evaluates Phi'
   Params out_tab; long out_tab_off;    // EPI_STORE_F32: if set, group g writes at out_tab[g] + out_tab_off
+};
+
+// Parameter gradients of one linear map per group, y = u W^T + b, from token-major operands (launch_gemm_tn):
+//   dW[m,n] = scale * sum over K tokens of dY[t,m] U[t,n],   db[m] = scale * sum over tokens of dY[t,m]
+struct GemmTnArgs {
+  int n_groups;
+  int M, N, K;                 // out features, in features, tokens
+  const void* A; long a_slot_stride; Slots a_slots;      // dY, packed [slot, K, M] of operand type
+  const void* B; long b_slot_stride; Slots b_slots;      // U, packed [slot, K, N]
+  Params out;                  // the group's gradient block (fp32)
+  long w_off, b_off;           // byte offsets of dW and db in it
+  float scale;
+  float* partial;              // scratch of gemm_tn_partial_floats() (null if that is 0)
 };
 
 }  // namespace mg

@@ -24,7 +24,7 @@ namespace mg {
 struct EpiPtrs {
   const float* bias;          // [N] or null
   void* out;                  // packed output (operand type or fp32)
-  void* aux;                  // EPI_GELU: z out (optional); EPI_DGELU: z in; EPI_RESID_OUTER: ybar
+  void* aux;                  // EPI_DGELU: gelu'(z) in; EPI_RESID_OUTER: ybar
   void* aux2;                 // EPI_GELU_BOTH: gelu'(z) out
   const float* base;          // EPI_RESID_INNER: optional addend
   const float* X;             // EPI_RESID_OUTER
@@ -68,7 +68,7 @@ template <> __device__ __forceinline__ f32x4 eload4<bf16>(const bf16* p) {
 }
 
 // OPT: what is known at compile time about the optional operands of an epilogue: -1 nothing (tested
-// per call), else bit 0 = the first one is there (ybar / base / the pre-activation output), bit 1 =
+// per call), else bit 0 = the first one is there (ybar / base), bit 1 =
 // RHS is there.  With OPT >= 0 a run of items is straight-line code.
 template <int OPT> __device__ __forceinline__ bool has_opt(int bit, const void* p) {
   return OPT < 0 ? p != nullptr : ((OPT >> bit) & 1) != 0;
@@ -76,8 +76,7 @@ template <int OPT> __device__ __forceinline__ bool has_opt(int bit, const void* 
 
 template <int EPI, typename TO, int OPT = -1>
 __device__ __forceinline__ void apply4(TO* __restrict__ out_op, float* __restrict__ out_f32,
-                                       TO* __restrict__ z_out, const TO* __restrict__ z_in,
-                                       TO* __restrict__ g_out,
+                                       const TO* __restrict__ z_in, TO* __restrict__ g_out,
                                        const float* __restrict__ base, const float* __restrict__ X,
                                        const float* __restrict__ ybar, const float* __restrict__ RHS,
                                        float* __restrict__ OUT, float hstep, float sgn, long idx, f32x4 acc) {
@@ -86,16 +85,13 @@ __device__ __forceinline__ void apply4(TO* __restrict__ out_op, float* __restric
   } else if constexpr (EPI == EPI_STORE_F32) {
     estore4<float>(out_f32 + idx, hstep * acc);
   } else if constexpr (EPI == EPI_GELU) {
-    if (has_opt<OPT>(0, z_out)) estore4<TO>(z_out + idx, acc);
     f32x4 y = {gelu_t<TO>(acc[0]), gelu_t<TO>(acc[1]), gelu_t<TO>(acc[2]), gelu_t<TO>(acc[3])};
     estore4<TO>(out_op + idx, y);
   } else if constexpr (EPI == EPI_GELU_PRIME) {
-    if (has_opt<OPT>(0, z_out)) estore4<TO>(z_out + idx, acc);
     f32x4 y = {gelu_prime_t<TO>(acc[0]), gelu_prime_t<TO>(acc[1]), gelu_prime_t<TO>(acc[2]),
                gelu_prime_t<TO>(acc[3])};
     estore4<TO>(out_op + idx, y);
   } else if constexpr (EPI == EPI_GELU_BOTH) {
-    if (has_opt<OPT>(0, z_out)) estore4<TO>(z_out + idx, acc);
     f32x4 y = {gelu_t<TO>(acc[0]), gelu_t<TO>(acc[1]), gelu_t<TO>(acc[2]), gelu_t<TO>(acc[3])};
     estore4<TO>(out_op + idx, y);
     f32x4 dy = {gelu_prime_t<TO>(acc[0]), gelu_prime_t<TO>(acc[1]), gelu_prime_t<TO>(acc[2]),
@@ -125,24 +121,21 @@ __device__ __forceinline__ void store8(bf16* p, f32x4 a, f32x4 b) {
   bf16x8 r = {(bf16)a[0], (bf16)a[1], (bf16)a[2], (bf16)a[3], (bf16)b[0], (bf16)b[1], (bf16)b[2], (bf16)b[3]};
   st_stream(reinterpret_cast<bf16x8*>(p), r);
 }
-template <int EPI, int OPT = -1>
-__device__ __forceinline__ void apply8(bf16* __restrict__ out, bf16* __restrict__ z_out,
-                                       const bf16* __restrict__ z_in, bf16* __restrict__ g_out, long idx,
+template <int EPI>
+__device__ __forceinline__ void apply8(bf16* __restrict__ out, const bf16* __restrict__ z_in,
+                                       bf16* __restrict__ g_out, long idx,
                                        f32x4 a, f32x4 b) {
   if constexpr (EPI == EPI_STORE) {
     store8(out + idx, a, b);
   } else if constexpr (EPI == EPI_GELU) {
-    if (has_opt<OPT>(0, z_out)) store8(z_out + idx, a, b);
 #pragma unroll
     for (int r = 0; r < 4; ++r) { a[r] = gelu_fast(a[r]); b[r] = gelu_fast(b[r]); }
     store8(out + idx, a, b);
   } else if constexpr (EPI == EPI_GELU_PRIME) {
-    if (has_opt<OPT>(0, z_out)) store8(z_out + idx, a, b);
 #pragma unroll
     for (int r = 0; r < 4; ++r) { a[r] = gelu_prime_fast(a[r]); b[r] = gelu_prime_fast(b[r]); }
     store8(out + idx, a, b);
   } else if constexpr (EPI == EPI_GELU_BOTH) {
-    if (has_opt<OPT>(0, z_out)) store8(z_out + idx, a, b);
     f32x4 da, db;
 #pragma unroll
     for (int r = 0; r < 4; ++r) {
@@ -163,8 +156,8 @@ __device__ __forceinline__ void apply8(bf16* __restrict__ out, bf16* __restrict_
 template <int EPI, typename TO>
 __device__ __forceinline__ void epilogue4(const EpiPtrs& p, float hstep, float sgn, int N, int m, int n, f32x4 acc) {
   if (p.bias) acc += *reinterpret_cast<const f32x4*>(p.bias + n);
-  apply4<EPI, TO>(static_cast<TO*>(p.out), static_cast<float*>(p.out), static_cast<TO*>(p.aux),
-                  static_cast<const TO*>(p.aux), static_cast<TO*>(p.aux2), p.base, p.X,
+  apply4<EPI, TO>(static_cast<TO*>(p.out), static_cast<float*>(p.out), static_cast<const TO*>(p.aux),
+                  static_cast<TO*>(p.aux2), p.base, p.X,
                   static_cast<const float*>(p.aux), p.RHS, p.OUT, hstep, sgn, (long)m * N + n, acc);
 }
 
@@ -176,7 +169,7 @@ constexpr int ce_gcd(int a, int b) { return b == 0 ? a : ce_gcd(b, a % b); }
 template <int EPI, typename TO, int TM, int TN, bool STAGED, bool RAGGED>
 __device__ __forceinline__ void tile_epilogue(
     f32x16 (&acc)[TM][TN], unsigned char* ep, const float* __restrict__ bias, TO* __restrict__ out_op,
-    float* __restrict__ out_f32, TO* __restrict__ z_out, const TO* __restrict__ z_in, TO* __restrict__ g_out,
+    float* __restrict__ out_f32, const TO* __restrict__ z_in, TO* __restrict__ g_out,
     const float* __restrict__ base, const float* __restrict__ X, const float* __restrict__ ybar,
     const float* __restrict__ RHS, float* __restrict__ OUT, float hstep, float sgn, int N, int M, int mrow0,
     int ncol0, int lane) {
@@ -236,21 +229,18 @@ __device__ __forceinline__ void tile_epilogue(
         if constexpr (WIDE) {
           const f32x4 v1 = *reinterpret_cast<const f32x4*>(src + 16) + bv[it % NB][1];
           if (inside)
-            apply8<EPI, OPT>(reinterpret_cast<bf16*>(out_op), reinterpret_cast<bf16*>(z_out),
-                             reinterpret_cast<const bf16*>(z_in), reinterpret_cast<bf16*>(g_out), idx, v0, v1);
+            apply8<EPI>(reinterpret_cast<bf16*>(out_op), reinterpret_cast<const bf16*>(z_in),
+                        reinterpret_cast<bf16*>(g_out), idx, v0, v1);
         } else {
           if (inside)
-            apply4<EPI, TO, OPT>(out_op, out_f32, z_out, z_in, g_out, base, X, ybar, RHS, OUT, hstep, sgn, idx, v0);
+            apply4<EPI, TO, OPT>(out_op, out_f32, z_in, g_out, base, X, ybar, RHS, OUT, hstep, sgn, idx, v0);
         }
       }
     };
     // which optional operands this launch has (uniform over the launch): resolved once, so that
     // the items carry no tests of their own
-    constexpr int NOPT = EPI == EPI_RESID_OUTER ? 4
-                         : (EPI == EPI_RESID_INNER || EPI == EPI_GELU || EPI == EPI_GELU_PRIME ||
-                            EPI == EPI_GELU_BOTH) ? 2 : 1;
-    const void* first = EPI == EPI_RESID_OUTER ? static_cast<const void*>(ybar)
-                        : EPI == EPI_RESID_INNER ? static_cast<const void*>(base) : static_cast<const void*>(z_out);
+    constexpr int NOPT = EPI == EPI_RESID_OUTER ? 4 : EPI == EPI_RESID_INNER ? 2 : 1;
+    const void* first = EPI == EPI_RESID_OUTER ? static_cast<const void*>(ybar) : static_cast<const void*>(base);
     const int opt = NOPT == 1 ? 0 : ((first ? 1 : 0) | (NOPT == 4 && RHS ? 2 : 0));
     auto all_rows = [&](auto guard_tag, auto opt_tag) {
 #pragma unroll
@@ -284,7 +274,7 @@ __device__ __forceinline__ void tile_epilogue(
           for (int q = 0; q < 4; ++q) {
             const int n = ncol0 + j * 32 + q * 8 + lh * 4;
             f32x4 v = {acc[i][j][4 * q], acc[i][j][4 * q + 1], acc[i][j][4 * q + 2], acc[i][j][4 * q + 3]};
-            apply4<EPI, TO>(out_op, out_f32, z_out, z_in, g_out, base, X, ybar, RHS, OUT, hstep, sgn,
+            apply4<EPI, TO>(out_op, out_f32, z_in, g_out, base, X, ybar, RHS, OUT, hstep, sgn,
                             (long)m * N + n, v + bv[j][q]);
           }
       }
@@ -514,8 +504,8 @@ gemm_mfma_kernel(const GemmArgs a, int tiles_m, int tiles_n, int total_tiles, in
   constexpr int EP_BYTES = (32 * (WTN * 4 + 16) + 1023) / 1024 * 1024;
   const EpiPtrs P = resolve_epi<TO>(a, g, EPI);
   tile_epilogue<EPI, TO, TM, TN, true, RAGGED>(acc, smem2 + wave * EP_BYTES, P.bias, static_cast<TO*>(P.out),
-                                         static_cast<float*>(P.out), static_cast<TO*>(P.aux),
-                                         static_cast<const TO*>(P.aux), static_cast<TO*>(P.aux2), P.base, P.X,
+                                         static_cast<float*>(P.out), static_cast<const TO*>(P.aux),
+                                         static_cast<TO*>(P.aux2), P.base, P.X,
                                          static_cast<const float*>(P.aux), P.RHS, P.OUT, a.hstep, a.rhs_sign, a.N,
                                          M, m0 + wm0, n0 + wn0, lane);
 }
@@ -566,10 +556,288 @@ gemm_f32_mfma_kernel(const GemmArgs a, int tiles_m, int tiles_n) {
   }
   const EpiPtrs P = resolve_epi<float>(a, g, EPI);
   tile_epilogue<EPI, float, 1, 1, false, false>(acc, nullptr, P.bias, static_cast<float*>(P.out), static_cast<float*>(P.out),
-                                         static_cast<float*>(P.aux), static_cast<const float*>(P.aux),
-                                         static_cast<float*>(P.aux2), P.base, P.X,
+                                         static_cast<const float*>(P.aux), static_cast<float*>(P.aux2), P.base, P.X,
                                          static_cast<const float*>(P.aux), P.RHS, P.OUT, a.hstep, a.rhs_sign, a.N, M,
                                          m0 + wm0, n0 + wn0, lane);
+}
+
+// ---------------------------------------------------------------------------
+// Parameter gradients of a linear map:  dW_g[m,n] = scale * sum_t dY_g[t,m] U_g[t,n],  db_g[m] = scale *
+// sum_t dY_g[t,m], both operands packed token-major.  The reduction runs over the rows of both, so the
+// k-tiles are staged as they lie in memory ([token][feature], global -> LDS directly, the ring of the kernel
+// above) and the fragments come out of LDS through the transposing read of gfx950 (ds_read_b64_tr_b16: 16
+// lanes read 4 rows of 16 columns and each lane gets one column's 4 values).  16-byte chunks are
+// XOR-swizzled by the row so that the 4 rows of a read fall on distinct banks; any token count works (rows
+// past K come from a zero chunk), and so does any width that is a multiple of 8.
+// The bias gradient is summed from the same fragments by the wavefronts of the first column of tiles.
+// This replaces a transposition of both operands (2.8 TB/s, with GELU or a LayerNorm recomputed on the way)
+// before a product of two reduction-contiguous operands.
+// ---------------------------------------------------------------------------
+
+template <int BM, int BN, int STAGES, int WM, int WN>
+__global__ void __launch_bounds__(64 * WM * WN, WM * WN / 4)
+gemm_tn_mfma_kernel(const GemmTnArgs a, int tiles_m, int tiles_n, int splits, int total_tiles, int per_xcd) {
+  constexpr int NW = WM * WN, BK = 64, KS = BK / 16;
+  constexpr int WTM = BM / WM, WTN = BN / WN, TM = WTM / 32, TN = WTN / 32;
+  constexpr int RA = BM * 2, RB = BN * 2;                // bytes per LDS row (one token)
+  constexpr int A_BYTES = BK * RA, B_BYTES = BK * RB, STAGE = A_BYTES + B_BYTES;
+  constexpr int A_LD = A_BYTES / 1024 / NW, B_LD = B_BYTES / 1024 / NW, PER_TILE = A_LD + B_LD;
+  static_assert(A_LD * 1024 * NW == A_BYTES && B_LD * 1024 * NW == B_BYTES, "tile/wave split");
+  extern __shared__ __attribute__((aligned(1024))) unsigned char smem2[];
+  const int tile = (blockIdx.x & 7) * per_xcd + (blockIdx.x >> 3);
+  if (tile >= total_tiles) return;
+  const int per_slice = tiles_m * tiles_n;
+  const int gs = tile / per_slice, tg = tile - gs * per_slice, tm = tg / tiles_n, tn = tg - tm * tiles_n;
+  const int g = gs / splits, sp = gs - g * splits;       // slice sp of the group's tokens
+  const int m0 = tm * BM, n0 = tn * BN, M = a.M, N = a.N;
+  const int all_tiles = (a.K + BK - 1) / BK;
+  const int kt0 = (int)((long)all_tiles * sp / splits), kt1 = (int)((long)all_tiles * (sp + 1) / splits);
+  const int K = (kt1 * BK < a.K ? kt1 * BK : a.K) - kt0 * BK;
+  const bf16* A = reinterpret_cast<const bf16*>(a.A) + a.a_slots.of(g) * a.a_slot_stride + (long)kt0 * BK * M;
+  const bf16* B = reinterpret_cast<const bf16*>(a.B) + a.b_slots.of(g) * a.b_slot_stride + (long)kt0 * BK * N;
+  const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63;
+  const int wm0 = (wave / WN) * WTM, wn0 = (wave % WN) * WTN;
+
+  // row r keeps logical chunk c at position c ^ f(r): 256-byte rows (or longer) repeat the banks every row,
+  // 128-byte rows every second one
+  auto swz_of = [](int row_bytes, int r) { return row_bytes >= 256 ? (r & 3) << 2 : ((r >> 1) & 1) << 2; };
+  unsigned aoff[A_LD], boff[B_LD];                       // element offsets inside a k-tile
+#pragma unroll
+  for (int j = 0; j < A_LD; ++j) {
+    const int row = (wave * A_LD + j) * (1024 / RA) + lane / (RA / 16);
+    int col = m0 + ((lane % (RA / 16)) ^ swz_of(RA, row)) * 8;
+    col = col < M ? col : 0;                             // columns past the edge: never stored
+    aoff[j] = (unsigned)row * (unsigned)M + col;
+  }
+#pragma unroll
+  for (int j = 0; j < B_LD; ++j) {
+    const int row = (wave * B_LD + j) * (1024 / RB) + lane / (RB / 16);
+    int col = n0 + ((lane % (RB / 16)) ^ swz_of(RB, row)) * 8;
+    col = col < N ? col : 0;
+    boff[j] = (unsigned)row * (unsigned)N + col;
+  }
+  auto issue_one = [&](int stage, int k0, int idx) {
+    const bool is_a = idx < A_LD;
+    const bf16* src = is_a ? A + (long)k0 * M + aoff[idx < A_LD ? idx : 0] : B + (long)k0 * N + boff[idx < A_LD ? 0 : idx - A_LD];
+    const int slot = is_a ? wave * A_LD + idx : wave * B_LD + idx - A_LD;
+    const int row = is_a ? slot * (1024 / RA) + lane / (RA / 16) : slot * (1024 / RB) + lane / (RB / 16);
+    if (row >= K - k0) src = reinterpret_cast<const bf16*>(g_zero_chunk);
+    unsigned char* dst = smem2 + stage * STAGE + (is_a ? 0 : A_BYTES) + slot * 1024;
+    __builtin_amdgcn_global_load_lds((gas_ptr)src, (las_ptr)dst, 16, 0, 0);
+  };
+  auto issue = [&](int stage, int k0) {
+#pragma unroll
+    for (int idx = 0; idx < PER_TILE; ++idx) issue_one(stage, k0, idx);
+  };
+  // this lane's address inside a fragment: token 8*lh + (lane%16)/4 (+ 4 for the second half), 16 columns per
+  // group of 16 lanes
+  const int lh = lane >> 5, trow = 8 * lh + ((lane & 15) >> 2), low = 2 * ((lane >> 4) & 1) + ((lane & 3) >> 1);
+  int offa[TM], offb[TN];
+#pragma unroll
+  for (int i = 0; i < TM; ++i)
+    offa[i] = trow * RA + (((((wm0 + 32 * i) >> 3) + low) ^ swz_of(RA, trow)) << 4) + (lane & 1) * 8;
+#pragma unroll
+  for (int j = 0; j < TN; ++j)
+    offb[j] = trow * RB + (((((wn0 + 32 * j) >> 3) + low) ^ swz_of(RB, trow)) << 4) + (lane & 1) * 8;
+  f32x16 acc[TM][TN];
+#pragma unroll
+  for (int i = 0; i < TM; ++i)
+#pragma unroll
+    for (int j = 0; j < TN; ++j)
+#pragma unroll
+      for (int r = 0; r < 16; ++r) acc[i][j][r] = 0.f;
+  float bsum[TM];
+#pragma unroll
+  for (int i = 0; i < TM; ++i) bsum[i] = 0.f;
+  const bool sums = tn == 0 && wn0 == 0;                       // wave-uniform
+
+  const int KT = (K + BK - 1) / BK;
+#pragma unroll
+  for (int s = 0; s < STAGES; ++s)
+    if (s < KT) issue(s, s * BK);
+  auto wait_tile = [&](int kt, int issued) {
+    const int behind = issued - 1 - kt;
+    if constexpr (STAGES >= 4) if (behind >= 3) { wait_vmcnt<3 * PER_TILE>(); return; }
+    if constexpr (STAGES >= 3) if (behind >= 2) { wait_vmcnt<2 * PER_TILE>(); return; }
+    if (behind >= 1) { wait_vmcnt<PER_TILE>(); return; }
+    wait_vmcnt<0>();
+  };
+  // Fragments are read DIST k-steps ahead of their products (1 where a step is long enough to hide the LDS
+  // latency, else 2); the step that first needs the next tile begins with its wait and barrier.
+  constexpr int NM = TM * TN, RD = TM + TN, DIST = NM >= 8 ? 1 : 2, BUFS = DIST == 1 ? 2 : 4;
+  const unsigned lds0 = lds_offset(smem2);
+  TrFrag fa[BUFS][TM], fb[BUFS][TN];
+  auto read = [&](auto ks_tag, unsigned stage_off, int u) {
+    constexpr int ks = decltype(ks_tag)::value, nb = ks % BUFS;
+    if (u < TN) tr_read<16 * ks * RB, (16 * ks + 4) * RB>(fb[nb][u < TN ? u : 0], lds0 + stage_off + A_BYTES + offb[u < TN ? u : 0]);
+    else tr_read<16 * ks * RA, (16 * ks + 4) * RA>(fa[nb][u < TN ? 0 : u - TN], lds0 + stage_off + offa[u < TN ? 0 : u - TN]);
+  };
+  wait_tile(0, STAGES < KT ? STAGES : KT);
+  bare_barrier();
+#pragma unroll
+  for (int u = 0; u < RD; ++u) read(std::integral_constant<int, 0>{}, 0, u);
+  if constexpr (DIST == 2) {
+#pragma unroll
+    for (int u = 0; u < RD; ++u) read(std::integral_constant<int, 1>{}, 0, u);
+  }
+  // one k-step: its products, with the reads of the step DIST ahead and (LOADS) of the refilled stage's loads
+  // in between
+  auto step = [&](auto ks_tag, auto loads_tag, unsigned read_stage, int stage, int pk0) {
+    constexpr int ks = decltype(ks_tag)::value, cb = ks % BUFS, rks = (ks + DIST) % KS;
+    if constexpr (DIST == 2) { asm volatile("s_waitcnt lgkmcnt(%0)" ::"n"(2 * RD) : "memory"); __builtin_amdgcn_sched_barrier(0); }
+    else wait_lgkm();
+    bf16x8 xa[TM], xb[TN];
+#pragma unroll
+    for (int i = 0; i < TM; ++i) xa[i] = tr_value(fa[cb][i]);
+#pragma unroll
+    for (int j = 0; j < TN; ++j) xb[j] = tr_value(fb[cb][j]);
+    __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+    for (int q = 0; q < NM; ++q) {
+      const int i = q / TN, j = q % TN;
+      acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(xb[j], xa[i], acc[i][j], 0, 0, 0);
+      const int r0 = (q * RD * 4 / 3 + NM - 1) / NM, r1 = ((q + 1) * RD * 4 / 3 + NM - 1) / NM;
+#pragma unroll
+      for (int u = 0; u < RD; ++u)
+        if (u >= r0 && (u < r1 || q == NM - 1)) read(std::integral_constant<int, rks>{}, read_stage, u);
+      if constexpr (decltype(loads_tag)::value) {
+        const int l0 = (q * PER_TILE + NM - 1) / NM, l1 = ((q + 1) * PER_TILE + NM - 1) / NM;
+#pragma unroll
+        for (int u = 0; u < PER_TILE; ++u)
+          if (u >= l0 && u < l1) issue_one(stage, pk0, u);
+      }
+      __builtin_amdgcn_sched_barrier(0);
+    }
+    if (sums) {
+#pragma unroll
+      for (int i = 0; i < TM; ++i)
+#pragma unroll
+        for (int e = 0; e < 8; ++e) bsum[i] += (float)xa[i][e];
+    }
+  };
+  int cur = 0;
+  auto tile_step = [&](int kt, auto loads_tag) {
+    const int nxt = cur + 1 == STAGES ? 0 : cur + 1;
+    const unsigned so = cur * STAGE, sn = nxt * STAGE;
+    auto handover = [&]() {                              // tile kt+1 is there, nobody reads tile kt any more
+      wait_lgkm();
+      wait_tile(kt + 1, kt + STAGES < KT ? kt + STAGES : KT);
+      bare_barrier();
+    };
+    step(std::integral_constant<int, 0>{}, std::false_type{}, so, 0, 0);
+    step(std::integral_constant<int, 1>{}, std::false_type{}, so, 0, 0);
+    if constexpr (DIST == 2) handover();
+    step(std::integral_constant<int, 2>{}, std::integral_constant<bool, DIST == 2 && decltype(loads_tag)::value>{},
+         DIST == 2 ? sn : so, cur, (kt + STAGES) * BK);
+    if constexpr (DIST == 1) handover();
+    step(std::integral_constant<int, 3>{}, std::integral_constant<bool, DIST == 1 && decltype(loads_tag)::value>{}, sn,
+         cur, (kt + STAGES) * BK);
+    cur = nxt;
+  };
+  int kt = 0;
+  for (; kt + STAGES < KT; ++kt) tile_step(kt, std::true_type{});
+  for (; kt < KT; ++kt) tile_step(kt, std::false_type{});
+  wait_lgkm();
+  bare_barrier();
+  // one slice: straight into the gradient block; several: unscaled into the slice's [M x N | M] of the scratch
+  float *dW, *db, scale = a.scale;
+  if (splits == 1) {
+    char* out = const_cast<char*>(a.out.at(g));
+    dW = reinterpret_cast<float*>(out + a.w_off);
+    db = reinterpret_cast<float*>(out + a.b_off);
+  } else {
+    dW = a.partial + (long)gs * ((long)M * N + M);
+    db = dW + (long)M * N;
+    scale = 1.f;
+  }
+  if (sums) {
+#pragma unroll
+    for (int i = 0; i < TM; ++i) {
+      const float t = bsum[i] + __shfl_xor(bsum[i], 32, 64);   // the two k halves
+      const int m = m0 + wm0 + 32 * i + (lane & 31);
+      if (lh == 0 && m < M) db[m] = scale * t;
+    }
+  }
+  constexpr int EP_BYTES = (32 * (WTN * 4 + 16) + 1023) / 1024 * 1024;
+  tile_epilogue<EPI_STORE_F32, bf16, TM, TN, true, true>(
+      acc, smem2 + wave * EP_BYTES, nullptr, static_cast<bf16*>(nullptr), dW, static_cast<const bf16*>(nullptr),
+      static_cast<bf16*>(nullptr), nullptr, nullptr, nullptr, nullptr, nullptr, scale, 1.f, N, M, m0 + wm0, n0 + wn0,
+      lane);
+}
+
+// sums of the slices, in order
+__global__ void __launch_bounds__(256) gemm_tn_reduce_kernel(const GemmTnArgs a, int splits) {
+  const int g = blockIdx.y;
+  const long mn = (long)a.M * a.N, each = mn + a.M;            // M and N are multiples of 4
+  const long i = ((long)blockIdx.x * 256 + threadIdx.x) * 4;
+  if (i >= each) return;
+  const float* p = a.partial + (long)g * splits * each + i;
+  f32x4 acc = {0.f, 0.f, 0.f, 0.f};
+  for (int s = 0; s < splits; ++s) acc += *reinterpret_cast<const f32x4*>(p + s * each);
+  char* out = const_cast<char*>(a.out.at(g));
+  float* o = i < mn ? reinterpret_cast<float*>(out + a.w_off) + i : reinterpret_cast<float*>(out + a.b_off) + (i - mn);
+  *reinterpret_cast<f32x4*>(o) = a.scale * acc;
+}
+
+// fp32 operands: 64x64 tile, 4 wavefronts of 32x32 on the 32x32x2 fp32 MFMA, 16 tokens per k-tile.  The
+// fragments of this product are contiguous in the token-major tiles, so no transposition is involved.
+__global__ void __launch_bounds__(256) gemm_tn_f32_kernel(const GemmTnArgs a, int tiles_n, int splits) {
+  constexpr int BT = 64, BKF = 16, LD = BT + 4;
+  __shared__ __attribute__((aligned(16))) float As[BKF * LD];
+  __shared__ __attribute__((aligned(16))) float Bs[BKF * LD];
+  const int g = blockIdx.z, tm = blockIdx.x / tiles_n, tn = blockIdx.x - tm * tiles_n, sp = blockIdx.y;
+  const int m0 = tm * BT, n0 = tn * BT, M = a.M, N = a.N;
+  const int all_tiles = (a.K + BKF - 1) / BKF;
+  const int kt0 = (int)((long)all_tiles * sp / splits), kt1 = (int)((long)all_tiles * (sp + 1) / splits);
+  const int K = (kt1 * BKF < a.K ? kt1 * BKF : a.K) - kt0 * BKF;
+  const float* A = reinterpret_cast<const float*>(a.A) + a.a_slots.of(g) * a.a_slot_stride + (long)kt0 * BKF * M;
+  const float* B = reinterpret_cast<const float*>(a.B) + a.b_slots.of(g) * a.b_slot_stride + (long)kt0 * BKF * N;
+  const int tid = threadIdx.x, wave = tid >> 6, lane = tid & 63, lr = lane & 31, lh = lane >> 5;
+  const int wm0 = (wave >> 1) * 32, wn0 = (wave & 1) * 32;
+  const int srow = tid >> 4, sc = (tid & 15) * 4;              // one float4 of each operand per thread
+  const int ac = m0 + sc < M ? m0 + sc : 0, bc = n0 + sc < N ? n0 + sc : 0;
+  const f32x4 zero = {0.f, 0.f, 0.f, 0.f};
+  f32x16 acc[1][1];
+#pragma unroll
+  for (int r = 0; r < 16; ++r) acc[0][0][r] = 0.f;
+  float bsum = 0.f;
+  auto ld = [&](const float* p, int stride, int col, int k) {
+    return k < K ? *reinterpret_cast<const f32x4*>(p + (long)k * stride + col) : zero;
+  };
+  f32x4 va = ld(A, M, ac, srow), vb = ld(B, N, bc, srow);
+  for (int k0 = 0; k0 < K; k0 += BKF) {
+    __syncthreads();
+    *reinterpret_cast<f32x4*>(&As[srow * LD + sc]) = va;
+    *reinterpret_cast<f32x4*>(&Bs[srow * LD + sc]) = vb;
+    __syncthreads();
+    if (k0 + BKF < K) { va = ld(A, M, ac, k0 + BKF + srow); vb = ld(B, N, bc, k0 + BKF + srow); }
+#pragma unroll
+    for (int ks = 0; ks < BKF; ks += 2)
+      acc[0][0] = __builtin_amdgcn_mfma_f32_32x32x2f32(Bs[(ks + lh) * LD + wn0 + lr], As[(ks + lh) * LD + wm0 + lr],
+                                                      acc[0][0], 0, 0, 0);
+    if (tn == 0 && tid < BT) {
+#pragma unroll
+      for (int k = 0; k < BKF; ++k) bsum += As[k * LD + tid];
+    }
+  }
+  float *W, *db, scale = a.scale;
+  if (splits == 1) {
+    char* out = const_cast<char*>(a.out.at(g));
+    W = reinterpret_cast<float*>(out + a.w_off);
+    db = reinterpret_cast<float*>(out + a.b_off);
+  } else {
+    W = a.partial + (long)(g * splits + sp) * ((long)M * N + M);
+    db = W + (long)M * N;
+    scale = 1.f;
+  }
+  if (tn == 0 && tid < BT && m0 + tid < M) db[m0 + tid] = scale * bsum;
+  const int m = m0 + wm0 + lr;
+#pragma unroll
+  for (int q = 0; q < 4; ++q) {
+    const int n = n0 + wn0 + 8 * q + 4 * lh;
+    const f32x4 v = {acc[0][0][4 * q], acc[0][0][4 * q + 1], acc[0][0][4 * q + 2], acc[0][0][4 * q + 3]};
+    if (m < M && n < N) *reinterpret_cast<f32x4*>(W + (long)m * N + n) = scale * v;
+  }
 }
 
 // ---------------------------------------------------------------------------
@@ -697,8 +965,8 @@ static double gemm_bytes(const GemmArgs& a, double esz) {
   const double G = a.n_groups, MN = (double)a.M * a.N;
   double b = G * ((a.a_slot_stride ? 1.0 : 1.0 / G) * a.M * a.K * esz + (double)a.N * a.K * esz);
   if (EPI == EPI_STORE) b += G * MN * esz;
-  if (EPI == EPI_GELU || EPI == EPI_GELU_PRIME) b += G * MN * esz * (a.aux ? 2 : 1);
-  if (EPI == EPI_GELU_BOTH) b += G * MN * esz * (a.aux ? 3 : 2);
+  if (EPI == EPI_GELU || EPI == EPI_GELU_PRIME) b += G * MN * esz;
+  if (EPI == EPI_GELU_BOTH) b += G * MN * esz * 2;
   if (EPI == EPI_DGELU) b += G * MN * esz * 2;
   if (EPI == EPI_STORE_F32) b += G * MN * 4;
   if (EPI == EPI_RESID_INNER) b += G * MN * 4 * (a.base ? 2 : 1);
@@ -783,6 +1051,84 @@ static hipError_t launch_epi(const GemmArgs& a, bool is_bf16, hipStream_t st) {
   const bool ragged = a.N % bn != 0 || a.K % 64 != 0;
   if (ragged && cfg == 3) return launch_cfg<EPI, true>(4, a, st);
   return ragged ? launch_cfg<EPI, true>(cfg, a, st) : launch_cfg<EPI, false>(cfg, a, st);
+}
+
+template <int BM, int BN, int STAGES, int WM, int WN>
+static hipError_t launch_tn(const GemmTnArgs& a, int splits, hipStream_t st) {
+  const int tiles_m = (a.M + BM - 1) / BM, tiles_n = (a.N + BN - 1) / BN;
+  const int total = tiles_m * tiles_n * a.n_groups * splits, per_xcd = (total + 7) / 8;
+  const size_t ring = (size_t)STAGES * (BM + BN) * 128;
+  const size_t staging = (size_t)WM * WN * ((32 * (BN / WN * 4 + 16) + 1023) / 1024 * 1024);
+  const size_t smem = ring > staging ? ring : staging;
+  auto kern = gemm_tn_mfma_kernel<BM, BN, STAGES, WM, WN>;
+  static bool attr_done = false;
+  if (!attr_done) {
+    hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(kern),
+                                       hipFuncAttributeMaxDynamicSharedMemorySize, (int)smem);
+    if (e != hipSuccess) return e;
+    attr_done = true;
+  }
+  hipLaunchKernelGGL(kern, dim3(per_xcd * 8), dim3(64 * WM * WN), smem, st, a, tiles_m, tiles_n, splits, total, per_xcd);
+  return hipGetLastError();
+}
+
+// Tile and number of token slices of a parameter-gradient product.  Microseconds of a round as in
+// kTileCfgs, measured at 768..3072 wide outputs and 4096 and 12608 tokens; the transposing reads deliver half
+// the bytes per clock of plain ones, so a k-tile takes longer than there.  Few output tiles and many tokens
+// (384 x 384 from 12608 tokens: 9 tiles of 128x128) are cut into slices of at least 8 k-tiles, which costs
+// writing and summing the slices' partial results.
+struct TnPlan { int cfg, splits; };
+static TnPlan choose_tn(int n_groups, int M, int N, int K, bool is_bf16) {
+  static const TileCfg bf[] = {{1, 256, 256, 1, 7.0, 2.05}, {6, 128, 128, 1, 3.0, 0.68}, {8, 64, 64, 2, 2.5, 0.50}};
+  static const TileCfg fp[] = {{0, 64, 64, 4, 2.5, 2.2}};
+  const long cus = compute_units();
+  const int ktiles = (K + 63) / 64;
+  TnPlan best = {6, 1};
+  double best_cost = 1e30;
+  for (const TileCfg* c = is_bf16 ? bf : fp; c != (is_bf16 ? bf + 3 : fp + 1); ++c) {
+    const long tiles = (long)((M + c->bm - 1) / c->bm) * ((N + c->bn - 1) / c->bn) * n_groups;
+    for (int s = 1; s <= 64 && (s == 1 || ktiles / s >= 8); s *= 2) {
+      const long rounds = (tiles * s + cus * c->per_cu - 1) / (cus * c->per_cu);
+      double cost = rounds * (c->fixed + c->per_ktile * ((ktiles + s - 1) / s));
+      if (s > 1) cost += 4.0 + 2.0 * s * n_groups * (double)M * N * 4.0 / 3e6;         // us at 3 TB/s
+      if (cost < best_cost) { best_cost = cost; best = {c->id, s}; }
+    }
+  }
+  return best;
+}
+
+size_t gemm_tn_partial_floats(int n_groups, int M, int N, int K, bool is_bf16) {
+  const int s = choose_tn(n_groups, M, N, K, is_bf16).splits;
+  return s == 1 ? 0 : (size_t)s * n_groups * ((size_t)M * N + M);
+}
+
+hipError_t launch_gemm_tn(const GemmTnArgs& a, bool is_bf16, hipStream_t st) {
+  if (a.n_groups <= 0 || a.K <= 0) return hipSuccess;
+  const double esz = is_bf16 ? 2 : 4, G = a.n_groups;
+  if (a.M % 8 != 0 || a.N % 8 != 0 || 64.0 * a.M > 4e9 || 64.0 * a.N > 4e9) return hipErrorInvalidValue;
+  const TnPlan plan = choose_tn(a.n_groups, a.M, a.N, a.K, is_bf16);
+  if (plan.splits > 1 && !a.partial) return hipErrorInvalidValue;
+  ProfScope ps(is_bf16 ? (a.n_groups > 1 ? PC_GEMM_MFMA : PC_GEMM_MFMA_SINGLE) + EPI_STORE_F32 : PC_GEMM_SIMPLE,
+               2.0 * G * a.M * (double)a.N * a.K,
+               G * ((double)a.K * (a.M + a.N) * esz + 4.0 * a.M * a.N), st);
+  hipError_t e;
+  if (!is_bf16) {
+    const int tiles_m = (a.M + 63) / 64, tiles_n = (a.N + 63) / 64;
+    hipLaunchKernelGGL(gemm_tn_f32_kernel, dim3(tiles_m * tiles_n, plan.splits, a.n_groups), dim3(256), 0, st, a,
+                       tiles_n, plan.splits);
+    e = hipGetLastError();
+  } else {
+    switch (plan.cfg) {
+      case 1: e = launch_tn<256, 256, 2, 2, 4>(a, plan.splits, st); break;
+      case 8: e = launch_tn<64, 64, 4, 2, 2>(a, plan.splits, st); break;
+      default: e = launch_tn<128, 128, 4, 4, 2>(a, plan.splits, st); break;
+    }
+  }
+  if (e != hipSuccess || plan.splits == 1) return e;
+  const long each = (long)a.M * a.N + a.M;
+  hipLaunchKernelGGL(gemm_tn_reduce_kernel, dim3((unsigned)((each / 4 + 255) / 256), a.n_groups), dim3(256), 0, st, a,
+                     plan.splits);
+  return hipGetLastError();
 }
 
 hipError_t launch_gemm(const GemmArgs& a, int epi, bool is_bf16, hipStream_t st) {

@@ -6,6 +6,8 @@ namespace mg {
 
 // ---- gemm.hip ----------------------------------------------------------------
 hipError_t launch_gemm(const GemmArgs& a, int epi, bool is_bf16, hipStream_t st);
+hipError_t launch_gemm_tn(const GemmTnArgs& a, bool is_bf16, hipStream_t st);
+size_t gemm_tn_partial_floats(int n_groups, int M, int N, int K, bool is_bf16);   // scratch floats of such a launch
 void gemm_force_simple(int on);
 void gemm_set_tile_config(int cfg);
 double gemm_model_cost(int n_groups, int M, int N, int K);
@@ -69,26 +71,24 @@ hipError_t launch_transpose(int n_groups, Params in, Params out, long off, int r
                             hipStream_t st);
 
 // ---- grads.hip ---------------------------------------------------------------
-// dst_g[c, r] = src_g[r, c] (or GELU of it) on packed operand-type buffers, src [rows, cols].
-// With `partial` (n_groups * transpose_row_blocks(rows) * cols floats of scratch) also
-// sum_out_g[c] (fp32, at byte offset sum_off of the group's output block) = sum_scale * sum over rows of src_g[r, c].
-int transpose_row_blocks(int rows);
-hipError_t launch_transpose_slots(int n_groups, const void* src, long src_slot_stride, Slots src_slots, int rows,
-                                  int cols, void* dst, long dst_slot_stride, Slots dst_slots, bool gelu,
-                                  bool is_bf16, float* partial, Params sum_out, long sum_off, float sum_scale,
-                                  hipStream_t st);
-// LayerNorm gain / shift gradients: sums over tokens of dy * xhat and dy, scaled
-struct LnParamArgs {
-  int n_groups, T, d;
+// LayerNorm gain / shift gradients of up to three LayerNorms of the same layers: sums over tokens of
+// dy * xhat and dy, scaled
+constexpr int LN_PARAM_MAX = 3;
+struct LnParamItem {
   const void* dy; long dy_slot_stride; Slots dy_slots;    // packed operand type: cotangent of the LN output
-  Rows X;                                                 // LN input = X rows (optional) + addend (optional)
-  const float* xp; long xp_slot_stride; Slots xp_slots;
-  Params out; long gamma_off, beta_off;                   // fp32 outputs inside the group's output block
+  const float* xp; long xp_slot_stride; Slots xp_slots;   // LN input = X rows + optional packed fp32 addend
+  long gamma_off, beta_off;                               // byte offsets of the fp32 results
+};
+struct LnParamArgs {
+  int n_groups, T, d, n_items;
+  Rows X;
+  Params out;                                             // the group's output block
   float scale, eps;
+  LnParamItem item[LN_PARAM_MAX];
 };
 // out[i] = scale * sum over s < n of in[s * elems + i]   (fixed order)
 hipError_t launch_sum_slots(const float* in, int n, long elems, float* out, float scale, hipStream_t st);
-int ln_param_partial_rows();          // partial: n_groups * ln_param_partial_rows() * 2 * d floats
+size_t ln_param_partial_floats(int n_groups, int T, int d, int n_items);
 hipError_t launch_ln_param_grad(const LnParamArgs& a, float* partial, bool is_bf16, hipStream_t st);
 
 // ---- attention.hip -----------------------------------------------------------

@@ -42,7 +42,10 @@ constexpr int DEFAULT_MAX_GROUPS = 4;
 // runs in whole rounds of tiles over the CUs, so the group count decides how full the last round of
 // every projection GEMM is (at d = 768, 5 groups of 4096 tokens make 240 tiles of 256x256 for the
 // d-wide outputs, one round; 4 groups need the smaller 256x192 tiles): take the count in 3..6 with the
-// smallest modelled GEMM time over the sweep, near-ties (1 %) going to the larger count.
+// smallest modelled GEMM time over the sweep.  The model adds the chunks up as if they ran one after the
+// other; on two lanes the emptier rounds of one chunk are filled by the other's, so near-ties (3 %) go to the
+// larger count (BERT shape, forward: 4 groups 31.6 ms, 5 30.4, 6 31.6; GPT-2 shape with gradients 193.4, 188.8,
+// 196.5; ViT shape 84.0, 83.4, 87.7).
 inline int default_groups(const mgrit_model_desc* md, int sweep) {
   if (md->dtype != MGRIT_DTYPE_BF16 || sweep < 2) return DEFAULT_MAX_GROUPS;
   const int T = md->batch * md->seq, d = md->d_model, f = md->d_ff;
@@ -61,7 +64,7 @@ inline int default_groups(const mgrit_model_desc* md, int sweep) {
   }
   int pick = DEFAULT_MAX_GROUPS;
   for (int gc = 3; gc <= 6; ++gc)
-    if (cost[gc] <= 1.01 * best) pick = gc;
+    if (cost[gc] <= 1.03 * best) pick = gc;
   return pick;
 }
 inline int max_groups(const mgrit_model_desc* md, int sweep) {
@@ -179,8 +182,9 @@ struct Engine {
   // adjoint: linearisation cache (n_cache slots) and work buffers (Gc slots)
   int n_cache;
   void *c_qkv, *c_o, *c_z;         // c_z holds gelu'(z): the adjoint only needs the derivative
-  void* c_zraw = nullptr;          // z itself, kept when parameter gradients are wanted (W2's needs GELU(z))
-  bool keep_z = false;
+  // kept when parameter gradients are wanted: the inputs of the linear maps, gelu(z) and the LayerNorm outputs
+  void *c_act = nullptr, *c_u1 = nullptr, *c_u2 = nullptr, *c_u3 = nullptr;
+  bool keep_inputs = false;
   float *c_lse, *c_xin;
   void *c_xh1, *c_xh2;             // normalised LN1 / LN2 inputs (operand type) ...
   float *c_rs1, *c_rs2;            // ... and their 1/std, one per token
@@ -188,11 +192,12 @@ struct Engine {
   float *c_lsec, *c_x3;
   void *cb, *dz, *du, *ds, *da, *dqkv;
   float *dxin, *Dbuf;
-  // parameter-gradient pass: transposed operands (Gc slots each), token-sum partials, table of tB slots
+  // cotangents of the LayerNorm outputs (du: LN2).  The chain of transposed steps needs one at a time; the
+  // parameter-gradient pass reads all of them after the chain, so they are then kept apart.
+  void *du1 = nullptr, *du3 = nullptr;
+  void *dsc = nullptr, *dqc = nullptr;   // cross-attention decoder: cotangents of ybar and of q_c (ds, dqkv unless kept)
   mgrit_theta_layout_t glay;       // layout of a gradient block: the fp32 parameter block of the model
-  void *tA = nullptr, *tB = nullptr;
-  float* gpart = nullptr;
-  void** tabTB = nullptr;
+  float* gpart = nullptr;          // partial sums of the parameter-gradient kernels
   void* dkvc = nullptr;            // cross-attention decoder: dK | dV of the cross attention, [Tm, 2d] per slot
   // decoder half of a stacked encoder-decoder grid: every group attends to the X part of its own
   // input state, so the operand-type copy of the memory is per launch slot ([Tm, d] each)
@@ -203,10 +208,6 @@ struct Engine {
   bool recompute = false;
   // sign of the step inside OUT = RHS + sign * (step): -1 while the driver forms a coarse right-hand side
   float rhs_sign = 1.f;
-  int Tmax() const { return T > Tm ? T : Tm; }
-  long tA_stride() const { return (long)(f > 3 * d ? f : 3 * d) * Tmax(); }   // elements per slot
-  long tB_stride() const { return (long)(f > d ? f : d) * Tmax(); }
-
   long Td() const { return (long)T * d; }
 
   void init(const mgrit_model_desc* m, hipStream_t s) {
@@ -246,7 +247,13 @@ struct Engine {
     c_qkv = b.take_bytes(C * T * 3 * d * esz);
     c_o = b.take_bytes(C * T * d * esz);
     c_z = b.take_bytes(C * T * f * esz);
-    c_zraw = keep_z ? b.take_bytes(C * T * f * esz) : nullptr;
+    c_act = c_u1 = c_u2 = c_u3 = nullptr;
+    if (keep_inputs) {
+      c_act = b.take_bytes(C * T * f * esz);
+      c_u1 = b.take_bytes(C * T * d * esz);
+      c_u2 = b.take_bytes(C * T * d * esz);
+      if (md.arch == MGRIT_ARCH_CROSS) c_u3 = b.take_bytes(C * T * d * esz);
+    }
     c_lse = b.take<float>(C * md.batch * H * md.seq);
     c_xin = b.take<float>(C * T * d);
     c_xh1 = b.take_bytes(C * T * d * esz);
@@ -264,8 +271,9 @@ struct Engine {
   }
   // the cache pointers of an engine laid out elsewhere (a forward plan that fills an adjoint plan's cache)
   void take_cache_from(const Engine& o) {
-    n_cache = o.n_cache; keep_z = o.keep_z;
-    c_qkv = o.c_qkv; c_o = o.c_o; c_z = o.c_z; c_zraw = o.c_zraw; c_lse = o.c_lse; c_xin = o.c_xin;
+    n_cache = o.n_cache; keep_inputs = o.keep_inputs;
+    c_act = o.c_act; c_u1 = o.c_u1; c_u2 = o.c_u2; c_u3 = o.c_u3;
+    c_qkv = o.c_qkv; c_o = o.c_o; c_z = o.c_z; c_lse = o.c_lse; c_xin = o.c_xin;
     c_xh1 = o.c_xh1; c_xh2 = o.c_xh2; c_rs1 = o.c_rs1; c_rs2 = o.c_rs2;
     c_qc = o.c_qc; c_kvc = o.c_kvc; c_oc = o.c_oc; c_lsec = o.c_lsec; c_x3 = o.c_x3;
   }
@@ -281,9 +289,14 @@ struct Engine {
     cb = b.take_bytes(G * T * d * esz);
     dz = b.take_bytes(G * T * f * esz);
     du = b.take_bytes(G * T * d * esz);
+    du1 = keep_inputs ? b.take_bytes(G * T * d * esz) : du;
+    du3 = keep_inputs && md.arch == MGRIT_ARCH_CROSS ? b.take_bytes(G * T * d * esz) : du;
     ds = b.take_bytes(G * T * d * esz);
     da = b.take_bytes(G * T * d * esz);
     dqkv = b.take_bytes(G * T * 3 * d * esz);
+    const bool keep_cross = keep_inputs && md.arch == MGRIT_ARCH_CROSS;
+    dsc = keep_cross ? b.take_bytes(G * T * d * esz) : ds;
+    dqc = keep_cross ? b.take_bytes(G * T * d * esz) : dqkv;
     dxin = b.take<float>(G * T * d);
     Dbuf = b.take<float>(G * md.batch * H * md.seq);
     qkv = o = act = nullptr; xin = nullptr;
@@ -294,12 +307,17 @@ struct Engine {
   }
   void carve_grad_work(Bump& b) {
     const size_t G = Gc;
-    tA = b.take_bytes(G * tA_stride() * esz);
-    tB = b.take_bytes(G * tB_stride() * esz);
-    const size_t widest = f > 3 * d ? f : 3 * d;
-    const size_t p1 = G * transpose_row_blocks(Tmax()) * widest, p2 = G * ln_param_partial_rows() * 2 * (size_t)d;
-    gpart = b.take<float>(p1 > p2 ? p1 : p2);
-    tabTB = b.take<void*>(G);
+    size_t most = 0;
+    auto need = [&](size_t floats) { if (floats > most) most = floats; };
+    for (int n = 1; n <= Gc; ++n) {
+      need(gemm_tn_partial_floats(n, 3 * d, d, T, bf16));
+      need(gemm_tn_partial_floats(n, d, d, T, bf16));
+      need(gemm_tn_partial_floats(n, f, d, T, bf16));
+      need(gemm_tn_partial_floats(n, d, f, T, bf16));
+      if (md.arch == MGRIT_ARCH_CROSS) need(gemm_tn_partial_floats(n, 2 * d, d, Tm, bf16));
+      for (int items = 2; items <= LN_PARAM_MAX; ++items) need(ln_param_partial_floats(n, T, d, items));
+    }
+    gpart = b.take<float>(most);
     if (!per_group_mem) dkvc = md.arch == MGRIT_ARCH_CROSS ? b.take_bytes(G * Tm * 2 * d * esz) : nullptr;
   }
 };
@@ -390,17 +408,21 @@ int forward_chunk(Engine& E, int n, Rows IN, Rows OUT, Rows RHS, Params TH, floa
   float* xin = cache ? E.c_xin : E.xin;
   const size_t esz = E.esz;
   const bool causal = E.md.arch != MGRIT_ARCH_ENCODER;
+  // LayerNorm outputs (the projections' inputs): a work buffer, or the cache where the parameter gradients need them
+  const bool keep = cache && E.keep_inputs;
+  void *u1 = keep ? E.c_u1 : E.u, *u2 = keep ? E.c_u2 : E.u, *u3 = keep ? E.c_u3 : E.u;
+  const Slots us = keep ? cs : loc;
 
   LnFwdArgs ln;
   memset(&ln, 0, sizeof(ln));
   ln.n_groups = n; ln.T = T; ln.d = d; ln.X = IN; ln.P = TH;
   ln.gamma_off = L.offset[MGRIT_P_LN1_G]; ln.beta_off = L.offset[MGRIT_P_LN1_B];
-  ln.out = E.u; ln.out_slot_stride = E.Td(); ln.out_slots = loc; ln.eps = E.md.ln_eps;
+  ln.out = u1; ln.out_slot_stride = E.Td(); ln.out_slots = us; ln.eps = E.md.ln_eps;
   if (cache) { ln.xhat = E.c_xh1; ln.xhat_slot_stride = E.Td(); ln.xhat_slots = cs; ln.rstd = E.c_rs1; }
   HIPCHK(launch_ln_fwd(ln, E.bf16, E.st));
   ln.xhat = nullptr; ln.rstd = nullptr;
 
-  GemmArgs g = gemm_base(n, T, 3 * d, d, E.u, E.Td(), loc, TH, L.offset[MGRIT_P_WQKV], L.offset[MGRIT_P_BQKV]);
+  GemmArgs g = gemm_base(n, T, 3 * d, d, u1, E.Td(), us, TH, L.offset[MGRIT_P_WQKV], L.offset[MGRIT_P_BQKV]);
   g.out = qkv; g.out_slot_stride = (long)T * 3 * d; g.out_slots = cs;
   HIPCHK(launch_gemm(g, EPI_STORE, E.bf16, E.st));
 
@@ -429,8 +451,9 @@ int forward_chunk(Engine& E, int n, Rows IN, Rows OUT, Rows RHS, Params TH, floa
     void* oc = cache ? E.c_oc : E.o;
     ln.X = IN; ln.xp = x3; ln.xp_slot_stride = E.Td(); ln.xp_slots = cs;         // LN3(X + s)
     ln.gamma_off = L.offset[MGRIT_P_LN3_G]; ln.beta_off = L.offset[MGRIT_P_LN3_B];
+    ln.out = u3;
     HIPCHK(launch_ln_fwd(ln, E.bf16, E.st));
-    g = gemm_base(n, T, d, d, E.u, E.Td(), loc, TH, L.offset[MGRIT_P_WQ_C], L.offset[MGRIT_P_BQ_C]);
+    g = gemm_base(n, T, d, d, u3, E.Td(), us, TH, L.offset[MGRIT_P_WQ_C], L.offset[MGRIT_P_BQ_C]);
     g.out = qc; g.out_slot_stride = E.Td(); g.out_slots = cs;
     HIPCHK(launch_gemm(g, EPI_STORE, E.bf16, E.st));
     if (MEM.present()) HIPCHK(launch_cast_rows(n, (long)E.Tm * d, MEM, E.membG, (long)E.Tm * d, loc, E.bf16, E.st));
@@ -456,60 +479,38 @@ int forward_chunk(Engine& E, int n, Rows IN, Rows OUT, Rows RHS, Params TH, floa
 
   ln.X = IN; ln.xp = xin; ln.xp_slot_stride = E.Td(); ln.xp_slots = cs;          // LN2(X + ybar)
   ln.gamma_off = L.offset[MGRIT_P_LN2_G]; ln.beta_off = L.offset[MGRIT_P_LN2_B];
+  ln.out = u2;
   if (cache) { ln.xhat = E.c_xh2; ln.xhat_slot_stride = E.Td(); ln.xhat_slots = cs; ln.rstd = E.c_rs2; }
   HIPCHK(launch_ln_fwd(ln, E.bf16, E.st));
 
-  g = gemm_base(n, T, f, d, E.u, E.Td(), loc, TH, L.offset[MGRIT_P_W1], L.offset[MGRIT_P_B1]);
-  if (cache == 1) {
+  g = gemm_base(n, T, f, d, u2, E.Td(), us, TH, L.offset[MGRIT_P_W1], L.offset[MGRIT_P_B1]);
+  void* act = keep ? E.c_act : E.act;
+  const Slots as = keep ? cs : loc;
+  if (cache == 1 && !keep) {
     g.out = E.c_z; g.out_slot_stride = (long)T * f; g.out_slots = cs;
-    g.aux = E.c_zraw; g.aux_slot_stride = (long)T * f; g.aux_slots = cs;
     HIPCHK(launch_gemm(g, EPI_GELU_PRIME, E.bf16, E.st));
     return MGRIT_OK;
   }
-  g.out = E.act; g.out_slot_stride = (long)T * f; g.out_slots = loc;
+  g.out = act; g.out_slot_stride = (long)T * f; g.out_slots = as;
   if (cache) {
     g.aux2 = E.c_z; g.aux2_slot_stride = (long)T * f; g.aux2_slots = cs;
-    g.aux = E.c_zraw; g.aux_slot_stride = (long)T * f; g.aux_slots = cs;
     HIPCHK(launch_gemm(g, EPI_GELU_BOTH, E.bf16, E.st));
+    if (cache == 1) return MGRIT_OK;
   } else {
     HIPCHK(launch_gemm(g, EPI_GELU, E.bf16, E.st));
   }
 
-  g = gemm_base(n, T, d, f, E.act, (long)T * f, loc, TH, L.offset[MGRIT_P_W2], L.offset[MGRIT_P_B2]);
+  g = gemm_base(n, T, d, f, act, (long)T * f, as, TH, L.offset[MGRIT_P_W2], L.offset[MGRIT_P_B2]);
   g.aux = xin; g.aux_slot_stride = E.Td(); g.aux_slots = cs;                    // ybar
   g.X = IN; g.OUT = OUT; g.RHS = RHS; g.hstep = hstep; g.rhs_sign = E.rhs_sign;
   HIPCHK(launch_gemm(g, EPI_RESID_OUTER, E.bf16, E.st));
   return MGRIT_OK;
 }
 
-// Weight and bias gradient of one linear map y = u W^T + b of the chunk's layers:
-//   dW[out,in] = scale * dY^T U,  db[out] = scale * sum over tokens of dY,
-// dY [T,out] and U [T,in] packed operand-type buffers.  The product runs on the same
-// "both operands reduction-contiguous" GEMM, on transposed copies of dY and U (reduction over
-// the T tokens); gelu_u: U = GELU(given buffer).  Results go into the layers' gradient blocks.
-int linear_param_grads(Engine& E, int n, const void* dY, long dy_stride, Slots dy_slots, int out_dim,
-                       const void* U, long u_stride, Slots u_slots, int in_dim, bool gelu_u, Params DT,
-                       int w_id, int b_id, float scale, int tokens = 0) {
-  const Slots loc = {0, 1};
-  const int T = tokens ? tokens : E.T;
-  const Params none = {nullptr, 0, 0};
-  HIPCHK(launch_transpose_slots(n, dY, dy_stride, dy_slots, T, out_dim, E.tA, E.tA_stride(), loc, false, E.bf16,
-                                E.gpart, DT, E.glay.offset[b_id], scale, E.st));
-  HIPCHK(launch_transpose_slots(n, U, u_stride, u_slots, T, in_dim, E.tB, E.tB_stride(), loc, gelu_u, E.bf16,
-                                nullptr, none, 0, 0.f, E.st));
-  GemmArgs g = gemm_base(n, out_dim, in_dim, T, E.tA, E.tA_stride(), loc, Params{(const void* const*)E.tabTB, 0, 1},
-                         0, -1);
-  g.out_tab = DT; g.out_tab_off = E.glay.offset[w_id]; g.hstep = scale;
-  HIPCHK(launch_gemm(g, EPI_STORE_F32, E.bf16, E.st));
-  return MGRIT_OK;
-}
-
-// One chunk of the adjoint step:  OUT = IN + hstep * J(LIN; theta)^T IN (+ RHS), from the cache.
-// THT: parameter blocks whose matrices are stored transposed; TH: the original blocks.
-// With DT (gradient blocks of the chunk's layers) the chunk is a parameter-gradient pass instead:
-// the same backward chain with IN = lambda_{n+1}, every linear map and LayerNorm also emitting
-// hstep * (its parameter cotangent), and no state written (paper section 3.1: theta enters the
-// step only through h F, so dtheta_n = h (dF/dtheta_n (Z_n))^T lambda_{n+1}).
+// What a run of transposed steps does besides advancing the state.  Parameter gradients (paper section 3.1:
+// theta enters the step only through h F, so dtheta_n = h (dF/dtheta_n (Z_n))^T lambda_{n+1}) come from the same
+// backward chain with IN = lambda_{n+1}: adjoint_chunk leaves the cotangents of every linear map's output in its
+// work buffers and param_grads_chunk turns them into the layers' gradient blocks.
 struct GradPass {
   const Params* DT = nullptr;      // gradient blocks of the chunk's layers, or null
   float* dE_all = nullptr;         // cross-attention decoder: [layer slot, Tm, d] fp32 memory-gradient terms, or null
@@ -543,57 +544,32 @@ struct CastShadow {
 };
 inline CastShadow shift(CastShadow c, int c0) { c.in_slots = shift(c.in_slots, c0); c.out_slots = shift(c.out_slots, c0); return c; }
 
+// One chunk of the adjoint step:  OUT = IN + hstep * J(LIN; theta)^T IN (+ RHS), from the cache.
+// THT: parameter blocks whose matrices are stored transposed; TH: the original blocks.
+// With gp the chunk also serves the parameter gradients (see GradPass): its cotangents stay in slots `loc` of
+// the work buffers, and without gp->write_state no state is written.
 int adjoint_chunk(Engine& E, int n, Rows IN, Rows OUT, Rows RHS, Params TH, Params THT, Rows LIN, Slots cs,
                   float hstep, const GradPass* gp = nullptr, const StackedDec* sd = nullptr,
-                  const CastShadow* sh = nullptr) {
-  const Params* DT = gp ? gp->DT : nullptr;
+                  const CastShadow* sh = nullptr, Slots loc = Slots{0, 1}) {
   const int T = E.T, d = E.d, f = E.f;
   const auto& L = E.lay;
-  const Slots loc = {0, 1};
   const size_t esz = E.esz;
 
   const void* cbuf = E.cb;                 // operand-type copy of the inputs
   Slots cbs = loc;
   if (sh && sh->have_inputs(n)) { cbuf = sh->in; cbs = sh->in_slots; }
   else HIPCHK(launch_cast_rows(n, E.Td(), IN, E.cb, E.Td(), loc, E.bf16, E.st));
-  LnFwdArgs lf;
-  LnParamArgs lp;
-  memset(&lf, 0, sizeof(lf));
-  memset(&lp, 0, sizeof(lp));
-  if (DT) {
-    // m = GELU(z) W2^T + b2
-    STCHK(linear_param_grads(E, n, cbuf, E.Td(), cbs, d, E.c_zraw, (long)T * f, cs, f, true, *DT, MGRIT_P_W2,
-                             MGRIT_P_B2, hstep));
-    lf.n_groups = n; lf.T = T; lf.d = d; lf.X = LIN; lf.P = TH; lf.eps = E.md.ln_eps;
-    lf.out = E.u; lf.out_slot_stride = E.Td(); lf.out_slots = loc;
-    lp.n_groups = n; lp.T = T; lp.d = d; lp.X = LIN; lp.out = *DT; lp.scale = hstep; lp.eps = E.md.ln_eps;
-    lp.dy = E.du; lp.dy_slot_stride = E.Td(); lp.dy_slots = loc;
-  }
 
   // dz = (c W2) * gelu'(z)        [T,d] x [d,f]: transposed W2 is [f,d]; gelu'(z) comes from the cache
   GemmArgs g = gemm_base(n, T, f, d, cbuf, E.Td(), cbs, THT, L.offset[MGRIT_P_W2], -1);
   g.out = E.dz; g.out_slot_stride = (long)T * f; g.out_slots = loc;
   g.aux = E.c_z; g.aux_slot_stride = (long)T * f; g.aux_slots = cs;
   HIPCHK(launch_gemm(g, EPI_DGELU, E.bf16, E.st));
-  if (DT) {
-    // z = LN2(X + ybar) W1^T + b1
-    lf.xp = E.c_xin; lf.xp_slot_stride = E.Td(); lf.xp_slots = cs;
-    lf.gamma_off = L.offset[MGRIT_P_LN2_G]; lf.beta_off = L.offset[MGRIT_P_LN2_B];
-    HIPCHK(launch_ln_fwd(lf, E.bf16, E.st));
-    STCHK(linear_param_grads(E, n, E.dz, (long)T * f, loc, f, E.u, E.Td(), loc, d, false, *DT, MGRIT_P_W1,
-                             MGRIT_P_B1, hstep));
-  }
 
   // du2 = dz W1                   [T,f] x [f,d]: transposed W1 is [d,f]
   g = gemm_base(n, T, d, f, E.dz, (long)T * f, loc, THT, L.offset[MGRIT_P_W1], -1);
   g.out = E.du; g.out_slot_stride = E.Td(); g.out_slots = loc;
   HIPCHK(launch_gemm(g, EPI_STORE, E.bf16, E.st));
-
-  if (DT) {
-    lp.xp = E.c_xin; lp.xp_slot_stride = E.Td(); lp.xp_slots = cs;
-    lp.gamma_off = E.glay.offset[MGRIT_P_LN2_G]; lp.beta_off = E.glay.offset[MGRIT_P_LN2_B];
-    HIPCHK(launch_ln_param_grad(lp, E.gpart, E.bf16, E.st));
-  }
 
   // dX' = LN2^T du2 ;  ds = c + dX'
   LnBwdArgs lb;
@@ -604,17 +580,14 @@ int adjoint_chunk(Engine& E, int n, Rows IN, Rows OUT, Rows RHS, Params TH, Para
   lb.P = TH; lb.gamma_off = L.offset[MGRIT_P_LN2_G];
   lb.out_f32 = E.dxin; lb.of_slot_stride = E.Td(); lb.of_slots = loc;
   lb.cop = cbuf; lb.cop_slot_stride = E.Td(); lb.cop_slots = cbs;
-  lb.out_op = E.ds; lb.oo_slot_stride = E.Td(); lb.oo_slots = loc;
+  const bool cross = E.md.arch == MGRIT_ARCH_CROSS;
+  lb.out_op = cross ? E.dsc : E.ds; lb.oo_slot_stride = E.Td(); lb.oo_slots = loc;
   HIPCHK(launch_ln_bwd(lb, E.bf16, E.st));
 
-  if (E.md.arch == MGRIT_ARCH_CROSS) {
-    // Here ds = c + dx2 is the cotangent of ybar = s + CA(LN3(Y + s), E); dxin = dx2.
-    // c = o_c Wo_c^T + bo_c
-    if (DT)
-      STCHK(linear_param_grads(E, n, E.ds, E.Td(), loc, d, E.c_oc, E.Td(), cs, d, false, *DT, MGRIT_P_WO_C,
-                               MGRIT_P_BO_C, hstep));
-    // do_c = ds Wo_c
-    g = gemm_base(n, T, d, d, E.ds, E.Td(), loc, THT, L.offset[MGRIT_P_WO_C], -1);
+  if (cross) {
+    // Here dsc = c + dx2 is the cotangent of ybar = s + CA(LN3(Y + s), E); dxin = dx2.
+    // do_c = dsc Wo_c
+    g = gemm_base(n, T, d, d, E.dsc, E.Td(), loc, THT, L.offset[MGRIT_P_WO_C], -1);
     g.out = E.da; g.out_slot_stride = E.Td(); g.out_slots = loc;
     HIPCHK(launch_gemm(g, EPI_STORE, E.bf16, E.st));
     // cross-attention backward: lambda needs dQ only; dK, dV feed the gradients of Wkv_c and of the memory
@@ -629,50 +602,28 @@ int adjoint_chunk(Engine& E, int n, Rows IN, Rows OUT, Rows RHS, Params TH, Para
     ac.o = E.c_oc; ac.o_row_stride = d; ac.o_slot_stride = E.Td(); ac.o_slots = cs;
     ac.lse = E.c_lsec; ac.lse_slot_stride = (long)E.md.batch * E.H * E.md.seq; ac.lse_slots = cs;
     ac.dO = E.da; ac.do_row_stride = d; ac.do_slot_stride = E.Td(); ac.do_slots = loc;
-    ac.dq = E.dqkv; ac.dk = nullptr; ac.dv = nullptr;
-    ac.dqkv_row_stride = d; ac.dqkv_slot_stride = (long)T * 3 * d; ac.dqkv_slots = loc;
+    ac.dq = E.dqc; ac.dk = nullptr; ac.dv = nullptr;
+    ac.dqkv_row_stride = d; ac.dqkv_slot_stride = E.Td(); ac.dqkv_slots = loc;
     if (gp || sd) {
       ac.dk = E.dkvc; ac.dv = (char*)E.dkvc + (size_t)d * esz;
       ac.dkv_row_stride = 2 * d; ac.dkv_slot_stride = (long)E.Tm * 2 * d;
     }
     ac.D = E.Dbuf; ac.D_slot_stride = (long)E.md.batch * E.H * E.md.seq; ac.D_slots = loc;
     HIPCHK(launch_attn_bwd(ac, E.bf16, E.st));
-    if (DT) {
-      // q_c = LN3(Y + s) Wq_c^T + bq_c ;  [k_c | v_c] = E Wkv_c^T + bkv_c
-      lf.xp = E.c_x3; lf.xp_slot_stride = E.Td(); lf.xp_slots = cs;
-      lf.gamma_off = L.offset[MGRIT_P_LN3_G]; lf.beta_off = L.offset[MGRIT_P_LN3_B];
-      HIPCHK(launch_ln_fwd(lf, E.bf16, E.st));
-      STCHK(linear_param_grads(E, n, E.dqkv, (long)T * 3 * d, loc, d, E.u, E.Td(), loc, d, false, *DT,
-                               MGRIT_P_WQ_C, MGRIT_P_BQ_C, hstep));
-      if (sd) HIPCHK(launch_cast_rows(n, (long)E.Tm * d, sd->MEM, E.membG, (long)E.Tm * d, loc, E.bf16, E.st));
-      STCHK(linear_param_grads(E, n, E.dkvc, (long)E.Tm * 2 * d, loc, 2 * d, sd ? E.membG : E.memb,
-                               sd ? (long)E.Tm * d : 0, loc, d, false, *DT, MGRIT_P_WKV_C, MGRIT_P_BKV_C, hstep, E.Tm));
-    }
     if (sd && (!gp || gp->write_state)) {
       // lambda_X <- lambda_X + hstep * [dK | dV] Wkv_c (+ rhs)    [Tm,2d] x [2d,d]: transposed Wkv_c is [d,2d]
       g = gemm_base(n, E.Tm, d, 2 * d, E.dkvc, (long)E.Tm * 2 * d, loc, THT, L.offset[MGRIT_P_WKV_C], -1);
       g.X = sd->INX; g.OUT = sd->OUTX; g.RHS = sd->RHSX; g.hstep = hstep;
       HIPCHK(launch_gemm(g, EPI_RESID_OUTER, E.bf16, E.st));
     }
-    if (gp && gp->dE_all) {
-      // this layer's term of dL/dE:  hstep * [dK | dV] Wkv_c       [Tm,2d] x [2d,d]: transposed Wkv_c is [d,2d]
-      g = gemm_base(n, E.Tm, d, 2 * d, E.dkvc, (long)E.Tm * 2 * d, loc, THT, L.offset[MGRIT_P_WKV_C], -1);
-      g.out = gp->dE_all; g.out_slot_stride = (long)E.Tm * d; g.out_slots = gp->dE_slots; g.hstep = hstep;
-      HIPCHK(launch_gemm(g, EPI_STORE_F32, E.bf16, E.st));
-    }
     // du3 = dq_c Wq_c
-    g = gemm_base(n, T, d, d, E.dqkv, (long)T * 3 * d, loc, THT, L.offset[MGRIT_P_WQ_C], -1);
-    g.out = E.du; g.out_slot_stride = E.Td(); g.out_slots = loc;
+    g = gemm_base(n, T, d, d, E.dqc, E.Td(), loc, THT, L.offset[MGRIT_P_WQ_C], -1);
+    g.out = E.du3; g.out_slot_stride = E.Td(); g.out_slots = loc;
     HIPCHK(launch_gemm(g, EPI_STORE, E.bf16, E.st));
-    if (DT) {
-      lp.xp = E.c_x3; lp.xp_slot_stride = E.Td(); lp.xp_slots = cs;
-      lp.gamma_off = E.glay.offset[MGRIT_P_LN3_G]; lp.beta_off = E.glay.offset[MGRIT_P_LN3_B];
-      HIPCHK(launch_ln_param_grad(lp, E.gpart, E.bf16, E.st));
-    }
     // dx3 = LN3^T du3 at Y + s;  dxin <- dx2 + dx3 (in place);  ds <- c + dx2 + dx3
     memset(&lb, 0, sizeof(lb));
     lb.n_groups = n; lb.T = T; lb.d = d; lb.eps = E.md.ln_eps;
-    lb.dy = E.du; lb.dy_slot_stride = E.Td(); lb.dy_slots = loc;
+    lb.dy = E.du3; lb.dy_slot_stride = E.Td(); lb.dy_slots = loc;
     lb.X = LIN; lb.xp = E.c_x3; lb.xp_slot_stride = E.Td(); lb.xp_slots = cs;
     lb.P = TH; lb.gamma_off = L.offset[MGRIT_P_LN3_G];
     lb.add = E.dxin; lb.add_slot_stride = E.Td(); lb.add_slots = loc;
@@ -680,11 +631,6 @@ int adjoint_chunk(Engine& E, int n, Rows IN, Rows OUT, Rows RHS, Params TH, Para
     lb.C = IN; lb.out_op = E.ds; lb.oo_slot_stride = E.Td(); lb.oo_slots = loc;
     HIPCHK(launch_ln_bwd(lb, E.bf16, E.st));
   }
-
-  // s = o Wo^T + bo
-  if (DT)
-    STCHK(linear_param_grads(E, n, E.ds, E.Td(), loc, d, E.c_o, E.Td(), cs, d, false, *DT, MGRIT_P_WO,
-                             MGRIT_P_BO, hstep));
 
   // da = ds Wo
   g = gemm_base(n, T, d, d, E.ds, E.Td(), loc, THT, L.offset[MGRIT_P_WO], -1);
@@ -708,37 +654,78 @@ int adjoint_chunk(Engine& E, int n, Rows IN, Rows OUT, Rows RHS, Params TH, Para
   at.D = E.Dbuf; at.D_slot_stride = (long)E.md.batch * E.H * E.md.seq; at.D_slots = loc;
   HIPCHK(launch_attn_bwd(at, E.bf16, E.st));
 
-  if (DT) {
-    // qkv = LN1(X) Wqkv^T + bqkv
-    lf.xp = nullptr;
-    lf.gamma_off = L.offset[MGRIT_P_LN1_G]; lf.beta_off = L.offset[MGRIT_P_LN1_B];
-    HIPCHK(launch_ln_fwd(lf, E.bf16, E.st));
-    STCHK(linear_param_grads(E, n, E.dqkv, (long)T * 3 * d, loc, 3 * d, E.u, E.Td(), loc, d, false, *DT,
-                             MGRIT_P_WQKV, MGRIT_P_BQKV, hstep));
-  }
-
   // du1 = dqkv Wqkv               [T,3d] x [3d,d]: transposed Wqkv is [d,3d]
   g = gemm_base(n, T, d, 3 * d, E.dqkv, (long)T * 3 * d, loc, THT, L.offset[MGRIT_P_WQKV], -1);
-  g.out = E.du; g.out_slot_stride = E.Td(); g.out_slots = loc;
+  g.out = E.du1; g.out_slot_stride = E.Td(); g.out_slots = loc;
   HIPCHK(launch_gemm(g, EPI_STORE, E.bf16, E.st));
-
-  if (DT) {
-    lp.xp = nullptr;
-    lp.gamma_off = E.glay.offset[MGRIT_P_LN1_G]; lp.beta_off = E.glay.offset[MGRIT_P_LN1_B];
-    HIPCHK(launch_ln_param_grad(lp, E.gpart, E.bf16, E.st));
-  }
   if (gp && !gp->write_state) return MGRIT_OK;           // a pure gradient pass writes no state
 
   // dX = dX' + LN1^T du1 ;  OUT = c + hstep dX (+ RHS)
   memset(&lb, 0, sizeof(lb));
   lb.n_groups = n; lb.T = T; lb.d = d; lb.eps = E.md.ln_eps;
-  lb.dy = E.du; lb.dy_slot_stride = E.Td(); lb.dy_slots = loc;
+  lb.dy = E.du1; lb.dy_slot_stride = E.Td(); lb.dy_slots = loc;
   lb.xhat = E.c_xh1; lb.xhat_slot_stride = E.Td(); lb.xhat_slots = cs; lb.rstd = E.c_rs1;
   lb.P = TH; lb.gamma_off = L.offset[MGRIT_P_LN1_G];
   lb.add = E.dxin; lb.add_slot_stride = E.Td(); lb.add_slots = loc;
   lb.C = IN; lb.OUT = OUT; lb.RHS = RHS; lb.hstep = hstep; lb.rhs_sign = E.rhs_sign;
   if (sh && sh->out) { lb.out_cast = sh->out; lb.oc_slot_stride = E.Td(); lb.oc_slots = sh->out_slots; }
   HIPCHK(launch_ln_bwd(lb, E.bf16, E.st));
+  return MGRIT_OK;
+}
+
+// Gradient blocks (and memory-gradient terms) of n layers from the cotangents that adjoint_chunk left in slots
+// 0 .. n-1 of the work buffers and from the cached inputs of the linear maps (slots cs).  cbuf: the operand-type
+// copy of lambda_{n+1} that adjoint_chunk started from (E.cb unless the shadow array held it).
+//   dW = hstep * dY^T U, db = hstep * sum of dY  for each linear map  y = u W^T + b
+int param_grads_chunk(Engine& E, int n, Params THT, Rows LIN, Slots cs, float hstep, const GradPass& gp,
+                      const void* cbuf, Slots cbs, const StackedDec* sd = nullptr) {
+  const int T = E.T, d = E.d, f = E.f;
+  const Slots loc = {0, 1};
+  const bool cross = E.md.arch == MGRIT_ARCH_CROSS;
+  if (gp.dE_all) {
+    // this layer's term of dL/dE:  hstep * [dK | dV] Wkv_c       [Tm,2d] x [2d,d]: transposed Wkv_c is [d,2d]
+    GemmArgs g = gemm_base(n, E.Tm, d, 2 * d, E.dkvc, (long)E.Tm * 2 * d, loc, THT, E.lay.offset[MGRIT_P_WKV_C], -1);
+    g.out = gp.dE_all; g.out_slot_stride = (long)E.Tm * d; g.out_slots = gp.dE_slots; g.hstep = hstep;
+    HIPCHK(launch_gemm(g, EPI_STORE_F32, E.bf16, E.st));
+  }
+  if (!gp.DT) return MGRIT_OK;
+  GemmTnArgs t;
+  memset(&t, 0, sizeof(t));
+  t.n_groups = n; t.out = *gp.DT; t.scale = hstep; t.partial = E.gpart;
+  auto linear = [&](const void* dY, Slots dy_slots, int out_dim, const void* U, long u_stride, Slots u_slots,
+                    int in_dim, int tokens, int w_id, int b_id) {
+    t.M = out_dim; t.N = in_dim; t.K = tokens;
+    t.A = dY; t.a_slot_stride = (long)tokens * out_dim; t.a_slots = dy_slots;
+    t.B = U; t.b_slot_stride = u_stride; t.b_slots = u_slots;
+    t.w_off = E.glay.offset[w_id]; t.b_off = E.glay.offset[b_id];
+    return launch_gemm_tn(t, E.bf16, E.st);
+  };
+  // m = gelu(z) W2^T + b2 ;  z = u2 W1^T + b1 ;  s = o Wo^T + bo ;  qkv = u1 Wqkv^T + bqkv
+  HIPCHK(linear(cbuf, cbs, d, E.c_act, (long)T * f, cs, f, T, MGRIT_P_W2, MGRIT_P_B2));
+  HIPCHK(linear(E.dz, loc, f, E.c_u2, E.Td(), cs, d, T, MGRIT_P_W1, MGRIT_P_B1));
+  HIPCHK(linear(E.ds, loc, d, E.c_o, E.Td(), cs, d, T, MGRIT_P_WO, MGRIT_P_BO));
+  HIPCHK(linear(E.dqkv, loc, 3 * d, E.c_u1, E.Td(), cs, d, T, MGRIT_P_WQKV, MGRIT_P_BQKV));
+  if (cross) {
+    // c = o_c Wo_c^T + bo_c ;  q_c = u3 Wq_c^T + bq_c ;  [k_c | v_c] = E Wkv_c^T + bkv_c
+    HIPCHK(linear(E.dsc, loc, d, E.c_oc, E.Td(), cs, d, T, MGRIT_P_WO_C, MGRIT_P_BO_C));
+    HIPCHK(linear(E.dqc, loc, d, E.c_u3, E.Td(), cs, d, T, MGRIT_P_WQ_C, MGRIT_P_BQ_C));
+    if (sd) HIPCHK(launch_cast_rows(n, (long)E.Tm * d, sd->MEM, E.membG, (long)E.Tm * d, loc, E.bf16, E.st));
+    HIPCHK(linear(E.dkvc, loc, 2 * d, sd ? E.membG : E.memb, sd ? (long)E.Tm * d : 0, loc, d, E.Tm, MGRIT_P_WKV_C,
+                  MGRIT_P_BKV_C));
+  }
+  LnParamArgs lp;
+  memset(&lp, 0, sizeof(lp));
+  lp.n_groups = n; lp.T = T; lp.d = d; lp.X = LIN; lp.out = *gp.DT; lp.scale = hstep; lp.eps = E.md.ln_eps;
+  auto norm = [&](const void* dy, const float* xp, int g_id, int b_id) {
+    LnParamItem& it = lp.item[lp.n_items++];
+    it.dy = dy; it.dy_slot_stride = E.Td(); it.dy_slots = loc;
+    it.xp = xp; it.xp_slot_stride = E.Td(); it.xp_slots = cs;
+    it.gamma_off = E.glay.offset[g_id]; it.beta_off = E.glay.offset[b_id];
+  };
+  norm(E.du1, nullptr, MGRIT_P_LN1_G, MGRIT_P_LN1_B);
+  norm(E.du, E.c_xin, MGRIT_P_LN2_G, MGRIT_P_LN2_B);
+  if (cross) norm(E.du3, E.c_x3, MGRIT_P_LN3_G, MGRIT_P_LN3_B);
+  HIPCHK(launch_ln_param_grad(lp, E.gpart, E.bf16, E.st));
   return MGRIT_OK;
 }
 
@@ -800,8 +787,12 @@ int adjoint_groups(Engine& E, Engine* E2, int G, Rows IN, Rows OUT, Rows RHS, Pa
       STCHK(forward_chunk(L, n, shift(LIN, c0), NO_ROWS, NO_ROWS, shift(TH, c0), 0.f, 1, slots,
                           sd ? s.MEM : NO_ROWS));
     }
-    return adjoint_chunk(L, n, shift(IN, c0), shift(OUT, c0), shift(RHS, c0), shift(TH, c0), shift(THT, c0),
-                         shift(LIN, c0), slots, hstep, emit ? &gp : nullptr, sd ? &s : nullptr, sh ? &shc : nullptr);
+    STCHK(adjoint_chunk(L, n, shift(IN, c0), shift(OUT, c0), shift(RHS, c0), shift(TH, c0), shift(THT, c0),
+                        shift(LIN, c0), slots, hstep, emit ? &gp : nullptr, sd ? &s : nullptr, sh ? &shc : nullptr));
+    if (!emit) return (int)MGRIT_OK;
+    const bool shadow = sh && shc.have_inputs(n);
+    return param_grads_chunk(L, n, shift(THT, c0), shift(LIN, c0), slots, hstep, gp, shadow ? shc.in : L.cb,
+                             shadow ? shc.in_slots : Slots{0, 1}, sd ? &s : nullptr);
   });
 }
 
@@ -822,8 +813,10 @@ int gradient_groups(Engine& E, Engine* E2, int G, Rows IN, Params TH, Params THT
       STCHK(forward_chunk(L, n, shift(LIN, c0), NO_ROWS, NO_ROWS, shift(TH, c0), 0.f, 1, slots,
                           sd ? s.MEM : NO_ROWS));
     }
-    return adjoint_chunk(L, n, shift(IN, c0), NO_ROWS, NO_ROWS, shift(TH, c0), shift(THT, c0), shift(LIN, c0),
-                         slots, hstep, &gp, sd ? &s : nullptr);
+    STCHK(adjoint_chunk(L, n, shift(IN, c0), NO_ROWS, NO_ROWS, shift(TH, c0), shift(THT, c0), shift(LIN, c0),
+                        slots, hstep, &gp, sd ? &s : nullptr));
+    return param_grads_chunk(L, n, shift(THT, c0), shift(LIN, c0), slots, hstep, gp, L.cb, Slots{0, 1},
+                             sd ? &s : nullptr);
   });
 }
 
@@ -1143,7 +1136,65 @@ struct Driver {
     return st;
   }
 
+  // Serial adjoint with parameter gradients: every step is one layer, whose launches leave much of the chip idle
+  // and form one dependent chain, while nothing in the chain waits for the gradients.  So the chain runs on the
+  // caller's stream with its cotangents going to successive slots of the work buffers, and after every Gc layers
+  // the helper lane turns them into gradients in launches over all of them; the two sets of work buffers (one per
+  // lane) alternate.  Same kernels on the same data as layer by layer.  BERT shape, 64 layers: a layer's gradients
+  // in the chain cost 190 us next to 330 us of chain.
+  int run_serial_emitting() {
+    AuxStream& a = aux_stream();
+    const int status = serial_emitting_chain();
+    const hipError_t e1 = hipEventRecord(a.join, E2->st);   // joined whatever happened (see run_chunks)
+    const hipError_t e2 = e1 == hipSuccess ? hipStreamWaitEvent(E->st, a.join, 0) : e1;
+    STCHK(status);
+    HIPCHK(e2);
+    return MGRIT_OK;
+  }
+  int serial_emitting_chain() {
+    AuxStream& a = aux_stream();
+    const int B = E->Gc;
+    Engine chain[2] = {*E, *E2}, grads[2] = {*E, *E2};
+    chain[1].st = E->st;
+    grads[0].st = E2->st;
+    HIPCHK(hipEventRecord(a.fork, E->st));
+    HIPCHK(hipStreamWaitEvent(E2->st, a.fork, 0));
+    const float hstep = h;
+    for (int j0 = 0, k = 0; j0 < N; j0 += B, ++k) {
+      const int b = k & 1, n = N - j0 < B ? N - j0 : B;
+      if (k >= 2) HIPCHK(hipStreamWaitEvent(E->st, a.pipe[b], 0));       // this set's last gradients are done
+      GradPass gp;
+      gp.write_state = true;
+      CastShadow sh;
+      sh.in = sh.out = shadow; sh.valid = shadow_valid.data();
+      for (int i = 0; i < n; ++i) {
+        const int j = j0 + i, layer = N - 1 - j;
+        ++evals; ++sweeps;
+        sh.in_slots = Slots{j, 1}; sh.out_slots = Slots{j + 1, 1};
+        STCHK(adjoint_chunk(chain[b], 1, W(0, j, 1), W(0, j + 1, 1), NO_ROWS, Params{(const void* const*)tabTh, layer, -1},
+                            Params{(const void* const*)tabThT, layer, -1}, Rows{(const void* const*)tabZ, layer, -1},
+                            Slots{layer, -1}, hstep, &gp, nullptr, &sh, Slots{i, 1}));
+        shadow_valid[(size_t)j + 1] = 1;
+      }
+      HIPCHK(hipEventRecord(a.pipe[2 + b], E->st));
+      HIPCHK(hipStreamWaitEvent(E2->st, a.pipe[2 + b], 0));
+      const int layer = N - 1 - j0;
+      const Params DT = {(const void* const*)tabDT, layer, -1};
+      gp.DT = tabDT ? &DT : nullptr;
+      gp.dE_all = dE_all;
+      gp.dE_slots = Slots{layer, -1};
+      STCHK(param_grads_chunk(grads[b], n, Params{(const void* const*)tabThT, layer, -1},
+                              Rows{(const void* const*)tabZ, layer, -1}, Slots{layer, -1}, hstep, gp, shadow,
+                              Slots{j0, 1}));
+      HIPCHK(hipEventRecord(a.pipe[b], E2->st));
+    }
+    emitted = true;
+    return MGRIT_OK;
+  }
+
   int run(int iters) {
+    if ((L == 1 || cf == 1) && adjoint && want_grads && E && E2 && !Ed && shadow && shadow_valid[0] && !E->recompute)
+      return run_serial_emitting();
     if (L == 1 || cf == 1) {
       emit_now = want_grads;
       cache_now = fill_cache;
@@ -1187,12 +1238,12 @@ int make_plan(Plan& P, const mgrit_model_desc* md, const mgrit_opts* op, int mod
   int gc = max_groups(md, M0);
   const int widest = adjoint ? (N > M0 ? N : M0) : M0;      // the cache pass batches over all N layers
   if (gc > widest) gc = widest;
-  E.keep_z = mode == 2;
+  E.keep_inputs = mode == 2;
   E.recompute = adjoint && !g_adjoint_cache;
   if (adjoint) E.carve_adjoint(b, gc, N); else E.carve_forward(b, gc);
   if (!adjoint && share_ws) {
     Bump shared(share_ws);
-    E.keep_z = share_mode == 2;
+    E.keep_inputs = share_mode == 2;
     E.carve_cache(shared, N);
     P.D.fill_cache = true;
   }
@@ -1210,13 +1261,8 @@ int make_plan(Plan& P, const mgrit_model_desc* md, const mgrit_opts* op, int mod
   if (mode == 2) {
     P.tabDT = b.take<void*>(N);
     if (md->arch == MGRIT_ARCH_CROSS) P.dE_all = b.take<float>((size_t)N * E.Tm * E.d);
-    for (Engine* L : {&E, P.two_lanes ? &P.E2 : nullptr}) {
-      if (!L) continue;
-      L->carve_grad_work(b);
-      if (ws && launch_fill_table(L->tabTB, static_cast<char*>(L->tB), L->tB_stride() * (long)L->esz, L->Gc, st) !=
-                    hipSuccess)
-        return MGRIT_HIP_ERROR;
-    }
+    for (Engine* L : {&E, P.two_lanes ? &P.E2 : nullptr})
+      if (L) L->carve_grad_work(b);
   }
   if (adjoint) {
     D.shadow = b.take_bytes((size_t)(N + 1) * E.T * E.d * E.esz);
@@ -1658,7 +1704,7 @@ int make_stacked_plan(StackedPlan& P, const mgrit_model_desc* md, const mgrit_op
   int gc = max_groups(md, M0);
   const int widest = adjoint ? (N > M0 ? N : M0) : M0;
   if (gc > widest) gc = widest;
-  P.Ee.keep_z = P.Ed.keep_z = mode == 2;
+  P.Ee.keep_inputs = P.Ed.keep_inputs = mode == 2;
   P.Ee.recompute = P.Ed.recompute = adjoint && !g_adjoint_cache;
   if (adjoint) { P.Ee.carve_adjoint(b, gc, n_enc); P.Ed.carve_adjoint(b, gc, n_dec); }
   else { P.Ee.carve_forward(b, gc); P.Ed.carve_forward(b, gc); }
@@ -1670,7 +1716,7 @@ int make_stacked_plan(StackedPlan& P, const mgrit_model_desc* md, const mgrit_op
     int gca = max_groups(md, M0);
     if (gca > widest_a) gca = widest_a;
     Engine te = P.Ee, td = P.Ed;
-    te.keep_z = td.keep_z = share_mode == 2;
+    te.keep_inputs = td.keep_inputs = share_mode == 2;
     te.recompute = td.recompute = false;
     te.carve_adjoint(shared, gca, n_enc);
     td.carve_adjoint(shared, gca, n_dec);
@@ -1694,13 +1740,8 @@ int make_stacked_plan(StackedPlan& P, const mgrit_model_desc* md, const mgrit_op
   }
   if (mode == 2) {
     P.tabDT = b.take<void*>(N);
-    for (Engine* L : {&P.Ee, &P.Ed, P.two_lanes ? &P.Ee2 : nullptr, P.two_lanes ? &P.Ed2 : nullptr}) {
-      if (!L) continue;
-      L->carve_grad_work(b);
-      if (ws && launch_fill_table(L->tabTB, static_cast<char*>(L->tB), L->tB_stride() * (long)L->esz, L->Gc, st) !=
-                    hipSuccess)
-        return MGRIT_HIP_ERROR;
-    }
+    for (Engine* L : {&P.Ee, &P.Ed, P.two_lanes ? &P.Ee2 : nullptr, P.two_lanes ? &P.Ed2 : nullptr})
+      if (L) L->carve_grad_work(b);
   }
   D.tabG.assign(D.L, nullptr);
   if (!serial) {
