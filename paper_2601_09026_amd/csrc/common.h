@@ -122,27 +122,28 @@ template <typename V> __device__ __forceinline__ V ld_stream(const V* p) {
 // ---------------------------------------------------------------------------
 // Transposed fragments from row-major LDS tiles (ds_read_b64_tr_b16, bf16): in each group of 16 lanes, lane l
 // addresses the 8 bytes at columns 4*(l%4).. of row l/4 of a 4 x 16 block and receives column l%16 of its 4 rows.
-// The reads are inline assembly because the compiler's wait-count pass puts a wait for every outstanding
-// global-to-LDS load before the builtin; their results are there after wait_lgkm() and pass through tr_value().
+// The restrict-qualified parameter matters: without it the compiler's wait-count pass takes the read for one that
+// may alias the global-to-LDS loads in flight and waits for all of them first, which empties the ring of k-tiles.
+// The kernels order the two themselves (counted waits and block barriers).
 // ---------------------------------------------------------------------------
 typedef __attribute__((__vector_size__(4 * sizeof(short)))) short s16x4;
 typedef __attribute__((__vector_size__(8 * sizeof(short)))) short s16x8;
+typedef __attribute__((address_space(3))) unsigned char lds_byte;
 struct TrFrag { s16x4 lo, hi; };           // 4 + 4 consecutive reduction indices of this lane's column
-__device__ __forceinline__ unsigned lds_offset(const void* p) {
-  return (unsigned)(size_t)(__attribute__((address_space(3))) const void*)p;
+__device__ __forceinline__ s16x4 tr_read4(const lds_byte* __restrict__ p) {
+  typedef __attribute__((address_space(3))) s16x4* ptr;
+  return __builtin_amdgcn_ds_read_tr16_b64_v4i16((ptr)p);
 }
-template <int LO, int HI> __device__ __forceinline__ void tr_read(TrFrag& f, unsigned addr) {
-  static_assert(LO >= 0 && HI >= 0 && LO < 65536 && HI < 65536, "16-bit immediate offsets");
-  asm volatile("ds_read_b64_tr_b16 %0, %1 offset:%2" : "=v"(f.lo) : "v"(addr), "n"(LO));
-  asm volatile("ds_read_b64_tr_b16 %0, %1 offset:%2" : "=v"(f.hi) : "v"(addr), "n"(HI));
+template <int LO, int HI> __device__ __forceinline__ void tr_read(TrFrag& f, const lds_byte* p) {
+  f.lo = tr_read4(p + LO);
+  f.hi = tr_read4(p + HI);
 }
 __device__ __forceinline__ void wait_lgkm() {
   asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
   __builtin_amdgcn_sched_barrier(0);
 }
-// the fragment as an MFMA operand; ties the values to this point (after the wait) for the compiler
-__device__ __forceinline__ bf16x8 tr_value(TrFrag& f) {
-  asm volatile("" : "+v"(f.lo), "+v"(f.hi));
+// the fragment as an MFMA operand
+__device__ __forceinline__ bf16x8 tr_value(const TrFrag& f) {
   const s16x8 v = {f.lo[0], f.lo[1], f.lo[2], f.lo[3], f.hi[0], f.hi[1], f.hi[2], f.hi[3]};
   return __builtin_bit_cast(bf16x8, v);
 }

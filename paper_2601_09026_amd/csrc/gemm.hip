@@ -665,7 +665,7 @@ gemm_tn_mfma_kernel(const GemmTnArgs a, int tiles_m, int tiles_n, int splits, in
   // Fragments are read DIST k-steps ahead of their products (1 where a step is long enough to hide the LDS
   // latency, else 2); the step that first needs the next tile begins with its wait and barrier.
   constexpr int NM = TM * TN, RD = TM + TN, DIST = NM >= 8 ? 1 : 2, BUFS = DIST == 1 ? 2 : 4;
-  const unsigned lds0 = lds_offset(smem2);
+  const lds_byte* lds0 = (const lds_byte*)smem2;
   TrFrag fa[BUFS][TM], fb[BUFS][TN];
   auto read = [&](auto ks_tag, unsigned stage_off, int u) {
     constexpr int ks = decltype(ks_tag)::value, nb = ks % BUFS;
@@ -684,8 +684,6 @@ gemm_tn_mfma_kernel(const GemmTnArgs a, int tiles_m, int tiles_n, int splits, in
   // in between
   auto step = [&](auto ks_tag, auto loads_tag, unsigned read_stage, int stage, int pk0) {
     constexpr int ks = decltype(ks_tag)::value, cb = ks % BUFS, rks = (ks + DIST) % KS;
-    if constexpr (DIST == 2) { asm volatile("s_waitcnt lgkmcnt(%0)" ::"n"(2 * RD) : "memory"); __builtin_amdgcn_sched_barrier(0); }
-    else wait_lgkm();
     bf16x8 xa[TM], xb[TN];
 #pragma unroll
     for (int i = 0; i < TM; ++i) xa[i] = tr_value(fa[cb][i]);
