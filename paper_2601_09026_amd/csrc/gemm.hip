@@ -3,10 +3,10 @@
 // its own weight matrix (the layer of its coarse interval), found through the
 // parameter pointer table.
 //
-// Three kernels:
+// The kernels:
 //  * gemm_mfma    : bf16 operands, fp32 accumulate on the 32x32x16 MFMA of gfx950; operands
 //                   stream global -> LDS directly through a ring of k-tiles, see below.
-//  * gemm_f32_mfma: fp32 operands on the 32x32x2 fp32 MFMA (the fp32 configuration).
+//  * gemm_f32_mfma: fp32 operands on the 32x32x2 fp32 MFMA; gemm_f32_small: small and ragged launches on the 16x16x4.
 //  * gemm_simple  : any operand type and shape, LDS-tiled FMA.
 #include <type_traits>
 
@@ -562,6 +562,99 @@ gemm_f32_mfma_kernel(const GemmArgs a, int tiles_m, int tiles_n) {
 }
 
 // ---------------------------------------------------------------------------
+// fp32 MFMA kernel for launches that leave the kernel above fewer than two tiles per CU, and for ragged shapes:
+// 32x32 block tile, four wavefronts of 16x16 on the 16x16x4 fp32 MFMA, k-tiles of 64.  What bounds such launches is
+// one wavefront's serial chain, which a quarter tile on 32-cycle MFMAs makes four times shorter, and first touches:
+// two k-tiles are in LDS and two more on their way in registers, and the one barrier per k-tile waits for LDS only.
+// Both operands permute the reduction alike, so that a lane's 16-byte LDS read is its operand of four MFMAs; the
+// row pitch of 68 floats puts 16 rows on 16 distinct 16-byte slots.
+// Any M; N and K multiples of 4: rows and columns past the edge are clamped, chunks past K become zeros.
+// Whole layer steps on the kernel above and on this one: 512 wide, 100 tokens, one layer 135 -> 77 us, transposed
+// 286 -> 175; 512 wide, 4 x 512 tokens 248 -> 218 and 465 -> 416; 200 wide, 600 hidden, 129 tokens (the FMA kernel
+// before) 132 -> 50 and 239 -> 110.
+// ---------------------------------------------------------------------------
+template <int EPI, bool RAGGED>
+__global__ void __launch_bounds__(256)
+gemm_f32_small_kernel(const GemmArgs a, int tiles_n) {
+  constexpr int BT = 32, BKF = 64, LD = BKF + 4;
+  constexpr int CPR = BKF / 4, RPP = 256 / CPR;                  // 16-byte chunks per row; rows per pass of the block
+  static_assert(2 * RPP == BT, "two chunks of each operand per thread");
+  __shared__ __attribute__((aligned(16))) float As[2][BT * LD], Bs[2][BT * LD];
+  const int g = blockIdx.z;
+  const int tm = blockIdx.x / tiles_n, tn = blockIdx.x - tm * tiles_n;
+  const int m0 = tm * BT, n0 = tn * BT;
+  const float* A = reinterpret_cast<const float*>(a.A) + a.a_slots.of(g) * a.a_slot_stride;
+  const float* B = reinterpret_cast<const float*>(a.B.at(g) + a.b_off);
+  const int M = a.M, N = a.N, K = a.K, tiles_k = (K + BKF - 1) / BKF;
+  const int tid = threadIdx.x, wave = tid >> 6, lane = tid & 63, lr = lane & 15, lg = lane >> 4;
+  const int wm0 = (wave >> 1) * 16, wn0 = (wave & 1) * 16;
+  const int srow = tid / CPR, sk = tid % CPR * 4;
+  const float *ap[2], *bp[2];
+#pragma unroll
+  for (int u = 0; u < 2; ++u) {
+    const int am = m0 + srow + u * RPP, bn = n0 + srow + u * RPP;
+    ap[u] = A + (long)(am < M ? am : M - 1) * K;
+    bp[u] = B + (long)(bn < N ? bn : N - 1) * K;
+  }
+  struct Regs { f32x4 x[2], w[2]; };
+  auto load = [&](Regs& v, int kt) {
+    if (kt >= tiles_k) return;
+    int k = kt * BKF + sk;
+    if (RAGGED) k = k < K ? k : 0;
+#pragma unroll
+    for (int u = 0; u < 2; ++u) {
+      v.x[u] = *reinterpret_cast<const f32x4*>(ap[u] + k);
+      v.w[u] = *reinterpret_cast<const f32x4*>(bp[u] + k);
+    }
+  };
+  auto store = [&](const Regs& v, int kt, int buf) {
+    if (kt >= tiles_k) return;
+    const bool inside = !RAGGED || kt * BKF + sk < K;
+    const f32x4 z = {0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+    for (int u = 0; u < 2; ++u) {
+      *reinterpret_cast<f32x4*>(&As[buf][(srow + u * RPP) * LD + sk]) = inside ? v.x[u] : z;
+      *reinterpret_cast<f32x4*>(&Bs[buf][(srow + u * RPP) * LD + sk]) = inside ? v.w[u] : z;
+    }
+  };
+  f32x4 acc = {0.f, 0.f, 0.f, 0.f};
+  auto multiply = [&](int buf) {
+    const float* pa = &As[buf][(wm0 + lr) * LD + 4 * lg];
+    const float* pb = &Bs[buf][(wn0 + lr) * LD + 4 * lg];
+#pragma unroll
+    for (int k = 0; k < BKF; k += 16) {
+      const f32x4 x = *reinterpret_cast<const f32x4*>(pa + k), w = *reinterpret_cast<const f32x4*>(pb + k);
+#pragma unroll
+      for (int e = 0; e < 4; ++e) acc = __builtin_amdgcn_mfma_f32_16x16x4f32(w[e], x[e], acc, 0, 0, 0);
+    }
+  };
+  auto lds_barrier = [&] {                               // loads into registers stay in flight
+    asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
+    bare_barrier();
+  };
+  // k-tile kt in buffer kt % 2: buffer b is written again only after the barrier that ends its tile
+  Regs r0, r1;
+  load(r0, 0);
+  load(r1, 1);
+  store(r0, 0, 0);
+  load(r0, 2);
+  lds_barrier();
+  for (int kt = 0; kt < tiles_k; kt += 2) {
+    store(r1, kt + 1, 1);
+    load(r1, kt + 3);
+    multiply(0);
+    lds_barrier();
+    if (kt + 1 >= tiles_k) break;                        // uniform over the block
+    store(r0, kt + 2, 0);
+    load(r0, kt + 4);
+    multiply(1);
+    lds_barrier();
+  }
+  const int m = m0 + wm0 + lr, n = n0 + wn0 + 4 * lg;
+  if (m < M && n < N) epilogue4<EPI, float>(resolve_epi<float>(a, g, EPI), a.hstep, a.rhs_sign, N, m, n, acc);
+}
+
+// ---------------------------------------------------------------------------
 // Parameter gradients of a linear map:  dW_g[m,n] = scale * sum_t dY_g[t,m] U_g[t,n],  db_g[m] = scale *
 // sum_t dY_g[t,m], both operands packed token-major.  The reduction runs over the rows of both, so the
 // k-tiles are staged as they lie in memory ([token][feature], global -> LDS directly, the ring of the kernel
@@ -941,11 +1034,20 @@ static hipError_t launch_mfma(const GemmArgs& a, hipStream_t st) {
   return hipGetLastError();
 }
 
+// Two 64x64 tiles per CU are where the larger tile takes over: below, 32x32 tiles are faster throughout (1.02 to 2
+// times for whole steps), above they lose up to 15 % to fetching each operand twice as often (1024 wide, 12 layers
+// of 1024 tokens: 3420 us against 3776).  Ragged shapes have no other matrix-core kernel.
 template <int EPI>
 static hipError_t launch_f32_mfma(const GemmArgs& a, hipStream_t st) {
-  const int tiles_m = (a.M + 63) / 64, tiles_n = a.N / 64;
-  hipLaunchKernelGGL((gemm_f32_mfma_kernel<EPI>), dim3(tiles_m * tiles_n, 1, a.n_groups), dim3(256), 0, st, a,
-                     tiles_m, tiles_n);
+  const int tiles_m = (a.M + 63) / 64, tiles_n = (a.N + 63) / 64;
+  if (a.N % 64 == 0 && a.K % 16 == 0 && (long)tiles_m * tiles_n * a.n_groups >= 2 * compute_units()) {
+    hipLaunchKernelGGL((gemm_f32_mfma_kernel<EPI>), dim3(tiles_m * tiles_n, 1, a.n_groups), dim3(256), 0, st, a,
+                       tiles_m, tiles_n);
+    return hipGetLastError();
+  }
+  const dim3 grid((a.M + 31) / 32 * ((a.N + 31) / 32), 1, a.n_groups);
+  if (a.K % 64) hipLaunchKernelGGL((gemm_f32_small_kernel<EPI, true>), grid, dim3(256), 0, st, a, (a.N + 31) / 32);
+  else hipLaunchKernelGGL((gemm_f32_small_kernel<EPI, false>), grid, dim3(256), 0, st, a, (a.N + 31) / 32);
   return hipGetLastError();
 }
 
@@ -1039,8 +1141,8 @@ static hipError_t launch_epi(const GemmArgs& a, bool is_bf16, hipStream_t st) {
   const int cls = mfma_ok ? (a.n_groups > 1 ? PC_GEMM_MFMA : PC_GEMM_MFMA_SINGLE) + EPI : PC_GEMM_SIMPLE;
   ProfScope ps(cls, flops, gemm_bytes<EPI>(a, is_bf16 ? 2 : 4), st);
   if (!is_bf16) {
-    // fp32: the 32x32x2 fp32 MFMA where the shape allows it (whole 64-column tiles, whole 16-deep k-tiles)
-    if (!g_force_simple && a.N % 64 == 0 && a.K % 16 == 0) return launch_f32_mfma<EPI>(a, st);
+    // fp32: the matrix cores, with 16-byte accesses of both operands and of the epilogue's
+    if (!g_force_simple && a.N % 4 == 0 && a.K % 4 == 0) return launch_f32_mfma<EPI>(a, st);
     return launch_simple<float, EPI>(a, st);
   }
   if (!mfma_ok) return launch_simple<bf16, EPI>(a, st);

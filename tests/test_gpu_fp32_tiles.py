@@ -1,6 +1,6 @@
 """The fp32 matrix-core kernels where they can go wrong, against the CPU oracle: projections whose columns end
-inside a 64- or 128-wide tile and whose reductions end inside a 32-deep k-tile (down to 8 elements), one row and
-one row past a tile; attention (all fp32 heads, bf16 heads that are not 64 or 128 wide) at every padded head width,
+inside a 32- or 64-wide tile and whose reductions end inside a 64- or 32-deep k-tile (down to 8 elements), one row
+and one row past a tile; attention (all fp32 heads, bf16 heads that are not 64 or 128 wide) at every padded head width,
 sequences of one row, around 16-row parts, around 64-row tiles, over several tiles, and key counts unlike the query
 counts.  The attention cases run forward and adjoint; sequences up to 64 take the one-launch backward."""
 import pytest
@@ -17,8 +17,9 @@ pytestmark = pytest.mark.gpu
     (40, 2, 72, 1, 65, 2),         # one k-tile and 8 elements; one row past a 64-row tile
     (64, 4, 256, 2, 32, 4),        # whole tiles
     (200, 5, 600, 3, 43, 2),       # ragged columns and reductions, 129 rows
-    (320, 5, 320, 16, 256, 5),     # enough rows for the 128-wide tiles, ragged columns
-    (512, 8, 1024, 8, 256, 4),     # the same, whole tiles
+    (200, 5, 600, 16, 129, 4),     # enough rows for the 64-wide tiles, ragged in every direction
+    (320, 5, 320, 16, 256, 5),     # the same, whole tiles
+    (512, 8, 1024, 8, 256, 4),
 ])
 def test_projection_tiles_fp32(d, H, f, B, S, G):
     wl = make(wls.ARCH_CAUSAL, wls.DTYPE_F32, d=d, H=H, f=f, B=B, S=S)
