@@ -566,8 +566,11 @@ gemm_f32_mfma_kernel(const GemmArgs a, int tiles_m, int tiles_n) {
 // 32x32 block tile, four wavefronts of 16x16 on the 16x16x4 fp32 MFMA, k-tiles of 64.  What bounds such launches is
 // one wavefront's serial chain, which a quarter tile on 32-cycle MFMAs makes four times shorter, and first touches:
 // two k-tiles are in LDS and two more on their way in registers, and the one barrier per k-tile waits for LDS only.
-// Both operands permute the reduction alike, so that a lane's 16-byte LDS read is its operand of four MFMAs; the
-// row pitch of 68 floats puts 16 rows on 16 distinct 16-byte slots.
+// The fp32 MFMAs add their products one by one in the order of the reduction index, so with the operands in natural
+// order this kernel, the one above and the FMA kernel give the same bits, and which of them a launch takes (it depends
+// on how many layers share the launch) cannot show in a result.  Groups of 16 reduction indices lie in LDS as a
+// transposed 4 x 4, so that a lane's 16-byte read is its operand of four MFMAs in that order; with the row pitch of 68
+// floats the 16 rows of a read fall on 16 distinct 16-byte slots and the 4-byte writes of a wavefront on 64 banks.
 // Any M; N and K multiples of 4: rows and columns past the edge are clamped, chunks past K become zeros.
 // Whole layer steps on the kernel above and on this one: 512 wide, 100 tokens, one layer 135 -> 77 us, transposed
 // 286 -> 175; 512 wide, 4 x 512 tokens 248 -> 218 and 465 -> 416; 200 wide, 600 hidden, 129 tokens (the FMA kernel
@@ -589,6 +592,7 @@ gemm_f32_small_kernel(const GemmArgs a, int tiles_n) {
   const int tid = threadIdx.x, wave = tid >> 6, lane = tid & 63, lr = lane & 15, lg = lane >> 4;
   const int wm0 = (wave >> 1) * 16, wn0 = (wave & 1) * 16;
   const int srow = tid / CPR, sk = tid % CPR * 4;
+  const int spos = (sk & ~15) + (sk >> 2 & 3);                   // of 16 reduction indices, 4e + j is kept at 4j + e
   const float *ap[2], *bp[2];
 #pragma unroll
   for (int u = 0; u < 2; ++u) {
@@ -613,8 +617,12 @@ gemm_f32_small_kernel(const GemmArgs a, int tiles_n) {
     const f32x4 z = {0.f, 0.f, 0.f, 0.f};
 #pragma unroll
     for (int u = 0; u < 2; ++u) {
-      *reinterpret_cast<f32x4*>(&As[buf][(srow + u * RPP) * LD + sk]) = inside ? v.x[u] : z;
-      *reinterpret_cast<f32x4*>(&Bs[buf][(srow + u * RPP) * LD + sk]) = inside ? v.w[u] : z;
+      const f32x4 x = inside ? v.x[u] : z, w = inside ? v.w[u] : z;
+#pragma unroll
+      for (int j = 0; j < 4; ++j) {
+        As[buf][(srow + u * RPP) * LD + spos + 4 * j] = x[j];
+        Bs[buf][(srow + u * RPP) * LD + spos + 4 * j] = w[j];
+      }
     }
   };
   f32x4 acc = {0.f, 0.f, 0.f, 0.f};
