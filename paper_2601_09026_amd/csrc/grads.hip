@@ -29,27 +29,30 @@ hipError_t launch_sum_slots(const float* in, int n, long elems, float* out, floa
 // ---------------------------------------------------------------------------
 // LayerNorm parameter gradients: dgamma[c] = sum_rows dy[r,c] * xhat[r,c], dbeta[c] = sum_rows
 // dy[r,c], xhat recomputed from the LayerNorm input (state row + optional packed addend).
-// One wavefront per row, a lane keeps the partial sums of its own columns in registers; the four wavefronts
+// One wavefront per row, a lane keeps the partial sums of its own columns in registers; the wavefronts
 // of a block add theirs through LDS: partial[item][g][block] = [dgamma | dbeta] (2d floats), summed over the
 // blocks by the second kernel.  All LayerNorms of a layer chunk go into one pair of launches.  Bound by
-// reading its rows (10 bytes per element): 2 LayerNorms of one 4096 x 768 layer 28 us, of five layers 86 us
-// (512 partial rows per group and one launch per LayerNorm took 2 x 47 + 4 x 8 and 2 x 125 + 4 x 8 us).
+// reading its rows (10 bytes per element): 2 LayerNorms of one 4096 x 768 layer 20 + 5 us, of four layers
+// 74 + 6 us (blocks of four wavefronts, 1024 over the launch: 20 + 8 and 74 + 10; 512 partial rows per group and one
+// launch per LayerNorm: 2 x 47 + 4 x 8 us for the one layer).
 // ---------------------------------------------------------------------------
 constexpr int LNP_MAXV = 8;         // d <= 2048
+constexpr int LNP_WAVES = 8;        // per block
 
-// blocks per (item, group): enough for a few wavefronts per SIMD, at least 4 rows per wavefront
-static int lnp_blocks(int n_groups, int T, int n_items) {
-  const int want = 1024 / (n_groups * n_items), most = (T + 15) / 16;
-  const int b = want < 32 ? 32 : want;
-  return b < most ? b : most;
+// Blocks per (item, group): the two LayerNorms of a single layer give every CU one block, and a wavefront has at
+// least 2 rows.  Their number follows from the rows alone: it decides the order of the sums, which must not depend on
+// how many layers share the launch.
+static int lnp_blocks(int T) {
+  const int most = (T + 2 * LNP_WAVES - 1) / (2 * LNP_WAVES);
+  return most < 128 ? most : 128;
 }
 size_t ln_param_partial_floats(int n_groups, int T, int d, int n_items) {
-  return (size_t)n_items * n_groups * lnp_blocks(n_groups, T, n_items) * 2 * d;
+  return (size_t)n_items * n_groups * lnp_blocks(T) * 2 * d;
 }
 
 template <typename TO, int NV>
-__global__ void __launch_bounds__(256) ln_param_partial_kernel(const LnParamArgs a, float* partial) {
-  __shared__ __attribute__((aligned(16))) float red[3][NV * 256];
+__global__ void __launch_bounds__(64 * LNP_WAVES) ln_param_partial_kernel(const LnParamArgs a, float* partial) {
+  __shared__ __attribute__((aligned(16))) float red[LNP_WAVES - 1][NV * 256];
   const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
   const int g = blockIdx.y, d = a.d;
   const LnParamItem it = a.item[blockIdx.z];
@@ -59,7 +62,7 @@ __global__ void __launch_bounds__(256) ln_param_partial_kernel(const LnParamArgs
   const TO* dyb = reinterpret_cast<const TO*>(it.dy) + it.dy_slots.of(g) * it.dy_slot_stride;
   const float* xb = a.X.at(g);
   const float* xab = it.xp ? it.xp + it.xp_slots.of(g) * it.xp_slot_stride : nullptr;
-  for (int t = blockIdx.x * 4 + wave; t < a.T; t += gridDim.x * 4) {
+  for (int t = blockIdx.x * LNP_WAVES + wave; t < a.T; t += gridDim.x * LNP_WAVES) {
     const long ro = (long)t * d;
     f32x4 v[NV], dy[NV];
     float s = 0.f;
@@ -105,7 +108,7 @@ __global__ void __launch_bounds__(256) ln_param_partial_kernel(const LnParamArgs
         const int c = (i * 64 + lane) * 4;
         f32x4 r = acc[i];
 #pragma unroll
-        for (int w = 0; w < 3; ++w) r += *reinterpret_cast<const f32x4*>(&red[w][c]);
+        for (int w = 0; w < LNP_WAVES - 1; ++w) r += *reinterpret_cast<const f32x4*>(&red[w][c]);
         if (c < d) *reinterpret_cast<f32x4*>(p + half * d + c) = r;
       }
     }
@@ -142,11 +145,11 @@ __global__ void __launch_bounds__(256) ln_param_reduce_kernel(const LnParamArgs 
 template <typename TO>
 static void lnp_dispatch(const LnParamArgs& a, float* partial, dim3 grid, hipStream_t st) {
   const int nv = (a.d + 255) / 256;
-  if (nv <= 1) hipLaunchKernelGGL((ln_param_partial_kernel<TO, 1>), grid, dim3(256), 0, st, a, partial);
-  else if (nv == 2) hipLaunchKernelGGL((ln_param_partial_kernel<TO, 2>), grid, dim3(256), 0, st, a, partial);
-  else if (nv == 3) hipLaunchKernelGGL((ln_param_partial_kernel<TO, 3>), grid, dim3(256), 0, st, a, partial);
-  else if (nv == 4) hipLaunchKernelGGL((ln_param_partial_kernel<TO, 4>), grid, dim3(256), 0, st, a, partial);
-  else hipLaunchKernelGGL((ln_param_partial_kernel<TO, 8>), grid, dim3(256), 0, st, a, partial);
+  if (nv <= 1) hipLaunchKernelGGL((ln_param_partial_kernel<TO, 1>), grid, dim3(64 * LNP_WAVES), 0, st, a, partial);
+  else if (nv == 2) hipLaunchKernelGGL((ln_param_partial_kernel<TO, 2>), grid, dim3(64 * LNP_WAVES), 0, st, a, partial);
+  else if (nv == 3) hipLaunchKernelGGL((ln_param_partial_kernel<TO, 3>), grid, dim3(64 * LNP_WAVES), 0, st, a, partial);
+  else if (nv == 4) hipLaunchKernelGGL((ln_param_partial_kernel<TO, 4>), grid, dim3(64 * LNP_WAVES), 0, st, a, partial);
+  else hipLaunchKernelGGL((ln_param_partial_kernel<TO, 8>), grid, dim3(64 * LNP_WAVES), 0, st, a, partial);
 }
 
 hipError_t launch_ln_param_grad(const LnParamArgs& a, float* partial, bool is_bf16, hipStream_t st) {
@@ -156,7 +159,7 @@ hipError_t launch_ln_param_grad(const LnParamArgs& a, float* partial, bool is_bf
   for (int i = 0; i < a.n_items; ++i)
     bytes += (double)a.n_groups * a.T * a.d * ((is_bf16 ? 2 : 4) + 4 + (a.item[i].xp ? 4 : 0));
   ProfScope ps(PC_ELEMENTWISE, 0.0, bytes, st);
-  const int nb = lnp_blocks(a.n_groups, a.T, a.n_items);
+  const int nb = lnp_blocks(a.T);
   const dim3 grid(nb, a.n_groups, a.n_items);
   if (is_bf16) lnp_dispatch<bf16>(a, partial, grid, st);
   else lnp_dispatch<float>(a, partial, grid, st);

@@ -52,3 +52,44 @@ def test_layer_step_bits(dtype, d, f, B, S, adjoint):
         mb.layer_step_batched(dm.desc, adjoint, ins, outs, dm.blocks, 0.5, lin_state=lin if adjoint else None)
         return {f"group {g}": o for g, o in enumerate(outs)}
     with_groups((1, 2, 4), run)
+
+
+# (the gains and shifts of the LayerNorms are summed by a kernel of their own)
+@pytest.mark.parametrize("norms", [True])
+@pytest.mark.parametrize("arch,dtype,d,f,B,S,Sm", [
+    (wls.ARCH_ENCODER, wls.DTYPE_BF16, 64, 192, 4, 1029, 0),     # token slices that pay for few layers only
+    (wls.ARCH_CROSS, wls.DTYPE_BF16, 128, 256, 4, 515, 260),
+    (wls.ARCH_ENCODER, wls.DTYPE_F32, 256, 512, 4, 509, 0)])
+def test_gradient_bits(arch, dtype, d, f, B, S, Sm, norms):
+    wl = wls.Workload("t", arch, d, 2, f, B, S, Sm, 4, 0.25, 1, 1, 1, dtype, 91)
+    print(f"[case] groups per launch, gradients arch={arch} dtype={dtype} d={d} f={f} B={B} S={S} Sm={Sm}", flush=True)
+    dm = DeviceModel(wl, weight_std=0.05, keep_host=False)
+    opts = mb.mgrit_opts(wl.N, wl.h, 1, 1, 0)
+    mem = wls.cross_memory(wl)
+    mem = None if mem is None else dev(mem)
+    Z, _ = mb.mgrit_forward(dm.desc, opts, dev(wls.initial_state(wl)), dm.blocks, memory=mem)
+    lamN = dev(wls.terminal_adjoint(wl))
+    floats = mb.grad_layout(dm.desc).block_bytes // 4
+
+    def run():
+        out = {}
+        for lanes, cache in ((1, True), (2, True), (2, False)):
+            mb.mgrit_set_lanes(lanes)            # two lanes: a serial chain hands its gradients over in batches ...
+            mb.mgrit_set_adjoint_cache(cache)    # ... unless it has no cache, then they are formed layer by layer
+            grads = [torch.zeros(floats, device="cuda") for _ in range(wl.N)]
+            dmem = None if mem is None else torch.full_like(mem, float("nan"))
+            try:
+                lam, _ = mb.mgrit_adjoint(dm.desc, opts, Z, dm.blocks, lamN, memory=mem,
+                                          dtheta=[g.view(torch.uint8) for g in grads], dmemory=dmem)
+            finally:
+                mb.mgrit_set_adjoint_cache(True)
+                mb.mgrit_set_lanes(1)
+            one = {"lambda": lam} if dmem is None else {"lambda": lam, "dmemory": dmem}
+            for n, g in enumerate(grads):
+                for name, t in mb.unpack_grad(dm.desc, g.view(torch.uint8)).items():
+                    if norms == name.startswith("ln"):
+                        one[f"{name} of layer {n}"] = torch.from_numpy(t)
+            for name, t in one.items():
+                assert torch.equal(t, out.setdefault(name, t)), f"lanes={lanes} cache={cache}: {name} differs"
+        return out
+    with_groups((1, 3, 4), run)
