@@ -1185,17 +1185,21 @@ static hipError_t launch_tn(const GemmTnArgs& a, int splits, hipStream_t st) {
 // the bytes per clock of plain ones, so a k-tile takes longer than there.  Few output tiles and many tokens
 // (384 x 384 from 12608 tokens: 9 tiles of 128x128) are cut into slices of at least 8 k-tiles, which costs
 // writing and summing the slices' partial results.
+// Slices change the order of the sums, so their number follows from the layer's sizes alone, as the best one for a
+// launch of TN_GROUPS layers (the usual chunk): a gradient does not depend on how many layers share its launch.  The
+// tile may follow from the launch: every tile adds a slice's tokens in the same order.
+constexpr int TN_GROUPS = 4;
 struct TnPlan { int cfg, splits; };
-static TnPlan choose_tn(int n_groups, int M, int N, int K, bool is_bf16) {
+static TnPlan choose_tn(int n_groups, int M, int N, int K, bool is_bf16, int first, int last) {
   static const TileCfg bf[] = {{1, 256, 256, 1, 7.0, 2.05}, {6, 128, 128, 1, 3.0, 0.68}, {8, 64, 64, 2, 2.5, 0.50}};
   static const TileCfg fp[] = {{0, 64, 64, 4, 2.5, 2.2}};
   const long cus = compute_units();
   const int ktiles = (K + 63) / 64;
-  TnPlan best = {6, 1};
+  TnPlan best = {6, first};
   double best_cost = 1e30;
   for (const TileCfg* c = is_bf16 ? bf : fp; c != (is_bf16 ? bf + 3 : fp + 1); ++c) {
     const long tiles = (long)((M + c->bm - 1) / c->bm) * ((N + c->bn - 1) / c->bn) * n_groups;
-    for (int s = 1; s <= 64 && (s == 1 || ktiles / s >= 8); s *= 2) {
+    for (int s = first; s <= last && (s == 1 || ktiles / s >= 8); s *= 2) {
       const long rounds = (tiles * s + cus * c->per_cu - 1) / (cus * c->per_cu);
       double cost = rounds * (c->fixed + c->per_ktile * ((ktiles + s - 1) / s));
       if (s > 1) cost += 4.0 + 2.0 * s * n_groups * (double)M * N * 4.0 / 3e6;         // us at 3 TB/s
@@ -1204,9 +1208,13 @@ static TnPlan choose_tn(int n_groups, int M, int N, int K, bool is_bf16) {
   }
   return best;
 }
+static TnPlan plan_tn(int n_groups, int M, int N, int K, bool is_bf16) {
+  const int s = choose_tn(TN_GROUPS, M, N, K, is_bf16, 1, 64).splits;
+  return choose_tn(n_groups, M, N, K, is_bf16, s, s);
+}
 
 size_t gemm_tn_partial_floats(int n_groups, int M, int N, int K, bool is_bf16) {
-  const int s = choose_tn(n_groups, M, N, K, is_bf16).splits;
+  const int s = plan_tn(n_groups, M, N, K, is_bf16).splits;
   return s == 1 ? 0 : (size_t)s * n_groups * ((size_t)M * N + M);
 }
 
@@ -1214,7 +1222,7 @@ hipError_t launch_gemm_tn(const GemmTnArgs& a, bool is_bf16, hipStream_t st) {
   if (a.n_groups <= 0 || a.K <= 0) return hipSuccess;
   const double esz = is_bf16 ? 2 : 4, G = a.n_groups;
   if (a.M % 8 != 0 || a.N % 8 != 0 || 64.0 * a.M > 4e9 || 64.0 * a.N > 4e9) return hipErrorInvalidValue;
-  const TnPlan plan = choose_tn(a.n_groups, a.M, a.N, a.K, is_bf16);
+  const TnPlan plan = plan_tn(a.n_groups, a.M, a.N, a.K, is_bf16);
   if (plan.splits > 1 && !a.partial) return hipErrorInvalidValue;
   ProfScope ps(is_bf16 ? (a.n_groups > 1 ? PC_GEMM_MFMA : PC_GEMM_MFMA_SINGLE) + EPI_STORE_F32 : PC_GEMM_SIMPLE,
                2.0 * G * a.M * (double)a.N * a.K,

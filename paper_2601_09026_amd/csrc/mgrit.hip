@@ -307,16 +307,14 @@ struct Engine {
   }
   void carve_grad_work(Bump& b) {
     const size_t G = Gc;
-    size_t most = 0;
+    size_t most = 0;                       // (all of these grow with the group count)
     auto need = [&](size_t floats) { if (floats > most) most = floats; };
-    for (int n = 1; n <= Gc; ++n) {
-      need(gemm_tn_partial_floats(n, 3 * d, d, T, bf16));
-      need(gemm_tn_partial_floats(n, d, d, T, bf16));
-      need(gemm_tn_partial_floats(n, f, d, T, bf16));
-      need(gemm_tn_partial_floats(n, d, f, T, bf16));
-      if (md.arch == MGRIT_ARCH_CROSS) need(gemm_tn_partial_floats(n, 2 * d, d, Tm, bf16));
-      for (int items = 2; items <= LN_PARAM_MAX; ++items) need(ln_param_partial_floats(n, T, d, items));
-    }
+    need(gemm_tn_partial_floats(Gc, 3 * d, d, T, bf16));
+    need(gemm_tn_partial_floats(Gc, d, d, T, bf16));
+    need(gemm_tn_partial_floats(Gc, f, d, T, bf16));
+    need(gemm_tn_partial_floats(Gc, d, f, T, bf16));
+    if (md.arch == MGRIT_ARCH_CROSS) need(gemm_tn_partial_floats(Gc, 2 * d, d, Tm, bf16));
+    need(ln_param_partial_floats(Gc, T, d, LN_PARAM_MAX));
     gpart = b.take<float>(most);
     if (!per_group_mem) dkvc = md.arch == MGRIT_ARCH_CROSS ? b.take_bytes(G * Tm * 2 * d * esz) : nullptr;
   }

@@ -55,7 +55,7 @@ def test_layer_step_bits(dtype, d, f, B, S, adjoint):
 
 
 # (the gains and shifts of the LayerNorms are summed by a kernel of their own)
-@pytest.mark.parametrize("norms", [True])
+@pytest.mark.parametrize("norms", [True, False])
 @pytest.mark.parametrize("arch,dtype,d,f,B,S,Sm", [
     (wls.ARCH_ENCODER, wls.DTYPE_BF16, 64, 192, 4, 1029, 0),     # token slices that pay for few layers only
     (wls.ARCH_CROSS, wls.DTYPE_BF16, 128, 256, 4, 515, 260),
