@@ -1,11 +1,15 @@
 """Parameter gradients at the edges of the token-major product: token counts that are no multiple of a k-tile
 (or of 4), widths inside a tile, reductions cut into slices, and serial runs whose layer count is no multiple of
 the layers per gradient launch (4: batches of 4, 4 and 1, both sets of buffers reused), against the CPU oracle."""
+import numpy as np
 import pytest
+import torch
 
+from paper_2601_09026_amd import binding as mb
 from paper_2601_09026_amd import workloads as wls
 
-from test_gpu_param_grads import run_case
+from gpu_util import DeviceModel
+from test_gpu_param_grads import grad_blocks, run_case
 
 pytestmark = pytest.mark.gpu
 
@@ -24,3 +28,27 @@ BF16, F32 = wls.DTYPE_BF16, wls.DTYPE_F32
 def test_weight_gradient_edges(arch, dtype, d, H, f, B, S, Sm, N, cf, levels):
     wl = wls.Workload("edges", arch, d, H, f, B, S, Sm, N, 1.0 / N, cf, levels, 2 if levels > 1 else 1, dtype, 77)
     run_case(wl, weight_std=0.05)
+
+
+@pytest.mark.parametrize("dtype", [BF16, F32])
+@pytest.mark.parametrize("d,B,S", [(256, 32, 512), (1024, 8, 512)])     # tokens cut into slices; not cut
+def test_bias_gradient_rounding(d, B, S, dtype):
+    """The gradient of b2 is h times the sum over tokens of lambda.  Positive terms, so that a rounding of a partial sum
+    is one of the result, most of them (fifth powers) far smaller than the sum.  Of the roundings a term takes part in,
+    six are in the sums of 32 tokens of a k-tile, two each in the sums of k-tiles and of slices, which carry their
+    errors, and one each in adding two halves and multiplying by h: twelve, however many tokens."""
+    wl = wls.Workload("sums", wls.ARCH_ENCODER, d, d // 64, d, B, S, 0, 1, 0.3, 1, 1, 1, dtype, 78)
+    print(f"[case] bias sums d={d} T={wl.tokens} dtype={dtype}", flush=True)
+    dm = DeviceModel(wl, keep_host=False)
+    opts = mb.mgrit_opts(1, wl.h, 1, 1, 0)
+    gen = torch.Generator(device="cuda").manual_seed(3)
+    lam = torch.randn((wl.tokens, d), generator=gen, device="cuda").abs_() ** 5
+    Z, _ = mb.mgrit_forward(dm.desc, opts, torch.randn((wl.tokens, d), generator=gen, device="cuda"), dm.blocks)
+    grad = grad_blocks(dm.desc, 1)
+    mb.mgrit_adjoint(dm.desc, opts, Z, dm.blocks, lam, dtheta=grad)
+    got = mb.unpack_grad(dm.desc, grad[0])["b2"].reshape(-1).astype(np.float64)
+    terms = lam.bfloat16() if dtype == BF16 else lam
+    ref = float(np.float32(wl.h)) * terms.double().sum(0).cpu().numpy()
+    worst = np.abs(got / ref - 1.0).max()
+    print(f"  largest relative error {worst:.2e}")
+    assert worst <= 12 * 2.0 ** -24
