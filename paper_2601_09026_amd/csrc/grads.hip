@@ -106,10 +106,15 @@ __global__ void __launch_bounds__(64 * LNP_WAVES) ln_param_partial_kernel(const 
 #pragma unroll
       for (int i = 0; i < NV; ++i) {
         const int c = (i * 64 + lane) * 4;
-        f32x4 r = acc[i];
+        f32x4 r[LNP_WAVES];
+        r[0] = acc[i];
 #pragma unroll
-        for (int w = 0; w < LNP_WAVES - 1; ++w) r += *reinterpret_cast<const f32x4*>(&red[w][c]);
-        if (c < d) *reinterpret_cast<f32x4*>(p + half * d + c) = r;
+        for (int w = 1; w < LNP_WAVES; ++w) r[w] = *reinterpret_cast<const f32x4*>(&red[w - 1][c]);
+#pragma unroll
+        for (int n = LNP_WAVES / 2; n > 0; n /= 2)         // pairwise
+#pragma unroll
+          for (int w = 0; w < n; ++w) r[w] += r[w + n];
+        if (c < d) *reinterpret_cast<f32x4*>(p + half * d + c) = r[0];
       }
     }
   }
