@@ -441,11 +441,17 @@ int mgrit_measure_event_bracket(double* us, void* stream);
 /* Test hook: route GEMMs (first flag) / attention (second flag) to the generic kernels. */
 void mgrit_debug_force_simple_kernels(int gemm, int attn);
 
-/* Tuning hook: tile configuration of the MFMA grouped GEMM (0 = chosen by shape, the default; k-tiles
+/* Tuning hook: tile configuration of the matrix-core products (0 = chosen by shape, the default; k-tiles
  * of 64: 1 = 256x256 and 3 = 256x192, one block per CU; 4 = 128x128, two blocks per CU; 6 = 128x128, four
  * stages, one block per CU; 8 and 9 = 64x64 with four and two stages, two and four blocks per CU).
- * 3 falls back to 4 where the shape is no multiple of it. */
+ * 3 falls back to 4 where the shape is no multiple of it.  The token-major products of the parameter gradients
+ * come as 1, 6 (also for 3 and 4) and 8 (also for 9).  fp32: 8 and 9 take the 32x32 tiles, the others the 64x64
+ * ones where the shape is a multiple of them. */
 void mgrit_debug_gemm_tile_config(int cfg);
+
+/* Tuning hook: slices of the token sums in the parameter gradients (0 = chosen by shape, the default; at most
+ * one per 64 tokens).  Changes the workspace size, and the last bits of the gradients. */
+void mgrit_debug_gradient_slices(int n);
 
 /* Tuning hook: which attention kernels use 256-row blocks.  Bits 0-2: forward, dQ pass, dK/dV
  * pass at d_head = 128 (sequences of more than 128 tokens; the backward passes only when the

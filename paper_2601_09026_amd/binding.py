@@ -160,6 +160,8 @@ def lib() -> C.CDLL:
         L.mgrit_debug_force_simple_kernels.restype = None
         L.mgrit_debug_gemm_tile_config.argtypes = [C.c_int]
         L.mgrit_debug_gemm_tile_config.restype = None
+        L.mgrit_debug_gradient_slices.argtypes = [C.c_int]
+        L.mgrit_debug_gradient_slices.restype = None
         L.mgrit_debug_attention_wide_blocks.argtypes = [C.c_int]
         L.mgrit_debug_attention_wide_blocks.restype = None
         L.mgrit_debug_pipeline_coarse_solve.argtypes = [C.c_int]

@@ -1017,8 +1017,10 @@ gemm_simple_kernel(const GemmArgs a, int tiles_m, int tiles_n) {
 // ---------------------------------------------------------------------------
 static int g_force_simple = 0;
 static int g_tile_cfg = 0;                 // 0 = choose by shape
+static int g_grad_slices = 0;              // the same
 void gemm_force_simple(int on) { g_force_simple = on; }
 void gemm_set_tile_config(int cfg) { g_tile_cfg = cfg; }
+void gemm_set_grad_slices(int n) { g_grad_slices = n > 0 ? n : 0; }
 
 // Compute units of the current device (256 if the query fails).
 static int compute_units() {
@@ -1069,7 +1071,8 @@ static hipError_t launch_mfma(const GemmArgs& a, hipStream_t st) {
 template <int EPI>
 static hipError_t launch_f32_mfma(const GemmArgs& a, hipStream_t st) {
   const int tiles_m = (a.M + 63) / 64, tiles_n = (a.N + 63) / 64;
-  if (a.N % 64 == 0 && a.K % 16 == 0 && (long)tiles_m * tiles_n * a.n_groups >= 2 * compute_units()) {
+  const bool large = g_tile_cfg ? g_tile_cfg < 8 : (long)tiles_m * tiles_n * a.n_groups >= 2 * compute_units();
+  if (a.N % 64 == 0 && a.K % 16 == 0 && large) {
     hipLaunchKernelGGL((gemm_f32_mfma_kernel<EPI>), dim3(tiles_m * tiles_n, 1, a.n_groups), dim3(256), 0, st, a,
                        tiles_m, tiles_n);
     return hipGetLastError();
@@ -1220,7 +1223,7 @@ static TnPlan choose_tn(int n_groups, int M, int N, int K, bool is_bf16, int fir
   double best_cost = 1e30;
   for (const TileCfg* c = is_bf16 ? bf : fp; c != (is_bf16 ? bf + 3 : fp + 1); ++c) {
     const long tiles = (long)((M + c->bm - 1) / c->bm) * ((N + c->bn - 1) / c->bn) * n_groups;
-    for (int s = first; s <= last && (s == 1 || ktiles / s >= 8); s *= 2) {
+    for (int s = first; s <= last && (s == first || ktiles / s >= 8); s *= 2) {
       const long rounds = (tiles * s + cus * c->per_cu - 1) / (cus * c->per_cu);
       double cost = rounds * (c->fixed + c->per_ktile * ((ktiles + s - 1) / s));
       if (s > 1) cost += 4.0 + 2.0 * s * n_groups * (double)M * N * 4.0 / 3e6;         // us at 3 TB/s
@@ -1230,8 +1233,12 @@ static TnPlan choose_tn(int n_groups, int M, int N, int K, bool is_bf16, int fir
   return best;
 }
 static TnPlan plan_tn(int n_groups, int M, int N, int K, bool is_bf16) {
-  const int s = choose_tn(TN_GROUPS, M, N, K, is_bf16, 1, 64).splits;
-  return choose_tn(n_groups, M, N, K, is_bf16, s, s);
+  const int ktiles = (K + 63) / 64;
+  const int s = !g_grad_slices ? choose_tn(TN_GROUPS, M, N, K, is_bf16, 1, 64).splits
+                               : g_grad_slices < ktiles ? g_grad_slices : ktiles;
+  TnPlan p = choose_tn(n_groups, M, N, K, is_bf16, s, s);
+  if (g_tile_cfg) p.cfg = g_tile_cfg == 1 ? 1 : g_tile_cfg < 8 ? 6 : 8;
+  return p;
 }
 
 size_t gemm_tn_partial_floats(int n_groups, int M, int N, int K, bool is_bf16) {

@@ -10,6 +10,7 @@ hipError_t launch_gemm_tn(const GemmTnArgs& a, bool is_bf16, hipStream_t st);
 size_t gemm_tn_partial_floats(int n_groups, int M, int N, int K, bool is_bf16);   // scratch floats of such a launch
 void gemm_force_simple(int on);
 void gemm_set_tile_config(int cfg);
+void gemm_set_grad_slices(int n);
 double gemm_model_cost(int n_groups, int M, int N, int K);
 void attn_set_wide_blocks(int mask);
 

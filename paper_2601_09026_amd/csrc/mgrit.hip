@@ -2177,6 +2177,7 @@ void mgrit_debug_force_simple_kernels(int gemm, int attn) {
 }
 
 void mgrit_debug_gemm_tile_config(int cfg) { gemm_set_tile_config(cfg); }
+void mgrit_debug_gradient_slices(int n) { gemm_set_grad_slices(n); }
 void mgrit_debug_attention_wide_blocks(int mask) { attn_set_wide_blocks(mask); }
 void mgrit_debug_pipeline_coarse_solve(int on) { g_pipeline = on ? 1 : 0; }
 void mgrit_debug_pipeline_chunk(int n) { g_pipe_chunk = n > 0 ? n : 0; }

@@ -5,6 +5,7 @@ sequences of one row, around 16-row parts, around 64-row tiles, over several til
 counts.  The attention cases run forward and adjoint; sequences up to 64 take the one-launch backward."""
 import pytest
 
+from paper_2601_09026_amd import binding as mb
 from paper_2601_09026_amd import workloads as wls
 
 from test_gpu_layer_step import make, run_adjoint_case, run_forward_case
@@ -17,8 +18,8 @@ pytestmark = pytest.mark.gpu
     (40, 2, 72, 1, 65, 2),         # one k-tile and 8 elements; one row past a 64-row tile
     (64, 4, 256, 2, 32, 4),        # whole tiles
     (200, 5, 600, 3, 43, 2),       # ragged columns and reductions, 129 rows
-    (200, 5, 600, 16, 129, 4),     # enough rows for the 64-wide tiles, ragged in every direction
-    (320, 5, 320, 16, 256, 5),     # the same, whole tiles
+    (200, 5, 600, 16, 129, 4),     # many rows, ragged in every direction (32x32 tiles as well)
+    (320, 5, 320, 16, 256, 5),     # enough rows for the 64x64 tiles
     (512, 8, 1024, 8, 256, 4),
 ])
 def test_projection_tiles_fp32(d, H, f, B, S, G):
@@ -26,6 +27,22 @@ def test_projection_tiles_fp32(d, H, f, B, S, G):
     run_forward_case(wl, G=G, hstep=0.5, with_rhs=True, weight_std=0.05, force_simple=0)
     if B * S <= 512:               # (the float64 oracle is slow at the largest shapes)
         run_adjoint_case(wl, G=G, hstep=0.5, with_rhs=True, weight_std=0.05, force_simple=0)
+
+
+@pytest.mark.parametrize("d,H,f,B,S", [
+    (256, 4, 512, 3, 50),          # 150 rows: two row tiles and 22 rows
+    (64, 4, 192, 1, 65),           # one row past a tile
+    (192, 2, 320, 2, 64),          # whole tiles
+])
+def test_projection_on_64x64_tiles_fp32(d, H, f, B, S):
+    """The tile of large launches, forward and adjoint, at sizes that the oracle can follow."""
+    wl = make(wls.ARCH_CAUSAL, wls.DTYPE_F32, d=d, H=H, f=f, B=B, S=S)
+    mb.lib().mgrit_debug_gemm_tile_config(1)
+    try:
+        run_forward_case(wl, G=2, hstep=0.5, with_rhs=True, weight_std=0.05, force_simple=0)
+        run_adjoint_case(wl, G=2, hstep=0.5, with_rhs=True, weight_std=0.05, force_simple=0)
+    finally:
+        mb.lib().mgrit_debug_gemm_tile_config(0)
 
 
 @pytest.mark.parametrize("dtype", [wls.DTYPE_F32, wls.DTYPE_BF16])

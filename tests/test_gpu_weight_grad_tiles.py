@@ -20,7 +20,7 @@ BF16, F32 = wls.DTYPE_BF16, wls.DTYPE_F32
     (wls.ARCH_CAUSAL, BF16, 72, 2, 136, 1, 21, 0, 4, 1, 1),        # 21 tokens, widths of one tile plus a chunk
     (wls.ARCH_ENCODER, BF16, 64, 1, 64, 2, 515, 0, 13, 1, 1),      # 17 k-tiles, the last with 6 tokens; batches 4 4 4 1
     (wls.ARCH_ENCODER, BF16, 64, 1, 128, 64, 64, 0, 2, 1, 1),      # 64 k-tiles of one output tile: slices
-    (wls.ARCH_CAUSAL, BF16, 264, 3, 520, 1, 130, 0, 4, 2, 2),      # one row and column chunk past 256
+    (wls.ARCH_CAUSAL, BF16, 264, 3, 520, 1, 130, 0, 4, 2, 2),      # one 8-row and 8-column chunk past whole 64x64 tiles
     (wls.ARCH_CROSS, BF16, 64, 1, 128, 1, 25, 19, 9, 1, 1),        # odd token and memory token counts, serial
     (wls.ARCH_CROSS, F32, 40, 2, 48, 1, 33, 7, 9, 1, 1),
     (wls.ARCH_ENCODER, F32, 64, 4, 64, 16, 64, 0, 4, 2, 2),        # slices in fp32
@@ -28,6 +28,24 @@ BF16, F32 = wls.DTYPE_BF16, wls.DTYPE_F32
 def test_weight_gradient_edges(arch, dtype, d, H, f, B, S, Sm, N, cf, levels):
     wl = wls.Workload("edges", arch, d, H, f, B, S, Sm, N, 1.0 / N, cf, levels, 2 if levels > 1 else 1, dtype, 77)
     run_case(wl, weight_std=0.05)
+
+
+@pytest.mark.parametrize("tiles,slices,dtype", [
+    (1, 0, BF16), (1, 3, BF16), (6, 0, BF16), (6, 3, BF16), (8, 0, BF16), (8, 2, BF16), (0, 3, F32)])
+@pytest.mark.parametrize("arch,d,H,f,B,S,Sm", [
+    (wls.ARCH_CAUSAL, 264, 3, 520, 1, 130, 0),       # one chunk past 256-wide and 128-wide tiles; k-tiles of 64, 64 and 2 tokens
+    (wls.ARCH_CROSS, 200, 5, 136, 3, 45, 24),        # inside them; 135 and 72 tokens
+])
+def test_each_tile_and_slice_at_its_edges(arch, d, H, f, B, S, Sm, tiles, slices, dtype):
+    wl = wls.Workload("edges", arch, d, H, f, B, S, Sm, 2, 0.5, 1, 1, 1, dtype, 79)
+    print(f"[case] tile configuration {tiles}, {slices} slices", flush=True)
+    mb.lib().mgrit_debug_gemm_tile_config(tiles)
+    mb.lib().mgrit_debug_gradient_slices(slices)
+    try:
+        run_case(wl, weight_std=0.05)
+    finally:
+        mb.lib().mgrit_debug_gemm_tile_config(0)
+        mb.lib().mgrit_debug_gradient_slices(0)
 
 
 @pytest.mark.parametrize("dtype", [BF16, F32])
