@@ -213,7 +213,7 @@ enum Epi : int {
   EPI_RESID_INNER = 2,  // ybar[m,n] (fp32, packed) = [base +] acc + bias      (sum of attention sublayers)
   EPI_RESID_OUTER = 3,  // OUT[m,n] = X + h*(ybar + acc + bias) + rhs          (the Euler update)
   EPI_DGELU = 4,        // out = acc * g[m,n], g = the cached gelu'(z)          (adjoint of the activation)
-  EPI_STORE_F32 = 5,    // out (fp32, packed or inside the group's output block) = hstep * (acc + bias)
+  EPI_STORE_F32 = 5,    // out (fp32, packed) = hstep * (acc + bias)
   EPI_GELU_PRIME = 6,   // out = gelu'(acc + bias) (operand type): the linearisation cache holds the derivative,
                         // evaluated once per layer
   EPI_GELU_BOTH = 7     // out = gelu(acc + bias) and aux2 = gelu'(acc + bias): a forward step that also leaves its
@@ -240,7 +240,6 @@ struct GemmArgs {
   float hstep;
   float rhs_sign;              // EPI_RESID_OUTER with RHS: OUT = RHS + rhs_sign * (X + h*(..)); +1 the step, -1 the
                                // coarse right-hand side g' = R - Phi'(w) formed in the step that evaluates Phi'
-  Params out_tab; long out_tab_off;    // EPI_STORE_F32: if set, group g writes at out_tab[g] + out_tab_off
 };
 
 // Parameter gradients of one linear map per group, y = u W^T + b, from token-major operands (launch_gemm_tn):

@@ -39,7 +39,6 @@ __device__ __forceinline__ EpiPtrs resolve_epi(const GemmArgs& a, int g, int epi
   const bool f32_out = epi == EPI_STORE_F32 || epi == EPI_RESID_INNER;
   const long osz = f32_out ? 4 : (long)sizeof(TO);
   p.out = a.out ? static_cast<char*>(a.out) + a.out_slots.of(g) * a.out_slot_stride * osz : nullptr;
-  if (a.out_tab.tab) p.out = const_cast<char*>(a.out_tab.at(g)) + a.out_tab_off;
   const long asz = epi == EPI_RESID_OUTER ? 4 : (long)sizeof(TO);
   p.aux = a.aux ? static_cast<char*>(a.aux) + a.aux_slots.of(g) * a.aux_slot_stride * asz : nullptr;
   p.aux2 = a.aux2 ? static_cast<char*>(a.aux2) + a.aux2_slots.of(g) * a.aux2_slot_stride * (long)sizeof(TO) : nullptr;
@@ -288,7 +287,7 @@ __device__ __forceinline__ void tile_epilogue(
 //    no register staging) through a ring of STAGES k-tiles of depth BK.
 //  * An LDS row holds the BK bf16 of one matrix row unpadded; its 16-byte chunks are XOR-swizzled by
 //    the row number so that the 16-byte fragment reads of 32 consecutive rows are bank-conflict free.
-//    A load instruction of a wavefront fills 1 KB = 8 (or 16) consecutive rows; the lane that will
+//    A load instruction of a wavefront fills 1 KB = 8 consecutive rows; the lane that will
 //    land at position p of row r fetches logical chunk p ^ f(r) of that row.
 //  * MFMA fragments are double-buffered in registers: the LDS reads of k-step s+1 are spread between
 //    the MFMAs of s, across the boundary of two k-tiles as well, and so are the loads that refill a stage.
@@ -323,12 +322,9 @@ __device__ __forceinline__ void bare_barrier() {
 }
 
 // LDS has 64 four-byte banks (256 bytes per clock); a 16-byte read is served 16 lanes at a
-// time, so 16 consecutive rows must land on 16 distinct 16-byte slots modulo 256 bytes.  With
-// 128-byte rows two rows share a 256-byte bank row: swizzle by the row pair; with 64-byte
-// rows four rows share it: swizzle by the row quad.
-template <int BK> __device__ __forceinline__ int swz(int row) {
-  return BK == 64 ? ((row >> 1) & 7) : ((row >> 2) & 3);
-}
+// time, so 16 consecutive rows must land on 16 distinct 16-byte slots modulo 256 bytes.  Two of the
+// 128-byte rows share a 256-byte bank row: swizzle by the row pair.
+__device__ __forceinline__ int swz(int row) { return (row >> 1) & 7; }
 
 // Source of the chunks of a last k-tile that lie past K.
 __device__ const __attribute__((aligned(16))) unsigned char g_zero_chunk[16] = {};
@@ -345,6 +341,7 @@ gemm_mfma_kernel(const GemmArgs a, int tiles_m, int tiles_n, int total_tiles, in
   constexpr int KS = BK / 16;                            // MFMA k-steps per tile
   constexpr int A_BYTES = BM * RB, B_BYTES = BN * RB, STAGE = A_BYTES + B_BYTES;
   constexpr int A_LD = BM / RPL / NW, B_LD = BN / RPL / NW; // load instructions per wave per k-tile
+  static_assert(BK == 64 && STAGES <= 4, "swz(), wait_tile()");
   static_assert(A_LD >= 1 && B_LD >= 1 && A_LD * RPL * NW == BM && B_LD * RPL * NW == BN, "tile/wave split");
   constexpr int PER_TILE = A_LD + B_LD;
   extern __shared__ __attribute__((aligned(1024))) unsigned char smem2[];
@@ -391,14 +388,14 @@ gemm_mfma_kernel(const GemmArgs a, int tiles_m, int tiles_n, int total_tiles, in
     const int row = (wave * A_LD + j) * RPL + lrow;            // row inside the tile
     int gm = m0 + row;
     gm = gm < M ? gm : M - 1;
-    aoff[j] = (unsigned)gm * (unsigned)K + (lpos ^ swz<BK>(row)) * 8;
+    aoff[j] = (unsigned)gm * (unsigned)K + (lpos ^ swz(row)) * 8;
   }
 #pragma unroll
   for (int j = 0; j < B_LD; ++j) {
     const int row = (wave * B_LD + j) * RPL + lrow;
     int gn = n0 + row;
     if (RAGGED) gn = gn < N ? gn : N - 1;
-    boff[j] = (unsigned)gn * (unsigned)K + (lpos ^ swz<BK>(row)) * 8;
+    boff[j] = (unsigned)gn * (unsigned)K + (lpos ^ swz(row)) * 8;
   }
 
   auto issue_one = [&](int stage, int k0, int idx) {
@@ -409,7 +406,7 @@ gemm_mfma_kernel(const GemmArgs a, int tiles_m, int tiles_n, int total_tiles, in
     if constexpr (RAGGED) {
       // the last k-tile reaches past K: its 16-byte chunks from K on are zeros (K is a multiple of 8)
       const int row = is_a ? (wave * A_LD + idx) * RPL + lrow : (wave * B_LD + idx - A_LD) * RPL + lrow;
-      if (k0 + (lpos ^ swz<BK>(row)) * 8 >= K) src = reinterpret_cast<const bf16*>(g_zero_chunk);
+      if (k0 + (lpos ^ swz(row)) * 8 >= K) src = reinterpret_cast<const bf16*>(g_zero_chunk);
     }
     __builtin_amdgcn_global_load_lds((gas_ptr)src, (las_ptr)dst, 16, 0, 0);
   };
@@ -421,7 +418,7 @@ gemm_mfma_kernel(const GemmArgs a, int tiles_m, int tiles_n, int total_tiles, in
   // fragment byte offsets inside a tile region: row lr, swizzled chunk of k-step ks
   int foff[KS];
 #pragma unroll
-  for (int ks = 0; ks < KS; ++ks) foff[ks] = lr * RB + (((2 * ks + lh) ^ swz<BK>(lr)) << 4);
+  for (int ks = 0; ks < KS; ++ks) foff[ks] = lr * RB + (((2 * ks + lh) ^ swz(lr)) << 4);
 
   f32x16 acc[TM][TN];
 #pragma unroll
@@ -441,7 +438,6 @@ gemm_mfma_kernel(const GemmArgs a, int tiles_m, int tiles_n, int total_tiles, in
     if (s < KT) issue(s, s * BK);
   auto wait_tile = [&](int kt, int issued) {               // own loads of tile kt have landed (issued: tiles so far)
     const int behind = issued - 1 - kt;
-    if constexpr (STAGES >= 5) if (behind >= 4) { wait_vmcnt<4 * PER_TILE>(); return; }
     if constexpr (STAGES >= 4) if (behind >= 3) { wait_vmcnt<3 * PER_TILE>(); return; }
     if constexpr (STAGES >= 3) if (behind >= 2) { wait_vmcnt<2 * PER_TILE>(); return; }
     if (behind >= 1) { wait_vmcnt<PER_TILE>(); return; }
