@@ -118,8 +118,8 @@ int mgrit_theta_layout(const mgrit_model_desc* desc, mgrit_theta_layout_t* out);
 
 /* Workspace sizes in bytes (0 on invalid arguments).  Host only.
  * mgrit_workspace_bytes: adjoint = 0 for mgrit_forward, 1 for mgrit_adjoint, 2 for
- * mgrit_adjoint called with dtheta or dmemory (the gradient pass needs transposed operand
- * copies and per-layer terms). */
+ * mgrit_adjoint called with dtheta or dmemory (which keeps the inputs of every layer's linear
+ * maps, the cotangents of their outputs and per-layer terms). */
 size_t mgrit_workspace_bytes(const mgrit_model_desc* desc, const mgrit_opts* opts, int adjoint);
 size_t mgrit_layer_step_workspace_bytes(const mgrit_model_desc* desc, int adjoint, int n_groups);
 
@@ -190,7 +190,7 @@ int mgrit_adjoint(const mgrit_model_desc* desc, const mgrit_opts* opts,
  * lambda_all, gradients and residual norms are bit-identical to those of the plain pair.
  *   adjoint_workspace        device, at least mgrit_workspace_bytes(desc, opts, with_gradients ? 2 : 1)
  *   with_gradients           non-zero iff the adjoint call will ask for dtheta or dmemory (the cache
- *                            then also keeps the feed-forward pre-activation)
+ *                            then also keeps the activation and the LayerNorm outputs)
  * The caller guarantees, between the two calls: the same desc, opts, theta and memory; Z_all of the
  * adjoint is the unmodified output of the forward call; `workspace` of the adjoint is the forward
  * call's `adjoint_workspace`, untouched in between, and with_gradients matches; the adjoint is
@@ -396,7 +396,8 @@ void mgrit_set_lanes(int n);
 /* Memory knob of mgrit_adjoint (and of the buffered and stacked forms): 1 (default) keeps the block
  * internals of all N layers at their linearisation states in the workspace -- filled once per call by
  * one forward pass batched over the layers, about 24 d_model bytes per token and layer (5 GB at the
- * BERT shape, 10 GB at the GPT-2 shape) -- so that every transposed step is pure backward work.
+ * BERT shape, 10 GB at the GPT-2 shape; 36 with parameter gradients, whose products read the
+ * activation and the LayerNorm outputs) -- so that every transposed step is pure backward work.
  * 0 is for callers who cannot spend that memory: the workspace then holds the internals of one launch
  * chunk per lane only, and every chunk of transposed steps first recomputes those of its own layers
  * (the forward block up to the FFN activation).  Results are identical bit for bit; the workspace
@@ -438,7 +439,9 @@ int mgrit_measure_copy_ceiling(const void* src, void* dst, size_t bytes, double*
  * microsecond; it matters for launches of 10-30 us.  0 on success, -1 / -4 as above. */
 int mgrit_measure_event_bracket(double* us, void* stream);
 
-/* Test hook: route GEMMs (first flag) / attention (second flag) to the generic kernels. */
+/* Test hook.  First flag: the products x W^T of the steps run on the FMA kernel (the token-major products
+ * of the parameter gradients have no other form).  Second flag: bf16 attention of 64- and 128-wide heads
+ * runs on the kernels of all other heads, which take its products in fp32. */
 void mgrit_debug_force_simple_kernels(int gemm, int attn);
 
 /* Tuning hook: tile configuration of the matrix-core products (0 = chosen by shape, the default; k-tiles
