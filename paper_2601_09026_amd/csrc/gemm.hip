@@ -301,10 +301,10 @@ __device__ __forceinline__ void tile_epilogue(
 //    walks them row-major, so every global access of the epilogue covers whole contiguous rows.
 //  * RAGGED: N no multiple of BN or K no multiple of BK (both multiples of 8): weight rows are clamped,
 //    columns guarded, and the chunks of the last k-tile that lie past K come from a zero chunk.
-// What bounds it: large launches the matrix cores at the clock the power limit leaves (the k loop of the
-// 256x256 tile runs at 1220 TFLOP/s on random operands, 1340-1500 without its loads) and then the epilogue,
-// which moves 4 to 16 bytes per output element with the matrix cores idle; launches of up to one tile per
-// CU the latency of first touches past the L2, which the deep ring covers.
+// What bounds it: large launches the matrix cores and then the epilogue, which moves 4 to 16 bytes per output
+// element with the matrix cores idle (in the step at the GPT-2 shape they are busy for 52 % of a 256x256 launch
+// with the plain store and for 37-44 % with the other epilogues: profiles/gpt2_small_fwd_adjoint_pmc_summary.txt);
+// launches of up to one tile per CU the latency of first touches past the L2, which the deep ring covers.
 // ---------------------------------------------------------------------------
 typedef __attribute__((address_space(1))) const void* gas_ptr;
 typedef __attribute__((address_space(3))) void* las_ptr;
@@ -568,9 +568,9 @@ gemm_f32_mfma_kernel(const GemmArgs a, int tiles_m, int tiles_n) {
 // transposed 4 x 4, so that a lane's 16-byte read is its operand of four MFMAs in that order; with the row pitch of 68
 // floats the 16 rows of a read fall on 16 distinct 16-byte slots and the 4-byte writes of a wavefront on 64 banks.
 // Any M; N and K multiples of 4: rows and columns past the edge are clamped, chunks past K become zeros.
-// Whole layer steps on the kernel above and on this one: 512 wide, 100 tokens, one layer 135 -> 77 us, transposed
-// 286 -> 175; 512 wide, 4 x 512 tokens 248 -> 218 and 465 -> 416; 200 wide, 600 hidden, 129 tokens (the FMA kernel
-// before) 132 -> 50 and 239 -> 110.
+// Whole layer steps on the kernel above and on this one: 512 wide, 100 tokens, one layer 138 -> 71 us, transposed
+// 292 -> 165; 512 wide, 4 x 512 tokens 230 -> 213 and 472 -> 446; 200 wide, 600 hidden, 129 tokens (the FMA kernel
+// before) 136 -> 55 and 257 -> 132.
 // ---------------------------------------------------------------------------
 template <int EPI, bool RAGGED>
 __global__ void __launch_bounds__(256)
@@ -1061,9 +1061,10 @@ static hipError_t launch_mfma(const GemmArgs& a, hipStream_t st) {
   return hipGetLastError();
 }
 
-// Two 64x64 tiles per CU are where the larger tile takes over: below, 32x32 tiles are faster throughout (1.02 to 2
-// times for whole steps), above they lose up to 15 % to fetching each operand twice as often (1024 wide, 12 layers
-// of 1024 tokens: 3420 us against 3776).  Ragged shapes have no other matrix-core kernel.
+// Two 64x64 tiles per CU are where the larger tile takes over: whole steps of small launches are up to twice as fast
+// on 32x32 tiles (1024 wide, 2 layers of 128 tokens: 171 us against 325), large ones lose up to 13 % to fetching each
+// operand twice as often (1024 wide, 4 layers of 1024 tokens: 1191 us against 1052), and near the line the two differ
+// by 2-8 % either way.  Ragged shapes have no other matrix-core kernel.
 template <int EPI>
 static hipError_t launch_f32_mfma(const GemmArgs& a, hipStream_t st) {
   const int tiles_m = (a.M + 63) / 64, tiles_n = (a.N + 63) / 64;
@@ -1104,15 +1105,15 @@ static double gemm_bytes(const GemmArgs& a, double esz) {
 
 // Tile configurations of the MFMA kernel (k-tiles of 64) and what a round of each takes on MI355X, in
 // microseconds: fixed + per_ktile * (k-tiles).  A launch runs in rounds of (CUs x resident blocks) tiles
-// whose time hardly depends on how full the round is; measured with launches of 9 to 3840 tiles and
-// reductions of 384 to 4096 (model within 10 % of the measured time for the better configurations):
+// whose time hardly depends on how full the round is.  The epilogue is not in the model: for the tile it picks it is
+// 12 % off in the median and 69 % at worst (fp32 epilogues of reductions of 384), yet over 64 shapes its pick is 0.6 %
+// slower than the best tile on average and 8 % at worst (profiles/gemm_tile_round_times.txt):
 //  1: 256x256, 8 wavefronts of 128x64, two stages: most reuse, what large launches run on;
 //  3: 256x192, 8 wavefronts of 64x96, two stages: where 256 columns leave a round much emptier;
 //  4: 128x128, two stages, two blocks per CU (one block's epilogue under the other's k loop);
 //  6: 128x128, four stages, one block per CU: launches of up to one tile per CU, which wait for memory
-//     latency and not for bandwidth (4096 x 768, reduction 3072: 49 us with two stages, 38 with four);
-//  8: 64x64, four stages, two blocks per CU, and 9: two stages, four blocks per CU: few rows or columns
-//     (768 x 768, reduction 4096: 43 us as 128x128 tiles, 24 as 64x64).
+//     latency and not for bandwidth (4096 x 768, reduction 3072: 51 us with two stages, 37 with four);
+//  8: 64x64, four stages, two blocks per CU, and 9: two stages, four blocks per CU: few rows or columns.
 struct TileCfg { int id, bm, bn, per_cu; double fixed, per_ktile; };
 static const TileCfg kTileCfgs[] = {{1, 256, 256, 1, 7.0, 1.60}, {3, 256, 192, 1, 5.5, 1.33}, {4, 128, 128, 2, 2.7, 1.07},
                                     {6, 128, 128, 1, 2.5, 0.55}, {8, 64, 64, 2, 2.5, 0.375}, {9, 64, 64, 4, 2.5, 0.75}};
@@ -1201,8 +1202,9 @@ static hipError_t launch_tn(const GemmTnArgs& a, int splits, hipStream_t st) {
 }
 
 // Tile and number of token slices of a parameter-gradient product.  Microseconds of a round as in
-// kTileCfgs, measured at 768..3072 wide outputs and 4096 and 12608 tokens; the transposing reads deliver half
-// the bytes per clock of plain ones, so a k-tile takes longer than there.  Few output tiles and many tokens
+// kTileCfgs, 8 % off in the median over 384 to 4096 wide outputs of 2048 to 12608 tokens, the pick 1 % slower than
+// the best tile on average and 13 % at worst (profiles/gemm_tile_round_times.txt); the transposing reads deliver
+// half the bytes per clock of plain ones, so a k-tile takes longer than there.  Few output tiles and many tokens
 // (384 x 384 from 12608 tokens: 9 tiles of 128x128) are cut into slices of at least 8 k-tiles, which costs
 // writing and summing the slices' partial results.
 // Slices change the order of the sums, so their number follows from the layer's sizes alone, as the best one for a

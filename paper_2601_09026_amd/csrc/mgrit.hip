@@ -8,7 +8,7 @@
 //   -> LN2(X+ybar) -> FFN1 (+GELU) -> FFN2 with the Euler update  out = X + h(ybar + m) + rhs
 // Adjoint step (the discrete transpose, sec. 3.1 backward problem): the block internals at
 // the linearisation state are produced once per layer by a forward pass that stops before
-// FFN2 ("linearisation cache": qkv, attention output and log-sum-exp, s, pre-GELU z);
+// FFN2 ("linearisation cache": qkv, attention output and log-sum-exp, s, gelu'(z));
 // each adjoint evaluation then runs only the transposed chain.  The cache is independent
 // of the step size, so coarse-level adjoint steps reuse the fine layer's entry.
 //
@@ -45,7 +45,9 @@ constexpr int DEFAULT_MAX_GROUPS = 4;
 // smallest modelled GEMM time over the sweep.  The model adds the chunks up as if they ran one after the
 // other; on two lanes the emptier rounds of one chunk are filled by the other's, so near-ties (3 %) go to the
 // larger count (BERT shape, forward: 4 groups 31.6 ms, 5 30.4, 6 31.6; GPT-2 shape with gradients 193.4, 188.8,
-// 196.5; ViT shape 84.0, 83.4, 87.7).
+// 196.5; ViT shape 84.0, 83.4, 87.7; where the pick changed at nine shapes of 256 to 1280 wide and 1024 to 16384
+// tokens it was 10 to 0.4 % faster up to 4096 tokens and 0.4 to 2 % slower above: the last table of
+// profiles/gemm_tile_round_times.txt).
 inline int default_groups(const mgrit_model_desc* md, int sweep) {
   if (md->dtype != MGRIT_DTYPE_BF16 || sweep < 2) return DEFAULT_MAX_GROUPS;
   const int T = md->batch * md->seq, d = md->d_model, f = md->d_ff;
@@ -1140,6 +1142,10 @@ struct Driver {
   // the helper lane turns them into gradients in launches over all of them; the two sets of work buffers (one per
   // lane) alternate.  Same kernels on the same data as layer by layer.  BERT shape, 64 layers: a layer's gradients
   // in the chain cost 190 us next to 330 us of chain.
+  // Only where a layer's internals stay put until the helper lane has read them, i.e. with the N-layer cache (a lane's
+  // recomputed internals are overwritten by its next layer), and on plain grids: the stacked one has two engines per
+  // lane with layer types of their own, and its copies of the frozen half would have to be handed over as well.  Those
+  // two stay in the chain (BERT shape without the cache, which recomputes as well, 35.5 ms a step, with it 23.6).
   int run_serial_emitting() {
     AuxStream& a = aux_stream();
     const int status = serial_emitting_chain();
