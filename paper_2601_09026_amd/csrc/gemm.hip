@@ -673,12 +673,12 @@ gemm_f32_small_kernel(const GemmArgs a, int tiles_n) {
 // ---------------------------------------------------------------------------
 
 // Sum that carries its rounding error along (Kahan): 16384 positive terms come out within 7e-8 of their sum, as a
-// plain chain within 8e-7 to 3e-6, depending on their spread.
-template <typename V> struct CarrySum {
-  V sum = V{}, err = V{};
-  __device__ __forceinline__ void add(V x) {
-    const V y = x - err, t = sum + y;
-    err = (t - sum) - y;
+// plain chain within 8e-7 to 3e-6, depending on their spread.  An infinite sum carries nothing, so it stays infinite.
+struct CarrySum {
+  float sum = 0.f, err = 0.f;
+  __device__ __forceinline__ void add(float x) {
+    const float y = x - err, t = sum + y;
+    err = __builtin_isfinite(t) ? (t - sum) - y : 0.f;
     sum = t;
   }
 };
@@ -755,7 +755,7 @@ gemm_tn_mfma_kernel(const GemmTnArgs a, int tiles_m, int tiles_n, int splits, in
     for (int j = 0; j < TN; ++j)
 #pragma unroll
       for (int r = 0; r < 16; ++r) acc[i][j][r] = 0.f;
-  CarrySum<float> bsum[TM];
+  CarrySum bsum[TM];
   float btile[TM];                                             // of the k-tile at hand
   const bool sums = tn == 0 && wn0 == 0;                       // wave-uniform
 
@@ -883,11 +883,15 @@ __global__ void __launch_bounds__(256) gemm_tn_reduce_kernel(const GemmTnArgs a,
   const long i = ((long)blockIdx.x * 256 + threadIdx.x) * 4;
   if (i >= each) return;
   const float* p = a.partial + (long)g * splits * each + i;
-  CarrySum<f32x4> acc;
-  for (int s = 0; s < splits; ++s) acc.add(*reinterpret_cast<const f32x4*>(p + s * each));
+  CarrySum acc[4];
+  for (int s = 0; s < splits; ++s) {
+    const f32x4 v = *reinterpret_cast<const f32x4*>(p + s * each);
+#pragma unroll
+    for (int e = 0; e < 4; ++e) acc[e].add(v[e]);
+  }
   char* out = const_cast<char*>(a.out.at(g));
   float* o = i < mn ? reinterpret_cast<float*>(out + a.w_off) + i : reinterpret_cast<float*>(out + a.b_off) + (i - mn);
-  *reinterpret_cast<f32x4*>(o) = a.scale * acc.sum;
+  *reinterpret_cast<f32x4*>(o) = a.scale * f32x4{acc[0].sum, acc[1].sum, acc[2].sum, acc[3].sum};
 }
 
 // fp32 operands: 64x64 tile, 4 wavefronts of 32x32 on the 32x32x2 fp32 MFMA, 16 tokens per k-tile.  The
@@ -911,7 +915,7 @@ __global__ void __launch_bounds__(256) gemm_tn_f32_kernel(const GemmTnArgs a, in
   f32x16 acc[1][1];
 #pragma unroll
   for (int r = 0; r < 16; ++r) acc[0][0][r] = 0.f;
-  CarrySum<float> bsum;
+  CarrySum bsum;
   auto ld = [&](const float* p, int stride, int col, int k) {
     return k < K ? *reinterpret_cast<const f32x4*>(p + (long)k * stride + col) : zero;
   };

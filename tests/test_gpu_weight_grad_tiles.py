@@ -70,3 +70,30 @@ def test_bias_gradient_rounding(d, B, S, dtype):
     worst = np.abs(got / ref - 1.0).max()
     print(f"  largest relative error {worst:.2e}")
     assert worst <= 12 * 2.0 ** -24
+
+
+@pytest.mark.parametrize("dtype", [BF16, F32])
+@pytest.mark.parametrize("slices", [1, 3])
+def test_infinite_terms_stay_infinite(slices, dtype):
+    """One infinite entry of lambda: its column of b2's gradient is infinite, the others are what they are without it."""
+    wl = wls.Workload("inf", wls.ARCH_ENCODER, 64, 2, 64, 2, 200, 0, 1, 0.5, 1, 1, 1, dtype, 80)
+    print(f"[case] infinite lambda, {slices} slices, dtype={dtype}", flush=True)
+    dm = DeviceModel(wl, keep_host=False)
+    opts = mb.mgrit_opts(1, wl.h, 1, 1, 0)
+    gen = torch.Generator(device="cuda").manual_seed(4)
+    lam = torch.randn((wl.tokens, wl.d_model), generator=gen, device="cuda")
+    Z, _ = mb.mgrit_forward(dm.desc, opts, torch.randn((wl.tokens, wl.d_model), generator=gen, device="cuda"), dm.blocks)
+    mb.lib().mgrit_debug_gradient_slices(slices)
+    try:
+        b2 = []
+        for bad in (False, True):
+            if bad:
+                lam[70, 5], lam[150, 9] = float("inf"), -float("inf")      # in the first and in a later slice
+            grad = grad_blocks(dm.desc, 1)
+            mb.mgrit_adjoint(dm.desc, opts, Z, dm.blocks, lam, dtheta=grad)
+            b2.append(mb.unpack_grad(dm.desc, grad[0])["b2"].reshape(-1))
+    finally:
+        mb.lib().mgrit_debug_gradient_slices(0)
+    want = b2[0].copy()
+    want[5], want[9] = np.inf, -np.inf
+    assert np.array_equal(b2[1], want)
