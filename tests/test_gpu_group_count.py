@@ -57,7 +57,7 @@ def test_layer_step_bits(dtype, d, f, B, S, adjoint):
 # (the gains and shifts of the LayerNorms are summed by a kernel of their own)
 @pytest.mark.parametrize("norms", [True, False])
 @pytest.mark.parametrize("arch,dtype,d,f,B,S,Sm", [
-    (wls.ARCH_ENCODER, wls.DTYPE_BF16, 64, 192, 4, 1029, 0),     # token slices that pay for few layers only
+    (wls.ARCH_ENCODER, wls.DTYPE_BF16, 256, 1024, 4, 509, 0),    # token slices would pay for one or two layers only
     (wls.ARCH_CROSS, wls.DTYPE_BF16, 128, 256, 4, 515, 260),
     (wls.ARCH_ENCODER, wls.DTYPE_F32, 256, 512, 4, 509, 0)])
 def test_gradient_bits(arch, dtype, d, f, B, S, Sm, norms):
@@ -73,13 +73,18 @@ def test_gradient_bits(arch, dtype, d, f, B, S, Sm, norms):
 
     def run():
         out = {}
-        for lanes, cache in ((1, True), (2, True), (2, False)):
+        for lanes, cache, pair in ((1, True, False), (2, True, False), (2, False, False), (2, True, True)):
             mb.mgrit_set_lanes(lanes)            # two lanes: a serial chain hands its gradients over in batches ...
             mb.mgrit_set_adjoint_cache(cache)    # ... unless it has no cache, then they are formed layer by layer
             grads = [torch.zeros(floats, device="cuda") for _ in range(wl.N)]
             dmem = None if mem is None else torch.full_like(mem, float("nan"))
             try:
-                lam, _ = mb.mgrit_adjoint(dm.desc, opts, Z, dm.blocks, lamN, memory=mem,
+                ws = torch.empty(mb.mgrit_workspace_bytes(dm.desc, opts, 2), dtype=torch.uint8, device="cuda")
+                if pair:                         # the forward solve fills the cache one layer after the other
+                    Zp, _ = mb.mgrit_forward(dm.desc, opts, Z[0].clone(), dm.blocks, memory=mem, adjoint_workspace=ws,
+                                             with_gradients=True)
+                    assert torch.equal(Zp, Z), f"lanes={lanes}: states differ"
+                lam, _ = mb.mgrit_adjoint(dm.desc, opts, Z, dm.blocks, lamN, memory=mem, workspace=ws, linearised=pair,
                                           dtheta=[g.view(torch.uint8) for g in grads], dmemory=dmem)
             finally:
                 mb.mgrit_set_adjoint_cache(True)
@@ -90,6 +95,6 @@ def test_gradient_bits(arch, dtype, d, f, B, S, Sm, norms):
                     if norms == name.startswith("ln"):
                         one[f"{name} of layer {n}"] = torch.from_numpy(t)
             for name, t in one.items():
-                assert torch.equal(t, out.setdefault(name, t)), f"lanes={lanes} cache={cache}: {name} differs"
+                assert torch.equal(t, out.setdefault(name, t)), f"lanes={lanes} cache={cache} pair={pair}: {name} differs"
         return out
     with_groups((1, 3, 4), run)
