@@ -119,6 +119,47 @@ template <typename V> __device__ __forceinline__ V ld_stream(const V* p) {
   return __builtin_nontemporal_load((gptr)p);
 }
 
+// the same without the hint
+template <typename V> __device__ __forceinline__ V ld_global(const V* p) {
+  typedef const __attribute__((address_space(1))) V* gptr;
+  return *(gptr)p;
+}
+
+// ---------------------------------------------------------------------------
+// Global-to-LDS loads and the order of their tiles
+// ---------------------------------------------------------------------------
+typedef __attribute__((address_space(1))) const void* gas_ptr;
+typedef __attribute__((address_space(3))) void* las_ptr;
+
+// Loads from global memory straight into LDS, 16 bytes per lane: lane l's bytes land at dst + 16*l.  As buffer loads
+// (uniform base, 32-bit lane and scalar offsets in bytes): the compiler takes the global_load_lds form for a flat
+// access that may touch LDS out of order, and then every wait on an LDS read in the loop waits for all reads in
+// flight (lgkmcnt(0)) instead of for the one that is needed.
+// The base is the same in every lane; readfirstlane says so where an index division went through vector registers (a
+// base that may differ between lanes makes a loop over the lanes out of every load).
+__device__ __forceinline__ __amdgpu_buffer_rsrc_t lds_source(const void* base) {
+  const unsigned long p = (unsigned long)base;
+  const unsigned lo = __builtin_amdgcn_readfirstlane((unsigned)p), hi = __builtin_amdgcn_readfirstlane((unsigned)(p >> 32));
+  return __builtin_amdgcn_make_buffer_rsrc((void*)((unsigned long)hi << 32 | lo), 0, 0xffffffffu, 0x00020000);
+}
+__device__ __forceinline__ void load_to_lds(__amdgpu_buffer_rsrc_t src, unsigned char* dst, int lane_offset,
+                                            int scalar_offset) {
+  __builtin_amdgcn_raw_ptr_buffer_load_lds(src, (__attribute__((address_space(3))) void*)dst, 16, lane_offset,
+                                           scalar_offset, 0, 0);
+}
+
+template <int N> __device__ __forceinline__ void wait_vmcnt() {
+  static_assert(N >= 0 && N < 64, "vmcnt range");
+  asm volatile("s_waitcnt vmcnt(%0)" ::"n"(N) : "memory");
+}
+// Block barrier that waits for nothing else.  __syncthreads() would first wait for every outstanding
+// vector-memory operation of the wavefront, i.e. drain the whole ring of k-tiles in flight.
+__device__ __forceinline__ void bare_barrier() {
+  __builtin_amdgcn_sched_barrier(0);
+  asm volatile("s_barrier" ::: "memory");
+  __builtin_amdgcn_sched_barrier(0);
+}
+
 // ---------------------------------------------------------------------------
 // Transposed fragments from row-major LDS tiles (ds_read_b64_tr_b16, bf16): in each group of 16 lanes, lane l
 // addresses the 8 bytes at columns 4*(l%4).. of row l/4 of a 4 x 16 block and receives column l%16 of its 4 rows.
@@ -146,6 +187,12 @@ __device__ __forceinline__ void wait_lgkm() {
 __device__ __forceinline__ bf16x8 tr_value(const TrFrag& f) {
   const s16x8 v = {f.lo[0], f.lo[1], f.lo[2], f.lo[3], f.hi[0], f.hi[1], f.hi[2], f.hi[3]};
   return __builtin_bit_cast(bf16x8, v);
+}
+
+// 16 bytes of an LDS tile that global-to-LDS loads fill (restrict: as above)
+__device__ __forceinline__ bf16x8 lds_read16(const lds_byte* __restrict__ p) {
+  typedef const __attribute__((address_space(3))) bf16x8* ptr;
+  return *(ptr)p;
 }
 
 // load / store 4 consecutive elements as floats

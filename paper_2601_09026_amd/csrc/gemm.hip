@@ -196,7 +196,7 @@ __device__ __forceinline__ void tile_epilogue(
         const f32x4 z = {0.f, 0.f, 0.f, 0.f};
         int n = ncol0 + CW * ((p * 64 + lane) % CI) + 4 * h;
         if (RAGGED) n = n < N ? n : 0;
-        bv[p][h] = bias ? *reinterpret_cast<const f32x4*>(bias + n) : z;
+        bv[p][h] = bias ? ld_global(reinterpret_cast<const f32x4*>(bias + n)) : z;
       }
     // The bias vectors have landed before the first item uses them; saying so once, outside the
     // row guards below, keeps the per-item waits on them from also waiting for every earlier
@@ -283,8 +283,12 @@ __device__ __forceinline__ void tile_epilogue(
 
 // ---------------------------------------------------------------------------
 // MFMA kernel.  WM x WN wavefronts, each owning a (BM/WM) x (BN/WN) tile of the output.
-//  * Operands go from global memory straight into LDS (global_load_lds, 16 bytes per lane,
-//    no register staging) through a ring of STAGES k-tiles of depth BK.
+//  * Operands go from global memory straight into LDS (buffer loads, 16 bytes per lane, no register
+//    staging; the ragged form, whose zero chunk needs an address per lane, as global_load_lds) through a
+//    ring of STAGES k-tiles of depth BK.  The buffer form lets the compiler wait for the fragment it needs
+//    instead of for all LDS reads in flight and takes the address arithmetic off the vector unit: with 5
+//    layers of 4096 rows 768 -> 2304 82 -> 78 us, 768 -> 3072 with GELU 116 -> 108, 3072 -> 768 84 -> 78;
+//    one layer 27 -> 23, 36.5 -> 33.
 //  * An LDS row holds the BK bf16 of one matrix row unpadded; its 16-byte chunks are XOR-swizzled by
 //    the row number so that the 16-byte fragment reads of 32 consecutive rows are bank-conflict free.
 //    A load instruction of a wavefront fills 1 KB = 8 consecutive rows; the lane that will
@@ -306,21 +310,6 @@ __device__ __forceinline__ void tile_epilogue(
 // with the plain store and for 37-44 % with the other epilogues: profiles/gpt2_small_fwd_adjoint_pmc_summary.txt);
 // launches of up to one tile per CU the latency of first touches past the L2, which the deep ring covers.
 // ---------------------------------------------------------------------------
-typedef __attribute__((address_space(1))) const void* gas_ptr;
-typedef __attribute__((address_space(3))) void* las_ptr;
-
-template <int N> __device__ __forceinline__ void wait_vmcnt() {
-  static_assert(N >= 0 && N < 64, "vmcnt range");
-  asm volatile("s_waitcnt vmcnt(%0)" ::"n"(N) : "memory");
-}
-// Block barrier that waits for nothing else.  __syncthreads() would first wait for every outstanding
-// vector-memory operation of the wavefront, i.e. drain the whole ring of k-tiles in flight.
-__device__ __forceinline__ void bare_barrier() {
-  __builtin_amdgcn_sched_barrier(0);
-  asm volatile("s_barrier" ::: "memory");
-  __builtin_amdgcn_sched_barrier(0);
-}
-
 // LDS has 64 four-byte banks (256 bytes per clock); a 16-byte read is served 16 lanes at a
 // time, so 16 consecutive rows must land on 16 distinct 16-byte slots modulo 256 bytes.  Two of the
 // 128-byte rows share a 256-byte bank row: swizzle by the row pair.
@@ -355,7 +344,7 @@ gemm_mfma_kernel(const GemmArgs a, int tiles_m, int tiles_n, int total_tiles, in
   const int tile = (pid & 7) * per_xcd + (pid >> 3);
   if (tile >= total_tiles) return;
   const int tiles_per_group = tiles_m * tiles_n;
-  const int g = tile / tiles_per_group;
+  const int g = __builtin_amdgcn_readfirstlane(tile / tiles_per_group);   // (the divisions go through vector registers)
   const int tg = tile - g * tiles_per_group;
   int tm, tn;
   if (pn > 0) {
@@ -368,7 +357,7 @@ gemm_mfma_kernel(const GemmArgs a, int tiles_m, int tiles_n, int total_tiles, in
     tm = tg / tiles_n;
     tn = tg - tm * tiles_n;
   }
-  const int m0 = tm * BM, n0 = tn * BN;
+  const int m0 = __builtin_amdgcn_readfirstlane(tm) * BM, n0 = __builtin_amdgcn_readfirstlane(tn) * BN;
 
   const bf16* A = reinterpret_cast<const bf16*>(a.A) + a.a_slots.of(g) * a.a_slot_stride;
   const char* pblock = a.B.at(g);
@@ -376,39 +365,41 @@ gemm_mfma_kernel(const GemmArgs a, int tiles_m, int tiles_n, int total_tiles, in
   const int K = a.K, M = a.M, N = a.N;
 
   const int tid = threadIdx.x;
-  const int wave = tid >> 6, lane = tid & 63;
+  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6), lane = tid & 63;
   const int lr = lane & 31, lh = lane >> 5;
   const int wm0 = (wave / WN) * WTM, wn0 = (wave % WN) * WTN;
 
-  // global -> LDS: this lane's element offsets (row clamped at the ragged tail of M)
+  // global -> LDS: this lane's byte offsets from the tile's first rows (row clamped at the ragged tail of M)
   const int lrow = lane / CPR, lpos = lane % CPR;
-  unsigned aoff[A_LD], boff[B_LD];
+  const char* Am = reinterpret_cast<const char*>(A + (long)m0 * K);
+  const char* Bn = reinterpret_cast<const char*>(B + (long)n0 * K);
+  const auto srcA = lds_source(Am), srcB = lds_source(Bn);
+  int aoff[A_LD], boff[B_LD];
 #pragma unroll
   for (int j = 0; j < A_LD; ++j) {
     const int row = (wave * A_LD + j) * RPL + lrow;            // row inside the tile
-    int gm = m0 + row;
-    gm = gm < M ? gm : M - 1;
-    aoff[j] = (unsigned)gm * (unsigned)K + (lpos ^ swz(row)) * 8;
+    aoff[j] = ((row < M - m0 ? row : M - 1 - m0) * K + (lpos ^ swz(row)) * 8) * 2;
   }
 #pragma unroll
   for (int j = 0; j < B_LD; ++j) {
     const int row = (wave * B_LD + j) * RPL + lrow;
-    int gn = n0 + row;
-    if (RAGGED) gn = gn < N ? gn : N - 1;
-    boff[j] = (unsigned)gn * (unsigned)K + (lpos ^ swz(row)) * 8;
+    boff[j] = ((RAGGED && row >= N - n0 ? N - 1 - n0 : row) * K + (lpos ^ swz(row)) * 8) * 2;
   }
 
   auto issue_one = [&](int stage, int k0, int idx) {
     unsigned char* sa = smem2 + stage * STAGE;
     const bool is_a = idx < A_LD;
-    const bf16* src = is_a ? A + aoff[idx < A_LD ? idx : 0] + k0 : B + boff[idx < A_LD ? 0 : idx - A_LD] + k0;
+    const int off = is_a ? aoff[idx < A_LD ? idx : 0] : boff[idx < A_LD ? 0 : idx - A_LD];
     unsigned char* dst = is_a ? sa + (wave * A_LD + idx) * 1024 : sa + A_BYTES + (wave * B_LD + idx - A_LD) * 1024;
     if constexpr (RAGGED) {
       // the last k-tile reaches past K: its 16-byte chunks from K on are zeros (K is a multiple of 8)
       const int row = is_a ? (wave * A_LD + idx) * RPL + lrow : (wave * B_LD + idx - A_LD) * RPL + lrow;
-      if (k0 + (lpos ^ swz(row)) * 8 >= K) src = reinterpret_cast<const bf16*>(g_zero_chunk);
+      const char* src = (is_a ? Am : Bn) + off + 2 * (long)k0;
+      if (k0 + (lpos ^ swz(row)) * 8 >= K) src = reinterpret_cast<const char*>(g_zero_chunk);
+      __builtin_amdgcn_global_load_lds((gas_ptr)src, (las_ptr)dst, 16, 0, 0);
+    } else {
+      load_to_lds(is_a ? srcA : srcB, dst, off, 2 * k0);
     }
-    __builtin_amdgcn_global_load_lds((gas_ptr)src, (las_ptr)dst, 16, 0, 0);
   };
   auto issue = [&](int stage, int k0) {
 #pragma unroll
@@ -443,17 +434,18 @@ gemm_mfma_kernel(const GemmArgs a, int tiles_m, int tiles_n, int total_tiles, in
     if (behind >= 1) { wait_vmcnt<PER_TILE>(); return; }
     wait_vmcnt<0>();
   };
+  const lds_byte* lds0 = (const lds_byte*)smem2;
   bf16x8 fa[2][TM], fb[2][TN];
   wait_tile(0, STAGES < KT ? STAGES : KT);
   bare_barrier();
 #pragma unroll
-  for (int j = 0; j < TN; ++j) fb[0][j] = *reinterpret_cast<const bf16x8*>(smem2 + A_BYTES + (wn0 + j * 32) * RB + foff[0]);
+  for (int j = 0; j < TN; ++j) fb[0][j] = lds_read16(lds0 + A_BYTES + (wn0 + j * 32) * RB + foff[0]);
 #pragma unroll
-  for (int i = 0; i < TM; ++i) fa[0][i] = *reinterpret_cast<const bf16x8*>(smem2 + (wm0 + i * 32) * RB + foff[0]);
+  for (int i = 0; i < TM; ++i) fa[0][i] = lds_read16(lds0 + (wm0 + i * 32) * RB + foff[0]);
   int cur = 0;
-  for (int kt = 0; kt < KT; ++kt) {
+  auto tile_step = [&](int kt, auto loads_tag) {
+    constexpr bool LOADS = decltype(loads_tag)::value;     // tile kt + STAGES exists
     const int nxt = cur + 1 == STAGES ? 0 : cur + 1;
-    const bool pf = kt + STAGES < KT;
     const int pk0 = (kt + STAGES) * BK;
 #pragma unroll
     for (int ks = 0; ks < KS; ++ks) {
@@ -461,12 +453,13 @@ gemm_mfma_kernel(const GemmArgs a, int tiles_m, int tiles_n, int total_tiles, in
       const bool last = ks == KS - 1;
       if (last) {
         asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
-        wait_tile(kt + 1, kt + STAGES < KT ? kt + STAGES : KT);
+        if constexpr (LOADS) wait_vmcnt<(STAGES - 2) * PER_TILE>();
+        else wait_tile(kt + 1, KT);
         bare_barrier();
       }
       const int rst = last ? nxt : cur, rks = last ? 0 : ks + 1;
-      const unsigned char* sA = smem2 + rst * STAGE + wm0 * RB;
-      const unsigned char* sB = smem2 + rst * STAGE + A_BYTES + wn0 * RB;
+      const lds_byte* sA = lds0 + rst * STAGE + wm0 * RB;
+      const lds_byte* sB = lds0 + rst * STAGE + A_BYTES + wn0 * RB;
       // The fragment reads of the next k-step and the loads of the refilled stage are spread between
       // the matrix instructions, fenced so that the scheduler keeps them apart: a wavefront that has to
       // wait for its turn at the LDS or the load unit has matrix work queued meanwhile.
@@ -479,20 +472,23 @@ gemm_mfma_kernel(const GemmArgs a, int tiles_m, int tiles_n, int total_tiles, in
 #pragma unroll
         for (int u = 0; u < RD; ++u)
           if (u >= r0 && (u < r1 || q == NM - 1)) {
-            if (u < TN) fb[nb][u] = *reinterpret_cast<const bf16x8*>(sB + u * 32 * RB + foff[rks]);
-            else fa[nb][u - TN] = *reinterpret_cast<const bf16x8*>(sA + (u - TN) * 32 * RB + foff[rks]);
+            if (u < TN) fb[nb][u] = lds_read16(sB + u * 32 * RB + foff[rks]);
+            else fa[nb][u - TN] = lds_read16(sA + (u - TN) * 32 * RB + foff[rks]);
           }
-        if (last) {
+        if (LOADS && last) {
           const int l0 = (q * PER_TILE + NM - 1) / NM, l1 = ((q + 1) * PER_TILE + NM - 1) / NM;
 #pragma unroll
           for (int u = 0; u < PER_TILE; ++u)
-            if (u >= l0 && u < l1 && pf) issue_one(cur, pk0, u);
+            if (u >= l0 && u < l1) issue_one(cur, pk0, u);
         }
         __builtin_amdgcn_sched_barrier(0);
       }
     }
     cur = nxt;
-  }
+  };
+  int kt = 0;
+  for (; kt + STAGES < KT; ++kt) tile_step(kt, std::true_type{});
+  for (; kt < KT; ++kt) tile_step(kt, std::false_type{});
   asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");       // (the reads ahead of a tile that does not exist)
   bare_barrier();
 
@@ -683,7 +679,7 @@ struct CarrySum {
   }
 };
 
-template <int BM, int BN, int STAGES, int WM, int WN>
+template <int BM, int BN, int STAGES, int WM, int WN, bool TAIL>
 __global__ void __launch_bounds__(64 * WM * WN, WM * WN / 4)
 gemm_tn_mfma_kernel(const GemmTnArgs a, int tiles_m, int tiles_n, int splits, int total_tiles, int per_xcd) {
   constexpr int NW = WM * WN, BK = 64, KS = BK / 16;
@@ -696,43 +692,49 @@ gemm_tn_mfma_kernel(const GemmTnArgs a, int tiles_m, int tiles_n, int splits, in
   const int tile = (blockIdx.x & 7) * per_xcd + (blockIdx.x >> 3);
   if (tile >= total_tiles) return;
   const int per_slice = tiles_m * tiles_n;
-  const int gs = tile / per_slice, tg = tile - gs * per_slice, tm = tg / tiles_n, tn = tg - tm * tiles_n;
-  const int g = gs / splits, sp = gs - g * splits;       // slice sp of the group's tokens
+  const int gs = __builtin_amdgcn_readfirstlane(tile / per_slice), tg = tile - gs * per_slice;
+  const int tm = __builtin_amdgcn_readfirstlane(tg / tiles_n), tn = tg - tm * tiles_n;
+  const int g = __builtin_amdgcn_readfirstlane(gs / splits), sp = gs - g * splits;       // slice sp of the group's tokens
   const int m0 = tm * BM, n0 = tn * BN, M = a.M, N = a.N;
   const int all_tiles = (a.K + BK - 1) / BK;
   const int kt0 = (int)((long)all_tiles * sp / splits), kt1 = (int)((long)all_tiles * (sp + 1) / splits);
   const int K = (kt1 * BK < a.K ? kt1 * BK : a.K) - kt0 * BK;
   const bf16* A = reinterpret_cast<const bf16*>(a.A) + a.a_slots.of(g) * a.a_slot_stride + (long)kt0 * BK * M;
   const bf16* B = reinterpret_cast<const bf16*>(a.B) + a.b_slots.of(g) * a.b_slot_stride + (long)kt0 * BK * N;
-  const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63;
+  const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), lane = threadIdx.x & 63;
   const int wm0 = (wave / WN) * WTM, wn0 = (wave % WN) * WTN;
 
   // row r keeps logical chunk c at position c ^ f(r): 256-byte rows (or longer) repeat the banks every row,
   // 128-byte rows every second one
   auto swz_of = [](int row_bytes, int r) { return row_bytes >= 256 ? (r & 3) << 2 : ((r >> 1) & 1) << 2; };
-  unsigned aoff[A_LD], boff[B_LD];                       // element offsets inside a k-tile
+  int aoff[A_LD], boff[B_LD];                            // element offsets inside a k-tile
 #pragma unroll
   for (int j = 0; j < A_LD; ++j) {
     const int row = (wave * A_LD + j) * (1024 / RA) + lane / (RA / 16);
     int col = m0 + ((lane % (RA / 16)) ^ swz_of(RA, row)) * 8;
     col = col < M ? col : 0;                             // columns past the edge: never stored
-    aoff[j] = (unsigned)row * (unsigned)M + col;
+    aoff[j] = row * M + col;
   }
 #pragma unroll
   for (int j = 0; j < B_LD; ++j) {
     const int row = (wave * B_LD + j) * (1024 / RB) + lane / (RB / 16);
     int col = n0 + ((lane % (RB / 16)) ^ swz_of(RB, row)) * 8;
     col = col < N ? col : 0;
-    boff[j] = (unsigned)row * (unsigned)N + col;
+    boff[j] = row * N + col;
   }
   auto issue_one = [&](int stage, int k0, int idx) {
     const bool is_a = idx < A_LD;
-    const bf16* src = is_a ? A + (long)k0 * M + aoff[idx < A_LD ? idx : 0] : B + (long)k0 * N + boff[idx < A_LD ? 0 : idx - A_LD];
     const int slot = is_a ? wave * A_LD + idx : wave * B_LD + idx - A_LD;
-    const int row = is_a ? slot * (1024 / RA) + lane / (RA / 16) : slot * (1024 / RB) + lane / (RB / 16);
-    if (row >= K - k0) src = reinterpret_cast<const bf16*>(g_zero_chunk);
     unsigned char* dst = smem2 + stage * STAGE + (is_a ? 0 : A_BYTES) + slot * 1024;
-    __builtin_amdgcn_global_load_lds((gas_ptr)src, (las_ptr)dst, 16, 0, 0);
+    const bf16* tile = is_a ? A + (long)k0 * M : B + (long)k0 * N;
+    const int off = is_a ? aoff[idx < A_LD ? idx : 0] : boff[idx < A_LD ? 0 : idx - A_LD];
+    if constexpr (TAIL) {                                  // tokens past the last one are zeros
+      const int row = is_a ? slot * (1024 / RA) + lane / (RA / 16) : slot * (1024 / RB) + lane / (RB / 16);
+      const bf16* src = row < K - k0 ? tile + off : reinterpret_cast<const bf16*>(g_zero_chunk);
+      __builtin_amdgcn_global_load_lds((gas_ptr)src, (las_ptr)dst, 16, 0, 0);
+    } else {
+      load_to_lds(lds_source(tile), dst, 2 * off, 0);
+    }
   };
   auto issue = [&](int stage, int k0) {
 #pragma unroll
@@ -1186,14 +1188,14 @@ static hipError_t launch_epi(const GemmArgs& a, bool is_bf16, hipStream_t st) {
   return ragged ? launch_cfg<EPI, true>(cfg, a, st) : launch_cfg<EPI, false>(cfg, a, st);
 }
 
-template <int BM, int BN, int STAGES, int WM, int WN>
-static hipError_t launch_tn(const GemmTnArgs& a, int splits, hipStream_t st) {
+template <int BM, int BN, int STAGES, int WM, int WN, bool TAIL>
+static hipError_t launch_tn_tile(const GemmTnArgs& a, int splits, hipStream_t st) {
   const int tiles_m = (a.M + BM - 1) / BM, tiles_n = (a.N + BN - 1) / BN;
   const int total = tiles_m * tiles_n * a.n_groups * splits, per_xcd = (total + 7) / 8;
   const size_t ring = (size_t)STAGES * (BM + BN) * 128;
   const size_t staging = (size_t)WM * WN * ((32 * (BN / WN * 4 + 16) + 1023) / 1024 * 1024);
   const size_t smem = ring > staging ? ring : staging;
-  auto kern = gemm_tn_mfma_kernel<BM, BN, STAGES, WM, WN>;
+  auto kern = gemm_tn_mfma_kernel<BM, BN, STAGES, WM, WN, TAIL>;
   static bool attr_done = false;
   if (!attr_done) {
     hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(kern),
@@ -1203,6 +1205,13 @@ static hipError_t launch_tn(const GemmTnArgs& a, int splits, hipStream_t st) {
   }
   hipLaunchKernelGGL(kern, dim3(per_xcd * 8), dim3(64 * WM * WN), smem, st, a, tiles_m, tiles_n, splits, total, per_xcd);
   return hipGetLastError();
+}
+
+// TAIL: the last 64-token k-tile is not whole
+template <int BM, int BN, int STAGES, int WM, int WN>
+static hipError_t launch_tn(const GemmTnArgs& a, int splits, hipStream_t st) {
+  return a.K % 64 ? launch_tn_tile<BM, BN, STAGES, WM, WN, true>(a, splits, st)
+                  : launch_tn_tile<BM, BN, STAGES, WM, WN, false>(a, splits, st);
 }
 
 // Tile and number of token slices of a parameter-gradient product.  Microseconds of a round as in
