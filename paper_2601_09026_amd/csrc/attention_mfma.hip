@@ -8,139 +8,129 @@
 //     lanes l and l+32): no cross-lane reductions over the score tile;
 //   * a score / probability tile, converted to bf16, already IS the B operand of the next
 //     product (registers 8t..8t+7 feed k-step t), provided the A operand enumerates the
-//     reduction index the same way: k-slot (half, e) <-> row 16t + 8*(e/4) + 4*half + e%4.
-//     A operands of that kind are read from a transposed LDS tile as two 8-byte pieces;
+//     reduction index the same way: k-slot (half, e) <-> row 16t + 8*(e/4) + 4*half + e%4,
+//     which is what two transposing LDS reads of a row-major tile deliver;
 //   * per-row scalars (running max, denominator, lse, D) scale whole accumulators in place.
-// A operands come from LDS (row-major tile, or the transposed copy made while staging), B
-// operands stay in registers for the whole kernel.
+// A operands come from LDS, B operands stay in registers for the whole kernel.
 //
 // Forward :  S^T = K Q^T,  P^T = exp2(c S^T - m),  O^T += V^T P^T           (online softmax)
 // dQ pass :  S^T, dP^T = V dO^T,  dA^T = P^T (dP^T - D),  dQ^T += K^T dA^T
 // dKV pass:  S = Q K^T, dP = dO V^T, P, dA;  dV^T += dO^T P,  dK^T += Q^T dA
 // No atomics: dQ and dK/dV are separate passes, so results are bit-reproducible.
+#include <type_traits>
+
 #include "common.h"
 #include "kernels.h"
 
 namespace mg {
 
-typedef __attribute__((__vector_size__(2 * sizeof(__bf16)))) __bf16 bf16x2;
-
-// LDS has 64 four-byte banks.  Row-major tiles are read 16 bytes per lane (16 lanes per
-// clock): rows of DH + 8 bf16 (144 or 272 bytes, an odd number of 16-byte units) put 16
-// consecutive rows on 16 distinct 16-byte slots.  Transposed tiles are read 8 bytes per lane
-// (32 lanes per clock): 136-byte rows (an odd number of 8-byte units) put 32 consecutive rows
-// on 32 distinct 8-byte slots.
-template <int DH> constexpr int fa_ld() { return DH + 8; }     // row-major tile [64][DH + 8 pad]
-constexpr int FA_LDT = 68;                // transposed tile [DH][64 + 4 pad]
 constexpr float LOG2E = 1.4426950408889634f;
 constexpr float LN2 = 0.6931471805599453f;
+#define MFMA(a, b, c) __builtin_amdgcn_mfma_f32_32x32x16_bf16((a), (b), (c), 0, 0, 0)
 
-// 64 rows x DH cols of bf16 from global (rows clamped to nrows-1) into a row-major LDS tile
-// and/or its transpose.  Work item = (row pair, 8-column chunk); the chunk varies fastest so
-// that DH/8 consecutive lanes fetch one whole row (coalesced global reads matter more
-// here than the two-way bank conflict the transposed 4-byte stores then have).
-template <int NT, int DH, bool PLAIN, bool TRANS>
-__device__ __forceinline__ void stage64(bf16* plain, bf16* trans, const bf16* src, long rs, int row0, int nrows) {
-  constexpr int FA_LD = fa_ld<DH>(), CH = DH / 8;
-#pragma unroll
-  for (int item = threadIdx.x; item < 32 * CH; item += NT) {
-    const int cc = item % CH, rp = item / CH;
-    int r0 = row0 + 2 * rp, r1 = r0 + 1;
-    r0 = r0 < nrows ? r0 : nrows - 1;
-    r1 = r1 < nrows ? r1 : nrows - 1;
-    const bf16x8 v0 = *reinterpret_cast<const bf16x8*>(src + (long)r0 * rs + 8 * cc);
-    const bf16x8 v1 = *reinterpret_cast<const bf16x8*>(src + (long)r1 * rs + 8 * cc);
-    if (PLAIN) {
-      *reinterpret_cast<bf16x8*>(plain + (2 * rp) * FA_LD + 8 * cc) = v0;
-      *reinterpret_cast<bf16x8*>(plain + (2 * rp + 1) * FA_LD + 8 * cc) = v1;
-    }
-    if (TRANS) {
-#pragma unroll
-      for (int i = 0; i < 8; ++i) {
-        bf16x2 pr = {v0[i], v1[i]};
-        *reinterpret_cast<bf16x2*>(trans + (8 * cc + i) * FA_LDT + 2 * rp) = pr;
-      }
-    }
+// LDS tiles: rows of DH bf16 as they lie in memory (global -> LDS directly, 16 bytes per lane), the 16-byte chunks of
+// a row XOR-swizzled by its number so that one layout serves both reads without bank conflicts (64 banks of 4
+// bytes): 16 consecutive rows at one chunk (the 16-byte reads of a row-major fragment) fall on 16 distinct slots, and
+// so do 4 rows at 4 chunks (the transposing 8-byte reads).
+template <int DH> struct Lay {
+  static constexpr int RB = DH * 2, CPR = DH / 8, RPI = 1024 / RB;      // bytes and chunks per row; rows per load
+  static constexpr int TILE = 64 * RB;                                  // bytes of 64 rows
+  __device__ static __forceinline__ int swz(int row) {
+    return DH == 64 ? (((row >> 1) & 1) << 2) | ((row >> 2) & 3) : ((row & 3) << 2) | ((row >> 2) & 3);
   }
-}
-
-// The same staging in two halves, for double-buffered tiles: tile_load leaves the 64 x DH values
-// in registers (global loads in flight while the current tile is being used), tile_store writes
-// them to the row-major tile and/or its transpose.
-template <int NT, int DH>
-struct TileRegs {
-  static constexpr int N = (32 * (DH / 8) + NT - 1) / NT;
-  bf16x8 v0[N], v1[N];
 };
-template <int NT, int DH>
-__device__ __forceinline__ void tile_load(TileRegs<NT, DH>& r, const bf16* src, long rs, int row0, int nrows) {
-  constexpr int CH = DH / 8;
-#pragma unroll
-  for (int j = 0; j < TileRegs<NT, DH>::N; ++j) {
-    const int item = threadIdx.x + j * NT;
-    if (32 * CH % NT == 0 || item < 32 * CH) {   // (no test where the items divide evenly)
-      const int cc = item % CH, rp = item / CH;
-      int r0 = row0 + 2 * rp, r1 = r0 + 1;
-      r0 = r0 < nrows ? r0 : nrows - 1;
-      r1 = r1 < nrows ? r1 : nrows - 1;
-      r.v0[j] = *reinterpret_cast<const bf16x8*>(src + (long)r0 * rs + 8 * cc);
-      r.v1[j] = *reinterpret_cast<const bf16x8*>(src + (long)r1 * rs + 8 * cc);
-    }
-  }
-}
-template <int NT, int DH, bool PLAIN, bool TRANS>
-__device__ __forceinline__ void tile_store(const TileRegs<NT, DH>& r, bf16* plain, bf16* trans) {
-  constexpr int FA_LD = fa_ld<DH>(), CH = DH / 8;
-#pragma unroll
-  for (int j = 0; j < TileRegs<NT, DH>::N; ++j) {
-    const int item = threadIdx.x + j * NT;
-    if (32 * CH % NT == 0 || item < 32 * CH) {   // (no test where the items divide evenly)
-      const int cc = item % CH, rp = item / CH;
-      if (PLAIN) {
-        *reinterpret_cast<bf16x8*>(plain + (2 * rp) * FA_LD + 8 * cc) = r.v0[j];
-        *reinterpret_cast<bf16x8*>(plain + (2 * rp + 1) * FA_LD + 8 * cc) = r.v1[j];
-      }
-      if (TRANS) {
-#pragma unroll
-        for (int i = 0; i < 8; ++i) {
-          bf16x2 pr = {r.v0[j][i], r.v1[j][i]};
-          *reinterpret_cast<bf16x2*>(trans + (8 * cc + i) * FA_LDT + 2 * rp) = pr;
-        }
-      }
-    }
-  }
-}
 
-// A operand from a row-major tile: row `row`, reduction chunk of k-step ks
-template <int DH>
-__device__ __forceinline__ bf16x8 frag_plain(const bf16* tile, int row, int ks, int lh) {
-  return *reinterpret_cast<const bf16x8*>(tile + row * fa_ld<DH>() + 16 * ks + 8 * lh);
-}
-// A operand from a transposed tile: row `row` (a feature), reduction over the tile's 64
-// staged rows, k-step t of 32-row tile rt, in the register-order enumeration
-__device__ __forceinline__ bf16x8 frag_trans(const bf16* tile, int row, int rt, int t, int lh) {
-  const bf16* p = tile + row * FA_LDT + 32 * rt + 16 * t + 4 * lh;
-  const bf16x4 lo = *reinterpret_cast<const bf16x4*>(p);
-  const bf16x4 hi = *reinterpret_cast<const bf16x4*>(p + 8);
-  bf16x8 r = {lo[0], lo[1], lo[2], lo[3], hi[0], hi[1], hi[2], hi[3]};
-  return r;
-}
+// Loads of NW wavefronts for 64 rows from row `row0` on (rows past the end repeat the last one).
+template <int NW, int DH> struct Stager {
+  using L = Lay<DH>;
+  static constexpr int N = L::TILE / 1024 / NW;          // load instructions per wavefront and tile
+  static_assert(N >= 1, "one load or more per wavefront");
+  int wave, row[N], chunk[N], off[N];                    // chunk, off: in bytes; off: inside a whole tile
+  int rs;                                                // bytes per row of the source
+  __device__ __forceinline__ Stager(long row_stride, int wave_, int lane) : wave(wave_), rs((int)row_stride * 2) {
+#pragma unroll
+    for (int j = 0; j < N; ++j) {
+      row[j] = (wave * N + j) * L::RPI + lane / L::CPR;
+      chunk[j] = ((lane % L::CPR) ^ L::swz(row[j])) * 16;
+      off[j] = row[j] * rs + chunk[j];
+    }
+  }
+  __device__ __forceinline__ void issue(unsigned char* dst, const bf16* src, int row0, int nrows) const {
+    const auto base = lds_source(reinterpret_cast<const char*>(src) + (long)row0 * rs);
+    const int left = nrows - 1 - row0;
+    if (left >= 63) {                                    // block-uniform
+#pragma unroll
+      for (int j = 0; j < N; ++j) load_to_lds(base, dst + (wave * N + j) * 1024, off[j], 0);
+    } else {
+#pragma unroll
+      for (int j = 0; j < N; ++j)
+        load_to_lds(base, dst + (wave * N + j) * 1024, (row[j] < left ? row[j] : left) * rs + chunk[j], 0);
+    }
+  }
+};
+
+// A operand of a product that reduces over features: row 32*rt + lane%32 of the tile, k-step ks
+template <int DH> struct Frags {
+  using L = Lay<DH>;
+  int plain, trans;                                      // this lane's byte offsets, see below
+  __device__ __forceinline__ explicit Frags(int lane) {
+    const int lr = lane & 31, lh = lane >> 5;
+    plain = lr * L::RB + ((lh ^ L::swz(lr)) << 4);
+    const int tr = 4 * lh + ((lane & 15) >> 2);
+    trans = tr * L::RB + (((2 * ((lane >> 4) & 1) + ((lane & 3) >> 1)) ^ L::swz(tr)) << 4) + (lane & 1) * 8;
+  }
+  // row 32*rt + l%32, features 16*ks + 8*(l/32) ..
+  __device__ __forceinline__ bf16x8 rows(const lds_byte* tile, int rt, int ks) const {
+    return lds_read16(tile + (plain ^ (ks << 5)) + 32 * rt * L::RB);
+  }
+  // feature 32*dt + l%32, reduction over the tile's rows 32*rt + 16*t .. in the register-order enumeration
+  __device__ __forceinline__ bf16x8 cols(const lds_byte* tile, int rt, int t, int dt) const {
+    const int lo = trans ^ (dt << 6);
+    TrFrag f;
+    f.lo = tr_read4(tile + lo + (32 * rt + 16 * t) * L::RB);
+    f.hi = tr_read4(tile + (lo ^ 32) + (32 * rt + 16 * t + 8) * L::RB);
+    return tr_value(f);
+  }
+};
+
 // registers 8t..8t+7 of a result tile as the bf16 B operand of k-step t
 __device__ __forceinline__ bf16x8 regs_to_b(const f32x16& v, int t) {
   bf16x8 r = {(bf16)v[8 * t], (bf16)v[8 * t + 1], (bf16)v[8 * t + 2], (bf16)v[8 * t + 3],
               (bf16)v[8 * t + 4], (bf16)v[8 * t + 5], (bf16)v[8 * t + 6], (bf16)v[8 * t + 7]};
   return r;
 }
-__device__ __forceinline__ f32x16 zero16() {
+__device__ __forceinline__ f32x16 splat16(float x) {
   f32x16 z;
 #pragma unroll
-  for (int i = 0; i < 16; ++i) z[i] = 0.f;
+  for (int i = 0; i < 16; ++i) z[i] = x;
   return z;
 }
 // 2^x as the bare hardware instruction: the library routine wraps it in a range reduction for
 // results below 2^-126, which a probability that small does not need (it is 0 in bf16 anyway)
 __device__ __forceinline__ float exp2_raw(float x) { return __builtin_amdgcn_exp2f(x); }
-#define MFMA(a, b, c) __builtin_amdgcn_mfma_f32_32x32x16_bf16((a), (b), (c), 0, 0, 0)
+// Keeps a value where it is computed: the optimiser moves arithmetic past branches towards its use otherwise, out of
+// the place between matrix instructions that it was given.
+template <typename T> __device__ __forceinline__ void pin(T& v) { asm volatile("" : "+v"(v)); }
+// combination of a value with that of the lane 32 apart, on the vector unit
+__device__ __forceinline__ float half_max(float x) {
+  const auto r = __builtin_amdgcn_permlane32_swap(__float_as_uint(x), __float_as_uint(x), false, false);
+  return fmaxf(__uint_as_float(r[0]), __uint_as_float(r[1]));
+}
+__device__ __forceinline__ float half_sum(float x) {
+  const auto r = __builtin_amdgcn_permlane32_swap(__float_as_uint(x), __float_as_uint(x), false, false);
+  return __uint_as_float(r[0]) + __uint_as_float(r[1]);
+}
+// Ring of tile sets (64 rows of two operands each) in dynamic LDS: set `it` lives in slot it % 3.  Two sets are on their
+// way while one is in use: turn(it) waits for this wavefront's own loads of set `it` by count, and from its barrier
+// on the set is complete and nobody reads set it-1 any more, whose slot set it+2 then takes.  Heads of one or two
+// sets never come round and are launched with that many slots (launch_ring()).
+constexpr int RING = 3;
+template <int PER_SET> __device__ __forceinline__ void ring_turn(bool more) {
+  asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
+  if (more) wait_vmcnt<PER_SET>();
+  else wait_vmcnt<0>();
+  bare_barrier();
+}
 
 struct HeadPtrs {
   const bf16 *Q, *K, *V, *O, *dO;
@@ -189,126 +179,178 @@ __device__ __forceinline__ void store_rows_T(bf16* dst, long row_stride, int row
 // ---------------------------------------------------------------------------
 // forward
 // ---------------------------------------------------------------------------
-// Resident blocks per CU the register budget is set for: the accumulators grow with DH.
-template <int DH, int NW = 4> constexpr int fa_fwd_blocks() { return NW == 8 ? 1 : DH == 64 ? 4 : 2; }
-template <int DH, int NW = 4> constexpr int fa_bwd_blocks() { return NW == 8 ? 1 : 2; }
+// Wavefronts per SIMD the register budget is set for: the accumulators grow with DH.
+template <int DH, int NW> constexpr int fa_waves() { return DH == 64 && NW == 4 ? 3 : DH == 64 || NW == 8 ? 2 : NW / 2; }
 
-template <int NW, int DH>
-__global__ void __launch_bounds__(NW * 64, (fa_fwd_blocks<DH, NW>())) attn_fwd_mfma_kernel(const AttnArgs a) {
+// LONG: more than two tile sets, where the pipelined loop pays; without it a fourth wavefront per SIMD fits at d_head 64,
+// which short sequences need more: they wait for memory.
+template <int NW, int DH, bool LONG>
+__global__ void __launch_bounds__(NW * 64, (DH == 64 && !LONG ? 4 : fa_waves<DH, NW>()))
+attn_fwd_mfma_kernel(const AttnArgs a) {
+  using L = Lay<DH>;
   constexpr int KS = DH / 16, DT = DH / 32;
-  // d_head = 128, blocks of 128 queries or more: two buffers per tile, the next key tile is
-  // fetched while this one is used and written after it, one barrier per tile (forward time -14 %
-  // at 2048 keys; at d_head = 64 the gain is within noise and costs a resident block)
-  constexpr bool DB = NW >= 4 && DH == 128;
-  __shared__ __attribute__((aligned(16))) bf16 Ksb[DB ? 2 : 1][64 * fa_ld<DH>()];    // [key][d]
-  __shared__ __attribute__((aligned(16))) bf16 Vtb[DB ? 2 : 1][DH * FA_LDT];          // [d][key]
+  extern __shared__ __attribute__((aligned(1024))) unsigned char smem[];         // ring of K and V tiles
   const BlockTask bt = block_task(a.causal, true);
   const int g = bt.g;
   const int b = bt.bh / a.H, h = bt.bh - b * a.H;
   const int q0 = bt.tile * (NW * 32);
-  const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63, lr = lane & 31, lh = lane >> 5;
+  const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), lane = threadIdx.x & 63, lr = lane & 31, lh = lane >> 5;
   const HeadPtrs P = head_ptrs(a, g, b, h);
-  const int qi = q0 + wave * 32 + lr;
+  const int q_first = q0 + wave * 32, qi = q_first + lr;
   const int qc = qi < a.Sq ? qi : a.Sq - 1;
+  const int k_end = a.causal ? min(a.Sk, min(q0 + NW * 32, a.Sq)) : a.Sk;        // keys the block needs
+  const int w_end = q_first >= a.Sq ? 0 : a.causal ? min(a.Sk, q_first + 32) : a.Sk;   // ... and the wavefront
+  const int n_blk = (k_end + 63) >> 6;
+  const Stager<NW, DH> sk(a.k_row_stride, wave, lane), sv(a.v_row_stride, wave, lane);
+  auto stage = [&](int slot, int it) {
+    sk.issue(smem + slot * 2 * L::TILE, P.K, it * 64, a.Sk);
+    sv.issue(smem + slot * 2 * L::TILE + L::TILE, P.V, it * 64, a.Sk);
+  };
+  stage(0, 0);
+  if (n_blk > 1) stage(1, 1);
   bf16x8 qf[KS];
 #pragma unroll
   for (int ks = 0; ks < KS; ++ks)
     qf[ks] = *reinterpret_cast<const bf16x8*>(P.Q + (long)qc * a.q_row_stride + 16 * ks + 8 * lh);
-
+  const Frags<DH> fr(lane);
+  const lds_byte* lds = (const lds_byte*)smem;
   const float c = rsqrtf((float)DH) * LOG2E;
+  const int limit = (a.causal ? min(qi, a.Sk - 1) : a.Sk - 1) - 4 * lh;   // last key of this lane's query
   float m = -INFINITY, l = 0.f;
   f32x16 o[DT];
 #pragma unroll
-  for (int dt = 0; dt < DT; ++dt) o[dt] = zero16();
-  const int q_blk_last = min(q0 + NW * 32, a.Sq) - 1;
-  const int k_end = a.causal ? min(a.Sk, q_blk_last + 1) : a.Sk;
-  const int q_wave_first = q0 + wave * 32, q_wave_last = q_wave_first + 31;
-  TileRegs<NW * 64, DH> kr, vr;
-  if constexpr (DB) {                                    // k_end >= 1: the launcher rejects empty sequences
-    tile_load(kr, P.K, a.k_row_stride, 0, a.Sk);
-    tile_load(vr, P.V, a.v_row_stride, 0, a.Sk);
-    tile_store<NW * 64, DH, true, false>(kr, Ksb[0], nullptr);
-    tile_store<NW * 64, DH, false, true>(vr, nullptr, Vtb[0]);
-    __syncthreads();
-    // every load issued so far has landed (the tile was waited for and loads return in order);
-    // saying so keeps the loop's waits on the query fragments from also covering its prefetches
-    __builtin_amdgcn_s_waitcnt(0x0F70);                  // vmcnt(0)
+  for (int dt = 0; dt < DT; ++dt) o[dt] = splat16(0.f);
+
+  // Unit j: 32 keys.  Step j multiplies the probabilities of unit j with its values and forms the scores of unit j+1, one
+  // stream of matrix instructions in fixed order with everything else placed between them: the fragment of each is
+  // read RD instructions ahead, the exponentials of unit j stand under the scores of unit j+1 and the first products,
+  // the maximum of unit j+1 under the last products.  Left to the compiler the two units ran one after the other.
+  constexpr int RD = 4, NOPS = KS + 2 * DT;
+  bf16x8 ring[RD];
+  float ms = 0.f, corr = 1.f;                            // what the exponentials of the unit at hand refer to
+  const lds_byte *Kc = lds, *Kn = lds;                   // key tiles of this set and the next
+  auto new_max = [&](const f32x16& s) {                  // of the raw scores; the scale c is positive
+    float x = fmaxf(s[0], s[1]);
+#pragma unroll
+    for (int i = 2; i < 16; ++i) x = fmaxf(x, s[i]);
+    const float mn = fmaxf(m, half_max(x) * c);
+    ms = mn == -INFINITY ? 0.f : mn;                     // fully masked so far: keep exp2 finite
+    corr = exp2_raw(m - ms);
+    m = mn;
+  };
+  auto step = [&](auto rt_tag, f32x16& s, f32x16& sn) {
+    constexpr int rt = decltype(rt_tag)::value;
+    const lds_byte* V = Kc + L::TILE;
+    // fragment of instruction n of this step (from NOPS on: of the next step)
+    auto read = [&](int n) {
+      if (n < KS) return fr.rows(rt == 0 ? Kc : Kn, rt == 0 ? 1 : 0, n);
+      if (n < NOPS) return fr.cols(V, rt, (n - KS) / DT, (n - KS) % DT);
+      return fr.rows(Kn, rt == 0 ? 0 : 1, n - NOPS);
+    };
+    float t[2] = {0.f, 0.f};
+    auto prob = [&](int i) {
+      s[i] = exp2_raw(fmaf(s[i], c, -ms));
+      t[i & 1] += s[i];
+    };
+#pragma unroll
+    for (int n = 0; n < KS; ++n) {
+      sn = MFMA(ring[n % RD], qf[n], n == 0 ? splat16(0.f) : sn);
+      ring[n % RD] = read(n + RD);
+#pragma unroll
+      for (int i = 0; i < 8; ++i)
+        if (i >= 8 * n / KS && i < 8 * (n + 1) / KS) prob(i);
+#pragma unroll
+      for (int dt = 0; dt < DT; ++dt)
+        if (dt >= DT * n / KS && dt < DT * (n + 1) / KS) o[dt] *= corr;
+      __builtin_amdgcn_sched_barrier(0);
+    }
+    bf16x8 pb = regs_to_b(s, 0);
+    __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+    for (int n = KS; n < NOPS; ++n) {
+      const int dt = (n - KS) % DT;
+      if (n == KS + DT) {
+        pb = regs_to_b(s, 1);
+        l = fmaf(l, corr, t[0] + t[1]);
+        __builtin_amdgcn_sched_barrier(0);
+      }
+      o[dt] = MFMA(ring[n % RD], pb, o[dt]);
+      ring[n % RD] = read(n + RD);
+      if (n < KS + DT) {
+#pragma unroll
+        for (int i = 0; i < 8; ++i)
+          if (i >= 8 * dt / DT && i < 8 * (dt + 1) / DT) prob(8 + i);
+        __builtin_amdgcn_sched_barrier(0);
+      }
+      if (n == KS + DT) new_max(sn);
+    }
+    __builtin_amdgcn_sched_barrier(0);
+  };
+
+  // iterations whose two steps only meet whole units of keys that every query of the wavefront attends to
+  const int whole = a.causal ? min(w_end, q_first) >> 5 : w_end >> 5;
+  const int fast = LONG && whole > 2 ? (whole - 1) >> 1 : 0;
+  int slot = 0, it = 0;
+  ring_turn<2 * Stager<NW, DH>::N>(n_blk > 1);           // set 0
+  if (LONG && fast > 0) {
+    f32x16 sa = splat16(0.f), sb;
+#pragma unroll
+    for (int ks = 0; ks < KS; ++ks) sa = MFMA(fr.rows(lds, 0, ks), qf[ks], sa);
+    new_max(sa);
+#pragma unroll
+    for (int n = 0; n < RD; ++n) ring[n] = fr.rows(lds, 1, n);
+    for (; it < fast; ++it) {                            // (set it+1 exists: unit 2*it+2 is in it)
+      const int next = slot == RING - 1 ? 0 : slot + 1;
+      ring_turn<0>(false);                               // set it+1
+      if (it + 2 < n_blk) stage(next == RING - 1 ? 0 : next + 1, it + 2);
+      Kc = lds + slot * 2 * L::TILE;
+      Kn = lds + next * 2 * L::TILE;
+      step(std::integral_constant<int, 0>{}, sa, sb);
+      step(std::integral_constant<int, 1>{}, sb, sa);
+      slot = next;
+    }
+    l *= corr;                                           // the next unit is formed once more below
+#pragma unroll
+    for (int dt = 0; dt < DT; ++dt) o[dt] *= corr;
   }
-  int cur = 0;
-  for (int k0 = 0; k0 < k_end; k0 += 64, cur ^= DB ? 1 : 0) {
-    const bool more = DB && k0 + 64 < k_end;               // block-uniform
-    if constexpr (!DB) {
-      __syncthreads();
-      stage64<NW * 64, DH, true, false>(Ksb[0], nullptr, P.K, a.k_row_stride, k0, a.Sk);
-      stage64<NW * 64, DH, false, true>(nullptr, Vtb[0], P.V, a.v_row_stride, k0, a.Sk);
-      __syncthreads();
-    } else if (more) {
-      tile_load(kr, P.K, a.k_row_stride, k0 + 64, a.Sk);
-      tile_load(vr, P.V, a.v_row_stride, k0 + 64, a.Sk);
-    }
-    const bf16* Ks = Ksb[cur];
-    const bf16* Vt = Vtb[cur];
-    if (!(a.causal && k0 > q_wave_last)) {               // wave-uniform: the tile lies above the diagonal
-    f32x16 s[2] = {zero16(), zero16()};
+  for (; it < n_blk; ++it) {
+    const int next = slot == RING - 1 ? 0 : slot + 1;
+    if (it + 1 < n_blk) ring_turn<0>(false);
+    if (it + 2 < n_blk) stage(next == RING - 1 ? 0 : next + 1, it + 2);
+    const lds_byte* K = lds + slot * 2 * L::TILE;
+    for (int rt = 0; rt < 2; ++rt) {
+      const int k0 = it * 64 + 32 * rt;
+      if (k0 >= w_end) break;
+      const lds_byte *Kh = K + 32 * rt * L::RB, *Vh = Kh + L::TILE;
+      f32x16 s = splat16(0.f);
 #pragma unroll
-    for (int kt = 0; kt < 2; ++kt)
+      for (int ks = 0; ks < KS; ++ks) s = MFMA(fr.rows(Kh, 0, ks), qf[ks], s);
+      // masked scores become -inf, whose exp2 is 0
+      if (k0 + 32 > a.Sk || (a.causal && k0 + 31 > q_first)) {
+        const int lim = limit - k0;
 #pragma unroll
-      for (int ks = 0; ks < KS; ++ks) s[kt] = MFMA(frag_plain<DH>(Ks, 32 * kt + lr, ks, lh), qf[ks], s[kt]);
-    // a tile whose 64 keys all exist and precede every query of the wavefront needs no mask
-    // (wave-uniform test); masked scores become -inf, whose exp2 is 0
-    const bool full = k0 + 64 <= a.Sk && (!a.causal || k0 + 63 <= q_wave_first);
-    if (!full) {
-#pragma unroll
-      for (int kt = 0; kt < 2; ++kt)
-#pragma unroll
-        for (int i = 0; i < 16; ++i) {
-          const int key = k0 + 32 * kt + 8 * (i >> 2) + 4 * lh + (i & 3);
-          const bool valid = key < a.Sk && (!a.causal || key <= qi);
-          s[kt][i] = valid ? s[kt][i] : -INFINITY;
-        }
-    }
-    float mloc = -INFINITY;                                // of the raw scores; the scale c is positive
-#pragma unroll
-    for (int kt = 0; kt < 2; ++kt)
-#pragma unroll
-      for (int i = 0; i < 16; ++i) mloc = fmaxf(mloc, s[kt][i]);
-    mloc = fmaxf(mloc, __shfl_xor(mloc, 32, 64));
-    const float mn = fmaxf(m, mloc * c);
-    const float ms = mn == -INFINITY ? 0.f : mn;         // fully masked so far: keep exp2 finite
-    const float corr = exp2_raw(m - ms);
-    float lsum = 0.f;
-#pragma unroll
-    for (int kt = 0; kt < 2; ++kt)
+        for (int i = 0; i < 16; ++i) s[i] = 8 * (i >> 2) + (i & 3) <= lim ? s[i] : -INFINITY;
+      }
+      new_max(s);
+      float t[2] = {0.f, 0.f};
 #pragma unroll
       for (int i = 0; i < 16; ++i) {
-        const float p = exp2_raw(fmaf(s[kt][i], c, -ms));
-        s[kt][i] = p;
-        lsum += p;
+        s[i] = exp2_raw(fmaf(s[i], c, -ms));
+        t[i & 1] += s[i];
       }
-    lsum += __shfl_xor(lsum, 32, 64);
-    l = l * corr + lsum;
-    m = mn;
+      l = fmaf(l, corr, t[0] + t[1]);
 #pragma unroll
-    for (int dt = 0; dt < DT; ++dt)
+      for (int dt = 0; dt < DT; ++dt) o[dt] *= corr;
 #pragma unroll
-      for (int i = 0; i < 16; ++i) o[dt][i] *= corr;
+      for (int t2 = 0; t2 < 2; ++t2) {
+        const bf16x8 pb = regs_to_b(s, t2);
 #pragma unroll
-    for (int kt = 0; kt < 2; ++kt)
-#pragma unroll
-      for (int t = 0; t < 2; ++t) {
-        const bf16x8 pb = regs_to_b(s[kt], t);
-#pragma unroll
-        for (int dt = 0; dt < DT; ++dt) o[dt] = MFMA(frag_trans(Vt, 32 * dt + lr, kt, t, lh), pb, o[dt]);
+        for (int dt = 0; dt < DT; ++dt) o[dt] = MFMA(fr.cols(Vh, 0, t2, dt), pb, o[dt]);
       }
     }
-    if constexpr (DB) {
-      if (more) {
-        tile_store<NW * 64, DH, true, false>(kr, Ksb[cur ^ 1], nullptr);
-        tile_store<NW * 64, DH, false, true>(vr, nullptr, Vtb[cur ^ 1]);
-      }
-      __syncthreads();    // the other buffer is complete, and nobody reads this one any more
-    }
+    slot = next;
   }
+  l = half_sum(l);
   if (qi < a.Sq) {
     store_rows_T<DH>(P.Ow, a.o_row_stride, qi, o, 1.0f / l, lh);
     if (P.lse && lh == 0) P.lse[qi] = (m + log2f(l)) * LN2;
@@ -316,243 +358,209 @@ __global__ void __launch_bounds__(NW * 64, (fa_fwd_blocks<DH, NW>())) attn_fwd_m
 }
 
 // ---------------------------------------------------------------------------
-// backward pass 1: D and dQ, one wavefront per 32 query rows
+// backward: the products of 32 own rows with 32 rows of a tile
 // ---------------------------------------------------------------------------
-// LDS of the two backward passes (bf16 elements): pass 1 stages K, V row-major and K transposed;
-// pass 2 stages Q, dO both ways.  The fused kernel runs them one after the other in the same buffer.
-template <int DH> constexpr int bwd_dq_lds() { return 2 * 64 * fa_ld<DH>() + DH * FA_LDT; }
-template <int DH> constexpr int bwd_dkv_lds() { return 2 * 64 * fa_ld<DH>() + 2 * DH * FA_LDT; }
+// dQ pass: own queries (fragments qf, dof, scalars lse2 = lse * log2(e), neg_d = -D), key half `rt` of the tiles K, V.
+// lim: last of the 32 keys this lane's query may attend to, less 4 * (lane / 32); masked: some pair is masked
+template <int DH>
+__device__ __forceinline__ void bwd_dq_half(const Frags<DH>& fr, const lds_byte* K, const lds_byte* V, int rt,
+                                            const bf16x8 (&qf)[DH / 16], const bf16x8 (&dof)[DH / 16], float c, float lse2,
+                                            float neg_d, bool masked, int lim, f32x16 (&dq)[DH / 32]) {
+  f32x16 s = splat16(0.f), dp = splat16(neg_d);          // dP - D comes out of the matrix unit
+#pragma unroll
+  for (int ks = 0; ks < DH / 16; ++ks) {
+    s = MFMA(fr.rows(K, rt, ks), qf[ks], s);
+    dp = MFMA(fr.rows(V, rt, ks), dof[ks], dp);
+  }
+  if (masked) {
+#pragma unroll
+    for (int i = 0; i < 16; ++i) s[i] = 8 * (i >> 2) + (i & 3) <= lim ? s[i] : -INFINITY;
+  }
+#pragma unroll
+  for (int i = 0; i < 16; ++i) s[i] = exp2_raw(fmaf(s[i], c, -lse2)) * dp[i];      // dA^T
+#pragma unroll
+  for (int t = 0; t < 2; ++t) {
+    const bf16x8 ab = regs_to_b(s, t);
+#pragma unroll
+    for (int dt = 0; dt < DH / 32; ++dt) dq[dt] = MFMA(fr.cols(K, rt, t, dt), ab, dq[dt]);
+  }
+}
 
-// d_local: if not null, D of the block's query rows is also left there (index = row - q0)
-// DB: `lds` holds two sets of tiles; the next key tile is fetched while the current one is used
-// and written after it, one barrier per tile
-template <int NW, int DH, bool DB = false>
-__device__ __forceinline__ void attn_bwd_dq_body(const AttnArgs& a, bf16* lds, float* d_local) {
-  constexpr int KS = DH / 16, DT = DH / 32, FA_LD = fa_ld<DH>();
-  // one set of tiles: K [key][d], V [key][d], K transposed [d][key]
-  constexpr int V_OFF = 64 * FA_LD, KT_OFF = 2 * 64 * FA_LD, SET = bwd_dq_lds<DH>();
+// dK/dV pass: own keys (fragments kf, vf), query half `rt` of the tiles Q, dO.  row_s, row_d: per query -lse / scale and
+// -D, what the two products start from (rows that do not exist: -inf and 0, so that P = dA = 0).
+// first: the first of the 32 queries that may attend to this lane's key, less 4 * (lane / 32)
+template <int DH>
+__device__ __forceinline__ void bwd_dkv_half(const Frags<DH>& fr, const lds_byte* Q, const lds_byte* dO, int rt,
+                                             const float* row_s, const float* row_d, const bf16x8 (&kf)[DH / 16],
+                                             const bf16x8 (&vf)[DH / 16], float c, bool masked, int first, int lh,
+                                             f32x16 (&dk)[DH / 32], f32x16 (&dv)[DH / 32]) {
+  f32x16 s, dp;
+#pragma unroll
+  for (int q = 0; q < 4; ++q) {
+    const f32x4 x = *reinterpret_cast<const f32x4*>(row_s + 32 * rt + 8 * q + 4 * lh);
+    const f32x4 y = *reinterpret_cast<const f32x4*>(row_d + 32 * rt + 8 * q + 4 * lh);
+#pragma unroll
+    for (int r = 0; r < 4; ++r) { s[4 * q + r] = x[r]; dp[4 * q + r] = y[r]; }
+  }
+#pragma unroll
+  for (int ks = 0; ks < DH / 16; ++ks) {
+    s = MFMA(fr.rows(Q, rt, ks), kf[ks], s);
+    dp = MFMA(fr.rows(dO, rt, ks), vf[ks], dp);
+  }
+  if (masked) {
+#pragma unroll
+    for (int i = 0; i < 16; ++i) s[i] = 8 * (i >> 2) + (i & 3) >= first ? s[i] : -INFINITY;
+  }
+#pragma unroll
+  for (int i = 0; i < 16; ++i) {
+    s[i] = exp2_raw(s[i] * c);                           // P
+    dp[i] *= s[i];                                       // dA
+  }
+#pragma unroll
+  for (int t = 0; t < 2; ++t) {
+    const bf16x8 pb = regs_to_b(s, t), ab = regs_to_b(dp, t);
+#pragma unroll
+    for (int dt = 0; dt < DH / 32; ++dt) {
+      dv[dt] = MFMA(fr.cols(dO, rt, t, dt), pb, dv[dt]);
+      dk[dt] = MFMA(fr.cols(Q, rt, t, dt), ab, dk[dt]);
+    }
+  }
+}
+
+// D of this lane's query (both halves of the wavefront get the sum)
+template <int DH>
+__device__ __forceinline__ float row_dot(const bf16x8 (&dof)[DH / 16], const bf16* o, int lh) {
+  float d = 0.f;
+#pragma unroll
+  for (int ks = 0; ks < DH / 16; ++ks) {
+    const bf16x8 of = *reinterpret_cast<const bf16x8*>(o + 16 * ks + 8 * lh);
+#pragma unroll
+    for (int e = 0; e < 8; ++e) d = fmaf((float)dof[ks][e], (float)of[e], d);
+  }
+  return half_sum(d);
+}
+
+template <int NW, int DH>
+__global__ void __launch_bounds__(NW * 64, (fa_waves<DH, NW>())) attn_bwd_dq_mfma_kernel(const AttnArgs a) {
+  using L = Lay<DH>;
+  constexpr int KS = DH / 16, DT = DH / 32;
+  extern __shared__ __attribute__((aligned(1024))) unsigned char smem[];         // ring of K and V tiles
   const BlockTask bt = block_task(a.causal, true);
   const int g = bt.g;
   const int b = bt.bh / a.H, h = bt.bh - b * a.H;
   const int q0 = bt.tile * (NW * 32);
-  const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63, lr = lane & 31, lh = lane >> 5;
+  const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), lane = threadIdx.x & 63, lr = lane & 31, lh = lane >> 5;
   const HeadPtrs P = head_ptrs(a, g, b, h);
-  const int qi = q0 + wave * 32 + lr;
+  const int q_first = q0 + wave * 32, qi = q_first + lr;
   const int qc = qi < a.Sq ? qi : a.Sq - 1;
+  const int k_end = a.causal ? min(a.Sk, min(q0 + NW * 32, a.Sq)) : a.Sk;
+  const int w_end = q_first >= a.Sq ? 0 : a.causal ? min(a.Sk, q_first + 32) : a.Sk;
+  const int n_blk = (k_end + 63) >> 6;
+  const Stager<NW, DH> sk(a.k_row_stride, wave, lane), sv(a.v_row_stride, wave, lane);
+  auto stage = [&](int slot, int it) {
+    sk.issue(smem + slot * 2 * L::TILE, P.K, it * 64, a.Sk);
+    sv.issue(smem + slot * 2 * L::TILE + L::TILE, P.V, it * 64, a.Sk);
+  };
+  stage(0, 0);
+  if (n_blk > 1) stage(1, 1);
   bf16x8 qf[KS], dof[KS];
-  float Dq = 0.f;
 #pragma unroll
   for (int ks = 0; ks < KS; ++ks) {
     qf[ks] = *reinterpret_cast<const bf16x8*>(P.Q + (long)qc * a.q_row_stride + 16 * ks + 8 * lh);
     dof[ks] = *reinterpret_cast<const bf16x8*>(P.dO + (long)qc * a.do_row_stride + 16 * ks + 8 * lh);
-    const bf16x8 of = *reinterpret_cast<const bf16x8*>(P.O + (long)qc * a.o_row_stride + 16 * ks + 8 * lh);
-#pragma unroll
-    for (int e = 0; e < 8; ++e) Dq = fmaf((float)dof[ks][e], (float)of[e], Dq);
   }
-  Dq += __shfl_xor(Dq, 32, 64);
+  const float D = row_dot<DH>(dof, P.O + (long)qc * a.o_row_stride, lh);
   const float lse2 = P.lse[qc] * LOG2E;
-  if (qi < a.Sq && lh == 0) P.D[qi] = Dq;
-  if (d_local && lh == 0) d_local[wave * 32 + lr] = Dq;
-
+  const Frags<DH> fr(lane);
+  const lds_byte* lds = (const lds_byte*)smem;
   const float c = rsqrtf((float)DH) * LOG2E;
+  const int limit = (a.causal ? min(qi, a.Sk - 1) : a.Sk - 1) - 4 * lh;
   f32x16 dq[DT];
 #pragma unroll
-  for (int dt = 0; dt < DT; ++dt) dq[dt] = zero16();
-  const int q_blk_last = min(q0 + NW * 32, a.Sq) - 1;
-  const int k_end = a.causal ? min(a.Sk, q_blk_last + 1) : a.Sk;
-  const int q_wave_first = q0 + wave * 32, q_wave_last = q_wave_first + 31;
-  TileRegs<NW * 64, DH> kr, vr;
-  if constexpr (DB) {                                    // k_end >= 1: the launcher rejects empty sequences
-    tile_load(kr, P.K, a.k_row_stride, 0, a.Sk);
-    tile_load(vr, P.V, a.v_row_stride, 0, a.Sk);
-    tile_store<NW * 64, DH, true, true>(kr, lds, lds + KT_OFF);
-    tile_store<NW * 64, DH, true, false>(vr, lds + V_OFF, nullptr);
-    __syncthreads();
-    // every load issued so far has landed (the tile was waited for and loads return in order);
-    // saying so keeps the loop's waits on the query fragments from also covering its prefetches
-    __builtin_amdgcn_s_waitcnt(0x0F70);                  // vmcnt(0)
-  }
-  int cur = 0;
-  for (int k0 = 0; k0 < k_end; k0 += 64, cur ^= DB ? 1 : 0) {
-    bf16* Ks = lds + cur * SET;
-    bf16* Vs = Ks + V_OFF;
-    bf16* Kt = Ks + KT_OFF;
-    const bool more = DB && k0 + 64 < k_end;               // block-uniform
-    if constexpr (!DB) {
-      __syncthreads();
-      stage64<NW * 64, DH, true, true>(Ks, Kt, P.K, a.k_row_stride, k0, a.Sk);
-      stage64<NW * 64, DH, true, false>(Vs, nullptr, P.V, a.v_row_stride, k0, a.Sk);
-      __syncthreads();
-    } else if (more) {
-      tile_load(kr, P.K, a.k_row_stride, k0 + 64, a.Sk);
-      tile_load(vr, P.V, a.v_row_stride, k0 + 64, a.Sk);
-    }
-    const bool full = k0 + 64 <= a.Sk && (!a.causal || k0 + 63 <= q_wave_first);   // no mask needed
-    if (!(a.causal && k0 > q_wave_last)) {                 // wave-uniform: the tile lies above the diagonal
+  for (int dt = 0; dt < DT; ++dt) dq[dt] = splat16(0.f);
+  int slot = 0;
+  for (int it = 0; it < n_blk; ++it) {
+    ring_turn<2 * Stager<NW, DH>::N>(it + 1 < n_blk);
+    if (it + 2 < n_blk) stage(slot == 0 ? 2 : slot - 1, it + 2);
+    const lds_byte* K = lds + slot * 2 * L::TILE;
 #pragma unroll
     for (int kt = 0; kt < 2; ++kt) {
-      f32x16 s = zero16(), dp = zero16();
-#pragma unroll
-      for (int ks = 0; ks < KS; ++ks) {
-        s = MFMA(frag_plain<DH>(Ks, 32 * kt + lr, ks, lh), qf[ks], s);
-        dp = MFMA(frag_plain<DH>(Vs, 32 * kt + lr, ks, lh), dof[ks], dp);
-      }
-      if (full) {
-#pragma unroll
-        for (int i = 0; i < 16; ++i) s[i] = exp2_raw(fmaf(s[i], c, -lse2)) * (dp[i] - Dq);      // dA^T
-      } else {
-#pragma unroll
-        for (int i = 0; i < 16; ++i) {
-          const int key = k0 + 32 * kt + 8 * (i >> 2) + 4 * lh + (i & 3);
-          const bool valid = key < a.Sk && (!a.causal || key <= qi);
-          const float p = valid ? exp2_raw(fmaf(s[i], c, -lse2)) : 0.f;
-          s[i] = p * (dp[i] - Dq);
-        }
-      }
-#pragma unroll
-      for (int t = 0; t < 2; ++t) {
-        const bf16x8 ab = regs_to_b(s, t);
-#pragma unroll
-        for (int dt = 0; dt < DT; ++dt) dq[dt] = MFMA(frag_trans(Kt, 32 * dt + lr, kt, t, lh), ab, dq[dt]);
-      }
+      const int k0 = it * 64 + 32 * kt;
+      if (k0 < w_end)                                    // wave-uniform
+        bwd_dq_half<DH>(fr, K, K + L::TILE, kt, qf, dof, c, lse2, -D, k0 + 32 > a.Sk || (a.causal && k0 + 31 > q_first),
+                        limit - k0, dq);
     }
-    }
-    if constexpr (DB) {
-      if (more) {
-        bf16* other = lds + (cur ^ 1) * SET;
-        tile_store<NW * 64, DH, true, true>(kr, other, other + KT_OFF);
-        tile_store<NW * 64, DH, true, false>(vr, other + V_OFF, nullptr);
-      }
-      __syncthreads();    // the other set is complete, and nobody reads this one any more
-    }
+    slot = slot == RING - 1 ? 0 : slot + 1;
   }
-  if (qi < a.Sq) store_rows_T<DH>(P.dQ, a.dqkv_row_stride, qi, dq, rsqrtf((float)DH), lh);
+  if (qi < a.Sq) {
+    if (lh == 0) P.D[qi] = D;                            // (not earlier: the first tile's wait would cover the store)
+    store_rows_T<DH>(P.dQ, a.dqkv_row_stride, qi, dq, rsqrtf((float)DH), lh);
+  }
 }
 
 template <int NW, int DH>
-__global__ void __launch_bounds__(NW * 64, (fa_bwd_blocks<DH, NW>())) attn_bwd_dq_mfma_kernel(const AttnArgs a) {
-  // the 256-row blocks at d_head = 128 (one block per CU) double-buffer their key tiles
-  constexpr bool DB = NW == 8 && DH == 128;
-  __shared__ __attribute__((aligned(16))) bf16 lds[(DB ? 2 : 1) * bwd_dq_lds<DH>()];
-  attn_bwd_dq_body<NW, DH, DB>(a, lds, nullptr);
-}
-
-// ---------------------------------------------------------------------------
-// backward pass 2: dK and dV, one wavefront per 32 key rows
-// ---------------------------------------------------------------------------
-// d_src: D of query row i at d_src[i] (the global array of pass 1, or the fused kernel's LDS copy)
-// VLDS: the wavefronts keep their V fragments there (64 lanes x 16 bytes per k-step and
-// wavefront in `vpriv`, each lane reading back what it wrote) instead of in registers: at d_head = 128 the two
-// accumulator sets and both fragment sets do not fit the 256 registers of two waves per SIMD, and a
-// register spilled to scratch costs far more than an LDS read
-template <int NW, int DH, bool VLDS = false>
-__device__ __forceinline__ void attn_bwd_dkv_body(const AttnArgs& a, bf16* lds, float* Ls, float* Ds,
-                                                  const float* d_src, bf16* vpriv = nullptr) {
-  constexpr int KS = DH / 16, DT = DH / 32, FA_LD = fa_ld<DH>();
-  bf16* Qs = lds;                        // [query][d]
-  bf16* dOs = Qs + 64 * FA_LD;           // [query][d]
-  bf16* Qt = dOs + 64 * FA_LD;           // [d][query]
-  bf16* dOt = Qt + DH * FA_LDT;          // [d][query]
+__global__ void __launch_bounds__(NW * 64, (fa_waves<DH, NW>())) attn_bwd_dkv_mfma_kernel(const AttnArgs a) {
+  using L = Lay<DH>;
+  constexpr int KS = DH / 16, DT = DH / 32;
+  extern __shared__ __attribute__((aligned(1024))) unsigned char smem[];         // ring of Q and dO tiles
+  __shared__ __attribute__((aligned(16))) float rows[RING][2][64];               // -lse / scale and -D of their queries
   const BlockTask bt = block_task(a.causal, false);
   const int g = bt.g;
   const int b = bt.bh / a.H, h = bt.bh - b * a.H;
   const int j0 = bt.tile * (NW * 32);
-  const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63, lr = lane & 31, lh = lane >> 5;
+  const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), lane = threadIdx.x & 63, lr = lane & 31, lh = lane >> 5;
   const HeadPtrs P = head_ptrs(a, g, b, h);
-  const int kj = j0 + wave * 32 + lr;
+  const int k_first = j0 + wave * 32, kj = k_first + lr;
   const int kc = kj < a.Sk ? kj : a.Sk - 1;
-  bf16x8 kf[KS], vf[VLDS ? 1 : KS];
-  bf16* vmine = VLDS ? vpriv + (wave * KS * 64 + lane) * 8 : nullptr;          // + ks * 512 per k-step
+  bf16x8 kf[KS], vf[KS];
 #pragma unroll
   for (int ks = 0; ks < KS; ++ks) {
     kf[ks] = *reinterpret_cast<const bf16x8*>(P.K + (long)kc * a.k_row_stride + 16 * ks + 8 * lh);
-    const bf16x8 v = *reinterpret_cast<const bf16x8*>(P.V + (long)kc * a.v_row_stride + 16 * ks + 8 * lh);
-    if constexpr (VLDS) *reinterpret_cast<bf16x8*>(vmine + ks * 512) = v;
-    else vf[ks] = v;
+    vf[ks] = *reinterpret_cast<const bf16x8*>(P.V + (long)kc * a.v_row_stride + 16 * ks + 8 * lh);
   }
+  const Stager<NW, DH> sq(a.q_row_stride, wave, lane), so(a.do_row_stride, wave, lane);
+  auto stage = [&](int slot, int it) {
+    sq.issue(smem + slot * 2 * L::TILE, P.Q, it * 64, a.Sq);
+    so.issue(smem + slot * 2 * L::TILE + L::TILE, P.dO, it * 64, a.Sq);
+  };
+  float st_s = 0.f, st_d = 0.f;                          // on their way to `rows` (first wavefront)
+  auto fetch_rows = [&](int it) {
+    const int qq = it * 64 + lane;
+    st_s = qq < a.Sq ? P.lse[qq] * -sqrtf((float)DH) : -INFINITY;
+    st_d = qq < a.Sq ? -P.D[qq] : 0.f;
+  };
+  auto publish = [&](int slot) { rows[slot][0][lane] = st_s; rows[slot][1][lane] = st_d; };
+  // causal: key j only receives from queries i >= j
+  const int it0 = a.causal ? j0 >> 6 : 0, n_blk = (a.Sq + 63) >> 6;
+  if (wave == 0) { fetch_rows(it0); publish(0); }
+  if (it0 < n_blk) stage(0, it0);
+  if (it0 + 1 < n_blk) stage(1, it0 + 1);
+  if (wave == 0) fetch_rows(it0 + 1);
+  const Frags<DH> fr(lane);
+  const lds_byte* lds = (const lds_byte*)smem;
   const float c = rsqrtf((float)DH) * LOG2E;
   f32x16 dk[DT], dv[DT];
 #pragma unroll
-  for (int dt = 0; dt < DT; ++dt) { dk[dt] = zero16(); dv[dt] = zero16(); }
-  // causal: key j only receives from queries i >= j
-  const int i_begin = a.causal ? (j0 / 64) * 64 : 0;
-  const int k_wave_first = j0 + wave * 32;
-  for (int i0 = i_begin; i0 < a.Sq; i0 += 64) {
-    __syncthreads();
-    stage64<NW * 64, DH, true, true>(Qs, Qt, P.Q, a.q_row_stride, i0, a.Sq);
-    stage64<NW * 64, DH, true, true>(dOs, dOt, P.dO, a.do_row_stride, i0, a.Sq);
-    if (threadIdx.x < 64) {
-      const int qq = i0 + threadIdx.x;
-      const int qcl = qq < a.Sq ? qq : a.Sq - 1;
-      Ls[threadIdx.x] = P.lse[qcl] * LOG2E;
-      Ds[threadIdx.x] = d_src ? d_src[qcl] : P.D[qcl];
+  for (int dt = 0; dt < DT; ++dt) { dk[dt] = splat16(0.f); dv[dt] = splat16(0.f); }
+  int slot = 0;
+  for (int it = it0; it < n_blk; ++it) {
+    ring_turn<2 * Stager<NW, DH>::N>(it + 1 < n_blk);
+    const int next = slot == RING - 1 ? 0 : slot + 1;
+    if (wave == 0 && it + 1 < n_blk) publish(next);      // before the barrier that opens set it+1
+    if (it + 2 < n_blk) {
+      stage(slot == 0 ? 2 : slot - 1, it + 2);
+      if (wave == 0) fetch_rows(it + 2);
     }
-    __syncthreads();
-    if (a.causal && i0 + 63 < k_wave_first) continue;      // every query of the tile precedes this wave's keys
-    // no mask needed: all 64 queries exist, the wavefront's keys exist and (causal) precede them all
-    const bool full = i0 + 64 <= a.Sq && k_wave_first + 32 <= a.Sk && (!a.causal || k_wave_first + 31 <= i0);
+    const lds_byte* Q = lds + slot * 2 * L::TILE;
 #pragma unroll
     for (int qt = 0; qt < 2; ++qt) {
-      f32x16 s = zero16(), dp = zero16();
-#pragma unroll
-      for (int ks = 0; ks < KS; ++ks) {
-        s = MFMA(frag_plain<DH>(Qs, 32 * qt + lr, ks, lh), kf[ks], s);
-        bf16x8 vk;
-        if constexpr (VLDS) vk = *reinterpret_cast<const bf16x8*>(vmine + ks * 512);
-        else vk = vf[ks];
-        dp = MFMA(frag_plain<DH>(dOs, 32 * qt + lr, ks, lh), vk, dp);
-      }
-      if (full) {
-#pragma unroll
-        for (int i = 0; i < 16; ++i) {
-          const int ql = 32 * qt + 8 * (i >> 2) + 4 * lh + (i & 3);
-          const float p = exp2_raw(fmaf(s[i], c, -Ls[ql]));
-          s[i] = p;
-          dp[i] = p * (dp[i] - Ds[ql]);
-        }
-      } else {
-#pragma unroll
-        for (int i = 0; i < 16; ++i) {
-          const int ql = 32 * qt + 8 * (i >> 2) + 4 * lh + (i & 3);
-          const int qq = i0 + ql;
-          const bool valid = qq < a.Sq && kj < a.Sk && (!a.causal || kj <= qq);
-          // computed for every pair and zeroed afterwards: a conditional evaluation would put the
-          // LDS read of the row's lse behind a branch per element
-          const float e = exp2_raw(fmaf(s[i], c, -Ls[ql]));
-          const float p = valid ? e : 0.f;
-          s[i] = p;
-          dp[i] = p * (dp[i] - Ds[ql]);
-        }
-      }
-#pragma unroll
-      for (int t = 0; t < 2; ++t) {
-        const bf16x8 pb = regs_to_b(s, t), ab = regs_to_b(dp, t);
-        if constexpr (DH == 128) {
-          // d_head = 128 runs at the register limit: the fragments of one feature tile are fetched
-          // while the products of the tile before it run, and a fence per tile keeps the scheduler
-          // from fetching all of them ahead (it then spills the key fragments to scratch)
-          bf16x8 fo = frag_trans(dOt, lr, qt, t, lh), fq = frag_trans(Qt, lr, qt, t, lh);
-#pragma unroll
-          for (int dt = 0; dt < DT; ++dt) {
-            bf16x8 fo_n = fo, fq_n = fq;
-            if (dt + 1 < DT) {
-              fo_n = frag_trans(dOt, 32 * (dt + 1) + lr, qt, t, lh);
-              fq_n = frag_trans(Qt, 32 * (dt + 1) + lr, qt, t, lh);
-            }
-            dv[dt] = MFMA(fo, pb, dv[dt]);
-            dk[dt] = MFMA(fq, ab, dk[dt]);
-            __builtin_amdgcn_sched_barrier(0);
-            fo = fo_n; fq = fq_n;
-          }
-        } else {
-#pragma unroll
-          for (int dt = 0; dt < DT; ++dt) {
-            dv[dt] = MFMA(frag_trans(dOt, 32 * dt + lr, qt, t, lh), pb, dv[dt]);
-            dk[dt] = MFMA(frag_trans(Qt, 32 * dt + lr, qt, t, lh), ab, dk[dt]);
-          }
-        }
-      }
+      const int i0 = it * 64 + 32 * qt;
+      // wave-uniform: queries exist, one of them may attend to these keys, the keys exist
+      if (i0 < a.Sq && (!a.causal || i0 + 31 >= k_first) && k_first < a.Sk)
+        bwd_dkv_half<DH>(fr, Q, Q + L::TILE, qt, rows[slot][0], rows[slot][1], kf, vf, c, a.causal && i0 < k_first + 31,
+                         kj - i0 - 4 * lh, lh, dk, dv);
     }
+    slot = next;
   }
   if (kj < a.Sk) {
     const long kv_rs = a.dkv_row_stride ? a.dkv_row_stride : a.dqkv_row_stride;
@@ -561,25 +569,84 @@ __device__ __forceinline__ void attn_bwd_dkv_body(const AttnArgs& a, bf16* lds, 
   }
 }
 
+// Sequences that fit one block (Sq, Sk <= 32 NW): both passes in one launch, the head's Q, K, V and dO in LDS as a
+// whole, read from memory once; nothing waits between the two passes but the exchange of D.
 template <int NW, int DH>
-__global__ void __launch_bounds__(NW * 64, (fa_bwd_blocks<DH, NW>())) attn_bwd_dkv_mfma_kernel(const AttnArgs a) {
-  // the 256-row blocks at d_head = 128 (one block per CU) park their V fragments in LDS
-  constexpr bool VLDS = NW == 8 && DH == 128;
-  __shared__ __attribute__((aligned(16))) bf16 lds[bwd_dkv_lds<DH>() + (VLDS ? NW * (DH / 16) * 64 * 8 : 0)];
-  __shared__ float Ls[64], Ds[64];
-  attn_bwd_dkv_body<NW, DH, VLDS>(a, lds, Ls, Ds, nullptr, lds + bwd_dkv_lds<DH>());
-}
-
-// Sequences that fit one block (Sq, Sk <= 32 NW): both passes in one launch.  The head's Q, K, V,
-// dO are then read from HBM once (pass 2 finds them in L2) and D never leaves the CU.
-template <int NW, int DH>
-__global__ void __launch_bounds__(NW * 64, (fa_bwd_blocks<DH, NW>())) attn_bwd_fused_mfma_kernel(const AttnArgs a) {
-  constexpr int LDS = bwd_dq_lds<DH>() > bwd_dkv_lds<DH>() ? bwd_dq_lds<DH>() : bwd_dkv_lds<DH>();
-  __shared__ __attribute__((aligned(16))) bf16 lds[LDS];
-  __shared__ float Ls[64], Ds[64], Dall[NW * 32];
-  attn_bwd_dq_body<NW, DH>(a, lds, Dall);
-  __syncthreads();
-  attn_bwd_dkv_body<NW, DH>(a, lds, Ls, Ds, Dall);
+__global__ void __launch_bounds__(NW * 64, (DH == 64 ? 2 : 1)) attn_bwd_fused_mfma_kernel(const AttnArgs a) {
+  using L = Lay<DH>;
+  constexpr int KS = DH / 16, DT = DH / 32, TILES = NW / 2, OPND = TILES * L::TILE;
+  __shared__ __attribute__((aligned(1024))) unsigned char smem[4 * OPND];        // K, V, Q, dO
+  __shared__ __attribute__((aligned(16))) float rows[2][NW * 32];
+  const int g = blockIdx.z, b = blockIdx.y / a.H, h = blockIdx.y - b * a.H;
+  const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), lane = threadIdx.x & 63, lr = lane & 31, lh = lane >> 5;
+  const HeadPtrs P = head_ptrs(a, g, b, h);
+  {
+    const Stager<NW, DH> sk(a.k_row_stride, wave, lane), sv(a.v_row_stride, wave, lane), sq(a.q_row_stride, wave, lane),
+        so(a.do_row_stride, wave, lane);
+#pragma unroll
+    for (int t = 0; t < TILES; ++t) {
+      if (t * 64 < a.Sk) {
+        sk.issue(smem + t * L::TILE, P.K, t * 64, a.Sk);
+        sv.issue(smem + OPND + t * L::TILE, P.V, t * 64, a.Sk);
+      }
+      if (t * 64 < a.Sq) {
+        sq.issue(smem + 2 * OPND + t * L::TILE, P.Q, t * 64, a.Sq);
+        so.issue(smem + 3 * OPND + t * L::TILE, P.dO, t * 64, a.Sq);
+      }
+    }
+  }
+  const Frags<DH> fr(lane);
+  const lds_byte* lK = (const lds_byte*)smem;
+  const lds_byte *lV = lK + OPND, *lQ = lK + 2 * OPND, *lO = lK + 3 * OPND;
+  const float c = rsqrtf((float)DH) * LOG2E;
+  const int first = wave * 32, own = first + lr;         // this lane's query, then its key
+  const int qc = own < a.Sq ? own : a.Sq - 1;
+  bf16x8 of[KS];
+#pragma unroll
+  for (int ks = 0; ks < KS; ++ks) of[ks] = *reinterpret_cast<const bf16x8*>(P.O + (long)qc * a.o_row_stride + 16 * ks + 8 * lh);
+  const float lse = P.lse[qc];
+  ring_turn<0>(false);
+  bf16x8 fa[KS], fb[KS];
+  if (first < a.Sq) {                                    // wave-uniform
+    float D = 0.f;
+#pragma unroll
+    for (int ks = 0; ks < KS; ++ks) {
+      fa[ks] = fr.rows(lQ, wave, ks);
+      fb[ks] = fr.rows(lO, wave, ks);
+#pragma unroll
+      for (int e = 0; e < 8; ++e) D = fmaf((float)fb[ks][e], (float)of[ks][e], D);
+    }
+    D = half_sum(D);
+    if (lh == 0) {
+      rows[0][own] = own < a.Sq ? lse * -sqrtf((float)DH) : -INFINITY;
+      rows[1][own] = own < a.Sq ? -D : 0.f;
+    }
+    const int w_end = a.causal ? min(a.Sk, first + 32) : a.Sk;
+    const int limit = (a.causal ? min(own, a.Sk - 1) : a.Sk - 1) - 4 * lh;
+    f32x16 dq[DT];
+#pragma unroll
+    for (int dt = 0; dt < DT; ++dt) dq[dt] = splat16(0.f);
+    for (int k0 = 0; k0 < w_end; k0 += 32)
+      bwd_dq_half<DH>(fr, lK + k0 * L::RB, lV + k0 * L::RB, 0, fa, fb, c, lse * LOG2E, -D,
+                      k0 + 32 > a.Sk || (a.causal && k0 + 31 > first), limit - k0, dq);
+    if (own < a.Sq) store_rows_T<DH>(P.dQ, a.dqkv_row_stride, own, dq, rsqrtf((float)DH), lh);
+  }
+  asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
+  bare_barrier();                                        // every row's lse and D are there
+  if (first >= a.Sk) return;
+#pragma unroll
+  for (int ks = 0; ks < KS; ++ks) { fa[ks] = fr.rows(lK, wave, ks); fb[ks] = fr.rows(lV, wave, ks); }
+  f32x16 dk[DT], dv[DT];
+#pragma unroll
+  for (int dt = 0; dt < DT; ++dt) { dk[dt] = splat16(0.f); dv[dt] = splat16(0.f); }
+  for (int i0 = a.causal ? first : 0; i0 < a.Sq; i0 += 32)
+    bwd_dkv_half<DH>(fr, lQ + i0 * L::RB, lO + i0 * L::RB, 0, rows[0] + i0, rows[1] + i0, fa, fb, c,
+                     a.causal && i0 < first + 31, own - i0 - 4 * lh, lh, dk, dv);
+  if (own < a.Sk) {
+    const long kv_rs = a.dkv_row_stride ? a.dkv_row_stride : a.dqkv_row_stride;
+    store_rows_T<DH>(P.dK, kv_rs, own, dk, rsqrtf((float)DH), lh);
+    store_rows_T<DH>(P.dV, kv_rs, own, dv, 1.0f, lh);
+  }
 }
 
 // ---------------------------------------------------------------------------
@@ -605,20 +672,30 @@ template <int DH> static bool attn_wide(int pass, int seq) {
   return pass == 0 || tail == 0 || tail > 128;
 }
 
+// Launch with a ring of as many tile sets as `seq` rows make, three at most.
+template <int DH, typename Kernel>
+static hipError_t launch_ring(Kernel kern, int block_rows, int own_rows, int seq, const AttnArgs& a, hipStream_t st) {
+  const int sets = (seq + 63) / 64, slots = sets < RING ? sets : RING;
+  const size_t smem = (size_t)slots * 2 * Lay<DH>::TILE;
+  if (smem > 65536) {
+    const hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(kern),
+                                             hipFuncAttributeMaxDynamicSharedMemorySize, (int)smem);
+    if (e != hipSuccess) return e;
+  }
+  hipLaunchKernelGGL(kern, dim3((own_rows + block_rows - 1) / block_rows, a.B * a.H, a.n_groups), dim3(2 * block_rows),
+                     smem, st, a);
+  return hipGetLastError();
+}
+
 template <int DH>
 static hipError_t attn_fwd_mfma_dh(const AttnArgs& a, hipStream_t st) {
   if (a.Sq <= 0 || a.Sk <= 0) return hipErrorInvalidValue;
-  if (a.Sq <= 64) {
-    dim3 grid((a.Sq + 63) / 64, a.B * a.H, a.n_groups);
-    hipLaunchKernelGGL((attn_fwd_mfma_kernel<2, DH>), grid, dim3(128), 0, st, a);
-  } else if (attn_wide<DH>(0, a.Sq)) {
-    dim3 grid((a.Sq + 255) / 256, a.B * a.H, a.n_groups);
-    hipLaunchKernelGGL((attn_fwd_mfma_kernel<8, DH>), grid, dim3(512), 0, st, a);
-  } else {
-    dim3 grid((a.Sq + 127) / 128, a.B * a.H, a.n_groups);
-    hipLaunchKernelGGL((attn_fwd_mfma_kernel<4, DH>), grid, dim3(256), 0, st, a);
-  }
-  return hipGetLastError();
+  const bool longer = a.Sk > 128;
+  if (a.Sq <= 64) return launch_ring<DH>(longer ? attn_fwd_mfma_kernel<2, DH, true> : attn_fwd_mfma_kernel<2, DH, false>,
+                                         64, a.Sq, a.Sk, a, st);
+  if (attn_wide<DH>(0, a.Sq)) return launch_ring<DH>(attn_fwd_mfma_kernel<8, DH, true>, 256, a.Sq, a.Sk, a, st);
+  return launch_ring<DH>(longer ? attn_fwd_mfma_kernel<4, DH, true> : attn_fwd_mfma_kernel<4, DH, false>, 128, a.Sq, a.Sk,
+                         a, st);
 }
 
 hipError_t attn_fwd_mfma(const AttnArgs& a, hipStream_t st) {
@@ -634,28 +711,14 @@ static hipError_t attn_bwd_mfma_dh(const AttnArgs& a, hipStream_t st) {
     else hipLaunchKernelGGL((attn_bwd_fused_mfma_kernel<4, DH>), grid, dim3(256), 0, st, a);
     return hipGetLastError();
   }
-  if (a.Sq <= 64) {
-    dim3 grid((a.Sq + 63) / 64, a.B * a.H, a.n_groups);
-    hipLaunchKernelGGL((attn_bwd_dq_mfma_kernel<2, DH>), grid, dim3(128), 0, st, a);
-  } else if (attn_wide<DH>(1, a.Sq)) {
-    dim3 grid((a.Sq + 255) / 256, a.B * a.H, a.n_groups);
-    hipLaunchKernelGGL((attn_bwd_dq_mfma_kernel<8, DH>), grid, dim3(512), 0, st, a);
-  } else {
-    dim3 grid((a.Sq + 127) / 128, a.B * a.H, a.n_groups);
-    hipLaunchKernelGGL((attn_bwd_dq_mfma_kernel<4, DH>), grid, dim3(256), 0, st, a);
-  }
-  if (!a.dk) return hipGetLastError();           // only dQ wanted (cross-attention: dK, dV feed the memory gradient)
-  if (a.Sk <= 64) {
-    dim3 grid((a.Sk + 63) / 64, a.B * a.H, a.n_groups);
-    hipLaunchKernelGGL((attn_bwd_dkv_mfma_kernel<2, DH>), grid, dim3(128), 0, st, a);
-  } else if (attn_wide<DH>(2, a.Sk)) {
-    dim3 grid((a.Sk + 255) / 256, a.B * a.H, a.n_groups);
-    hipLaunchKernelGGL((attn_bwd_dkv_mfma_kernel<8, DH>), grid, dim3(512), 0, st, a);
-  } else {
-    dim3 grid((a.Sk + 127) / 128, a.B * a.H, a.n_groups);
-    hipLaunchKernelGGL((attn_bwd_dkv_mfma_kernel<4, DH>), grid, dim3(256), 0, st, a);
-  }
-  return hipGetLastError();
+  hipError_t e;
+  if (a.Sq <= 64) e = launch_ring<DH>(attn_bwd_dq_mfma_kernel<2, DH>, 64, a.Sq, a.Sk, a, st);
+  else if (attn_wide<DH>(1, a.Sq)) e = launch_ring<DH>(attn_bwd_dq_mfma_kernel<8, DH>, 256, a.Sq, a.Sk, a, st);
+  else e = launch_ring<DH>(attn_bwd_dq_mfma_kernel<4, DH>, 128, a.Sq, a.Sk, a, st);
+  if (e != hipSuccess || !a.dk) return e;        // only dQ wanted (cross-attention: dK, dV feed the memory gradient)
+  if (a.Sk <= 64) return launch_ring<DH>(attn_bwd_dkv_mfma_kernel<2, DH>, 64, a.Sk, a.Sq, a, st);
+  if (attn_wide<DH>(2, a.Sk)) return launch_ring<DH>(attn_bwd_dkv_mfma_kernel<8, DH>, 256, a.Sk, a.Sq, a, st);
+  return launch_ring<DH>(attn_bwd_dkv_mfma_kernel<4, DH>, 128, a.Sk, a.Sq, a, st);
 }
 
 hipError_t attn_bwd_mfma(const AttnArgs& a, hipStream_t st) {
