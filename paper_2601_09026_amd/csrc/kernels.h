@@ -65,11 +65,11 @@ hipError_t launch_resnorm(int n_groups, long elems, Rows A, Rows B, double* part
                           float* out, hipStream_t st);
 // tab[i] = base + i*stride_bytes, i < n
 hipError_t launch_fill_table(void** tab, char* base, long stride_bytes, int n, hipStream_t st);
-// tab[i] = ptrs[i]: pointers travel as kernel arguments (safe for any host memory, capturable)
+// tab[i] = ptrs[i]: pointers travel as kernel arguments, 128 a launch (safe for any host memory, capturable)
 hipError_t upload_pointers(void** tab, const void* const* host_ptrs, int n, hipStream_t st);
-// out_g[c, r] = in_g[r, c] for every group; in/out found at byte offset `off` of the blocks
-hipError_t launch_transpose(int n_groups, Params in, Params out, long off, int rows, int cols, int elem_bytes,
-                            hipStream_t st);
+// out_g[c, r] = in_g[r, c] for every group and every matrix of the list (at most 7 per block: byte offset, shape)
+struct TransposeList { int n; int rows[7], cols[7], tiles[7]; long off[7]; };
+hipError_t launch_transpose(int n_groups, Params in, Params out, const TransposeList& l, int elem_bytes, hipStream_t st);
 
 // ---- grads.hip ---------------------------------------------------------------
 // LayerNorm gain / shift gradients of up to three LayerNorms of the same layers: sums over tokens of

@@ -48,9 +48,22 @@ constexpr int DEFAULT_MAX_GROUPS = 4;
 // 196.5; ViT shape 84.0, 83.4, 87.7; where the pick changed at nine shapes of 256 to 1280 wide and 1024 to 16384
 // tokens it was 10 to 0.4 % faster up to 4096 tokens and 0.4 to 2 % slower above: the last table of
 // profiles/gemm_tile_round_times.txt).
-inline int default_groups(const mgrit_model_desc* md, int sweep) {
-  if (md->dtype != MGRIT_DTYPE_BF16 || sweep < 2) return DEFAULT_MAX_GROUPS;
+//
+// Layers of few tokens go into one launch (up to SMALL_GROUPS of them) until it has SMALL_ROWS rows or its intermediates
+// SMALL_BYTES: their launches take a few microseconds each however many layers they hold, and the host needs as long
+// to enqueue one.  (few_tokens = false: the rule without that, for scratch memory of a fixed size.)
+constexpr int SMALL_ROWS = 4096, SMALL_GROUPS = 64;
+constexpr long SMALL_BYTES = 16 << 20;
+inline int default_groups(const mgrit_model_desc* md, int sweep, bool few_tokens = true) {
   const int T = md->batch * md->seq, d = md->d_model, f = md->d_ff;
+  if (few_tokens) {
+    const long rows = T + (long)md->batch * md->mem_seq;
+    long fit = SMALL_ROWS / rows;
+    if (fit > SMALL_BYTES / (rows * (8L * d + f) * 4)) fit = SMALL_BYTES / (rows * (8L * d + f) * 4);
+    if (fit > SMALL_GROUPS) fit = SMALL_GROUPS;
+    if (fit > 6) return fit < sweep ? (int)fit : sweep > DEFAULT_MAX_GROUPS ? sweep : DEFAULT_MAX_GROUPS;
+  }
+  if (md->dtype != MGRIT_DTYPE_BF16 || sweep < 2) return DEFAULT_MAX_GROUPS;
   double cost[7] = {0};
   double best = 1e300;
   for (int gc = 3; gc <= 6; ++gc) {
@@ -69,8 +82,8 @@ inline int default_groups(const mgrit_model_desc* md, int sweep) {
     if (cost[gc] <= 1.03 * best) pick = gc;
   return pick;
 }
-inline int max_groups(const mgrit_model_desc* md, int sweep) {
-  return g_max_groups > 0 ? g_max_groups : default_groups(md, sweep);
+inline int max_groups(const mgrit_model_desc* md, int sweep, bool few_tokens = true) {
+  return g_max_groups > 0 ? g_max_groups : default_groups(md, sweep, few_tokens);
 }
 
 #define HIPCHK(expr)                                   \
@@ -729,11 +742,29 @@ int param_grads_chunk(Engine& E, int n, Params THT, Rows LIN, Slots cs, float hs
   return MGRIT_OK;
 }
 
+// A sweep that fits one launch chunk and whose products take less than the host needs to enqueue a second chain of
+// launches (about 8 kernels and the events of the fork and join, 3-4 us each) stays in one piece.  Microseconds of the
+// four products of a layer step: bf16 from the tile model, fp32 at 100 TFLOP/s and 3 us a launch.
+// Whole calls, split and in one piece (with the larger chunks above): four layers of 64 tokens, fp32, 111 -> 37 us;
+// transposed steps of 6 layers of 462 tokens, 320 wide, 235 -> 103 us; training step of 16 layers of 64 tokens
+// 3.41 -> 2.42 ms.
+constexpr double SMALL_SWEEP_US = 40.0;
+inline bool small_sweep(const Engine& E, int G) {
+  if (G > E.Gc) return false;
+  double us;
+  if (E.bf16)
+    us = gemm_model_cost(G, E.T, 3 * E.d, E.d) + gemm_model_cost(G, E.T, E.d, E.d) + gemm_model_cost(G, E.T, E.f, E.d) +
+         gemm_model_cost(G, E.T, E.d, E.f);
+  else
+    us = 12.0 + (double)G * E.T * (8.0 * E.d * E.d + 4.0 * E.d * E.f) / 1e8;
+  return us < SMALL_SWEEP_US;
+}
+
 // Runs `fn(lane engine, first group, count)` over chunks of a sweep; with a second lane the
 // chunks alternate between the two streams.
 template <typename F>
 int run_chunks(Engine& E, Engine* E2, int G, F fn) {
-  const bool two = E2 != nullptr && G >= 2;
+  const bool two = E2 != nullptr && G >= 2 && !small_sweep(E, G);
   int chunk = E.Gc;
   if (two && (G + 1) / 2 < chunk) chunk = (G + 1) / 2;
   if (!two) {
@@ -823,11 +854,13 @@ int gradient_groups(Engine& E, Engine* E2, int G, Rows IN, Params TH, Params THT
 int transpose_blocks(Engine& E, int n, Params TH, Params THT) {
   static const int mats[] = {MGRIT_P_WQKV, MGRIT_P_WO, MGRIT_P_W1, MGRIT_P_W2, MGRIT_P_WQ_C, MGRIT_P_WO_C,
                              MGRIT_P_WKV_C};
+  TransposeList l;
+  memset(&l, 0, sizeof(l));
   for (int id : mats) {
     if (E.lay.offset[id] < 0) continue;
-    HIPCHK(launch_transpose(n, TH, THT, E.lay.offset[id], E.lay.rows[id], E.lay.cols[id], E.lay.elem_bytes[id],
-                            E.st));
+    l.off[l.n] = E.lay.offset[id]; l.rows[l.n] = E.lay.rows[id]; l.cols[l.n++] = E.lay.cols[id];
   }
+  HIPCHK(launch_transpose(n, TH, THT, l, (int)E.esz, E.st));
   return MGRIT_OK;
 }
 
@@ -1310,7 +1343,7 @@ size_t layer_step_bytes(const mgrit_model_desc* desc, int adjoint, int n_groups,
   Engine E;
   E.init(desc, nullptr);
   Bump b(nullptr);
-  int gc = max_groups(desc, n_groups) < n_groups ? max_groups(desc, n_groups) : n_groups;
+  const int most = max_groups(desc, n_groups, second_lane), gc = most < n_groups ? most : n_groups;
   Engine E2;
   if (adjoint) {
     E.carve_adjoint(b, gc, n_groups);
@@ -1348,7 +1381,7 @@ int layer_step_on(const mgrit_model_desc* desc, int adjoint, int n_groups, const
   Engine E;
   E.init(desc, st);
   Bump b(workspace);
-  const int gc = max_groups(desc, n_groups) < n_groups ? max_groups(desc, n_groups) : n_groups;
+  const int most = max_groups(desc, n_groups, second_lane), gc = most < n_groups ? most : n_groups;
   const int G = n_groups;
   Engine E2;
   Engine* L2 = nullptr;
@@ -1359,12 +1392,13 @@ int layer_step_on(const mgrit_model_desc* desc, int adjoint, int n_groups, const
     void** tabs = b.take<void*>((size_t)G * 6);
     void **tIn = tabs, **tOut = tabs + G, **tTh = tabs + 2 * G, **tLin = tabs + 3 * G, **tRhs = tabs + 4 * G,
          **tThT = tabs + 5 * G;
-    HIPCHK(upload_pointers(tIn, in, G, st));
-    HIPCHK(upload_pointers(tOut, (const void* const*)out, G, st));
-    HIPCHK(upload_pointers(tTh, theta, G, st));
-    HIPCHK(upload_pointers(tLin, lin_state, G, st));
-    if (rhs) HIPCHK(upload_pointers(tRhs, rhs, G, st));
-    HIPCHK(launch_fill_table(tThT, tblocks, (long)E.lay.block_bytes, G, st));
+    std::vector<const void*> ptrs((size_t)G * 6, nullptr);  // in the order of the tables above
+    for (int g = 0; g < G; ++g) {
+      ptrs[g] = in[g]; ptrs[G + g] = out[g]; ptrs[2 * G + g] = theta[g]; ptrs[3 * G + g] = lin_state[g];
+      if (rhs) ptrs[4 * G + g] = rhs[g];
+      ptrs[5 * G + g] = tblocks + (size_t)g * E.lay.block_bytes;
+    }
+    HIPCHK(upload_pointers(tabs, ptrs.data(), 6 * G, st));
     Params TH = {(const void* const*)tTh, 0, 1}, THT = {(const void* const*)tThT, 0, 1};
     Rows IN = {(const void* const*)tIn, 0, 1}, OUT = {(const void* const*)tOut, 0, 1};
     Rows LIN = {(const void* const*)tLin, 0, 1};
@@ -1379,10 +1413,12 @@ int layer_step_on(const mgrit_model_desc* desc, int adjoint, int n_groups, const
   if (second_lane && G >= 2 && make_lane(E2, E, b, false, false)) L2 = &E2;
   void** tabs = b.take<void*>((size_t)G * 4);
   void **tIn = tabs, **tOut = tabs + G, **tTh = tabs + 2 * G, **tRhs = tabs + 3 * G;
-  HIPCHK(upload_pointers(tIn, in, G, st));
-  HIPCHK(upload_pointers(tOut, (const void* const*)out, G, st));
-  HIPCHK(upload_pointers(tTh, theta, G, st));
-  if (rhs) HIPCHK(upload_pointers(tRhs, rhs, G, st));
+  std::vector<const void*> ptrs((size_t)G * 4, nullptr);
+  for (int g = 0; g < G; ++g) {
+    ptrs[g] = in[g]; ptrs[G + g] = out[g]; ptrs[2 * G + g] = theta[g];
+    if (rhs) ptrs[3 * G + g] = rhs[g];
+  }
+  HIPCHK(upload_pointers(tabs, ptrs.data(), (rhs ? 4 : 3) * G, st));
   if (desc->arch == MGRIT_ARCH_CROSS)
     HIPCHK(launch_cast_flat(static_cast<const float*>(memory), E.memb, (long)E.Tm * E.d, E.bf16, st));
   Params TH = {(const void* const*)tTh, 0, 1};

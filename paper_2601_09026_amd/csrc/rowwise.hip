@@ -449,53 +449,77 @@ hipError_t launch_fill_table(void** tab, char* base, long stride_bytes, int n, h
   return hipGetLastError();
 }
 
-struct PtrPack { const void* p[32]; };
-__global__ void upload_ptrs_kernel(void** tab, PtrPack pack, int n) {
+constexpr int PACK = 128;                  // 1 KB of kernel arguments
+struct PtrPack { const void* p[PACK]; };
+__global__ void __launch_bounds__(PACK) upload_ptrs_kernel(void** tab, PtrPack pack, int n) {
   const int i = threadIdx.x;
   if (i < n) tab[i] = const_cast<void*>(pack.p[i]);
 }
 
 hipError_t upload_pointers(void** tab, const void* const* host_ptrs, int n, hipStream_t st) {
-  for (int i0 = 0; i0 < n; i0 += 32) {
+  for (int i0 = 0; i0 < n; i0 += PACK) {
     PtrPack pack;
-    const int m = n - i0 < 32 ? n - i0 : 32;
-    for (int i = 0; i < 32; ++i) pack.p[i] = i < m ? host_ptrs[i0 + i] : nullptr;
-    hipLaunchKernelGGL(upload_ptrs_kernel, dim3(1), dim3(32), 0, st, tab + i0, pack, m);
+    const int m = n - i0 < PACK ? n - i0 : PACK;
+    for (int i = 0; i < PACK; ++i) pack.p[i] = i < m ? host_ptrs[i0 + i] : nullptr;
+    hipLaunchKernelGGL(upload_ptrs_kernel, dim3(1), dim3(PACK), 0, st, tab + i0, pack, m);
   }
   return hipGetLastError();
 }
 
 // ---------------------------------------------------------------------------
-// weight transposition (adjoint): out_g[c,r] = in_g[r,c]
+// weight transposition (adjoint): out_g[c,r] = in_g[r,c] for every matrix of a block, all of them in one launch.
+// Bound by memory: a block moves 64 x 64 elements through LDS, 16 bytes per lane both ways (eight lanes fill 128 bytes of
+// a row; the row pitch of an odd number of dwords puts the column reads of a wavefront on distinct banks).
 // ---------------------------------------------------------------------------
 template <typename U>
-__global__ void __launch_bounds__(256) transpose_kernel(Params in, Params out, long off, int rows, int cols) {
-  __shared__ U tile[32][33];
-  const int g = blockIdx.z;
-  const U* src = reinterpret_cast<const U*>(in.at(g) + off);
-  U* dst = reinterpret_cast<U*>(const_cast<char*>(out.at(g)) + off);
-  const int c0 = blockIdx.x * 32, r0 = blockIdx.y * 32;
-  const int tx = threadIdx.x & 31, ty = threadIdx.x >> 5;
-  for (int i = ty; i < 32; i += 8) {
-    const int r = r0 + i, c = c0 + tx;
-    if (r < rows && c < cols) tile[i][tx] = src[(long)r * cols + c];
+__global__ void __launch_bounds__(256) transpose_kernel(Params in, Params out, TransposeList list) {
+  constexpr int V = 16 / sizeof(U), CH = 64 / V;           // elements per access, accesses per row of a tile
+  constexpr int LD = 64 + (sizeof(U) == 2 ? 2 : 1);
+  typedef __attribute__((__vector_size__(16))) U vec;
+  __shared__ U tile[64 * LD];
+  const int g = blockIdx.y;
+  int m = 0, t = blockIdx.x;
+  while (t >= list.tiles[m]) t -= list.tiles[m++];
+  const int rows = list.rows[m], cols = list.cols[m], across = (cols + 63) >> 6;
+  const int r0 = t / across * 64, c0 = t % across * 64;
+  const U* src = reinterpret_cast<const U*>(in.at(g) + list.off[m]);
+  U* dst = reinterpret_cast<U*>(const_cast<char*>(out.at(g)) + list.off[m]);
+#pragma unroll
+  for (int k = 0; k < 64 * CH / 256; ++k) {                // rows and columns are multiples of 8
+    const int item = k * 256 + threadIdx.x, r = item / CH, c = item % CH * V;
+    if (r0 + r < rows && c0 + c < cols) {
+      const vec v = *reinterpret_cast<const vec*>(src + (long)(r0 + r) * cols + c0 + c);
+#pragma unroll
+      for (int e = 0; e < V; ++e) tile[r * LD + c + e] = v[e];
+    }
   }
   __syncthreads();
-  for (int i = ty; i < 32; i += 8) {
-    const int c = c0 + i, r = r0 + tx;
-    if (r < rows && c < cols) dst[(long)c * rows + r] = tile[tx][i];
+#pragma unroll
+  for (int k = 0; k < 64 * CH / 256; ++k) {
+    const int item = k * 256 + threadIdx.x, c = item / CH, r = item % CH * V;
+    if (r0 + r < rows && c0 + c < cols) {
+      vec v;
+#pragma unroll
+      for (int e = 0; e < V; ++e) v[e] = tile[(r + e) * LD + c];
+      *reinterpret_cast<vec*>(dst + (long)(c0 + c) * rows + r0 + r) = v;
+    }
   }
 }
 
-hipError_t launch_transpose(int n_groups, Params in, Params out, long off, int rows, int cols, int elem_bytes,
-                            hipStream_t st) {
-  if (n_groups <= 0) return hipSuccess;
-  dim3 grid((cols + 31) / 32, (rows + 31) / 32, n_groups);
-  ProfScope ps(PC_ELEMENTWISE, 0.0, 2.0 * n_groups * rows * cols * elem_bytes, st);
-  if (elem_bytes == 2)
-    hipLaunchKernelGGL(transpose_kernel<uint16_t>, grid, dim3(256), 0, st, in, out, off, rows, cols);
-  else
-    hipLaunchKernelGGL(transpose_kernel<uint32_t>, grid, dim3(256), 0, st, in, out, off, rows, cols);
+hipError_t launch_transpose(int n_groups, Params in, Params out, const TransposeList& l, int elem_bytes, hipStream_t st) {
+  if (n_groups <= 0 || l.n == 0) return hipSuccess;
+  TransposeList list = l;
+  int total = 0;
+  double elems = 0.0;
+  for (int i = 0; i < list.n; ++i) {
+    list.tiles[i] = (list.rows[i] + 63) / 64 * ((list.cols[i] + 63) / 64);
+    total += list.tiles[i];
+    elems += (double)list.rows[i] * list.cols[i];
+  }
+  const dim3 grid(total, n_groups);
+  ProfScope ps(PC_ELEMENTWISE, 0.0, 2.0 * n_groups * elems * elem_bytes, st);
+  if (elem_bytes == 2) hipLaunchKernelGGL(transpose_kernel<uint16_t>, grid, dim3(256), 0, st, in, out, list);
+  else hipLaunchKernelGGL(transpose_kernel<uint32_t>, grid, dim3(256), 0, st, in, out, list);
   return hipGetLastError();
 }
 
