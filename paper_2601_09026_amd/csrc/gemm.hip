@@ -502,6 +502,225 @@ gemm_mfma_kernel(const GemmArgs a, int tiles_m, int tiles_n, int total_tiles, in
                                          M, m0 + wm0, n0 + wn0, lane);
 }
 
+// Pointer tables do not change while a kernel runs: read as constant memory, i.e. by scalar loads also behind stores
+// (a vector load would be waited for together with every store before it).
+__device__ __forceinline__ const char* table_entry(const void* const* tab, long i) {
+  typedef const void* const __attribute__((address_space(4)))* cptr;
+  return (const char*)((cptr)tab)[i];
+}
+
+typedef __attribute__((__vector_size__(16))) unsigned u32x4;
+typedef __attribute__((address_space(3))) f32x4 lds_f32x4;
+
+// Epilogue of one wavefront of the kernel below: 128 x 64 outputs in pieces of 16 rows through 4 KB of LDS that the ring
+// of k-tiles leaves free (the next tile's k-tiles are in it already), 16-byte chunks swizzled by the row instead of padded.
+// Rows past M lie past the end of the buffers: their loads give zeros and their stores are dropped, so every tile issues
+// the same operations.
+__device__ __forceinline__ void dgelu_epilogue(f32x16 (&acc)[4][2], lds_byte* ep, const char* g_in, char* out, int N, int M,
+                                               int mrow0, int ncol0, int lane) {
+  const int lr = lane & 31, lh = lane >> 5, ci = lane & 7, rr = lane >> 3, r16 = lr & 15;
+  const long first = 2 * ((long)mrow0 * N + ncol0);
+  const unsigned left = M > mrow0 ? (unsigned)((M - mrow0) * N - ncol0) * 2u : 0u;
+  auto buf = [&](const char* p) {
+    const unsigned long b = (unsigned long)(p + first);
+    const unsigned lo = __builtin_amdgcn_readfirstlane((unsigned)b), hi = __builtin_amdgcn_readfirstlane((unsigned)(b >> 32));
+    return __builtin_amdgcn_make_buffer_rsrc((void*)((unsigned long)hi << 32 | lo), 0, __builtin_amdgcn_readfirstlane(left), 0x00020000);
+  };
+  const auto bo = buf(out), bg = buf(g_in);
+  const int off = 2 * (rr * N + 8 * ci);
+  // the cached derivatives, fetched two pieces ahead: no wait for them then covers a store just issued
+  constexpr int STREAM = 2;                                // non-temporal
+  bf16x8 g[2][2];
+  auto fetch = [&](int piece) {
+#pragma unroll
+    for (int it = 0; it < 2; ++it)
+      g[piece & 1][it] = __builtin_bit_cast(
+          bf16x8, __builtin_amdgcn_raw_buffer_load_b128(bg, off + 2 * N * (16 * piece + 8 * it), 0, STREAM));
+  };
+  fetch(0);
+  fetch(1);
+#pragma unroll
+  for (int p = 0; p < 8; ++p) {                            // rows 16 p ..
+    // the lanes read what others wrote: nothing may move across these two points, nor be taken into a branch
+    __builtin_amdgcn_wave_barrier();
+    if ((lr >> 4) == (p & 1)) {
+#pragma unroll
+      for (int j = 0; j < 2; ++j)
+#pragma unroll
+        for (int q = 0; q < 4; ++q) {
+          const f32x16& c = acc[p >> 1][j];
+          const f32x4 v = {c[4 * q], c[4 * q + 1], c[4 * q + 2], c[4 * q + 3]};
+          *(lds_f32x4*)(ep + r16 * 256 + (((8 * j + 2 * q + lh) ^ r16) << 4)) = v;
+        }
+    }
+    __builtin_amdgcn_wave_barrier();
+#pragma unroll
+    for (int it = 0; it < 2; ++it) {
+      const int row = it * 8 + rr;
+      const f32x4 x = *(const lds_f32x4*)(ep + row * 256 + (((2 * ci) ^ row) << 4));
+      const f32x4 y = *(const lds_f32x4*)(ep + row * 256 + (((2 * ci + 1) ^ row) << 4));
+      bf16x8 r;
+#pragma unroll
+      for (int e = 0; e < 4; ++e) {
+        r[e] = (bf16)(x[e] * (float)g[p & 1][it][e]);
+        r[4 + e] = (bf16)(y[e] * (float)g[p & 1][it][4 + e]);
+      }
+      if (it == 1 && p + 2 < 8) fetch(p + 2);
+      __builtin_amdgcn_raw_buffer_store_b128(__builtin_bit_cast(u32x4, r), bo, off + 2 * N * (16 * p + 8 * it), 0, STREAM);
+    }
+  }
+}
+
+// ---------------------------------------------------------------------------
+// Multiply-by-GELU' products of more than one round of whole 256x256 tiles: one block per CU walks the tiles of its XCD, and
+// its ring of k-tiles runs on from one tile into the next.  What bounds such a launch besides the matrix cores is the time
+// they stand still between two tiles: start of a block, pointer tables, first loads, and an epilogue that reads and
+// writes the output's size.  Here the first two k-tiles of the next tile are on their way during the last two of this
+// one, and the stores drain under its first products (waited for by count).  5 x 4096 rows, 768 -> 3072: 125 -> 119 us;
+// 5 x 12608 rows, 384 -> 1536: 125 -> 117; 6 x 4096 rows, 512 -> 2048: 81 -> 77; training steps 0.7 % (GPT-2, ViT and MT
+// shapes).  The other epilogues gained nothing in this form (store 79 -> 79 us, bias+GELU 110 -> 112).
+// ---------------------------------------------------------------------------
+__global__ void __launch_bounds__(512, 2)
+gemm_mfma_dgelu_walk_kernel(const GemmArgs a, int tiles_m, int tiles_n, int total_tiles, int per_xcd, int pm, int pn) {
+  constexpr int BM = 256, BN = 256, BK = 64, WN = 4, WTM = 128, WTN = 64, TM = 4, TN = 2;
+  constexpr int RB = BK * 2, CPR = RB / 16, RPL = 1024 / RB, KS = BK / 16;
+  constexpr int A_BYTES = BM * RB, STAGE = A_BYTES + BN * RB, LD_ = 4, PER_TILE = 8, RING = 2 * STAGE;
+  extern __shared__ __attribute__((aligned(1024))) unsigned char smem2[];
+  const int tid = threadIdx.x;
+  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6), lane = tid & 63, lr = lane & 31, lh = lane >> 5;
+  const int wm0 = (wave / WN) * WTM, wn0 = (wave % WN) * WTN;
+  const int K = a.K, M = a.M, KT = K / BK, per_group = tiles_m * tiles_n, walkers = gridDim.x >> 3;
+  const int lrow = lane / CPR, lpos = lane % CPR;
+  const int end = min(((int)(blockIdx.x & 7) + 1) * per_xcd, total_tiles);
+  int tile = (blockIdx.x & 7) * per_xcd + (blockIdx.x >> 3);
+  if (tile >= end) return;
+
+  struct Place { int g, m0, n0; __amdgpu_buffer_rsrc_t A, B; int aoff[LD_]; };
+  auto locate = [&](Place& p, int t) {
+    p.g = __builtin_amdgcn_readfirstlane(t / per_group);
+    const int tg = t - p.g * per_group;
+    int tm, tn;
+    if (pn > 0) {
+      const int patch = pm * pn, patches_n = tiles_n / pn, b = tg / patch, w = tg - b * patch, bm = b / patches_n;
+      tm = bm * pm + w / pn;
+      tn = (b - bm * patches_n) * pn + w % pn;
+    } else {
+      tm = tg / tiles_n;
+      tn = tg - tm * tiles_n;
+    }
+    p.m0 = __builtin_amdgcn_readfirstlane(tm) * BM;
+    p.n0 = __builtin_amdgcn_readfirstlane(tn) * BN;
+    p.A = lds_source(reinterpret_cast<const bf16*>(a.A) + a.a_slots.of(p.g) * a.a_slot_stride + (long)p.m0 * K);
+    p.B = lds_source(table_entry(a.B.tab, a.B.i0 + (long)p.g * a.B.is) + a.b_off + 2 * (long)p.n0 * K);
+#pragma unroll
+    for (int j = 0; j < LD_; ++j) {
+      const int row = (wave * LD_ + j) * RPL + lrow;
+      p.aoff[j] = ((row < M - p.m0 ? row : M - 1 - p.m0) * K + (lpos ^ swz(row)) * 8) * 2;
+    }
+  };
+  int boff[LD_];
+#pragma unroll
+  for (int j = 0; j < LD_; ++j) {
+    const int row = (wave * LD_ + j) * RPL + lrow;
+    boff[j] = (row * K + (lpos ^ swz(row)) * 8) * 2;
+  }
+  auto issue_one = [&](const Place& p, int stage, int k0, int idx) {
+    unsigned char* sa = smem2 + stage * STAGE + (idx < LD_ ? 0 : A_BYTES) + (wave * LD_ + (idx & (LD_ - 1))) * 1024;
+    if (idx < LD_) load_to_lds(p.A, sa, p.aoff[idx & (LD_ - 1)], 2 * k0);
+    else load_to_lds(p.B, sa, boff[idx & (LD_ - 1)], 2 * k0);
+  };
+  int foff[KS];
+#pragma unroll
+  for (int ks = 0; ks < KS; ++ks) foff[ks] = lr * RB + (((2 * ks + lh) ^ swz(lr)) << 4);
+  const lds_byte* lds0 = (const lds_byte*)smem2;
+
+  Place cur, nxt;
+  locate(cur, tile);
+#pragma unroll
+  for (int s = 0; s < 2; ++s)
+#pragma unroll
+    for (int u = 0; u < PER_TILE; ++u) issue_one(cur, s, s * BK, u);     // KT >= 2
+  f32x16 acc[TM][TN];
+#pragma unroll
+  for (int i = 0; i < TM; ++i)
+#pragma unroll
+    for (int j = 0; j < TN; ++j)
+#pragma unroll
+      for (int r = 0; r < 16; ++r) acc[i][j][r] = 0.f;
+  wait_vmcnt<PER_TILE>();
+  bare_barrier();
+  bf16x8 fa[2][TM], fb[2][TN];
+#pragma unroll
+  for (int j = 0; j < TN; ++j) fb[0][j] = lds_read16(lds0 + A_BYTES + (wn0 + j * 32) * RB + foff[0]);
+#pragma unroll
+  for (int i = 0; i < TM; ++i) fa[0][i] = lds_read16(lds0 + (wm0 + i * 32) * RB + foff[0]);
+
+  constexpr int EP_OPS = 16;                               // at least so many operations follow a tile's last loads
+  int st = 0;                                              // stage of the k-tile at hand
+  bool stores = false;                                     // the last epilogue's are in flight
+  while (true) {
+    const bool more = tile + walkers < end;
+    nxt = cur;                                             // (after the last tile its own first k-tiles once more)
+    if (more) locate(nxt, tile + walkers);
+    int kt = 0;
+    do {                                                   // KT >= 2
+      const bool ahead = kt + 2 >= KT;                     // the loads are the next tile's
+      const int k0 = (ahead ? kt + 2 - KT : kt + 2) * BK;
+      Place from;
+      from.A = ahead ? nxt.A : cur.A;
+      from.B = ahead ? nxt.B : cur.B;
+#pragma unroll
+      for (int u = 0; u < LD_; ++u) from.aoff[u] = ahead ? nxt.aoff[u] : cur.aoff[u];
+#pragma unroll
+      for (int ks = 0; ks < KS; ++ks) {
+        const int cb = ks & 1, nb = cb ^ 1;
+        const bool last = ks == KS - 1;
+        if (last) {
+          asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
+          if (stores) wait_vmcnt<EP_OPS>();
+          else wait_vmcnt<0>();
+          stores = false;
+          bare_barrier();
+        }
+        const int rst = last ? st ^ 1 : st, rks = last ? 0 : ks + 1;
+        const lds_byte* sA = lds0 + rst * STAGE + wm0 * RB;
+        const lds_byte* sB = lds0 + rst * STAGE + A_BYTES + wn0 * RB;
+        constexpr int NM = TM * TN, RD = TM + TN;
+#pragma unroll
+        for (int q = 0; q < NM; ++q) {
+          const int i = q / TN, j = q % TN;
+          acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(fb[cb][j], fa[cb][i], acc[i][j], 0, 0, 0);
+          const int r0 = (q * RD * 4 / 3 + NM - 1) / NM, r1 = ((q + 1) * RD * 4 / 3 + NM - 1) / NM;
+#pragma unroll
+          for (int u = 0; u < RD; ++u)
+            if (u >= r0 && (u < r1 || q == NM - 1)) {
+              if (u < TN) fb[nb][u] = lds_read16(sB + u * 32 * RB + foff[rks]);
+              else fa[nb][u - TN] = lds_read16(sA + (u - TN) * 32 * RB + foff[rks]);
+            }
+          if (last) issue_one(from, st, k0, q);
+          __builtin_amdgcn_sched_barrier(0);
+        }
+      }
+      st ^= 1;
+    } while (++kt < KT);
+    dgelu_epilogue(acc, (lds_byte*)smem2 + RING + wave * 4096,
+                   static_cast<const char*>(a.aux) + 2 * a.aux_slots.of(cur.g) * a.aux_slot_stride,
+                   static_cast<char*>(a.out) + 2 * a.out_slots.of(cur.g) * a.out_slot_stride, a.N, M, cur.m0 + wm0, cur.n0 + wn0,
+                   lane);
+    if (!more) break;
+#pragma unroll
+    for (int i = 0; i < TM; ++i)
+#pragma unroll
+      for (int j = 0; j < TN; ++j)
+#pragma unroll
+        for (int r = 0; r < 16; ++r) acc[i][j][r] = 0.f;
+    stores = true;
+    tile += walkers;
+    cur = nxt;
+  }
+  wait_vmcnt<0>();                                         // (the loads behind the last tile)
+}
+
 // ---------------------------------------------------------------------------
 // fp32 MFMA kernel (fp32 parameters and operands): 64x64 block tile, 4 wavefronts of 32x32 on
 // the 32x32x2 fp32 MFMA, k-tiles of 16 staged through LDS.  As in the bf16 kernel the weight
@@ -1067,6 +1286,28 @@ static hipError_t launch_mfma(const GemmArgs& a, hipStream_t st) {
   return hipGetLastError();
 }
 
+// The walking form of the 256x256 tile: more than one tile per CU, two k-tiles or more, byte offsets of 32 bits.
+static bool dgelu_walks(const GemmArgs& a) {
+  const long tiles = (long)((a.M + 255) / 256) * (a.N / 256) * a.n_groups;
+  return tiles > compute_units() && a.K >= 128 && a.bias_off < 0 && (double)a.M * a.N < 2e9;
+}
+static hipError_t launch_dgelu_walk(const GemmArgs& a, hipStream_t st) {
+  const int tiles_m = (a.M + 255) / 256, tiles_n = a.N / 256, total = tiles_m * tiles_n * a.n_groups, per_xcd = (total + 7) / 8;
+  const int smem = 2 * 512 * 128 + 8 * 4096;               // ring and eight staging regions: all of a CU's LDS
+  int pm = 0, pn = 0;                                      // as in launch_mfma
+  if (tiles_n > 4 && tiles_n % 4 == 0 && compute_units() == 256 && tiles_m % 4 == 0) pm = pn = 4;
+  static bool attr_done = false;
+  if (!attr_done) {
+    const hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(gemm_mfma_dgelu_walk_kernel),
+                                             hipFuncAttributeMaxDynamicSharedMemorySize, smem);
+    if (e != hipSuccess) return e;
+    attr_done = true;
+  }
+  hipLaunchKernelGGL(gemm_mfma_dgelu_walk_kernel, dim3(compute_units() / 8 * 8), dim3(512), smem, st, a, tiles_m, tiles_n,
+                     total, per_xcd, pm, pn);
+  return hipGetLastError();
+}
+
 // Two 64x64 tiles per CU are where the larger tile takes over: whole steps of small launches are up to twice as fast
 // on 32x32 tiles (1024 wide, 2 layers of 128 tokens: 171 us against 325), large ones lose up to 13 % to fetching each
 // operand twice as often (1024 wide, 4 layers of 1024 tokens: 1191 us against 1052), and near the line the two differ
@@ -1151,7 +1392,10 @@ double gemm_model_cost(int n_groups, int M, int N, int K) {
 template <int EPI, bool RAGGED>
 static hipError_t launch_cfg(int cfg, const GemmArgs& a, hipStream_t st) {
   switch (cfg) {
-    case 1: return launch_mfma<256, 256, 64, 2, 1, RAGGED, EPI, 2, 4>(a, st);
+    case 1:
+      if constexpr (!RAGGED && EPI == EPI_DGELU)
+        if (dgelu_walks(a)) return launch_dgelu_walk(a, st);
+      return launch_mfma<256, 256, 64, 2, 1, RAGGED, EPI, 2, 4>(a, st);
     case 3:
       if constexpr (!RAGGED) return launch_mfma<256, 192, 64, 2, 1, false, EPI, 4, 2>(a, st);
       break;

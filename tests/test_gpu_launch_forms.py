@@ -1,0 +1,85 @@
+"""Forms of a launch that a rule on its size chooses, at the edges of those rules: the walking form of the
+multiply-by-GELU' products (more than one 256x256 tile per compute unit) against 128x128 tiles, bit for bit; bf16
+attention at the edges of its 32-row units, 64-row tiles and rings of three tiles against the CPU oracle; many layers of
+few tokens in one launch against one layer per launch, bit for bit."""
+import pytest
+import torch
+
+from paper_2601_09026_amd import binding as mb
+from paper_2601_09026_amd import workloads as wls
+
+from gpu_util import DeviceModel, dev
+from test_gpu_layer_step import make, run_adjoint_case, run_forward_case
+
+pytestmark = pytest.mark.gpu
+
+
+def step(dm, wl, adjoint, G, seed=3):
+    rng = torch.Generator(device="cuda")
+    rng.manual_seed(seed)
+    ins, lin = (list(torch.randn((G, wl.tokens, wl.d_model), generator=rng, device="cuda")) for _ in range(2))
+    mem = wls.cross_memory(wl)
+    outs = [torch.full_like(x, float("nan")) for x in ins]
+    mb.layer_step_batched(dm.desc, adjoint, ins, outs, dm.blocks, 0.5, lin_state=lin if adjoint else None,
+                          memory=None if mem is None else dev(mem))
+    torch.cuda.synchronize()
+    return outs
+
+
+@pytest.mark.parametrize("d,H,f,B,S,G", [
+    (128, 2, 512, 4, 2050, 4),      # two k-tiles a tile, 264 tiles, two columns of them; the last row tile holds 8 rows
+    (192, 3, 1280, 1, 3329, 4),     # three k-tiles, five columns, one row past 13 row tiles
+    (256, 4, 2048, 8, 256, 5),      # whole tiles, eight columns in 4x4 patches
+])
+def test_walking_products_bits(d, H, f, B, S, G):
+    wl = make(wls.ARCH_ENCODER, wls.DTYPE_BF16, d=d, H=H, f=f, B=B, S=S)
+    print(f"[case] walking products d={d} f={f} B={B} S={S} G={G}", flush=True)
+    dm = DeviceModel(wl, n_layers=G, weight_std=0.05, keep_host=False)
+    mb.mgrit_set_lanes(1)
+    mb.mgrit_set_max_groups_per_launch(G)
+    try:
+        out = {}
+        for cfg in (4, 1):
+            mb.lib().mgrit_debug_gemm_tile_config(cfg)
+            out[cfg] = step(dm, wl, True, G)
+    finally:
+        mb.lib().mgrit_debug_gemm_tile_config(0)
+        mb.mgrit_set_max_groups_per_launch(0)
+        mb.mgrit_set_lanes(2)
+    for g in range(G):
+        assert torch.isfinite(out[1][g]).all(), f"group {g}"
+        assert torch.equal(out[1][g], out[4][g]), f"group {g}"
+
+
+@pytest.mark.parametrize("arch,dh,S,Sm", [
+    *[(wls.ARCH_CAUSAL, 64, S, 0) for S in (32, 33, 64, 65, 96, 97, 128, 129, 161, 192, 193, 257)],
+    *[(wls.ARCH_ENCODER, 64, S, 0) for S in (1, 63, 127, 160, 191, 225)],
+    *[(wls.ARCH_CROSS, 64, S, Sm) for S, Sm in ((33, 129), (65, 31), (129, 257), (130, 64), (1, 200))],
+    *[(wls.ARCH_CAUSAL, 128, S, 0) for S in (33, 129, 193)], (wls.ARCH_CROSS, 128, 97, 161), (wls.ARCH_ENCODER, 128, 257, 0),
+])
+def test_attention_edges_bf16(arch, dh, S, Sm):
+    wl = make(arch, wls.DTYPE_BF16, d=2 * dh, H=2, f=128, B=1, S=S, Sm=Sm)
+    run_forward_case(wl, G=1, hstep=0.5, with_rhs=False, weight_std=0.1, force_simple=0)
+    run_adjoint_case(wl, G=1, hstep=0.5, with_rhs=False, weight_std=0.1, force_simple=0)
+
+
+@pytest.mark.parametrize("adjoint", [False, True])
+@pytest.mark.parametrize("arch,dtype,d,f,B,S,Sm,G", [
+    (wls.ARCH_ENCODER, wls.DTYPE_F32, 64, 256, 2, 32, 0, 67),      # more than one launch of 64 layers, more than 128 pointers
+    (wls.ARCH_CROSS, wls.DTYPE_BF16, 72, 136, 1, 33, 20, 9),       # matrices that are no multiple of the transposed tiles
+    (wls.ARCH_CAUSAL, wls.DTYPE_BF16, 128, 512, 1, 600, 0, 7),     # six layers a launch by the rule for few tokens
+])
+def test_few_tokens_bits(arch, dtype, d, f, B, S, Sm, G, adjoint):
+    wl = make(arch, dtype, d=d, H=2, f=f, B=B, S=S, Sm=Sm)
+    print(f"[case] few tokens arch={arch} dtype={dtype} d={d} B={B} S={S} G={G} adjoint={adjoint}", flush=True)
+    dm = DeviceModel(wl, n_layers=G, weight_std=0.05, keep_host=False)
+    together = step(dm, wl, adjoint, G)
+    mb.mgrit_set_lanes(1)
+    mb.mgrit_set_max_groups_per_launch(1)
+    try:
+        alone = step(dm, wl, adjoint, G)
+    finally:
+        mb.mgrit_set_max_groups_per_launch(0)
+        mb.mgrit_set_lanes(2)
+    for g in range(G):
+        assert torch.isfinite(together[g]).all() and torch.equal(together[g], alone[g]), f"group {g}"
