@@ -119,7 +119,9 @@ int mgrit_theta_layout(const mgrit_model_desc* desc, mgrit_theta_layout_t* out);
 /* Workspace sizes in bytes (0 on invalid arguments).  Host only.
  * mgrit_workspace_bytes: adjoint = 0 for mgrit_forward, 1 for mgrit_adjoint, 2 for
  * mgrit_adjoint called with dtheta or dmemory (which keeps the inputs of every layer's linear
- * maps, the cotangents of their outputs and per-layer terms). */
+ * maps, the cotangents of their outputs and per-layer terms).  For mgrit_forward of a cross-attention
+ * decoder the size has room for every layer's keys and values of the memory; the size queried with the
+ * adjoint cache switched off has not, is also accepted, and gives the same results more slowly. */
 size_t mgrit_workspace_bytes(const mgrit_model_desc* desc, const mgrit_opts* opts, int adjoint);
 size_t mgrit_layer_step_workspace_bytes(const mgrit_model_desc* desc, int adjoint, int n_groups);
 

@@ -193,6 +193,7 @@ struct Engine {
   int Gc;                          // groups per launch chunk
   // forward work buffers, Gc slots each
   void *u, *qkv, *o, *act, *qc, *kvc, *memb;
+  void* kv_all = nullptr;          // forward: K | V of the shared memory of every layer ([N, Tm, 2d], slot = layer), or null
   float *xin, *x3;
   // adjoint: linearisation cache (n_cache slots) and work buffers (Gc slots)
   int n_cache;
@@ -248,12 +249,13 @@ struct Engine {
     if (md.arch == MGRIT_ARCH_CROSS) {
       x3 = b.take<float>(G * T * d);
       qc = b.take_bytes(G * T * d * esz);
-      kvc = b.take_bytes(G * Tm * 2 * d * esz);
+      kvc = kv_all ? nullptr : b.take_bytes(G * Tm * 2 * d * esz);
       if (per_group_mem) membG = b.take_bytes(G * Tm * d * esz);
     }
   }
-  void carve_forward(Bump& b, int gc) {
+  void carve_forward(Bump& b, int gc, int n_kv = 0) {
     memb = md.arch == MGRIT_ARCH_CROSS ? b.take_bytes((size_t)Tm * d * esz) : nullptr;
+    kv_all = n_kv ? b.take_bytes((size_t)n_kv * Tm * 2 * d * esz) : nullptr;
     carve_forward_work(b, gc);
   }
   void carve_cache(Bump& b, int ncache) {
@@ -403,6 +405,18 @@ GemmArgs gemm_base(int n, int M, int N, int K, const void* A, long a_stride, Slo
   return g;
 }
 
+// K | V of the cross attention for n layers, from the shared memory or (MEM) each group's own
+int memory_kv(Engine& E, int n, Rows MEM, Params TH, void* out, Slots slots) {
+  const int d = E.d;
+  const Slots loc = {0, 1};
+  if (MEM.present()) HIPCHK(launch_cast_rows(n, (long)E.Tm * d, MEM, E.membG, (long)E.Tm * d, loc, E.bf16, E.st));
+  GemmArgs g = gemm_base(n, E.Tm, 2 * d, d, MEM.present() ? E.membG : E.memb, MEM.present() ? (long)E.Tm * d : 0, loc, TH,
+                         E.lay.offset[MGRIT_P_WKV_C], E.lay.offset[MGRIT_P_BKV_C]);
+  g.out = out; g.out_slot_stride = (long)E.Tm * 2 * d; g.out_slots = slots;
+  HIPCHK(launch_gemm(g, EPI_STORE, E.bf16, E.st));
+  return MGRIT_OK;
+}
+
 // One chunk (n <= Gc groups) of the forward layer step.  `cache`: write the linearisation
 // cache at `cslots` instead of advancing the state (stops before FFN2).
 // MEM (decoder of a stacked grid): group g's cross-attention memory is the fp32 rows MEM.at(g).
@@ -460,7 +474,8 @@ int forward_chunk(Engine& E, int n, Rows IN, Rows OUT, Rows RHS, Params TH, floa
 
   if (cross) {
     void* qc = cache ? E.c_qc : E.qc;
-    void* kvc = cache ? E.c_kvc : E.kvc;
+    void* kvc = E.kv_all ? E.kv_all : cache ? E.c_kvc : E.kvc;
+    const Slots kvs = E.kv_all ? Slots{(int)TH.i0, (int)TH.is} : cs;
     void* oc = cache ? E.c_oc : E.o;
     ln.X = IN; ln.xp = x3; ln.xp_slot_stride = E.Td(); ln.xp_slots = cs;         // LN3(X + s)
     ln.gamma_off = L.offset[MGRIT_P_LN3_G]; ln.beta_off = L.offset[MGRIT_P_LN3_B];
@@ -469,18 +484,14 @@ int forward_chunk(Engine& E, int n, Rows IN, Rows OUT, Rows RHS, Params TH, floa
     g = gemm_base(n, T, d, d, u3, E.Td(), us, TH, L.offset[MGRIT_P_WQ_C], L.offset[MGRIT_P_BQ_C]);
     g.out = qc; g.out_slot_stride = E.Td(); g.out_slots = cs;
     HIPCHK(launch_gemm(g, EPI_STORE, E.bf16, E.st));
-    if (MEM.present()) HIPCHK(launch_cast_rows(n, (long)E.Tm * d, MEM, E.membG, (long)E.Tm * d, loc, E.bf16, E.st));
-    g = gemm_base(n, E.Tm, 2 * d, d, MEM.present() ? E.membG : E.memb, MEM.present() ? (long)E.Tm * d : 0, loc, TH,
-                  L.offset[MGRIT_P_WKV_C], L.offset[MGRIT_P_BKV_C]);
-    g.out = kvc; g.out_slot_stride = (long)E.Tm * 2 * d; g.out_slots = cs;
-    HIPCHK(launch_gemm(g, EPI_STORE, E.bf16, E.st));
+    if (!E.kv_all) STCHK(memory_kv(E, n, MEM, TH, kvc, kvs));
     memset(&at, 0, sizeof(at));
     at.n_groups = n; at.B = E.md.batch; at.H = E.H; at.dh = E.dh; at.Sq = E.md.seq; at.Sk = E.md.mem_seq;
     at.causal = 0;
     at.q = qc; at.q_row_stride = d; at.q_slot_stride = E.Td(); at.q_slots = cs;
     at.k = kvc; at.v = (char*)kvc + (size_t)d * esz;
     at.k_row_stride = at.v_row_stride = 2 * d;
-    at.k_slot_stride = at.v_slot_stride = (long)E.Tm * 2 * d; at.k_slots = cs;
+    at.k_slot_stride = at.v_slot_stride = (long)E.Tm * 2 * d; at.k_slots = kvs;
     at.o = oc; at.o_row_stride = d; at.o_slot_stride = E.Td(); at.o_slots = cs;
     if (cache) { at.lse = E.c_lsec; at.lse_slot_stride = (long)E.md.batch * E.H * E.md.seq; at.lse_slots = cs; }
     HIPCHK(launch_attn_fwd(at, E.bf16, E.st));
@@ -1249,6 +1260,16 @@ struct Driver {
   bool serial() const { return L == 1 || cf == 1; }
 };
 
+// Cross attention on a memory that all steps share: K | V of a layer depend on its parameters and the memory alone, and
+// an MGRIT solve evaluates a layer several times (184 evaluations of 32 layers with c_f = 4, two levels, two cycles), so
+// the forward solve forms them once per layer, in one launch over all of them (workspace of N x Tm x 2d operands, the size
+// of the states where Tm = T).  With Tm = T they are an eighth of a step's products: 512 wide, 4096 tokens of 64,
+// 13.69 -> 12.78 ms per solve.  A serial run evaluates a layer once; without the adjoint cache a caller has asked for
+// little memory; a workspace without room for them (forward_bytes) runs with them formed in every step.
+bool keeps_kv(const mgrit_model_desc* md, const mgrit_opts* op) {
+  return md->arch == MGRIT_ARCH_CROSS && !serial_run(op) && g_adjoint_cache;
+}
+
 struct Plan {                       // workspace of mgrit_forward / mgrit_adjoint
   Engine E, E2;
   bool two_lanes = false;
@@ -1263,8 +1284,9 @@ struct Plan {                       // workspace of mgrit_forward / mgrit_adjoin
 // share_ws, share_mode: a forward plan whose closing relaxation fills the linearisation cache of the
 // adjoint plan (mode 1 or 2) that will be laid out in share_ws: the cache is the first thing an adjoint
 // plan carves, so carving it again from the same base gives the same addresses.
+// keep_kv: a forward plan keeps the memory's K | V of every layer where that can pay (see keeps_kv).
 int make_plan(Plan& P, const mgrit_model_desc* md, const mgrit_opts* op, int mode, void* ws, hipStream_t st,
-              void* share_ws = nullptr, int share_mode = 0) {
+              void* share_ws = nullptr, int share_mode = 0, bool keep_kv = true) {
   const bool adjoint = mode != 0;
   Bump b(ws);
   Engine& E = P.E;
@@ -1277,11 +1299,12 @@ int make_plan(Plan& P, const mgrit_model_desc* md, const mgrit_opts* op, int mod
   if (gc > widest) gc = widest;
   E.keep_inputs = mode == 2;
   E.recompute = adjoint && !g_adjoint_cache;
-  if (adjoint) E.carve_adjoint(b, gc, N); else E.carve_forward(b, gc);
+  if (adjoint) E.carve_adjoint(b, gc, N); else E.carve_forward(b, gc, keep_kv && keeps_kv(md, op) ? N : 0);
   if (!adjoint && share_ws) {
     Bump shared(share_ws);
     E.keep_inputs = share_mode == 2;
     E.carve_cache(shared, N);
+    if (E.kv_all) E.kv_all = E.c_kvc;       // the adjoint wants the same values, under the same slots
     P.D.fill_cache = true;
   }
   P.two_lanes = widest >= 2 && make_lane(P.E2, E, b, adjoint, ws == nullptr);
@@ -1502,6 +1525,12 @@ int64_t mgrit_step_depth(const mgrit_opts* opts) {
 }  // extern "C"
 
 namespace {
+// What mgrit_forward needs at least (keep_kv = false) and at most
+size_t forward_bytes(const mgrit_model_desc* desc, const mgrit_opts* opts, bool keep_kv) {
+  Plan P;
+  return make_plan(P, desc, opts, 0, nullptr, nullptr, nullptr, 0, keep_kv) == MGRIT_OK ? P.bytes : 0;
+}
+
 // share_ws != null: the forward solve also fills the linearisation cache of the adjoint workspace share_ws
 int forward_impl(const mgrit_model_desc* desc, const mgrit_opts* opts, const void* Z0,
                  const void* const* theta, const void* memory, void* Z_all, float* resnorm, void* workspace,
@@ -1512,7 +1541,8 @@ int forward_impl(const mgrit_model_desc* desc, const mgrit_opts* opts, const voi
   if (!Z0 || !Z_all || !workspace) return MGRIT_INVALID_ARG;
   STCHK(check_ptr_array(theta, opts->N));
   if (desc->arch == MGRIT_ARCH_CROSS && !memory) return MGRIT_INVALID_ARG;
-  const size_t need = mgrit_workspace_bytes(desc, opts, 0);
+  const bool keep_kv = workspace_bytes >= mgrit_workspace_bytes(desc, opts, 0);
+  const size_t need = forward_bytes(desc, opts, keep_kv);
   if (need == 0) return MGRIT_INVALID_ARG;
   if (workspace_bytes < need) return MGRIT_WORKSPACE_TOO_SMALL;
   if (share_ws) {
@@ -1524,7 +1554,7 @@ int forward_impl(const mgrit_model_desc* desc, const mgrit_opts* opts, const voi
   hipStream_t st = static_cast<hipStream_t>(stream);
 
   Plan P;
-  STCHK(make_plan(P, desc, opts, 0, workspace, st, share_ws, share_mode));
+  STCHK(make_plan(P, desc, opts, 0, workspace, st, share_ws, share_mode, keep_kv));
   Engine& E = P.E;
   Driver& D = P.D;
   const int N = opts->N;
@@ -1533,6 +1563,8 @@ int forward_impl(const mgrit_model_desc* desc, const mgrit_opts* opts, const voi
   HIPCHK(upload_pointers(D.tabTh, theta, N, st));
   if (desc->arch == MGRIT_ARCH_CROSS)
     HIPCHK(launch_cast_flat(static_cast<const float*>(memory), E.memb, (long)E.Tm * E.d, E.bf16, st));
+  if (E.kv_all)
+    STCHK(memory_kv(E, N, NO_ROWS, Params{(const void* const*)D.tabTh, 0, 1}, E.kv_all, Slots{0, 1}));
   // initial values (Z0 may be row 0 of Z_all itself)
   if (Z0 != Z_all) HIPCHK(hipMemcpyAsync(Z_all, Z0, state, hipMemcpyDeviceToDevice, st));
   if (!serial_run(opts) && opts->init_guess == 0) {
@@ -2048,8 +2080,14 @@ static int forward_buffered_impl(const mgrit_model_desc* desc, const mgrit_opts*
   STCHK(validate_opts(opts));
   STCHK(validate_buffer(buf));
   if (!Z0 || !Z_all || !theta) return MGRIT_INVALID_ARG;
-  const size_t need = mgrit_buffered_workspace_bytes(desc, opts, buf, 0);
+  size_t need = forward_bytes(desc, opts, false);        // each segment takes of the workspace what it needs
   if (need == 0) return MGRIT_INVALID_ARG;
+  for (int n : {buf->n_open, buf->n_close}) {
+    if (n == 0) continue;
+    const mgrit_opts so = serial_opts(n, buf->h_buffer);
+    const size_t w = forward_bytes(desc, &so, false);
+    if (w > need) need = w;
+  }
   if (!workspace || workspace_bytes < need) return workspace ? MGRIT_WORKSPACE_TOO_SMALL : MGRIT_INVALID_ARG;
   BufferedRegions R;
   if (share_ws) {

@@ -1,7 +1,10 @@
 """Forms of a launch that a rule on its size chooses, at the edges of those rules: the walking form of the
 multiply-by-GELU' products (more than one 256x256 tile per compute unit) against 128x128 tiles, bit for bit; bf16
 attention at the edges of its 32-row units, 64-row tiles and rings of three tiles against the CPU oracle; many layers of
-few tokens in one launch against one layer per launch, bit for bit."""
+few tokens in one launch against one layer per launch, bit for bit; keys and values of the decoder's memory formed once
+per layer against formed in every step, bit for bit."""
+import ctypes as C
+
 import pytest
 import torch
 
@@ -83,3 +86,45 @@ def test_few_tokens_bits(arch, dtype, d, f, B, S, Sm, G, adjoint):
         mb.mgrit_set_lanes(2)
     for g in range(G):
         assert torch.isfinite(together[g]).all() and torch.equal(together[g], alone[g]), f"group {g}"
+
+
+@pytest.mark.parametrize("dtype,d,S,Sm,N,cf,levels,relax,lanes,mg", [
+    (wls.DTYPE_BF16, 128, 40, 24, 16, 4, 2, 1, 2, 0),
+    (wls.DTYPE_BF16, 128, 17, 65, 8, 2, 3, 0, 1, 0),
+    (wls.DTYPE_BF16, 256, 40, 1, 32, 4, 3, 1, 2, 3),
+    (wls.DTYPE_F32, 128, 24, 40, 8, 2, 2, 1, 2, 2),
+])
+def test_kept_memory_projections_bits(dtype, d, S, Sm, N, cf, levels, relax, lanes, mg):
+    wl = wls.Workload("t", wls.ARCH_CROSS, d, d // 64, 2 * d, 2, S, Sm, N, 0.5, cf, levels, 2, dtype, 93, relax=relax)
+    print(f"[case] kept memory projections dtype={dtype} d={d} S={S} Sm={Sm} N={N} cf={cf} L={levels}", flush=True)
+    dm = DeviceModel(wl, weight_std=0.05, keep_host=False)
+    opts, buf = mb.mgrit_opts(N, wl.h, cf, levels, 2, relax), mb.BufferOpts(0, 0, 0.0)
+    mem, Z0 = dev(wls.cross_memory(wl)), dev(wls.initial_state(wl))
+    mb.mgrit_set_lanes(lanes)
+    mb.mgrit_set_max_groups_per_launch(mg)
+    try:
+        room = mb.mgrit_workspace_bytes(dm.desc, opts, 0)
+        mb.mgrit_set_adjoint_cache(False)
+        least = mb.mgrit_workspace_bytes(dm.desc, opts, 0)
+        mb.mgrit_set_adjoint_cache(True)
+        outs = []
+        for size in (room, room - 256, least):
+            ws = torch.full((size // 4,), float("nan"), device="cuda").view(torch.uint8)
+            outs.append(mb.mgrit_forward(dm.desc, opts, Z0, dm.blocks, memory=mem, workspace=ws))
+            torch.cuda.synchronize()
+        Z, r = torch.empty_like(outs[0][0]), torch.empty_like(outs[0][1])         # a buffered run in the least space
+        assert mb.lib().mgrit_forward_buffered(C.byref(dm.desc), C.byref(opts), C.byref(buf), mb._ptr(Z0),
+                                               mb._ptr_array(dm.blocks), mb._ptr(mem), mb._ptr(Z), mb._ptr(r),
+                                               mb._ptr(ws), ws.numel(), mb._stream_handle(None)) == mb.MGRIT_OK
+        torch.cuda.synchronize()
+        outs.append((Z, r))
+        with pytest.raises(mb.MgritError) as e:
+            mb.mgrit_forward(dm.desc, opts, Z0, dm.blocks, memory=mem, workspace=ws[:-256])
+        assert e.value.status == mb.MGRIT_WORKSPACE_TOO_SMALL
+    finally:
+        mb.mgrit_set_adjoint_cache(True)
+        mb.mgrit_set_max_groups_per_launch(0)
+        mb.mgrit_set_lanes(2)
+    assert torch.isfinite(outs[0][0]).all() and torch.isfinite(outs[0][1]).all()
+    for Z, r in outs[1:]:
+        assert torch.equal(Z, outs[0][0]) and torch.equal(r, outs[0][1])
