@@ -17,6 +17,17 @@
 // dQ pass :  S^T, dP^T = V dO^T,  dA^T = P^T (dP^T - D),  dQ^T += K^T dA^T
 // dKV pass:  S = Q K^T, dP = dO V^T, P, dA;  dV^T += dO^T P,  dK^T += Q^T dA
 // No atomics: dQ and dK/dV are separate passes, so results are bit-reproducible.
+//
+// What bounds them: the chain of a wavefront, scores - exponentials - products, with three wavefronts per SIMD at most.  In
+// a step of 8 x 512 tokens, heads of 64, the vector unit issues for 56 % of the forward kernel (a 32 x 32 unit of scores
+// is 16 exponentials of 8 clocks and about 130 other instructions of 4) and the matrix cores work for 20 %; in the backward
+// passes 24-28 % and 20-23 %; with one head of 128 the matrix cores work for 42 / 52 / 38 % (forward, dQ, dK/dV).  Sequences
+// of 128 tokens and fewer wait for memory instead.  Hence tiles straight from memory to LDS in one
+// layout that serves the plain and the transposing reads (no transposed copy, no registers in between), and no scores for
+// halves of a tile that no pair is in.  Microseconds per launch, with tiles staged through registers and
+// transposed in LDS -> now, forward / whole backward: 5 layers of 8 x 512 causal, 12 heads of 64: 47 -> 45 / 142 -> 119;
+// 5 of 64 x 197, 6 of 64: 69 -> 63 / 230 -> 177; 5 of 32 x 128, 12 of 64: 29 -> 28 / 88 -> 70; 6 of 64 x 64, 8 of 64:
+// 25 -> 24 / 70 -> 48; 4 of 8 x 2048, one of 128: 95 -> 90 / 265 -> 256.
 #include <type_traits>
 
 #include "common.h"
@@ -179,11 +190,15 @@ __device__ __forceinline__ void store_rows_T(bf16* dst, long row_stride, int row
 // ---------------------------------------------------------------------------
 // forward
 // ---------------------------------------------------------------------------
-// Wavefronts per SIMD the register budget is set for: the accumulators grow with DH.
+// Wavefronts per SIMD the register budget is set for: the accumulators grow with DH.  d_head 64 holds three (168
+// registers); the dQ and dK/dV passes with both operands' fragments fetched ahead spill there and lose more than the
+// earlier reads gain (5 layers of 8 x 512: whole backward 119 -> 126 to 163 us).
 template <int DH, int NW> constexpr int fa_waves() { return DH == 64 && NW == 4 ? 3 : DH == 64 || NW == 8 ? 2 : NW / 2; }
 
-// LONG: more than two tile sets, where the pipelined loop pays; without it a fourth wavefront per SIMD fits at d_head 64,
-// which short sequences need more: they wait for memory.
+// LONG: more than two tile sets, where the pipelined loop pays (the next unit's scores are begun before this one's
+// exponentials, so that the matrix and the vector unit work at the same time); without it a fourth wavefront per SIMD fits
+// at d_head 64, which short sequences need more: they wait for memory.  The running maximum is exact: rescaling only
+// when it grew by more than a threshold is faster and loses 4 % of the output's precision.
 template <int NW, int DH, bool LONG>
 __global__ void __launch_bounds__(NW * 64, (DH == 64 && !LONG ? 4 : fa_waves<DH, NW>()))
 attn_fwd_mfma_kernel(const AttnArgs a) {
@@ -570,7 +585,8 @@ __global__ void __launch_bounds__(NW * 64, (fa_waves<DH, NW>())) attn_bwd_dkv_mf
 }
 
 // Sequences that fit one block (Sq, Sk <= 32 NW): both passes in one launch, the head's Q, K, V and dO in LDS as a
-// whole, read from memory once; nothing waits between the two passes but the exchange of D.
+// whole, read from memory once; nothing waits between the two passes but the exchange of D.  Two wavefronts per SIMD at
+// d_head 64: with three the dK/dV half spills.
 template <int NW, int DH>
 __global__ void __launch_bounds__(NW * 64, (DH == 64 ? 2 : 1)) attn_bwd_fused_mfma_kernel(const AttnArgs a) {
   using L = Lay<DH>;
@@ -657,12 +673,12 @@ bool attn_mfma_supported(const AttnArgs& a) {
          (a.v_row_stride % 8 == 0) && (a.o_row_stride % 8 == 0);
 }
 
-// Blocks of 256 rows halve the K/V (Q/dO) bytes staged from L2 per flop, which is what bounds these
-// kernels once a head no longer fits a block of 128.  Mask bits 0-2: forward, dQ pass, dK/dV pass at
-// d_head = 128, where these blocks also double-buffer their tiles (forward, dQ) or keep their V
-// fragments in LDS (dK/dV): they win from 129 tokens on; the two backward passes keep 128-row
-// blocks when the last 256-row block would be at most half full.  Bits 4-6: the same at d_head = 64
-// (from 512 tokens; measured slower, off).  Default: all three passes at d_head = 128.
+// Blocks of 256 rows halve the K/V (Q/dO) bytes staged from L2 per flop.  Mask bits 0-2: forward, dQ pass, dK/dV pass
+// at d_head = 128, from 129 tokens on; the two backward passes keep 128-row blocks when the last 256-row block would be at
+// most half full.  Bits 4-6: the same at d_head = 64 from 512 tokens on.  Milliseconds of a training step of 8 x 2048
+// tokens, one head of 128: all three 148.4; without the forward pass's 153.5, the dQ pass's 154.3, the dK/dV pass's 192.0,
+// any 204.2.  8 x 512 tokens, 12 heads of 64 (three wavefronts per SIMD in 128-row blocks, two in these): none 179.0,
+// forward 179.3, dQ 180.5, dK/dV 181.3, all 182.5.
 int g_attn_wide = 7;
 void attn_set_wide_blocks(int mask) { g_attn_wide = mask & 0x77; }
 template <int DH> static bool attn_wide(int pass, int seq) {

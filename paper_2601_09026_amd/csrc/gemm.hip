@@ -6,6 +6,8 @@
 // The kernels:
 //  * gemm_mfma    : bf16 operands, fp32 accumulate on the 32x32x16 MFMA of gfx950; operands
 //                   stream global -> LDS directly through a ring of k-tiles, see below.
+//  * gemm_mfma_dgelu_walk: the same with resident blocks that walk over the tiles of a multiply-by-GELU' launch.
+//  * gemm_tn_mfma, gemm_tn_f32: token-major products of the parameter gradients.
 //  * gemm_f32_mfma: fp32 operands on the 32x32x2 fp32 MFMA; gemm_f32_small: small and ragged launches on the 16x16x4.
 //  * gemm_simple  : any operand type and shape, LDS-tiled FMA.
 #include <type_traits>
@@ -306,8 +308,8 @@ __device__ __forceinline__ void tile_epilogue(
 //  * RAGGED: N no multiple of BN or K no multiple of BK (both multiples of 8): weight rows are clamped,
 //    columns guarded, and the chunks of the last k-tile that lie past K come from a zero chunk.
 // What bounds it: large launches the matrix cores and then the epilogue, which moves 4 to 16 bytes per output
-// element with the matrix cores idle (in the step at the GPT-2 shape they are busy for 52 % of a 256x256 launch
-// with the plain store and for 37-44 % with the other epilogues: profiles/gpt2_small_fwd_adjoint_pmc_summary.txt);
+// element with the matrix cores idle (in the step at the GPT-2 shape they are busy for 56 % of a 256x256 launch
+// with the plain store and for 37-47 % with the other epilogues: profiles/gpt2_small_fwd_adjoint_pmc_summary.txt);
 // launches of up to one tile per CU the latency of first touches past the L2, which the deep ring covers.
 // ---------------------------------------------------------------------------
 // LDS has 64 four-byte banks (256 bytes per clock); a 16-byte read is served 16 lanes at a
@@ -1353,8 +1355,8 @@ static double gemm_bytes(const GemmArgs& a, double esz) {
 // Tile configurations of the MFMA kernel (k-tiles of 64) and what a round of each takes on MI355X, in
 // microseconds: fixed + per_ktile * (k-tiles).  A launch runs in rounds of (CUs x resident blocks) tiles
 // whose time hardly depends on how full the round is.  The epilogue is not in the model: for the tile it picks it is
-// 12 % off in the median and 69 % at worst (fp32 epilogues of reductions of 384), yet over 64 shapes its pick is 0.6 %
-// slower than the best tile on average and 8 % at worst (profiles/gemm_tile_round_times.txt):
+// 11 % off in the median and 66 % at worst (fp32 epilogues of reductions of 384), yet over 64 shapes its pick is 0.7 %
+// slower than the best tile on average and 16 % at worst (profiles/gemm_tile_round_times.txt):
 //  1: 256x256, 8 wavefronts of 128x64, two stages: most reuse, what large launches run on;
 //  3: 256x192, 8 wavefronts of 64x96, two stages: where 256 columns leave a round much emptier;
 //  4: 128x128, two stages, two blocks per CU (one block's epilogue under the other's k loop);
@@ -1459,11 +1461,11 @@ static hipError_t launch_tn(const GemmTnArgs& a, int splits, hipStream_t st) {
 }
 
 // Tile and number of token slices of a parameter-gradient product.  Microseconds of a round as in
-// kTileCfgs, 8 % off in the median over 384 to 4096 wide outputs of 2048 to 12608 tokens, the pick 1 % slower than
-// the best tile on average and 13 % at worst (profiles/gemm_tile_round_times.txt); the transposing reads deliver
-// half the bytes per clock of plain ones, so a k-tile takes longer than there.  Few output tiles and many tokens
-// (384 x 384 from 12608 tokens: 9 tiles of 128x128) are cut into slices of at least 8 k-tiles, which costs
-// writing and summing the slices' partial results.
+// kTileCfgs, 17 % off in the median over 384 to 4096 wide outputs of 2048 to 12608 tokens, the pick 0.8 % slower than
+// the best tile on average and 9 % at worst (profiles/gemm_tile_round_times.txt); a fragment takes two transposing
+// 8-byte reads here instead of one of 16, so a k-tile takes longer than there.  Few output tiles and many tokens (384 x 384
+// from 12608 tokens: 9 tiles of 128x128) are cut into slices of at least 8 k-tiles, which costs writing and summing the
+// slices' partial results.
 // Slices change the order of the sums, so their number follows from the layer's sizes alone, as the best one for a
 // launch of TN_GROUPS layers (the usual chunk): a gradient does not depend on how many layers share its launch.  The
 // tile may follow from the launch: every tile adds a slice's tokens in the same order.
