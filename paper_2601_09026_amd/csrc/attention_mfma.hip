@@ -688,12 +688,15 @@ template <int DH> static bool attn_wide(int pass, int seq) {
   return pass == 0 || tail == 0 || tail > 128;
 }
 
-// Launch with a ring of as many tile sets as `seq` rows make, three at most.
+// Launch with a ring of as many tile sets as `seq` rows make, three at most.  fixed: bytes of LDS that the kernel
+// declares itself; a block of more than 64 KB in all needs the limit of its dynamic part raised (two sets at d_head 128
+// are 64 KB: the dK/dV kernel's rows come on top).
 template <int DH, typename Kernel>
-static hipError_t launch_ring(Kernel kern, int block_rows, int own_rows, int seq, const AttnArgs& a, hipStream_t st) {
+static hipError_t launch_ring(Kernel kern, int block_rows, int own_rows, int seq, const AttnArgs& a, hipStream_t st,
+                              size_t fixed = 0) {
   const int sets = (seq + 63) / 64, slots = sets < RING ? sets : RING;
   const size_t smem = (size_t)slots * 2 * Lay<DH>::TILE;
-  if (smem > 65536) {
+  if (smem + fixed > 65536) {
     const hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(kern),
                                              hipFuncAttributeMaxDynamicSharedMemorySize, (int)smem);
     if (e != hipSuccess) return e;
@@ -732,9 +735,10 @@ static hipError_t attn_bwd_mfma_dh(const AttnArgs& a, hipStream_t st) {
   else if (attn_wide<DH>(1, a.Sq)) e = launch_ring<DH>(attn_bwd_dq_mfma_kernel<8, DH>, 256, a.Sq, a.Sk, a, st);
   else e = launch_ring<DH>(attn_bwd_dq_mfma_kernel<4, DH>, 128, a.Sq, a.Sk, a, st);
   if (e != hipSuccess || !a.dk) return e;        // only dQ wanted (cross-attention: dK, dV feed the memory gradient)
-  if (a.Sk <= 64) return launch_ring<DH>(attn_bwd_dkv_mfma_kernel<2, DH>, 64, a.Sk, a.Sq, a, st);
-  if (attn_wide<DH>(2, a.Sk)) return launch_ring<DH>(attn_bwd_dkv_mfma_kernel<8, DH>, 256, a.Sk, a.Sq, a, st);
-  return launch_ring<DH>(attn_bwd_dkv_mfma_kernel<4, DH>, 128, a.Sk, a.Sq, a, st);
+  constexpr size_t rows = sizeof(float) * RING * 2 * 64;   // the kernel's own
+  if (a.Sk <= 64) return launch_ring<DH>(attn_bwd_dkv_mfma_kernel<2, DH>, 64, a.Sk, a.Sq, a, st, rows);
+  if (attn_wide<DH>(2, a.Sk)) return launch_ring<DH>(attn_bwd_dkv_mfma_kernel<8, DH>, 256, a.Sk, a.Sq, a, st, rows);
+  return launch_ring<DH>(attn_bwd_dkv_mfma_kernel<4, DH>, 128, a.Sk, a.Sq, a, st, rows);
 }
 
 hipError_t attn_bwd_mfma(const AttnArgs& a, hipStream_t st) {

@@ -13,6 +13,7 @@ from paper_2601_09026_amd import workloads as wls
 
 from gpu_util import DeviceModel, dev
 from test_gpu_layer_step import make, run_adjoint_case, run_forward_case
+from test_gpu_param_grads import run_case
 
 pytestmark = pytest.mark.gpu
 
@@ -64,6 +65,17 @@ def test_attention_edges_bf16(arch, dh, S, Sm):
     wl = make(arch, wls.DTYPE_BF16, d=2 * dh, H=2, f=128, B=1, S=S, Sm=Sm)
     run_forward_case(wl, G=1, hstep=0.5, with_rhs=False, weight_std=0.1, force_simple=0)
     run_adjoint_case(wl, G=1, hstep=0.5, with_rhs=False, weight_std=0.1, force_simple=0)
+
+
+@pytest.mark.parametrize("dh", [64, 128])
+@pytest.mark.parametrize("S,Sm", [
+    (40, 200),          # dK/dV pass over one tile set of queries
+    (65, 129), (128, 300),                     # over two: 64 KB of tiles at d_head 128, and the rows' scalars beside them
+    (200, 40),          # 64-row blocks of keys over a ring of three sets
+])
+def test_cross_gradients_unequal_lengths(dh, S, Sm):
+    wl = wls.Workload("cross", wls.ARCH_CROSS, 2 * dh, 2, 128, 2, S, Sm, 2, 0.5, 2, 1, 1, wls.DTYPE_BF16, 71)
+    run_case(wl, weight_std=0.1)
 
 
 @pytest.mark.parametrize("adjoint", [False, True])
