@@ -131,11 +131,14 @@ __device__ __forceinline__ float half_sum(float x) {
   const auto r = __builtin_amdgcn_permlane32_swap(__float_as_uint(x), __float_as_uint(x), false, false);
   return __uint_as_float(r[0]) + __uint_as_float(r[1]);
 }
-// Ring of tile sets (64 rows of two operands each) in dynamic LDS: set `it` lives in slot it % 3.  Two sets are on their
-// way while one is in use: turn(it) waits for this wavefront's own loads of set `it` by count, and from its barrier
-// on the set is complete and nobody reads set it-1 any more, whose slot set it+2 then takes.  Heads of one or two
-// sets never come round and are launched with that many slots (launch_ring()).
-constexpr int RING = 3;
+// Ring of tile sets (64 rows of two operands each) in dynamic LDS, waited for by count: ring_turn() leaves PER_SET of
+// this wavefront's loads in flight (`more`) or none, and from its barrier on the set before those is complete.
+//  * The pipelined forward loop needs set it+1 while it works on set it: three slots (set `it` in slot it % 3).  It turns
+//    to set it+1 with nothing left in flight, and set it+2 then takes the slot of set it-1, which nobody reads any more.
+//  * All other loops use a set at a time: two slots, set it+1 on its way meanwhile, and a barrier behind the last read of
+//    a slot before it is filled again; or one slot, where more blocks per compute unit hide the wait better.
+// Heads of fewer sets are launched with that many slots and never come round (launch_ring()).
+constexpr int RING = 3;                                  // of the pipelined loop
 template <int PER_SET> __device__ __forceinline__ void ring_turn(bool more) {
   asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
   if (more) wait_vmcnt<PER_SET>();
@@ -195,13 +198,14 @@ __device__ __forceinline__ void store_rows_T(bf16* dst, long row_stride, int row
 // earlier reads gain (5 layers of 8 x 512: whole backward 119 -> 126 to 163 us).
 template <int DH, int NW> constexpr int fa_waves() { return DH == 64 && NW == 4 ? 3 : DH == 64 || NW == 8 ? 2 : NW / 2; }
 
-// LONG: more than two tile sets, where the pipelined loop pays (the next unit's scores are begun before this one's
-// exponentials, so that the matrix and the vector unit work at the same time); without it a fourth wavefront per SIMD fits
-// at d_head 64, which short sequences need more: they wait for memory.  The running maximum is exact: rescaling only
-// when it grew by more than a threshold is faster and loses 4 % of the output's precision.
+// LONG: the pipelined loop over a ring of three sets (the next unit's scores are begun before this one's exponentials, so
+// that the matrix and the vector unit work at the same time); without it a fourth wavefront per SIMD fits at d_head 64 and
+// one or two sets do (`slots`).  Same operations on the same numbers in the same order: which of the two runs may
+// follow from the launch (attn_fwd_mfma_dh()).  The running maximum is exact: rescaling only when it grew by more than a
+// threshold is faster and loses 4 % of the output's precision.
 template <int NW, int DH, bool LONG>
 __global__ void __launch_bounds__(NW * 64, (DH == 64 && !LONG ? 4 : fa_waves<DH, NW>()))
-attn_fwd_mfma_kernel(const AttnArgs a) {
+attn_fwd_mfma_kernel(const AttnArgs a, int slots) {
   using L = Lay<DH>;
   constexpr int KS = DH / 16, DT = DH / 32;
   extern __shared__ __attribute__((aligned(1024))) unsigned char smem[];         // ring of K and V tiles
@@ -221,17 +225,25 @@ attn_fwd_mfma_kernel(const AttnArgs a) {
     sk.issue(smem + slot * 2 * L::TILE, P.K, it * 64, a.Sk);
     sv.issue(smem + slot * 2 * L::TILE + L::TILE, P.V, it * 64, a.Sk);
   };
+  auto refill = [&](int slot, int it) {                  // once the block has read it
+    asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
+    bare_barrier();
+    stage(slot, it);
+  };
   stage(0, 0);
-  if (n_blk > 1) stage(1, 1);
+  if (LONG && n_blk > 1) stage(1, 1);
+  __builtin_amdgcn_sched_barrier(0);                     // (else own rows before set 1: their wait leaves it in flight)
   bf16x8 qf[KS];
 #pragma unroll
   for (int ks = 0; ks < KS; ++ks)
     qf[ks] = *reinterpret_cast<const bf16x8*>(P.Q + (long)qc * a.q_row_stride + 16 * ks + 8 * lh);
+  __builtin_amdgcn_sched_barrier(0);
+  if (!LONG && n_blk > 1 && slots > 1) stage(1, 1);
   const Frags<DH> fr(lane);
   const lds_byte* lds = (const lds_byte*)smem;
   const float c = rsqrtf((float)DH) * LOG2E;
   const int limit = (a.causal ? min(qi, a.Sk - 1) : a.Sk - 1) - 4 * lh;   // last key of this lane's query
-  float m = -INFINITY, l = 0.f;
+  float m = -INFINITY, m_before = -INFINITY, l = 0.f;    // running maximum, the same without the unit at hand, denominator
   f32x16 o[DT];
 #pragma unroll
   for (int dt = 0; dt < DT; ++dt) o[dt] = splat16(0.f);
@@ -249,6 +261,7 @@ attn_fwd_mfma_kernel(const AttnArgs a) {
 #pragma unroll
     for (int i = 2; i < 16; ++i) x = fmaxf(x, s[i]);
     const float mn = fmaxf(m, half_max(x) * c);
+    if (LONG) m_before = m;
     ms = mn == -INFINITY ? 0.f : mn;                     // fully masked so far: keep exp2 finite
     corr = exp2_raw(m - ms);
     m = mn;
@@ -306,7 +319,7 @@ attn_fwd_mfma_kernel(const AttnArgs a) {
   const int whole = a.causal ? min(w_end, q_first) >> 5 : w_end >> 5;
   const int fast = LONG && whole > 2 ? (whole - 1) >> 1 : 0;
   int slot = 0, it = 0;
-  ring_turn<2 * Stager<NW, DH>::N>(n_blk > 1);           // set 0
+  if (LONG) ring_turn<2 * Stager<NW, DH>::N>(n_blk > 1);           // set 0
   if (LONG && fast > 0) {
     f32x16 sa = splat16(0.f), sb;
 #pragma unroll
@@ -324,14 +337,16 @@ attn_fwd_mfma_kernel(const AttnArgs a) {
       step(std::integral_constant<int, 1>{}, sb, sa);
       slot = next;
     }
-    l *= corr;                                           // the next unit is formed once more below
-#pragma unroll
-    for (int dt = 0; dt < DT; ++dt) o[dt] *= corr;
+    m = m_before;                                        // the next unit is formed once more below
   }
   for (; it < n_blk; ++it) {
-    const int next = slot == RING - 1 ? 0 : slot + 1;
-    if (it + 1 < n_blk) ring_turn<0>(false);
-    if (it + 2 < n_blk) stage(next == RING - 1 ? 0 : next + 1, it + 2);
+    const int next = slot == (LONG ? RING : slots) - 1 ? 0 : slot + 1;
+    if (LONG) {                                          // (in step with wavefronts that are still in the loop above)
+      if (it + 1 < n_blk) ring_turn<0>(false);
+      if (it + 2 < n_blk) stage(next == RING - 1 ? 0 : next + 1, it + 2);
+    } else {
+      ring_turn<2 * Stager<NW, DH>::N>(slots > 1 && it + 1 < n_blk);
+    }
     const lds_byte* K = lds + slot * 2 * L::TILE;
     for (int rt = 0; rt < 2; ++rt) {
       const int k0 = it * 64 + 32 * rt;
@@ -363,6 +378,7 @@ attn_fwd_mfma_kernel(const AttnArgs a) {
         for (int dt = 0; dt < DT; ++dt) o[dt] = MFMA(fr.cols(Vh, 0, t2, dt), pb, o[dt]);
       }
     }
+    if (!LONG && it + slots < n_blk) refill(slot, it + slots);
     slot = next;
   }
   l = half_sum(l);
@@ -476,6 +492,11 @@ __global__ void __launch_bounds__(NW * 64, (fa_waves<DH, NW>())) attn_bwd_dq_mfm
     sk.issue(smem + slot * 2 * L::TILE, P.K, it * 64, a.Sk);
     sv.issue(smem + slot * 2 * L::TILE + L::TILE, P.V, it * 64, a.Sk);
   };
+  auto refill = [&](int slot, int it) {                  // once the block has read it
+    asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
+    bare_barrier();
+    stage(slot, it);
+  };
   stage(0, 0);
   if (n_blk > 1) stage(1, 1);
   bf16x8 qf[KS], dof[KS];
@@ -496,7 +517,6 @@ __global__ void __launch_bounds__(NW * 64, (fa_waves<DH, NW>())) attn_bwd_dq_mfm
   int slot = 0;
   for (int it = 0; it < n_blk; ++it) {
     ring_turn<2 * Stager<NW, DH>::N>(it + 1 < n_blk);
-    if (it + 2 < n_blk) stage(slot == 0 ? 2 : slot - 1, it + 2);
     const lds_byte* K = lds + slot * 2 * L::TILE;
 #pragma unroll
     for (int kt = 0; kt < 2; ++kt) {
@@ -505,7 +525,8 @@ __global__ void __launch_bounds__(NW * 64, (fa_waves<DH, NW>())) attn_bwd_dq_mfm
         bwd_dq_half<DH>(fr, K, K + L::TILE, kt, qf, dof, c, lse2, -D, k0 + 32 > a.Sk || (a.causal && k0 + 31 > q_first),
                         limit - k0, dq);
     }
-    slot = slot == RING - 1 ? 0 : slot + 1;
+    if (it + 2 < n_blk) refill(slot, it + 2);
+    slot ^= 1;
   }
   if (qi < a.Sq) {
     if (lh == 0) P.D[qi] = D;                            // (not earlier: the first tile's wait would cover the store)
@@ -518,7 +539,7 @@ __global__ void __launch_bounds__(NW * 64, (fa_waves<DH, NW>())) attn_bwd_dkv_mf
   using L = Lay<DH>;
   constexpr int KS = DH / 16, DT = DH / 32;
   extern __shared__ __attribute__((aligned(1024))) unsigned char smem[];         // ring of Q and dO tiles
-  __shared__ __attribute__((aligned(16))) float rows[RING][2][64];               // -lse / scale and -D of their queries
+  __shared__ __attribute__((aligned(16))) float rows[2][2][64];               // -lse / scale and -D of their queries
   const BlockTask bt = block_task(a.causal, false);
   const int g = bt.g;
   const int b = bt.bh / a.H, h = bt.bh - b * a.H;
@@ -537,6 +558,11 @@ __global__ void __launch_bounds__(NW * 64, (fa_waves<DH, NW>())) attn_bwd_dkv_mf
   auto stage = [&](int slot, int it) {
     sq.issue(smem + slot * 2 * L::TILE, P.Q, it * 64, a.Sq);
     so.issue(smem + slot * 2 * L::TILE + L::TILE, P.dO, it * 64, a.Sq);
+  };
+  auto refill = [&](int slot, int it) {                  // once the block has read it
+    asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
+    bare_barrier();
+    stage(slot, it);
   };
   float st_s = 0.f, st_d = 0.f;                          // on their way to `rows` (first wavefront)
   auto fetch_rows = [&](int it) {
@@ -560,12 +586,8 @@ __global__ void __launch_bounds__(NW * 64, (fa_waves<DH, NW>())) attn_bwd_dkv_mf
   int slot = 0;
   for (int it = it0; it < n_blk; ++it) {
     ring_turn<2 * Stager<NW, DH>::N>(it + 1 < n_blk);
-    const int next = slot == RING - 1 ? 0 : slot + 1;
-    if (wave == 0 && it + 1 < n_blk) publish(next);      // before the barrier that opens set it+1
-    if (it + 2 < n_blk) {
-      stage(slot == 0 ? 2 : slot - 1, it + 2);
-      if (wave == 0) fetch_rows(it + 2);
-    }
+    if (wave == 0 && it + 1 < n_blk) publish(slot ^ 1);  // before the barrier that opens set it+1
+    if (wave == 0 && it + 2 < n_blk) fetch_rows(it + 2);
     const lds_byte* Q = lds + slot * 2 * L::TILE;
 #pragma unroll
     for (int qt = 0; qt < 2; ++qt) {
@@ -575,7 +597,8 @@ __global__ void __launch_bounds__(NW * 64, (fa_waves<DH, NW>())) attn_bwd_dkv_mf
         bwd_dkv_half<DH>(fr, Q, Q + L::TILE, qt, rows[slot][0], rows[slot][1], kf, vf, c, a.causal && i0 < k_first + 31,
                          kj - i0 - 4 * lh, lh, dk, dv);
     }
-    slot = next;
+    if (it + 2 < n_blk) refill(slot, it + 2);
+    slot ^= 1;
   }
   if (kj < a.Sk) {
     const long kv_rs = a.dkv_row_stride ? a.dkv_row_stride : a.dqkv_row_stride;
@@ -688,33 +711,51 @@ template <int DH> static bool attn_wide(int pass, int seq) {
   return pass == 0 || tail == 0 || tail > 128;
 }
 
-// Launch with a ring of as many tile sets as `seq` rows make, three at most.  fixed: bytes of LDS that the kernel
+// Launch with a ring of as many tile sets as `seq` rows make, `most` at most.  fixed: bytes of LDS that the kernel
 // declares itself; a block of more than 64 KB in all needs the limit of its dynamic part raised (two sets at d_head 128
 // are 64 KB: the dK/dV kernel's rows come on top).
 template <int DH, typename Kernel>
 static hipError_t launch_ring(Kernel kern, int block_rows, int own_rows, int seq, const AttnArgs& a, hipStream_t st,
-                              size_t fixed = 0) {
-  const int sets = (seq + 63) / 64, slots = sets < RING ? sets : RING;
+                              int most, size_t fixed = 0) {
+  const int sets = (seq + 63) / 64, slots = sets < most ? sets : most;
   const size_t smem = (size_t)slots * 2 * Lay<DH>::TILE;
   if (smem + fixed > 65536) {
     const hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(kern),
                                              hipFuncAttributeMaxDynamicSharedMemorySize, (int)smem);
     if (e != hipSuccess) return e;
   }
-  hipLaunchKernelGGL(kern, dim3((own_rows + block_rows - 1) / block_rows, a.B * a.H, a.n_groups), dim3(2 * block_rows),
-                     smem, st, a);
+  const dim3 grid((own_rows + block_rows - 1) / block_rows, a.B * a.H, a.n_groups), block(2 * block_rows);
+  if constexpr (std::is_invocable_v<Kernel, AttnArgs, int>) hipLaunchKernelGGL(kern, grid, block, smem, st, a, slots);
+  else hipLaunchKernelGGL(kern, grid, block, smem, st, a);
   return hipGetLastError();
 }
 
 template <int DH>
 static hipError_t attn_fwd_mfma_dh(const AttnArgs& a, hipStream_t st) {
   if (a.Sq <= 0 || a.Sk <= 0) return hipErrorInvalidValue;
-  const bool longer = a.Sk > 128;
-  if (a.Sq <= 64) return launch_ring<DH>(longer ? attn_fwd_mfma_kernel<2, DH, true> : attn_fwd_mfma_kernel<2, DH, false>,
-                                         64, a.Sq, a.Sk, a, st);
-  if (attn_wide<DH>(0, a.Sq)) return launch_ring<DH>(attn_fwd_mfma_kernel<8, DH, true>, 256, a.Sq, a.Sk, a, st);
-  return launch_ring<DH>(longer ? attn_fwd_mfma_kernel<4, DH, true> : attn_fwd_mfma_kernel<4, DH, false>, 128, a.Sq, a.Sk,
-                         a, st);
+  if (attn_wide<DH>(0, a.Sq)) return launch_ring<DH>(attn_fwd_mfma_kernel<8, DH, true>, 256, a.Sq, a.Sk, a, st, RING);
+  const int rows = a.Sq <= 64 ? 64 : 128;
+  const long blocks = (long)((a.Sq + rows - 1) / rows) * a.B * a.H * a.n_groups;
+  // How many sets a block gets decides how many blocks a compute unit holds (160 KB of LDS).  The pipelined loop hides the
+  // chain of a block by itself and pays as long as all blocks run at once: 1024 keys, 64 queries, blocks of the launch
+  // 256 / 512 / 1024, microseconds with one set -> three: d_head 64 27 -> 18, 32 -> 27, 49 -> 61; d_head 128 45 -> 36,
+  // 63 -> 70, 115 -> 143.  Beyond that, one set: other blocks hide the waits.  Exceptions: 128 queries at d_head 64
+  // have enough wavefronts in three blocks, and from about 450 keys on the pipelined loop is ahead there again (4096
+  // blocks: 512 causal 74 -> 76 us, 512 not causal 103 -> 99, 2048 100 -> 95); d_head 128 with a few blocks more than fit
+  // (512: 63 -> 59) or long memories keeps two.  Up to 128 keys, the whole head in two sets where that does not cost
+  // blocks, or where a head is read from memory once (32 x 128 tokens, 12 heads, 5 layers: 27.5 -> 26.2; causal 27.6 with two,
+  // 26.0 with one).
+  auto at_once = [&](int sets) { return blocks <= compute_units() * (163840L / (sets * 2 * Lay<DH>::TILE)); };
+  int sets;
+  if (a.Sk <= 128) sets = at_once(2) || (DH == 64 && !a.causal && a.Sq <= 128) ? 2 : 1;
+  else if (at_once(RING) || (DH == 64 && rows == 128 && (a.causal ? (a.Sk + 128) / 2 : a.Sk) > 448)) sets = RING;
+  else sets = DH == 128 && (at_once(2) || (rows == 128 && a.Sk >= 512)) ? 2 : 1;
+  const bool pipelined = sets == RING;
+  if (rows == 64)
+    return launch_ring<DH>(pipelined ? attn_fwd_mfma_kernel<2, DH, true> : attn_fwd_mfma_kernel<2, DH, false>, 64, a.Sq, a.Sk,
+                           a, st, sets);
+  return launch_ring<DH>(pipelined ? attn_fwd_mfma_kernel<4, DH, true> : attn_fwd_mfma_kernel<4, DH, false>, 128, a.Sq, a.Sk,
+                         a, st, sets);
 }
 
 hipError_t attn_fwd_mfma(const AttnArgs& a, hipStream_t st) {
@@ -730,15 +771,17 @@ static hipError_t attn_bwd_mfma_dh(const AttnArgs& a, hipStream_t st) {
     else hipLaunchKernelGGL((attn_bwd_fused_mfma_kernel<4, DH>), grid, dim3(256), 0, st, a);
     return hipGetLastError();
   }
+  // Two sets: a third one gains nothing for a block (within 2 % at 64 to 2048 rows) and costs a resident block: 64 queries on
+  // 192 keys, 1024 blocks, dQ pass 17.7 us with two, 20.4 with three at d_head 64; 19.1 and 25.3 at 128 (512 blocks).
   hipError_t e;
-  if (a.Sq <= 64) e = launch_ring<DH>(attn_bwd_dq_mfma_kernel<2, DH>, 64, a.Sq, a.Sk, a, st);
-  else if (attn_wide<DH>(1, a.Sq)) e = launch_ring<DH>(attn_bwd_dq_mfma_kernel<8, DH>, 256, a.Sq, a.Sk, a, st);
-  else e = launch_ring<DH>(attn_bwd_dq_mfma_kernel<4, DH>, 128, a.Sq, a.Sk, a, st);
+  if (a.Sq <= 64) e = launch_ring<DH>(attn_bwd_dq_mfma_kernel<2, DH>, 64, a.Sq, a.Sk, a, st, 2);
+  else if (attn_wide<DH>(1, a.Sq)) e = launch_ring<DH>(attn_bwd_dq_mfma_kernel<8, DH>, 256, a.Sq, a.Sk, a, st, 2);
+  else e = launch_ring<DH>(attn_bwd_dq_mfma_kernel<4, DH>, 128, a.Sq, a.Sk, a, st, 2);
   if (e != hipSuccess || !a.dk) return e;        // only dQ wanted (cross-attention: dK, dV feed the memory gradient)
-  constexpr size_t rows = sizeof(float) * RING * 2 * 64;   // the kernel's own
-  if (a.Sk <= 64) return launch_ring<DH>(attn_bwd_dkv_mfma_kernel<2, DH>, 64, a.Sk, a.Sq, a, st, rows);
-  if (attn_wide<DH>(2, a.Sk)) return launch_ring<DH>(attn_bwd_dkv_mfma_kernel<8, DH>, 256, a.Sk, a.Sq, a, st, rows);
-  return launch_ring<DH>(attn_bwd_dkv_mfma_kernel<4, DH>, 128, a.Sk, a.Sq, a, st, rows);
+  constexpr size_t rows = sizeof(float) * 2 * 2 * 64;      // the kernel's own
+  if (a.Sk <= 64) return launch_ring<DH>(attn_bwd_dkv_mfma_kernel<2, DH>, 64, a.Sk, a.Sq, a, st, 2, rows);
+  if (attn_wide<DH>(2, a.Sk)) return launch_ring<DH>(attn_bwd_dkv_mfma_kernel<8, DH>, 256, a.Sk, a.Sq, a, st, 2, rows);
+  return launch_ring<DH>(attn_bwd_dkv_mfma_kernel<4, DH>, 128, a.Sk, a.Sq, a, st, 2, rows);
 }
 
 hipError_t attn_bwd_mfma(const AttnArgs& a, hipStream_t st) {

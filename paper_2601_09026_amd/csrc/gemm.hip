@@ -1246,7 +1246,7 @@ void gemm_set_tile_config(int cfg) { g_tile_cfg = cfg; }
 void gemm_set_grad_slices(int n) { g_grad_slices = n > 0 ? n : 0; }
 
 // Compute units of the current device (256 if the query fails).
-static int compute_units() {
+int compute_units() {
   static int n = 0;
   if (n == 0) {
     int dev = 0, cus = 0;

@@ -12,6 +12,7 @@ void gemm_force_simple(int on);
 void gemm_set_tile_config(int cfg);
 void gemm_set_grad_slices(int n);
 double gemm_model_cost(int n_groups, int M, int N, int K);
+int compute_units();                                        // of the current device
 void attn_set_wide_blocks(int mask);
 
 // ---- rowwise.hip -------------------------------------------------------------

@@ -67,11 +67,38 @@ def test_attention_edges_bf16(arch, dh, S, Sm):
     run_adjoint_case(wl, G=1, hstep=0.5, with_rhs=False, weight_std=0.1, force_simple=0)
 
 
+@pytest.mark.parametrize("dh,arch,B,S,Sm,counts", [
+    (64, wls.ARCH_ENCODER, 8, 300, 0, (1, 4, 5)),        # 192 blocks of 128 queries a layer: pipelined up to 768 of them
+    (64, wls.ARCH_CAUSAL, 8, 300, 0, (4, 5)),
+    (64, wls.ARCH_CROSS, 16, 40, 200, (1, 6, 7)),        # 128 blocks of 64 queries
+    (128, wls.ARCH_CROSS, 16, 64, 330, (4, 5, 9)),       # 64 blocks: three sets up to 256, two up to 512, then one
+    (128, wls.ARCH_CROSS, 16, 100, 190, (4, 8, 9)),
+])
+def test_attention_ring_bits(dh, arch, B, S, Sm, counts):
+    """How many tile sets a block of attention gets follows from the launch and must not show in the result."""
+    wl = make(arch, wls.DTYPE_BF16, d=512, H=512 // dh, f=64, B=B, S=S, Sm=Sm)
+    print(f"[case] attention rings dh={dh} arch={arch} B={B} S={S} Sm={Sm}", flush=True)
+    G = max(counts)
+    dm = DeviceModel(wl, n_layers=G, weight_std=0.08, keep_host=False)
+    out = {}
+    mb.mgrit_set_lanes(1)
+    try:
+        for n in counts:
+            mb.mgrit_set_max_groups_per_launch(n)
+            out[n] = step(dm, wl, False, G) + step(dm, wl, True, G)
+    finally:
+        mb.mgrit_set_max_groups_per_launch(0)
+        mb.mgrit_set_lanes(2)
+    for n in counts[1:]:
+        for g, (x, y) in enumerate(zip(out[counts[0]], out[n])):
+            assert torch.isfinite(x).all() and torch.equal(x, y), f"{n} layers a launch, state {g}"
+
+
 @pytest.mark.parametrize("dh", [64, 128])
 @pytest.mark.parametrize("S,Sm", [
     (40, 200),          # dK/dV pass over one tile set of queries
     (65, 129), (128, 300),                     # over two: 64 KB of tiles at d_head 128, and the rows' scalars beside them
-    (200, 40),          # 64-row blocks of keys over a ring of three sets
+    (200, 40), (400, 50),                      # 64-row blocks of keys, a ring that comes round
 ])
 def test_cross_gradients_unequal_lengths(dh, S, Sm):
     wl = wls.Workload("cross", wls.ARCH_CROSS, 2 * dh, 2, 128, 2, S, Sm, 2, 0.5, 2, 1, 1, wls.DTYPE_BF16, 71)
