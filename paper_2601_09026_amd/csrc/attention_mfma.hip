@@ -51,31 +51,36 @@ template <int DH> struct Lay {
   }
 };
 
+// Keeps a value where it is computed: the optimiser moves arithmetic out of loops and past branches otherwise.
+template <typename T> __device__ __forceinline__ void pin(T& v) { asm volatile("" : "+v"(v)); }
+
 // Loads of NW wavefronts for 64 rows from row `row0` on (rows past the end repeat the last one).
-template <int NW, int DH> struct Stager {
+// AGAIN: the lane's offsets are formed at each use instead of kept in 3 registers per load, for the dK/dV pass at d_head
+// 128: its accumulators and own rows take 192 of 256 registers, and with the offsets kept 13 or 20 went to scratch (whole
+// backward, 4 layers of 8 x 2048, one head: 246 -> 221 us, causal 209 -> 183; 5 of 16 x 300, 6 heads: 178 -> 150).
+template <int NW, int DH, bool AGAIN = false> struct Stager {
   using L = Lay<DH>;
   static constexpr int N = L::TILE / 1024 / NW;          // load instructions per wavefront and tile
   static_assert(N >= 1, "one load or more per wavefront");
-  int wave, row[N], chunk[N], off[N];                    // chunk, off: in bytes; off: inside a whole tile
+  int wave, lane;
   int rs;                                                // bytes per row of the source
-  __device__ __forceinline__ Stager(long row_stride, int wave_, int lane) : wave(wave_), rs((int)row_stride * 2) {
-#pragma unroll
-    for (int j = 0; j < N; ++j) {
-      row[j] = (wave * N + j) * L::RPI + lane / L::CPR;
-      chunk[j] = ((lane % L::CPR) ^ L::swz(row[j])) * 16;
-      off[j] = row[j] * rs + chunk[j];
-    }
-  }
+  __device__ __forceinline__ Stager(long row_stride, int wave_, int lane_)
+      : wave(wave_), lane(lane_), rs((int)row_stride * 2) {}
   __device__ __forceinline__ void issue(unsigned char* dst, const bf16* src, int row0, int nrows) const {
     const auto base = lds_source(reinterpret_cast<const char*>(src) + (long)row0 * rs);
     const int left = nrows - 1 - row0;
+    int l = lane;
+    if constexpr (AGAIN) pin(l);
+    auto load = [&](int j, bool whole) {
+      const int r = (wave * N + j) * L::RPI + l / L::CPR, chunk = ((l % L::CPR) ^ L::swz(r)) * 16;
+      load_to_lds(base, dst + (wave * N + j) * 1024, (whole || r < left ? r : left) * rs + chunk, 0);
+    };
     if (left >= 63) {                                    // block-uniform
 #pragma unroll
-      for (int j = 0; j < N; ++j) load_to_lds(base, dst + (wave * N + j) * 1024, off[j], 0);
+      for (int j = 0; j < N; ++j) load(j, true);
     } else {
 #pragma unroll
-      for (int j = 0; j < N; ++j)
-        load_to_lds(base, dst + (wave * N + j) * 1024, (row[j] < left ? row[j] : left) * rs + chunk[j], 0);
+      for (int j = 0; j < N; ++j) load(j, false);
     }
   }
 };
@@ -119,9 +124,6 @@ __device__ __forceinline__ f32x16 splat16(float x) {
 // 2^x as the bare hardware instruction: the library routine wraps it in a range reduction for
 // results below 2^-126, which a probability that small does not need (it is 0 in bf16 anyway)
 __device__ __forceinline__ float exp2_raw(float x) { return __builtin_amdgcn_exp2f(x); }
-// Keeps a value where it is computed: the optimiser moves arithmetic past branches towards its use otherwise, out of
-// the place between matrix instructions that it was given.
-template <typename T> __device__ __forceinline__ void pin(T& v) { asm volatile("" : "+v"(v)); }
 // combination of a value with that of the lane 32 apart, on the vector unit
 __device__ __forceinline__ float half_max(float x) {
   const auto r = __builtin_amdgcn_permlane32_swap(__float_as_uint(x), __float_as_uint(x), false, false);
@@ -554,7 +556,8 @@ __global__ void __launch_bounds__(NW * 64, (fa_waves<DH, NW>())) attn_bwd_dkv_mf
     kf[ks] = *reinterpret_cast<const bf16x8*>(P.K + (long)kc * a.k_row_stride + 16 * ks + 8 * lh);
     vf[ks] = *reinterpret_cast<const bf16x8*>(P.V + (long)kc * a.v_row_stride + 16 * ks + 8 * lh);
   }
-  const Stager<NW, DH> sq(a.q_row_stride, wave, lane), so(a.do_row_stride, wave, lane);
+  constexpr bool AGAIN = DH == 128;
+  const Stager<NW, DH, AGAIN> sq(a.q_row_stride, wave, lane), so(a.do_row_stride, wave, lane);
   auto stage = [&](int slot, int it) {
     sq.issue(smem + slot * 2 * L::TILE, P.Q, it * 64, a.Sq);
     so.issue(smem + slot * 2 * L::TILE + L::TILE, P.dO, it * 64, a.Sq);

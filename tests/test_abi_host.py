@@ -26,6 +26,20 @@ def test_library_exports_every_declared_symbol():
         assert hasattr(L, n), n
 
 
+def test_attention_kernels_do_not_spill():
+    """The attention kernels on the bf16 matrix cores run at the register limit.  The kernel descriptions of
+    the code objects inside the library say how many vector registers of each went to scratch memory."""
+    raw = open(mb.LIB_PATH, "rb").read()
+    spills = {}
+    for m in re.finditer(rb"\.vgpr_spill_count", raw):
+        v = raw[m.end():m.end() + 3]
+        n = v[0] if v[0] < 0x80 else v[1] if v[0] == 0xcc else 256 * v[1] + v[2]
+        names = re.findall(rb"\.symbol.*?(_Z[\x20-\x7e]+?)\.kd", raw[max(0, m.start() - 500):m.start()], re.S)
+        spills[names[-1].decode()] = n
+    attn = {k: n for k, n in spills.items() if "_mfma_kernel" in k and "attn" in k}
+    assert len(attn) >= 20 and not any(attn.values()), {k: n for k, n in attn.items() if n}
+
+
 @pytest.mark.parametrize("name", list(wls.named_workloads()))
 def test_theta_layout_matches_the_documented_order(name):
     wl = wls.named_workloads()[name]
