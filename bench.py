@@ -203,7 +203,8 @@ def main():
     shared = adjoint and not args.plain_pair and not args.no_adjoint_cache
     ws_fwd = ws
     if shared:
-        fwd_bytes = mb.mgrit_stacked_workspace_bytes(desc, opts, sw.n_enc, 0) if sw else mb.mgrit_workspace_bytes(desc, opts, 0)
+        fwd_bytes = (mb.mgrit_stacked_workspace_bytes(desc, opts, sw.n_enc, 0) if sw else
+                     mb.mgrit_linearising_workspace_bytes(desc, opts))
         ws_fwd = torch.empty(max(fwd_bytes, 256), dtype=torch.uint8, device="cuda")
         ws_bytes += ws_fwd.numel()
     n_phi = mb.mgrit_step_evaluations(opts)

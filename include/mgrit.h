@@ -121,7 +121,8 @@ int mgrit_theta_layout(const mgrit_model_desc* desc, mgrit_theta_layout_t* out);
  * mgrit_adjoint called with dtheta or dmemory (which keeps the inputs of every layer's linear
  * maps, the cotangents of their outputs and per-layer terms).  For mgrit_forward of a cross-attention
  * decoder the size has room for every layer's keys and values of the memory; the size queried with the
- * adjoint cache switched off has not, is also accepted, and gives the same results more slowly. */
+ * adjoint cache switched off has not, is also accepted, and gives the same results more slowly.  (Not so
+ * for mgrit_forward_linearising: mgrit_linearising_workspace_bytes.) */
 size_t mgrit_workspace_bytes(const mgrit_model_desc* desc, const mgrit_opts* opts, int adjoint);
 size_t mgrit_layer_step_workspace_bytes(const mgrit_model_desc* desc, int adjoint, int n_groups);
 
@@ -198,7 +199,12 @@ int mgrit_adjoint(const mgrit_model_desc* desc, const mgrit_opts* opts,
  * call's `adjoint_workspace`, untouched in between, and with_gradients matches; the adjoint is
  * enqueued after the forward call on the same stream; the linearisation cache is switched on
  * (mgrit_set_adjoint_cache, the default; MGRIT_INVALID_ARG otherwise).  None of this can be checked
- * by the library: a violation gives wrong lambda without an error.  Everything else as above. */
+ * by the library: a violation gives wrong lambda without an error.  Everything else as above.
+ *
+ * mgrit_linearising_workspace_bytes is what `workspace` of mgrit_forward_linearising needs (0 on invalid
+ * arguments; host only).  A cross-attention decoder's keys and values of the memory lie in the adjoint's
+ * workspace there, so it is less than mgrit_workspace_bytes(.., 0). */
+size_t mgrit_linearising_workspace_bytes(const mgrit_model_desc* desc, const mgrit_opts* opts);
 int mgrit_forward_linearising(const mgrit_model_desc* desc, const mgrit_opts* opts,
                               const void* Z0, const void* const* theta, const void* memory,
                               void* Z_all, float* resnorm,

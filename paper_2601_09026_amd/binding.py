@@ -78,6 +78,8 @@ def lib() -> C.CDLL:
         L.mgrit_theta_layout.restype = C.c_int
         L.mgrit_workspace_bytes.argtypes = [C.POINTER(ModelDesc), C.POINTER(Opts), C.c_int]
         L.mgrit_workspace_bytes.restype = C.c_size_t
+        L.mgrit_linearising_workspace_bytes.argtypes = [C.POINTER(ModelDesc), C.POINTER(Opts)]
+        L.mgrit_linearising_workspace_bytes.restype = C.c_size_t
         L.mgrit_layer_step_workspace_bytes.argtypes = [C.POINTER(ModelDesc), C.c_int, C.c_int]
         L.mgrit_layer_step_workspace_bytes.restype = C.c_size_t
         L.mgrit_step_evaluations.argtypes = [C.POINTER(Opts)]
@@ -199,6 +201,11 @@ def mgrit_theta_layout(desc: ModelDesc) -> ThetaLayout:
 def mgrit_workspace_bytes(desc: ModelDesc, opts: Opts, adjoint) -> int:
     """adjoint: 0/False forward, 1/True adjoint, 2 adjoint with parameter gradients."""
     return int(lib().mgrit_workspace_bytes(C.byref(desc), C.byref(opts), int(adjoint)))
+
+
+def mgrit_linearising_workspace_bytes(desc: ModelDesc, opts: Opts) -> int:
+    """Workspace of mgrit_forward with an adjoint_workspace."""
+    return int(lib().mgrit_linearising_workspace_bytes(C.byref(desc), C.byref(opts)))
 
 
 def grad_layout(desc: ModelDesc) -> ThetaLayout:
@@ -388,8 +395,9 @@ def mgrit_forward(desc: ModelDesc, opts: Opts, Z0: torch.Tensor, theta: List[tor
     _check_state(Z_all, (opts.N + 1, T, d), "Z_all")
     if resnorm is None:
         resnorm = torch.zeros(max(opts.iters, 1), dtype=torch.float32, device=Z0.device)
-    need = mgrit_workspace_bytes(desc, opts, False)
     if workspace is None:
+        need = (mgrit_workspace_bytes(desc, opts, False) if adjoint_workspace is None else
+                mgrit_linearising_workspace_bytes(desc, opts))
         workspace = torch.empty(max(need, 256), dtype=torch.uint8, device=Z0.device)
     if adjoint_workspace is not None:
         st = lib().mgrit_forward_linearising(C.byref(desc), C.byref(opts), _ptr(Z0), _ptr_array(theta), _ptr(memory),

@@ -193,7 +193,8 @@ struct Engine {
   int Gc;                          // groups per launch chunk
   // forward work buffers, Gc slots each
   void *u, *qkv, *o, *act, *qc, *kvc, *memb;
-  void* kv_all = nullptr;          // forward: K | V of the shared memory of every layer ([N, Tm, 2d], slot = layer), or null
+  bool keep_kv = false;            // forward: K | V of the shared memory are kept for every layer, in kv_all ...
+  void* kv_all = nullptr;          // ... ([N, Tm, 2d], slot = layer)
   float *xin, *x3;
   // adjoint: linearisation cache (n_cache slots) and work buffers (Gc slots)
   int n_cache;
@@ -249,7 +250,7 @@ struct Engine {
     if (md.arch == MGRIT_ARCH_CROSS) {
       x3 = b.take<float>(G * T * d);
       qc = b.take_bytes(G * T * d * esz);
-      kvc = kv_all ? nullptr : b.take_bytes(G * Tm * 2 * d * esz);
+      kvc = keep_kv ? nullptr : b.take_bytes(G * Tm * 2 * d * esz);
       if (per_group_mem) membG = b.take_bytes(G * Tm * d * esz);
     }
   }
@@ -474,8 +475,8 @@ int forward_chunk(Engine& E, int n, Rows IN, Rows OUT, Rows RHS, Params TH, floa
 
   if (cross) {
     void* qc = cache ? E.c_qc : E.qc;
-    void* kvc = E.kv_all ? E.kv_all : cache ? E.c_kvc : E.kvc;
-    const Slots kvs = E.kv_all ? Slots{(int)TH.i0, (int)TH.is} : cs;
+    void* kvc = E.keep_kv ? E.kv_all : cache ? E.c_kvc : E.kvc;
+    const Slots kvs = E.keep_kv ? Slots{(int)TH.i0, (int)TH.is} : cs;
     void* oc = cache ? E.c_oc : E.o;
     ln.X = IN; ln.xp = x3; ln.xp_slot_stride = E.Td(); ln.xp_slots = cs;         // LN3(X + s)
     ln.gamma_off = L.offset[MGRIT_P_LN3_G]; ln.beta_off = L.offset[MGRIT_P_LN3_B];
@@ -484,7 +485,7 @@ int forward_chunk(Engine& E, int n, Rows IN, Rows OUT, Rows RHS, Params TH, floa
     g = gemm_base(n, T, d, d, u3, E.Td(), us, TH, L.offset[MGRIT_P_WQ_C], L.offset[MGRIT_P_BQ_C]);
     g.out = qc; g.out_slot_stride = E.Td(); g.out_slots = cs;
     HIPCHK(launch_gemm(g, EPI_STORE, E.bf16, E.st));
-    if (!E.kv_all) STCHK(memory_kv(E, n, MEM, TH, kvc, kvs));
+    if (!E.keep_kv) STCHK(memory_kv(E, n, MEM, TH, kvc, kvs));
     memset(&at, 0, sizeof(at));
     at.n_groups = n; at.B = E.md.batch; at.H = E.H; at.dh = E.dh; at.Sq = E.md.seq; at.Sk = E.md.mem_seq;
     at.causal = 0;
@@ -1263,7 +1264,7 @@ struct Driver {
 // Cross attention on a memory that all steps share: K | V of a layer depend on its parameters and the memory alone, and
 // an MGRIT solve evaluates a layer several times (184 evaluations of 32 layers with c_f = 4, two levels, two cycles), so
 // the forward solve forms them once per layer, in one launch over all of them (workspace of N x Tm x 2d operands, the size
-// of the states where Tm = T).  With Tm = T they are an eighth of a step's products: 512 wide, 4096 tokens of 64,
+// of the states where Tm = T; on behalf of an adjoint they go where its cache has them and take no room of their own).  With Tm = T they are an eighth of a step's products: 512 wide, 4096 tokens of 64,
 // 13.69 -> 12.78 ms per solve.  A serial run evaluates a layer once; without the adjoint cache a caller has asked for
 // little memory; a workspace without room for them (forward_bytes) runs with them formed in every step.
 bool keeps_kv(const mgrit_model_desc* md, const mgrit_opts* op) {
@@ -1284,6 +1285,7 @@ struct Plan {                       // workspace of mgrit_forward / mgrit_adjoin
 // share_ws, share_mode: a forward plan whose closing relaxation fills the linearisation cache of the
 // adjoint plan (mode 1 or 2) that will be laid out in share_ws: the cache is the first thing an adjoint
 // plan carves, so carving it again from the same base gives the same addresses.
+// (share_mode without share_ws: its size.)
 // keep_kv: a forward plan keeps the memory's K | V of every layer where that can pay (see keeps_kv).
 int make_plan(Plan& P, const mgrit_model_desc* md, const mgrit_opts* op, int mode, void* ws, hipStream_t st,
               void* share_ws = nullptr, int share_mode = 0, bool keep_kv = true) {
@@ -1299,12 +1301,13 @@ int make_plan(Plan& P, const mgrit_model_desc* md, const mgrit_opts* op, int mod
   if (gc > widest) gc = widest;
   E.keep_inputs = mode == 2;
   E.recompute = adjoint && !g_adjoint_cache;
-  if (adjoint) E.carve_adjoint(b, gc, N); else E.carve_forward(b, gc, keep_kv && keeps_kv(md, op) ? N : 0);
-  if (!adjoint && share_ws) {
+  E.keep_kv = !adjoint && keep_kv && keeps_kv(md, op);
+  if (adjoint) E.carve_adjoint(b, gc, N); else E.carve_forward(b, gc, E.keep_kv && !share_mode ? N : 0);
+  if (!adjoint && share_mode) {
     Bump shared(share_ws);
     E.keep_inputs = share_mode == 2;
     E.carve_cache(shared, N);
-    if (E.kv_all) E.kv_all = E.c_kvc;       // the adjoint wants the same values, under the same slots
+    if (E.keep_kv) E.kv_all = E.c_kvc;      // the adjoint wants the same values, under the same slots
     P.D.fill_cache = true;
   }
   P.two_lanes = widest >= 2 && make_lane(P.E2, E, b, adjoint, ws == nullptr);
@@ -1525,10 +1528,10 @@ int64_t mgrit_step_depth(const mgrit_opts* opts) {
 }  // extern "C"
 
 namespace {
-// What mgrit_forward needs at least (keep_kv = false) and at most
-size_t forward_bytes(const mgrit_model_desc* desc, const mgrit_opts* opts, bool keep_kv) {
+// What mgrit_forward needs at least (keep_kv = false) and at most; share_mode: on behalf of an adjoint
+size_t forward_bytes(const mgrit_model_desc* desc, const mgrit_opts* opts, bool keep_kv, int share_mode = 0) {
   Plan P;
-  return make_plan(P, desc, opts, 0, nullptr, nullptr, nullptr, 0, keep_kv) == MGRIT_OK ? P.bytes : 0;
+  return make_plan(P, desc, opts, 0, nullptr, nullptr, nullptr, share_mode, keep_kv) == MGRIT_OK ? P.bytes : 0;
 }
 
 // share_ws != null: the forward solve also fills the linearisation cache of the adjoint workspace share_ws
@@ -1541,8 +1544,8 @@ int forward_impl(const mgrit_model_desc* desc, const mgrit_opts* opts, const voi
   if (!Z0 || !Z_all || !workspace) return MGRIT_INVALID_ARG;
   STCHK(check_ptr_array(theta, opts->N));
   if (desc->arch == MGRIT_ARCH_CROSS && !memory) return MGRIT_INVALID_ARG;
-  const bool keep_kv = workspace_bytes >= mgrit_workspace_bytes(desc, opts, 0);
-  const size_t need = forward_bytes(desc, opts, keep_kv);
+  const bool keep_kv = share_ws || workspace_bytes >= forward_bytes(desc, opts, true);
+  const size_t need = forward_bytes(desc, opts, keep_kv, share_mode);
   if (need == 0) return MGRIT_INVALID_ARG;
   if (workspace_bytes < need) return MGRIT_WORKSPACE_TOO_SMALL;
   if (share_ws) {
@@ -1701,6 +1704,11 @@ int mgrit_forward(const mgrit_model_desc* desc, const mgrit_opts* opts, const vo
                   size_t workspace_bytes, void* stream) {
   return forward_impl(desc, opts, Z0, theta, memory, Z_all, resnorm, workspace, workspace_bytes, nullptr, 0, 0,
                       stream);
+}
+
+size_t mgrit_linearising_workspace_bytes(const mgrit_model_desc* desc, const mgrit_opts* opts) {
+  if (validate_desc(desc) != MGRIT_OK || validate_opts(opts) != MGRIT_OK) return 0;
+  return forward_bytes(desc, opts, true, 1);
 }
 
 int mgrit_forward_linearising(const mgrit_model_desc* desc, const mgrit_opts* opts, const void* Z0,
@@ -2080,12 +2088,13 @@ static int forward_buffered_impl(const mgrit_model_desc* desc, const mgrit_opts*
   STCHK(validate_opts(opts));
   STCHK(validate_buffer(buf));
   if (!Z0 || !Z_all || !theta) return MGRIT_INVALID_ARG;
-  size_t need = forward_bytes(desc, opts, false);        // each segment takes of the workspace what it needs
+  const bool share = share_ws != nullptr;
+  size_t need = forward_bytes(desc, opts, share, share_mode);   // each segment takes of the workspace what it needs
   if (need == 0) return MGRIT_INVALID_ARG;
   for (int n : {buf->n_open, buf->n_close}) {
     if (n == 0) continue;
     const mgrit_opts so = serial_opts(n, buf->h_buffer);
-    const size_t w = forward_bytes(desc, &so, false);
+    const size_t w = forward_bytes(desc, &so, share, share_mode);
     if (w > need) need = w;
   }
   if (!workspace || workspace_bytes < need) return workspace ? MGRIT_WORKSPACE_TOO_SMALL : MGRIT_INVALID_ARG;

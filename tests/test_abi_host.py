@@ -206,6 +206,25 @@ def test_stacked_grid_workspace_and_argument_checks():
                                    None) == -1
 
 
+@pytest.mark.parametrize("B,S,Sm,levels", [(8, 16, 512, 2), (64, 64, 64, 2), (8, 16, 512, 1)])
+def test_linearising_workspace_has_no_second_copy_of_the_memory(B, S, Sm, levels):
+    """A decoder's keys and values of the memory for all layers (N x B Sm x 2d operands) belong to the forward
+    solve's workspace, but to the adjoint's where there is one."""
+    N, d = 128, 512
+    desc, opts = mb.ModelDesc(2, d, 8, 2048, B, S, Sm, 1, 1e-5), mb.mgrit_opts(N, 1 / N, 4, levels, 2)
+    kept = N * B * Sm * 2 * d * 2 if levels > 1 else 0
+    plain, pair = mb.mgrit_workspace_bytes(desc, opts, 0), mb.mgrit_linearising_workspace_bytes(desc, opts)
+    try:
+        mb.mgrit_set_adjoint_cache(False)
+        least = mb.mgrit_workspace_bytes(desc, opts, 0)
+    finally:
+        mb.mgrit_set_adjoint_cache(True)
+    assert 0 < pair <= least and pair == plain - kept, (plain, pair, least)
+    enc = mb.encoder_desc(desc)
+    assert mb.mgrit_linearising_workspace_bytes(enc, opts) == mb.mgrit_workspace_bytes(enc, opts, 0)
+    assert mb.mgrit_linearising_workspace_bytes(desc, mb.mgrit_opts(10, 0.1, 4, 2, 1)) == 0
+
+
 def test_default_groups_per_launch_follow_the_tile_model():
     """Without a caller's choice the launch chunk comes from the GEMM tile model: 3..6 groups for bf16
     models (5 at d = 768, where five groups of 4096 tokens fill one round of 256x256 tiles for the d-wide

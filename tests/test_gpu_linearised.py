@@ -5,6 +5,8 @@ Z, lambda, residual norms, parameter gradients and the memory gradient must agre
 block types, two and three levels, F and FCF relaxation, a serial run, one and two lanes, with and without
 gradients; the stacked encoder-decoder grid (switch layer aligned with the intervals and inside one); buffer
 layers; and the argument checks of the entry points."""
+import ctypes as C
+
 import pytest
 import torch
 
@@ -75,6 +77,43 @@ def test_linearising_pair_equals_plain_pair(arch, dtype, levels, cf, N, relax, l
     finally:
         mb.mgrit_set_lanes(2)
         mb.mgrit_set_max_groups_per_launch(0)
+
+
+@pytest.mark.parametrize("buffered", [False, True])
+@pytest.mark.parametrize("dtype,Sm,grads", [(wls.DTYPE_BF16, 24, True), (wls.DTYPE_BF16, 200, False),
+                                            (wls.DTYPE_F32, 33, True)])
+def test_linearising_decoder_in_the_least_workspace(dtype, Sm, grads, buffered):
+    """The keys and values of the memory go to the adjoint's cache whatever the size of the forward workspace."""
+    N = 8
+    wl = wls.Workload("t", wls.ARCH_CROSS, 128, 2, 256, 2, 40, Sm, N, 0.5, 4, 2, 2, dtype, 95)
+    print(f"[case] linearising decoder, least workspace dtype={dtype} Sm={Sm} grads={grads} buffered={buffered}", flush=True)
+    dm = DeviceModel(wl, weight_std=0.05, keep_host=False)
+    opts, buf = mb.mgrit_opts(N, wl.h, 4, 2, 2), mb.BufferOpts(0, 0, 0.0)
+    mem, Z0 = dev(wls.cross_memory(wl)), dev(wls.initial_state(wl))
+    adj = mb.mgrit_workspace_bytes(dm.desc, opts, 2 if grads else 1)
+    least = mb.mgrit_linearising_workspace_bytes(dm.desc, opts)
+    outs = []
+    for size in (mb.mgrit_workspace_bytes(dm.desc, opts, 0), least, least - 256):
+        ws, ws_adj = poisoned(size), poisoned(adj)
+        Z, r = torch.empty((N + 1, wl.tokens, 128), device="cuda"), torch.empty(2, device="cuda")
+        if buffered:
+            st = mb.lib().mgrit_forward_buffered_linearising(
+                C.byref(dm.desc), C.byref(opts), C.byref(buf), mb._ptr(Z0), mb._ptr_array(dm.blocks), mb._ptr(mem),
+                mb._ptr(Z), mb._ptr(r), mb._ptr(ws), size, mb._ptr(ws_adj), adj, int(grads), mb._stream_handle(None))
+        else:
+            st = mb.lib().mgrit_forward_linearising(
+                C.byref(dm.desc), C.byref(opts), mb._ptr(Z0), mb._ptr_array(dm.blocks), mb._ptr(mem), mb._ptr(Z),
+                mb._ptr(r), mb._ptr(ws), size, mb._ptr(ws_adj), adj, int(grads), mb._stream_handle(None))
+        assert st == (mb.MGRIT_WORKSPACE_TOO_SMALL if size < least else mb.MGRIT_OK)
+        if size < least:
+            continue
+        gb = grad_blocks(dm.desc, N) if grads else None
+        lam, _ = mb.mgrit_adjoint(dm.desc, opts, Z, dm.blocks, dev(wls.terminal_adjoint(wl)), memory=mem, dtheta=gb,
+                                  workspace=ws_adj, linearised=True)
+        torch.cuda.synchronize()
+        outs.append([Z, r, lam] + [b.view(torch.float32) for b in gb or []])
+    for x, y in zip(*outs):
+        assert torch.isfinite(x).all() and torch.equal(x, y)
 
 
 def test_linearising_entry_points_check_their_arguments():
