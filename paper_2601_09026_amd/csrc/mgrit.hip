@@ -51,7 +51,9 @@ constexpr int DEFAULT_MAX_GROUPS = 4;
 //
 // Layers of few tokens go into one launch (up to SMALL_GROUPS of them) until it has SMALL_ROWS rows or its intermediates
 // SMALL_BYTES: their launches take a few microseconds each however many layers they hold, and the host needs as long
-// to enqueue one.  (few_tokens = false: the rule without that, for scratch memory of a fixed size.)
+// to enqueue one.  (few_tokens = false: the rule without that, for scratch memory of a fixed size and for an adjoint
+// without its N-layer cache, whose launch chunk holds the internals as well: 128 wide, 64 tokens, 128 layers, 58 MiB of
+// workspace instead of 79, with the cache 91.)
 constexpr int SMALL_ROWS = 4096, SMALL_GROUPS = 64;
 constexpr long SMALL_BYTES = 16 << 20;
 inline int default_groups(const mgrit_model_desc* md, int sweep, bool few_tokens = true) {
@@ -1296,11 +1298,11 @@ int make_plan(Plan& P, const mgrit_model_desc* md, const mgrit_opts* op, int mod
   const int N = op->N;
   const bool serial = serial_run(op);
   const int M0 = serial ? 1 : N / op->cf;
-  int gc = max_groups(md, M0);
-  const int widest = adjoint ? (N > M0 ? N : M0) : M0;      // the cache pass batches over all N layers
-  if (gc > widest) gc = widest;
   E.keep_inputs = mode == 2;
   E.recompute = adjoint && !g_adjoint_cache;
+  int gc = max_groups(md, M0, !E.recompute);
+  const int widest = adjoint ? (N > M0 ? N : M0) : M0;      // the cache pass batches over all N layers
+  if (gc > widest) gc = widest;
   E.keep_kv = !adjoint && keep_kv && keeps_kv(md, op);
   if (adjoint) E.carve_adjoint(b, gc, N); else E.carve_forward(b, gc, E.keep_kv && !share_mode ? N : 0);
   if (!adjoint && share_mode) {
@@ -1781,11 +1783,11 @@ int make_stacked_plan(StackedPlan& P, const mgrit_model_desc* md, const mgrit_op
   const int N = op->N, n_dec = N - n_enc;
   const bool serial = serial_run(op);
   const int M0 = serial ? 1 : N / op->cf;
-  int gc = max_groups(md, M0);
-  const int widest = adjoint ? (N > M0 ? N : M0) : M0;
-  if (gc > widest) gc = widest;
   P.Ee.keep_inputs = P.Ed.keep_inputs = mode == 2;
   P.Ee.recompute = P.Ed.recompute = adjoint && !g_adjoint_cache;
+  int gc = max_groups(md, M0, !P.Ee.recompute);
+  const int widest = adjoint ? (N > M0 ? N : M0) : M0;
+  if (gc > widest) gc = widest;
   if (adjoint) { P.Ee.carve_adjoint(b, gc, n_enc); P.Ed.carve_adjoint(b, gc, n_dec); }
   else { P.Ee.carve_forward(b, gc); P.Ed.carve_forward(b, gc); }
   if (!adjoint && share_ws) {

@@ -225,6 +225,26 @@ def test_linearising_workspace_has_no_second_copy_of_the_memory(B, S, Sm, levels
     assert mb.mgrit_linearising_workspace_bytes(desc, mb.mgrit_opts(10, 0.1, 4, 2, 1)) == 0
 
 
+@pytest.mark.parametrize("dtype,d,tokens,mode", [(1, 128, 64, 1), (1, 128, 64, 2), (0, 64, 64, 1), (0, 64, 64, 2)])
+def test_recompute_mode_keeps_small_chunks(dtype, d, tokens, mode):
+    """Without the adjoint cache the workspace holds the internals of one launch chunk per lane, so many layers of
+    few tokens do not share a launch there: no more memory than with chunks of 6 (bf16) or 4 (fp32)."""
+    desc = mb.ModelDesc(0, d, 2, 4 * d, 1, tokens, 0, dtype, 1e-5)
+    dec = mb.ModelDesc(2, d, 2, 4 * d, 1, tokens // 2, tokens // 2, dtype, 1e-5)
+    opts = mb.mgrit_opts(128, 1 / 128, 4, 2, 2)
+    size = lambda: (mb.mgrit_workspace_bytes(desc, opts, mode), mb.mgrit_stacked_workspace_bytes(dec, opts, 64, mode))
+    cached = size()
+    try:
+        mb.mgrit_set_adjoint_cache(False)
+        auto = size()
+        mb.mgrit_set_max_groups_per_launch(6 if dtype else 4)
+        bound = size()
+    finally:
+        mb.mgrit_set_max_groups_per_launch(0)
+        mb.mgrit_set_adjoint_cache(True)
+    assert all(a <= b < c for a, b, c in zip(auto, bound, cached)), (auto, bound, cached)
+
+
 def test_default_groups_per_launch_follow_the_tile_model():
     """Without a caller's choice the launch chunk comes from the GEMM tile model: 3..6 groups for bf16
     models (5 at d = 768, where five groups of 4096 tokens fill one round of 256x256 tiles for the d-wide
