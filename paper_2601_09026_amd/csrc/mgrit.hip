@@ -87,6 +87,11 @@ inline int default_groups(const mgrit_model_desc* md, int sweep, bool few_tokens
 inline int max_groups(const mgrit_model_desc* md, int sweep, bool few_tokens = true) {
   return g_max_groups > 0 ? g_max_groups : default_groups(md, sweep, few_tokens);
 }
+// of a solve; recompute: an adjoint without its N-layer cache
+inline int solve_groups(const mgrit_model_desc* md, int sweep, bool recompute) {
+  const int gc = max_groups(md, sweep), small = recompute ? max_groups(md, sweep, false) : gc;
+  return small < gc ? small : gc;
+}
 
 #define HIPCHK(expr)                                   \
   do {                                                 \
@@ -1300,7 +1305,7 @@ int make_plan(Plan& P, const mgrit_model_desc* md, const mgrit_opts* op, int mod
   const int M0 = serial ? 1 : N / op->cf;
   E.keep_inputs = mode == 2;
   E.recompute = adjoint && !g_adjoint_cache;
-  int gc = max_groups(md, M0, !E.recompute);
+  int gc = solve_groups(md, M0, E.recompute);
   const int widest = adjoint ? (N > M0 ? N : M0) : M0;      // the cache pass batches over all N layers
   if (gc > widest) gc = widest;
   E.keep_kv = !adjoint && keep_kv && keeps_kv(md, op);
@@ -1785,7 +1790,7 @@ int make_stacked_plan(StackedPlan& P, const mgrit_model_desc* md, const mgrit_op
   const int M0 = serial ? 1 : N / op->cf;
   P.Ee.keep_inputs = P.Ed.keep_inputs = mode == 2;
   P.Ee.recompute = P.Ed.recompute = adjoint && !g_adjoint_cache;
-  int gc = max_groups(md, M0, !P.Ee.recompute);
+  int gc = solve_groups(md, M0, P.Ee.recompute);
   const int widest = adjoint ? (N > M0 ? N : M0) : M0;
   if (gc > widest) gc = widest;
   if (adjoint) { P.Ee.carve_adjoint(b, gc, n_enc); P.Ed.carve_adjoint(b, gc, n_dec); }
