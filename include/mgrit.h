@@ -122,7 +122,10 @@ int mgrit_theta_layout(const mgrit_model_desc* desc, mgrit_theta_layout_t* out);
  * maps, the cotangents of their outputs and per-layer terms).  For mgrit_forward of a cross-attention
  * decoder the size has room for every layer's keys and values of the memory; the size queried with the
  * adjoint cache switched off has not, is also accepted, and gives the same results more slowly.  (Not so
- * for mgrit_forward_linearising: mgrit_linearising_workspace_bytes.) */
+ * for mgrit_forward_linearising: mgrit_linearising_workspace_bytes.)
+ * For models of few tokens these sizes, and those of the stacked and buffered forms below, are for launches
+ * of many layers; a workspace that has room for chunks of 3..6 layers (4 in fp32) only is also accepted,
+ * with the same results. */
 size_t mgrit_workspace_bytes(const mgrit_model_desc* desc, const mgrit_opts* opts, int adjoint);
 size_t mgrit_layer_step_workspace_bytes(const mgrit_model_desc* desc, int adjoint, int n_groups);
 

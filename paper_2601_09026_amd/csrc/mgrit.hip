@@ -88,8 +88,8 @@ inline int max_groups(const mgrit_model_desc* md, int sweep, bool few_tokens = t
   return g_max_groups > 0 ? g_max_groups : default_groups(md, sweep, few_tokens);
 }
 // of a solve; recompute: an adjoint without its N-layer cache
-inline int solve_groups(const mgrit_model_desc* md, int sweep, bool recompute) {
-  const int gc = max_groups(md, sweep), small = recompute ? max_groups(md, sweep, false) : gc;
+inline int solve_groups(const mgrit_model_desc* md, int sweep, bool recompute, bool few_tokens) {
+  const int gc = max_groups(md, sweep, few_tokens), small = recompute ? max_groups(md, sweep, false) : gc;
   return small < gc ? small : gc;
 }
 
@@ -304,6 +304,9 @@ struct Engine {
   }
   void carve_adjoint(Bump& b, int gc, int ncache) {
     carve_cache(b, recompute ? gc : ncache);
+    carve_adjoint_rest(b, gc);
+  }
+  void carve_adjoint_rest(Bump& b, int gc) {
     memb = md.arch == MGRIT_ARCH_CROSS ? b.take_bytes((size_t)Tm * d * esz) : nullptr;
     carve_adjoint_work(b, gc);
   }
@@ -1273,10 +1276,17 @@ struct Driver {
 // the forward solve forms them once per layer, in one launch over all of them (workspace of N x Tm x 2d operands, the size
 // of the states where Tm = T; on behalf of an adjoint they go where its cache has them and take no room of their own).  With Tm = T they are an eighth of a step's products: 512 wide, 4096 tokens of 64,
 // 13.69 -> 12.78 ms per solve.  A serial run evaluates a layer once; without the adjoint cache a caller has asked for
-// little memory; a workspace without room for them (forward_bytes) runs with them formed in every step.
+// little memory; a workspace without room for them (fit_plan) runs with them formed in every step.
 bool keeps_kv(const mgrit_model_desc* md, const mgrit_opts* op) {
   return md->arch == MGRIT_ARCH_CROSS && !serial_run(op) && g_adjoint_cache;
 }
+
+// What a solve takes more workspace for than it could do with.  The size queries count both; the calls take what the given
+// workspace has room for (fit_plan), so that a size that was enough without them still is.  Same results either way.
+struct Extras {
+  bool kv = true;                   // forward: the memory's K | V of every layer where that can pay (see keeps_kv)
+  bool few = true;                  // launch chunks for layers of few tokens (see default_groups)
+};
 
 struct Plan {                       // workspace of mgrit_forward / mgrit_adjoint
   Engine E, E2;
@@ -1293,9 +1303,8 @@ struct Plan {                       // workspace of mgrit_forward / mgrit_adjoin
 // adjoint plan (mode 1 or 2) that will be laid out in share_ws: the cache is the first thing an adjoint
 // plan carves, so carving it again from the same base gives the same addresses.
 // (share_mode without share_ws: its size.)
-// keep_kv: a forward plan keeps the memory's K | V of every layer where that can pay (see keeps_kv).
 int make_plan(Plan& P, const mgrit_model_desc* md, const mgrit_opts* op, int mode, void* ws, hipStream_t st,
-              void* share_ws = nullptr, int share_mode = 0, bool keep_kv = true) {
+              void* share_ws = nullptr, int share_mode = 0, Extras extras = {}) {
   const bool adjoint = mode != 0;
   Bump b(ws);
   Engine& E = P.E;
@@ -1305,10 +1314,10 @@ int make_plan(Plan& P, const mgrit_model_desc* md, const mgrit_opts* op, int mod
   const int M0 = serial ? 1 : N / op->cf;
   E.keep_inputs = mode == 2;
   E.recompute = adjoint && !g_adjoint_cache;
-  int gc = solve_groups(md, M0, E.recompute);
+  int gc = solve_groups(md, M0, E.recompute, extras.few);
   const int widest = adjoint ? (N > M0 ? N : M0) : M0;      // the cache pass batches over all N layers
   if (gc > widest) gc = widest;
-  E.keep_kv = !adjoint && keep_kv && keeps_kv(md, op);
+  E.keep_kv = !adjoint && extras.kv && keeps_kv(md, op);
   if (adjoint) E.carve_adjoint(b, gc, N); else E.carve_forward(b, gc, E.keep_kv && !share_mode ? N : 0);
   if (!adjoint && share_mode) {
     Bump shared(share_ws);
@@ -1370,13 +1379,13 @@ int check_ptr_array(const void* const* a, int n) {
 }
 
 // Scratch need of one batched layer step; second_lane: the helper lane's work buffers included
-// (when two lanes are switched on and there are at least two groups).
-size_t layer_step_bytes(const mgrit_model_desc* desc, int adjoint, int n_groups, bool second_lane) {
+// (when two lanes are switched on and there are at least two groups); few: as in Extras.
+size_t layer_step_bytes(const mgrit_model_desc* desc, int adjoint, int n_groups, bool second_lane, bool few) {
   if (validate_desc(desc) != MGRIT_OK || n_groups < 1) return 0;
   Engine E;
   E.init(desc, nullptr);
   Bump b(nullptr);
-  const int most = max_groups(desc, n_groups, second_lane), gc = most < n_groups ? most : n_groups;
+  const int most = max_groups(desc, n_groups, few), gc = most < n_groups ? most : n_groups;
   Engine E2;
   if (adjoint) {
     E.carve_adjoint(b, gc, n_groups);
@@ -1406,7 +1415,9 @@ int layer_step_on(const mgrit_model_desc* desc, int adjoint, int n_groups, const
   if (rhs) STCHK(check_ptr_array(rhs, n_groups));
   if (adjoint) STCHK(check_ptr_array(lin_state, n_groups));
   if (desc->arch == MGRIT_ARCH_CROSS && !memory) return MGRIT_INVALID_ARG;
-  const size_t need = layer_step_bytes(desc, adjoint, n_groups, second_lane);
+  bool few = second_lane;
+  if (few && workspace_bytes < layer_step_bytes(desc, adjoint, n_groups, second_lane, true)) few = false;
+  const size_t need = layer_step_bytes(desc, adjoint, n_groups, second_lane, few);
   if (need == 0) return MGRIT_INVALID_ARG;
   if (workspace_bytes < need) return MGRIT_WORKSPACE_TOO_SMALL;
   hipStream_t st = static_cast<hipStream_t>(stream);
@@ -1414,7 +1425,7 @@ int layer_step_on(const mgrit_model_desc* desc, int adjoint, int n_groups, const
   Engine E;
   E.init(desc, st);
   Bump b(workspace);
-  const int most = max_groups(desc, n_groups, second_lane), gc = most < n_groups ? most : n_groups;
+  const int most = max_groups(desc, n_groups, few), gc = most < n_groups ? most : n_groups;
   const int G = n_groups;
   Engine E2;
   Engine* L2 = nullptr;
@@ -1511,7 +1522,7 @@ size_t mgrit_workspace_bytes(const mgrit_model_desc* desc, const mgrit_opts* opt
 }
 
 size_t mgrit_layer_step_workspace_bytes(const mgrit_model_desc* desc, int adjoint, int n_groups) {
-  return layer_step_bytes(desc, adjoint, n_groups, true);
+  return layer_step_bytes(desc, adjoint, n_groups, true, true);
 }
 
 int64_t mgrit_step_evaluations(const mgrit_opts* opts) {
@@ -1535,10 +1546,27 @@ int64_t mgrit_step_depth(const mgrit_opts* opts) {
 }  // extern "C"
 
 namespace {
-// What mgrit_forward needs at least (keep_kv = false) and at most; share_mode: on behalf of an adjoint
-size_t forward_bytes(const mgrit_model_desc* desc, const mgrit_opts* opts, bool keep_kv, int share_mode = 0) {
+// mode, share_mode: as in make_plan
+size_t plan_bytes(const mgrit_model_desc* desc, const mgrit_opts* opts, int mode, int share_mode, Extras x) {
   Plan P;
-  return make_plan(P, desc, opts, 0, nullptr, nullptr, nullptr, share_mode, keep_kv) == MGRIT_OK ? P.bytes : 0;
+  return make_plan(P, desc, opts, mode, nullptr, nullptr, nullptr, share_mode, x) == MGRIT_OK ? P.bytes : 0;
+}
+// The least workspace of a solve.
+size_t least_bytes(const mgrit_model_desc* desc, const mgrit_opts* opts, int mode, int share_mode) {
+  const bool kv = share_mode != 0;                       // (takes no room then)
+  const size_t a = plan_bytes(desc, opts, mode, share_mode, {kv, false}), b = plan_bytes(desc, opts, mode, share_mode, {kv, true});
+  return a < b ? a : b;
+}
+// The first of the plans, fastest first, that a workspace of that size has room for; false: none.
+bool fit_plan(const mgrit_model_desc* desc, const mgrit_opts* opts, int mode, int share_mode, size_t bytes, Extras& x) {
+  for (bool kv : {true, false}) {
+    if (!kv && (mode || share_mode || !keeps_kv(desc, opts))) break;
+    for (bool few : {true, false}) {
+      x = {kv, few};
+      if (plan_bytes(desc, opts, mode, share_mode, x) <= bytes) return true;
+    }
+  }
+  return false;
 }
 
 // share_ws != null: the forward solve also fills the linearisation cache of the adjoint workspace share_ws
@@ -1551,20 +1579,16 @@ int forward_impl(const mgrit_model_desc* desc, const mgrit_opts* opts, const voi
   if (!Z0 || !Z_all || !workspace) return MGRIT_INVALID_ARG;
   STCHK(check_ptr_array(theta, opts->N));
   if (desc->arch == MGRIT_ARCH_CROSS && !memory) return MGRIT_INVALID_ARG;
-  const bool keep_kv = share_ws || workspace_bytes >= forward_bytes(desc, opts, true);
-  const size_t need = forward_bytes(desc, opts, keep_kv, share_mode);
-  if (need == 0) return MGRIT_INVALID_ARG;
-  if (workspace_bytes < need) return MGRIT_WORKSPACE_TOO_SMALL;
+  Extras extras;
+  if (!fit_plan(desc, opts, 0, share_mode, workspace_bytes, extras)) return MGRIT_WORKSPACE_TOO_SMALL;
   if (share_ws) {
     if (!g_adjoint_cache) return MGRIT_INVALID_ARG;       // there is no N-layer cache to fill
-    const size_t need_adj = mgrit_workspace_bytes(desc, opts, share_mode);
-    if (need_adj == 0) return MGRIT_INVALID_ARG;
-    if (share_bytes < need_adj) return MGRIT_WORKSPACE_TOO_SMALL;
+    if (share_bytes < least_bytes(desc, opts, share_mode, 0)) return MGRIT_WORKSPACE_TOO_SMALL;
   }
   hipStream_t st = static_cast<hipStream_t>(stream);
 
   Plan P;
-  STCHK(make_plan(P, desc, opts, 0, workspace, st, share_ws, share_mode, keep_kv));
+  STCHK(make_plan(P, desc, opts, 0, workspace, st, share_ws, share_mode, extras));
   Engine& E = P.E;
   Driver& D = P.D;
   const int N = opts->N;
@@ -1601,13 +1625,12 @@ int adjoint_impl(const mgrit_model_desc* desc, const mgrit_opts* opts, const voi
   STCHK(check_ptr_array(theta, opts->N));
   if (dtheta) STCHK(check_ptr_array((const void* const*)dtheta, opts->N));
   const int mode = (dtheta || dmemory) ? 2 : 1;
-  const size_t need = mgrit_workspace_bytes(desc, opts, mode);
-  if (need == 0) return MGRIT_INVALID_ARG;
-  if (workspace_bytes < need) return MGRIT_WORKSPACE_TOO_SMALL;
+  Extras extras;
+  if (!fit_plan(desc, opts, mode, 0, workspace_bytes, extras)) return MGRIT_WORKSPACE_TOO_SMALL;
   hipStream_t st = static_cast<hipStream_t>(stream);
 
   Plan P;
-  STCHK(make_plan(P, desc, opts, mode, workspace, st));
+  STCHK(make_plan(P, desc, opts, mode, workspace, st, nullptr, 0, extras));
   Engine& E = P.E;
   Driver& D = P.D;
   const int N = opts->N;
@@ -1715,7 +1738,7 @@ int mgrit_forward(const mgrit_model_desc* desc, const mgrit_opts* opts, const vo
 
 size_t mgrit_linearising_workspace_bytes(const mgrit_model_desc* desc, const mgrit_opts* opts) {
   if (validate_desc(desc) != MGRIT_OK || validate_opts(opts) != MGRIT_OK) return 0;
-  return forward_bytes(desc, opts, true, 1);
+  return plan_bytes(desc, opts, 0, 1, {});
 }
 
 int mgrit_forward_linearising(const mgrit_model_desc* desc, const mgrit_opts* opts, const void* Z0,
@@ -1776,7 +1799,7 @@ int validate_stacked(const mgrit_model_desc* desc, const mgrit_opts* opts, int n
 // mode: 0 forward, 1 adjoint, 2 adjoint followed by the parameter-gradient pass
 // share_ws, share_mode: as in make_plan (a forward plan that fills the caches of the adjoint plan in share_ws)
 int make_stacked_plan(StackedPlan& P, const mgrit_model_desc* md, const mgrit_opts* op, int n_enc, int mode,
-                      void* ws, hipStream_t st, void* share_ws = nullptr, int share_mode = 0) {
+                      void* ws, hipStream_t st, void* share_ws = nullptr, int share_mode = 0, bool few = true) {
   const bool adjoint = mode != 0;
   Bump b(ws);
   const mgrit_model_desc me = encoder_of(md);
@@ -1790,23 +1813,25 @@ int make_stacked_plan(StackedPlan& P, const mgrit_model_desc* md, const mgrit_op
   const int M0 = serial ? 1 : N / op->cf;
   P.Ee.keep_inputs = P.Ed.keep_inputs = mode == 2;
   P.Ee.recompute = P.Ed.recompute = adjoint && !g_adjoint_cache;
-  int gc = solve_groups(md, M0, P.Ee.recompute);
+  int gc = solve_groups(md, M0, P.Ee.recompute, few);
   const int widest = adjoint ? (N > M0 ? N : M0) : M0;
   if (gc > widest) gc = widest;
-  if (adjoint) { P.Ee.carve_adjoint(b, gc, n_enc); P.Ed.carve_adjoint(b, gc, n_dec); }
-  else { P.Ee.carve_forward(b, gc); P.Ed.carve_forward(b, gc); }
+  if (adjoint) {
+    // the caches first: their places follow from the model alone, so a forward plan finds them
+    P.Ee.carve_cache(b, P.Ee.recompute ? gc : n_enc);
+    P.Ed.carve_cache(b, P.Ed.recompute ? gc : n_dec);
+    P.Ee.carve_adjoint_rest(b, gc);
+    P.Ed.carve_adjoint_rest(b, gc);
+  } else {
+    P.Ee.carve_forward(b, gc);
+    P.Ed.carve_forward(b, gc);
+  }
   if (!adjoint && share_ws) {
-    // the adjoint plan's first carvings repeated on copies of the engines, in its order and with its chunk
-    // size (the encoder's cache, memory copy and work buffers come before the decoder's cache)
     Bump shared(share_ws);
-    const int widest_a = N > M0 ? N : M0;
-    int gca = max_groups(md, M0);
-    if (gca > widest_a) gca = widest_a;
     Engine te = P.Ee, td = P.Ed;
     te.keep_inputs = td.keep_inputs = share_mode == 2;
-    te.recompute = td.recompute = false;
-    te.carve_adjoint(shared, gca, n_enc);
-    td.carve_adjoint(shared, gca, n_dec);
+    te.carve_cache(shared, n_enc);
+    td.carve_cache(shared, n_dec);
     P.Ee.take_cache_from(te);
     P.Ed.take_cache_from(td);
     P.D.fill_cache = true;
@@ -1866,6 +1891,19 @@ size_t mgrit_stacked_workspace_bytes(const mgrit_model_desc* desc, const mgrit_o
 }  // extern "C"
 
 namespace {
+// As plan_bytes and fit_plan (no keys and values are kept here: every step has a memory of its own).
+size_t stacked_bytes(const mgrit_model_desc* desc, const mgrit_opts* opts, int n_enc, int mode, bool few) {
+  StackedPlan P;
+  return make_stacked_plan(P, desc, opts, n_enc, mode, nullptr, nullptr, nullptr, 0, few) == MGRIT_OK ? P.bytes : SIZE_MAX;
+}
+bool fit_stacked(const mgrit_model_desc* desc, const mgrit_opts* opts, int n_enc, int mode, size_t bytes, bool& few) {
+  for (bool f : {true, false}) {
+    few = f;
+    if (stacked_bytes(desc, opts, n_enc, mode, f) <= bytes) return true;
+  }
+  return false;
+}
+
 int forward_stacked_impl(const mgrit_model_desc* desc, const mgrit_opts* opts, int n_enc, const void* Z0,
                          const void* const* theta, void* Z_all, float* resnorm, void* workspace,
                          size_t workspace_bytes, void* share_ws, size_t share_bytes, int share_mode, void* stream) {
@@ -1873,19 +1911,16 @@ int forward_stacked_impl(const mgrit_model_desc* desc, const mgrit_opts* opts, i
   STCHK(validate_stacked(desc, opts, n_enc));
   if (!Z0 || !Z_all || !workspace) return MGRIT_INVALID_ARG;
   STCHK(check_ptr_array(theta, opts->N));
-  const size_t need = mgrit_stacked_workspace_bytes(desc, opts, n_enc, 0);
-  if (need == 0) return MGRIT_INVALID_ARG;
-  if (workspace_bytes < need) return MGRIT_WORKSPACE_TOO_SMALL;
+  bool few, few_adj;
+  if (!fit_stacked(desc, opts, n_enc, 0, workspace_bytes, few)) return MGRIT_WORKSPACE_TOO_SMALL;
   if (share_ws) {
     if (!g_adjoint_cache) return MGRIT_INVALID_ARG;
-    const size_t need_adj = mgrit_stacked_workspace_bytes(desc, opts, n_enc, share_mode);
-    if (need_adj == 0) return MGRIT_INVALID_ARG;
-    if (share_bytes < need_adj) return MGRIT_WORKSPACE_TOO_SMALL;
+    if (!fit_stacked(desc, opts, n_enc, share_mode, share_bytes, few_adj)) return MGRIT_WORKSPACE_TOO_SMALL;
   }
   hipStream_t st = static_cast<hipStream_t>(stream);
 
   StackedPlan P;
-  STCHK(make_stacked_plan(P, desc, opts, n_enc, 0, workspace, st, share_ws, share_mode));
+  STCHK(make_stacked_plan(P, desc, opts, n_enc, 0, workspace, st, share_ws, share_mode, few));
   Driver& D = P.D;
   const int N = opts->N;
   const size_t state = (size_t)D.state_elems() * sizeof(float);
@@ -1911,13 +1946,12 @@ int adjoint_stacked_impl(const mgrit_model_desc* desc, const mgrit_opts* opts, i
   STCHK(check_ptr_array(theta, opts->N));
   if (dtheta) STCHK(check_ptr_array((const void* const*)dtheta, opts->N));
   const int mode = dtheta ? 2 : 1;
-  const size_t need = mgrit_stacked_workspace_bytes(desc, opts, n_enc, mode);
-  if (need == 0) return MGRIT_INVALID_ARG;
-  if (workspace_bytes < need) return MGRIT_WORKSPACE_TOO_SMALL;
+  bool few;
+  if (!fit_stacked(desc, opts, n_enc, mode, workspace_bytes, few)) return MGRIT_WORKSPACE_TOO_SMALL;
   hipStream_t st = static_cast<hipStream_t>(stream);
 
   StackedPlan P;
-  STCHK(make_stacked_plan(P, desc, opts, n_enc, mode, workspace, st));
+  STCHK(make_stacked_plan(P, desc, opts, n_enc, mode, workspace, st, nullptr, 0, few));
   Driver& D = P.D;
   const int N = opts->N, n_dec = N - n_enc;
   const size_t state = (size_t)D.state_elems() * sizeof(float);
@@ -2057,23 +2091,26 @@ size_t mgrit_buffered_workspace_bytes(const mgrit_model_desc* desc, const mgrit_
 }
 
 // Segments of a buffered run: the open layers (serial), the MGRIT middle, the close layers (serial).  The
-// linearising pair gives each segment's adjoint plan a region of its own in one workspace, in this order.
+// linearising pair gives each segment's adjoint plan a region of its own in one workspace, the middle's last: it takes
+// what the workspace has (the others have no use for more than the least).
 struct BufferedRegions {
-  size_t off[3] = {0, 0, 0}, bytes[3] = {0, 0, 0}, total = 0;
+  size_t off[3] = {0, 0, 0}, bytes[3] = {0, 0, 0}, total = 0, least = 0;
+  void give(size_t workspace_bytes) { bytes[1] = workspace_bytes - off[1]; }
 };
 static int buffered_regions(const mgrit_model_desc* desc, const mgrit_opts* opts, const mgrit_buffer_opts* buf,
                             int mode, BufferedRegions& R) {
   const mgrit_opts so_open = serial_opts(buf->n_open, buf->h_buffer), so_close = serial_opts(buf->n_close, buf->h_buffer);
   const mgrit_opts* seg[3] = {buf->n_open > 0 ? &so_open : nullptr, opts, buf->n_close > 0 ? &so_close : nullptr};
   size_t off = 0;
-  for (int i = 0; i < 3; ++i) {
+  for (int i : {0, 2, 1}) {
     R.off[i] = off;
     if (!seg[i]) continue;
     R.bytes[i] = mgrit_workspace_bytes(desc, seg[i], mode);
     if (R.bytes[i] == 0) return MGRIT_INVALID_ARG;
-    off += (R.bytes[i] + 255) / 256 * 256;
+    off += R.bytes[i];
   }
   R.total = off;
+  R.least = R.off[1] + least_bytes(desc, opts, mode, 0);
   return MGRIT_OK;
 }
 
@@ -2083,6 +2120,19 @@ size_t mgrit_buffered_linearised_workspace_bytes(const mgrit_model_desc* desc, c
   BufferedRegions R;
   if (buffered_regions(desc, opts, buf, with_gradients ? 2 : 1, R) != MGRIT_OK) return 0;
   return R.total;
+}
+
+// All segments use the same workspace, each as much of it as it has use for.
+static size_t buffered_least_bytes(const mgrit_model_desc* desc, const mgrit_opts* opts, const mgrit_buffer_opts* buf,
+                                   int mode, int share_mode) {
+  size_t need = least_bytes(desc, opts, mode, share_mode);
+  for (int n : {buf->n_open, buf->n_close}) {
+    if (n == 0) continue;
+    const mgrit_opts so = serial_opts(n, buf->h_buffer);
+    const size_t w = least_bytes(desc, &so, mode, share_mode);
+    if (w > need) need = w;
+  }
+  return need;
 }
 
 // share_ws: the adjoint workspace of the linearising pair (regions as above), or null
@@ -2095,21 +2145,14 @@ static int forward_buffered_impl(const mgrit_model_desc* desc, const mgrit_opts*
   STCHK(validate_opts(opts));
   STCHK(validate_buffer(buf));
   if (!Z0 || !Z_all || !theta) return MGRIT_INVALID_ARG;
-  const bool share = share_ws != nullptr;
-  size_t need = forward_bytes(desc, opts, share, share_mode);   // each segment takes of the workspace what it needs
-  if (need == 0) return MGRIT_INVALID_ARG;
-  for (int n : {buf->n_open, buf->n_close}) {
-    if (n == 0) continue;
-    const mgrit_opts so = serial_opts(n, buf->h_buffer);
-    const size_t w = forward_bytes(desc, &so, share, share_mode);
-    if (w > need) need = w;
-  }
+  const size_t need = buffered_least_bytes(desc, opts, buf, 0, share_mode);
   if (!workspace || workspace_bytes < need) return workspace ? MGRIT_WORKSPACE_TOO_SMALL : MGRIT_INVALID_ARG;
   BufferedRegions R;
   if (share_ws) {
     if (!g_adjoint_cache) return MGRIT_INVALID_ARG;
     STCHK(buffered_regions(desc, opts, buf, share_mode, R));
-    if (share_bytes < R.total) return MGRIT_WORKSPACE_TOO_SMALL;
+    if (share_bytes < R.least) return MGRIT_WORKSPACE_TOO_SMALL;
+    R.give(share_bytes);
   }
   char* sw = static_cast<char*>(share_ws);
   const size_t state = (size_t)desc->batch * desc->seq * desc->d_model * sizeof(float);
@@ -2149,14 +2192,14 @@ static int adjoint_buffered_impl(const mgrit_model_desc* desc, const mgrit_opts*
   if (dmemory) return MGRIT_UNSUPPORTED;
   const int mode = dtheta ? 2 : 1;
   BufferedRegions R;                                   // all three segments share the workspace unless prefilled
-  size_t need = mgrit_buffered_workspace_bytes(desc, opts, buf, mode);
-  if (need == 0) return MGRIT_INVALID_ARG;
+  size_t need = buffered_least_bytes(desc, opts, buf, mode, 0);
   if (prefilled) {
     if (!g_adjoint_cache) return MGRIT_INVALID_ARG;
     STCHK(buffered_regions(desc, opts, buf, mode, R));
-    need = R.total;
+    need = R.least;
   }
   if (!workspace || workspace_bytes < need) return workspace ? MGRIT_WORKSPACE_TOO_SMALL : MGRIT_INVALID_ARG;
+  if (prefilled) R.give(workspace_bytes);
   char* ws = static_cast<char*>(workspace);
   auto region = [&](int i) { return prefilled ? static_cast<void*>(ws + R.off[i]) : workspace; };
   auto region_bytes = [&](int i) { return prefilled ? R.bytes[i] : workspace_bytes; };
@@ -2227,7 +2270,7 @@ int layer_step_batched(const mgrit_model_desc* desc, int adjoint, int n_groups, 
 }
 
 size_t mgrit_layer_step_static_bytes(const mgrit_model_desc* desc, int adjoint, int n_groups) {
-  return layer_step_bytes(desc, adjoint, n_groups, false);
+  return layer_step_bytes(desc, adjoint, n_groups, false, false);
 }
 
 int layer_step_batched_static(const mgrit_model_desc* desc, int adjoint, int n_groups, const void* const* in,
@@ -2235,7 +2278,7 @@ int layer_step_batched_static(const mgrit_model_desc* desc, int adjoint, int n_g
                               const void* const* rhs, const void* memory, float hstep, void* stream) {
   STCHK(validate_desc(desc));
   if (n_groups < 1) return MGRIT_INVALID_ARG;
-  const size_t need = layer_step_bytes(desc, adjoint, n_groups, false);
+  const size_t need = layer_step_bytes(desc, adjoint, n_groups, false, false);
   if (need == 0) return MGRIT_INVALID_ARG;
   if (need > (size_t)MGRIT_STATIC_SCRATCH_BYTES) return MGRIT_WORKSPACE_TOO_SMALL;
   void* ws = nullptr;
