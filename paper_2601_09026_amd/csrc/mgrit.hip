@@ -1436,13 +1436,9 @@ int layer_step_on(const mgrit_model_desc* desc, int adjoint, int n_groups, const
     void** tabs = b.take<void*>((size_t)G * 6);
     void **tIn = tabs, **tOut = tabs + G, **tTh = tabs + 2 * G, **tLin = tabs + 3 * G, **tRhs = tabs + 4 * G,
          **tThT = tabs + 5 * G;
-    std::vector<const void*> ptrs((size_t)G * 6, nullptr);  // in the order of the tables above
-    for (int g = 0; g < G; ++g) {
-      ptrs[g] = in[g]; ptrs[G + g] = out[g]; ptrs[2 * G + g] = theta[g]; ptrs[3 * G + g] = lin_state[g];
-      if (rhs) ptrs[4 * G + g] = rhs[g];
-      ptrs[5 * G + g] = tblocks + (size_t)g * E.lay.block_bytes;
-    }
-    HIPCHK(upload_pointers(tabs, ptrs.data(), 6 * G, st));
+    const PtrSource src[6] = {{in, nullptr, 0}, {out, nullptr, 0}, {theta, nullptr, 0}, {lin_state, nullptr, 0},
+                              {rhs, nullptr, 0}, {nullptr, tblocks, (long)E.lay.block_bytes}};   // as the tables above
+    HIPCHK(upload_tables(tabs, src, 6, G, st));
     Params TH = {(const void* const*)tTh, 0, 1}, THT = {(const void* const*)tThT, 0, 1};
     Rows IN = {(const void* const*)tIn, 0, 1}, OUT = {(const void* const*)tOut, 0, 1};
     Rows LIN = {(const void* const*)tLin, 0, 1};
@@ -1457,12 +1453,8 @@ int layer_step_on(const mgrit_model_desc* desc, int adjoint, int n_groups, const
   if (second_lane && G >= 2 && make_lane(E2, E, b, false, false)) L2 = &E2;
   void** tabs = b.take<void*>((size_t)G * 4);
   void **tIn = tabs, **tOut = tabs + G, **tTh = tabs + 2 * G, **tRhs = tabs + 3 * G;
-  std::vector<const void*> ptrs((size_t)G * 4, nullptr);
-  for (int g = 0; g < G; ++g) {
-    ptrs[g] = in[g]; ptrs[G + g] = out[g]; ptrs[2 * G + g] = theta[g];
-    if (rhs) ptrs[3 * G + g] = rhs[g];
-  }
-  HIPCHK(upload_pointers(tabs, ptrs.data(), (rhs ? 4 : 3) * G, st));
+  const PtrSource src[4] = {{in, nullptr, 0}, {out, nullptr, 0}, {theta, nullptr, 0}, {rhs, nullptr, 0}};
+  HIPCHK(upload_tables(tabs, src, rhs ? 4 : 3, G, st));
   if (desc->arch == MGRIT_ARCH_CROSS)
     HIPCHK(launch_cast_flat(static_cast<const float*>(memory), E.memb, (long)E.Tm * E.d, E.bf16, st));
   Params TH = {(const void* const*)tTh, 0, 1};

@@ -459,14 +459,22 @@ __global__ void __launch_bounds__(PACK) upload_ptrs_kernel(void** tab, PtrPack p
   if (i < n) tab[i] = const_cast<void*>(pack.p[i]);
 }
 
-hipError_t upload_pointers(void** tab, const void* const* host_ptrs, int n, hipStream_t st) {
-  for (int i0 = 0; i0 < n; i0 += PACK) {
-    PtrPack pack;
-    const int m = n - i0 < PACK ? n - i0 : PACK;
-    for (int i = 0; i < PACK; ++i) pack.p[i] = i < m ? host_ptrs[i0 + i] : nullptr;
-    hipLaunchKernelGGL(upload_ptrs_kernel, dim3(1), dim3(PACK), 0, st, tab + i0, pack, m);
-  }
+hipError_t upload_tables(void** tab, const PtrSource* src, int n_src, int n, hipStream_t st) {
+  PtrPack pack;
+  int m = 0;
+  for (int s = 0; s < n_src; ++s)
+    for (int i = 0; i < n; ++i) {
+      pack.p[m++] = src[s].list ? src[s].list[i] : src[s].base + i * src[s].stride;
+      if (m < PACK && !(s == n_src - 1 && i == n - 1)) continue;
+      hipLaunchKernelGGL(upload_ptrs_kernel, dim3(1), dim3(PACK), 0, st, tab, pack, m);
+      tab += m;
+      m = 0;
+    }
   return hipGetLastError();
+}
+hipError_t upload_pointers(void** tab, const void* const* host_ptrs, int n, hipStream_t st) {
+  const PtrSource src = {host_ptrs, nullptr, 0};
+  return upload_tables(tab, &src, 1, n, st);
 }
 
 // ---------------------------------------------------------------------------

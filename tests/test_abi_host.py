@@ -4,9 +4,12 @@ driver does, and rejects bad arguments before touching the device."""
 import ctypes as C
 import os
 import re
+import subprocess
+import sys
 
 import numpy as np
 import pytest
+import torch
 
 from oracle import mgrit as omgrit
 from paper_2601_09026_amd import binding as mb
@@ -267,6 +270,32 @@ def test_default_groups_per_launch_follow_the_tile_model():
         mb.mgrit_set_max_groups_per_launch(0)
     bad = mb.ModelDesc(0, 770, 12, 3072, 32, 128, 0, 1, 1e-5)
     assert L.mgrit_default_groups_per_launch(C.byref(bad), 16) == 0
+
+
+NO_MEMORY = """
+import ctypes as C, resource, sys
+L = C.CDLL(sys.argv[1])
+n = 1 << 22
+ptrs = (C.c_void_p * n)(*[256] * n)
+desc = (C.c_int32 * 9)(0, 64, 4, 256, 1, 8, 0, 0, 0x3727c5ac)             # an fp32 encoder, ln_eps = 1e-5
+fn = L.layer_step_batched
+fn.argtypes = [C.c_void_p, C.c_int, C.c_int] + [C.c_void_p] * 6 + [C.c_float, C.c_void_p, C.c_size_t, C.c_void_p]
+def call(adjoint, n):
+    return fn(desc, adjoint, n, ptrs, ptrs, ptrs, ptrs if adjoint else None, None, None, 0.5, 256, 1 << 60, None)
+first = call(0, 1)                                                     # whatever the runtime allocates, now
+used = int(open("/proc/self/statm").read().split()[0]) * resource.getpagesize()
+resource.setrlimit(resource.RLIMIT_AS, (used + (64 << 20), resource.RLIM_INFINITY))
+print(first, call(0, n), call(1, n))
+"""
+
+
+@pytest.mark.skipif(torch.cuda.is_available(), reason="addresses that must not reach a GPU")
+def test_layer_step_needs_no_host_memory_for_its_tables():
+    """Four million layers with 64 MB of address space left: without a device the call ends in MGRIT_HIP_ERROR, not in an
+    allocation that fails inside the library (an exception has no way out of a C function)."""
+    run = subprocess.run([sys.executable, "-c", NO_MEMORY, mb.LIB_PATH], capture_output=True, text=True, timeout=120)
+    assert run.returncode == 0, (run.returncode, run.stderr[-500:])
+    assert run.stdout.split() == ["-4"] * 3, run.stdout
 
 
 def test_workspace_grows_with_groups_and_levels():
