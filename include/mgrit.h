@@ -389,7 +389,8 @@ int         mgrit_last_hip_error(void);          /* hipError_t of the last MGRIT
 /* Tuning knob: at most this many groups go into one kernel launch (larger sweeps
  * are split into chunks that run one after another).  0 restores the default, which the library
  * chooses per model and sweep width (3..6 for bf16 models: the count whose projection GEMMs fill
- * their last round of tiles best; 4 for fp32); mgrit_default_groups_per_launch reports it for
+ * their last round of tiles best; 4 for fp32; up to 64 where a launch of that many layers has no more than
+ * 4096 rows and 16 MiB of intermediates); mgrit_default_groups_per_launch reports it for
  * sweeps of `sweep` groups (opts->N / opts->cf intervals on level 0).  Host only. */
 void mgrit_set_max_groups_per_launch(int n);
 int  mgrit_default_groups_per_launch(const mgrit_model_desc* desc, int sweep);

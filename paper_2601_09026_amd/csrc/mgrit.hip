@@ -51,7 +51,7 @@ constexpr int DEFAULT_MAX_GROUPS = 4;
 //
 // Layers of few tokens go into one launch (up to SMALL_GROUPS of them) until it has SMALL_ROWS rows or its intermediates
 // SMALL_BYTES: their launches take a few microseconds each however many layers they hold, and the host needs as long
-// to enqueue one.  (few_tokens = false: the rule without that, for scratch memory of a fixed size and for an adjoint
+// to enqueue one.  Where that gives no more than the model's largest pick of six, the model decides.  (few_tokens = false: the rule without that, for scratch memory of a fixed size and for an adjoint
 // without its N-layer cache, whose launch chunk holds the internals as well: 128 wide, 64 tokens, 128 layers, 58 MiB of
 // workspace instead of 79, with the cache 91.)
 constexpr int SMALL_ROWS = 4096, SMALL_GROUPS = 64;
@@ -765,11 +765,18 @@ int param_grads_chunk(Engine& E, int n, Params THT, Rows LIN, Slots cs, float hs
 }
 
 // A sweep that fits one launch chunk and whose products take less than the host needs to enqueue a second chain of
-// launches (about 8 kernels and the events of the fork and join, 3-4 us each) stays in one piece.  Microseconds of the
-// four products of a layer step: bf16 from the tile model, fp32 at 100 TFLOP/s and 3 us a launch.
+// launches (about 8 kernels and the events of the fork and join, 3-4 us each) stays in one piece.  The measure is the
+// four products of an encoder's forward step alone, whatever the sweep runs (bf16 from the tile model, fp32 at 100 TFLOP/s
+// and 3 us a launch): attention, cross attention and the transposed products add to both sides alike.
 // Whole calls, split and in one piece (with the larger chunks above): four layers of 64 tokens, fp32, 111 -> 37 us;
 // transposed steps of 6 layers of 462 tokens, 320 wide, 235 -> 103 us; training step of 16 layers of 64 tokens
 // 3.41 -> 2.42 ms.
+// Over 284 layer steps of 2 to 8 layers, 64 to 1024 wide, 64 to 16384 tokens, both directions and types, cross attention
+// and sequences of 2048 tokens among them, no sweep below the line is faster split (attention of 2048 tokens, 128 wide, 29 us
+// by this measure: four layers of 8 sequences 204 split, 187 in one piece; transposed 558, 528).  Above it both happen: 42
+// to 60 us mostly still in one piece (768 wide, four layers of 512 tokens 125 -> 85), but five layers of 8 x 2048 tokens,
+// 128 wide (48 us), split: 260 -> 280, a training step of such sweeps 22.8 -> 24.9 ms; and from about 400 us on the
+// overlap wins (768 wide, six layers of 4096 tokens 564 -> 576, transposed 1133 -> 1215).
 constexpr double SMALL_SWEEP_US = 40.0;
 inline bool small_sweep(const Engine& E, int G) {
   if (G > E.Gc) return false;
@@ -1079,6 +1086,9 @@ struct Driver {
   //    step k: after every `chunk` steps an event hands the finished intervals to the helper lane,
   //    which runs their cf-1 dependent F-steps meanwhile; the last chunk relaxes on this stream.
   // Same kernels on the same data as the sequential order: results are identical.
+  // The chunk is the launch chunk.  Layers of few tokens have chunks of 7 to 64 intervals, often all of them: then nothing
+  // overlaps, which is right where the host's enqueueing bounds the call (64 wide, 64 tokens, training step of 64 layers,
+  // 16 intervals: 3.7 ms, in chunks of 8 4.0, of 4 5.2; 128 wide, 256 tokens, chunks of 10 5.7, of 4 6.8).
   int coarse_solve_with_relaxation(int lvl, int M, Rows R, Rows Gn) {
     AuxStream& a = aux_stream();
     const int status = coarse_solve_pipeline(lvl, M, R, Gn);

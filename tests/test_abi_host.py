@@ -249,14 +249,17 @@ def test_recompute_mode_keeps_small_chunks(dtype, d, tokens, mode):
 
 
 def test_default_groups_per_launch_follow_the_tile_model():
-    """Without a caller's choice the launch chunk comes from the GEMM tile model: 3..6 groups for bf16
-    models (5 at d = 768, where five groups of 4096 tokens fill one round of 256x256 tiles for the d-wide
-    outputs), 4 for fp32, and the workspace is sized for it."""
+    """Without a caller's choice the launch chunk of the benchmark models comes from the GEMM tile model: 3..6 groups
+    for bf16 (5 at d = 768, where five groups of 4096 tokens fill one round of 256x256 tiles for the d-wide outputs),
+    and the workspace is sized for it.  The tiny fp32 model is one of few tokens: its sweeps of four go into one launch,
+    wider ones up to 64 at a time."""
     L = mb.lib()
     for name, wl in wls.named_workloads().items():
         desc = mb.model_desc(wl)
         g = L.mgrit_default_groups_per_launch(C.byref(desc), wl.N // wl.cf)
         assert (g == 4) if wl.dtype == wls.DTYPE_F32 else (3 <= g <= 6), (name, g)
+    tiny = mb.model_desc(wls.named_workloads()["tiny_encoder"])
+    assert [L.mgrit_default_groups_per_launch(C.byref(tiny), n) for n in (1, 4, 9, 100)] == [4, 4, 9, 64]
     bert = mb.model_desc(wls.named_workloads()["bert_base"])
     assert L.mgrit_default_groups_per_launch(C.byref(bert), 16) == 5
     opts = mb.mgrit_opts(64, 1 / 64, 4, 2, 2)

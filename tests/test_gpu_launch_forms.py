@@ -109,12 +109,18 @@ def test_cross_gradients_unequal_lengths(dh, S, Sm):
 @pytest.mark.parametrize("arch,dtype,d,f,B,S,Sm,G", [
     (wls.ARCH_ENCODER, wls.DTYPE_F32, 64, 256, 2, 32, 0, 67),      # more than one launch of 64 layers, more than 128 pointers
     (wls.ARCH_CROSS, wls.DTYPE_BF16, 72, 136, 1, 33, 20, 9),       # matrices that are no multiple of the transposed tiles
-    (wls.ARCH_CAUSAL, wls.DTYPE_BF16, 128, 512, 1, 600, 0, 7),     # six layers a launch by the rule for few tokens
+    (wls.ARCH_CAUSAL, wls.DTYPE_BF16, 64, 64, 4, 128, 0, 19),      # 4096 rows a launch: 8, 8 and 3 layers
+    (wls.ARCH_ENCODER, wls.DTYPE_F32, 256, 1024, 1, 64, 0, 25),    # 16 MiB of intermediates a launch: 21 and 4 layers
+    (wls.ARCH_CAUSAL, wls.DTYPE_BF16, 128, 512, 1, 600, 0, 7),     # four would fit by that: the tile model's six and one
 ])
 def test_few_tokens_bits(arch, dtype, d, f, B, S, Sm, G, adjoint):
     wl = make(arch, dtype, d=d, H=2, f=f, B=B, S=S, Sm=Sm)
     print(f"[case] few tokens arch={arch} dtype={dtype} d={d} B={B} S={S} G={G} adjoint={adjoint}", flush=True)
     dm = DeviceModel(wl, n_layers=G, weight_std=0.05, keep_host=False)
+    rows, width = wl.tokens + B * Sm, 4 * (8 * d + f)
+    fit = min(4096 // rows, (16 << 20) // (rows * width), 64)
+    chunk = mb.lib().mgrit_default_groups_per_launch(C.byref(dm.desc), G)
+    assert chunk == min(fit, G) if fit > 6 else chunk <= 6
     together = step(dm, wl, adjoint, G)
     mb.mgrit_set_lanes(1)
     mb.mgrit_set_max_groups_per_launch(1)
@@ -125,6 +131,26 @@ def test_few_tokens_bits(arch, dtype, d, f, B, S, Sm, G, adjoint):
         mb.mgrit_set_lanes(2)
     for g in range(G):
         assert torch.isfinite(together[g]).all() and torch.equal(together[g], alone[g]), f"group {g}"
+
+
+@pytest.mark.parametrize("adjoint", [False, True])
+@pytest.mark.parametrize("arch,dtype,G", [
+    (wls.ARCH_CAUSAL, wls.DTYPE_BF16, 2), (wls.ARCH_CAUSAL, wls.DTYPE_BF16, 3),        # 33.8 and 42.5 us by the tile model
+    (wls.ARCH_CROSS, wls.DTYPE_BF16, 2), (wls.ARCH_CROSS, wls.DTYPE_BF16, 3)])
+def test_sweeps_in_one_piece_and_split(arch, dtype, G, adjoint):
+    """Sweeps that fit a launch, on either side of the line (40 us of products) from which on two lanes share them."""
+    wl = make(arch, dtype, d=512, H=8, f=2048, B=8, S=128, Sm=64)
+    print(f"[case] one piece or split arch={arch} G={G} adjoint={adjoint}", flush=True)
+    dm = DeviceModel(wl, n_layers=G, weight_std=0.05, keep_host=False)
+    out = {}
+    try:
+        for lanes in (2, 1):
+            mb.mgrit_set_lanes(lanes)
+            out[lanes] = step(dm, wl, adjoint, G)
+    finally:
+        mb.mgrit_set_lanes(2)
+    for x, y in zip(out[1], out[2]):
+        assert torch.isfinite(x).all() and torch.equal(x, y)
 
 
 @pytest.mark.parametrize("dtype,d,S,Sm,N,cf,levels,relax,lanes,mg", [
