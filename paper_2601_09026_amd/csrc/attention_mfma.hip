@@ -245,7 +245,7 @@ attn_fwd_mfma_kernel(const AttnArgs a, int slots) {
   const lds_byte* lds = (const lds_byte*)smem;
   const float c = rsqrtf((float)DH) * LOG2E;
   const int limit = (a.causal ? min(qi, a.Sk - 1) : a.Sk - 1) - 4 * lh;   // last key of this lane's query
-  float m = -INFINITY, m_before = -INFINITY, l = 0.f;    // running maximum, the same without the unit at hand, denominator
+  float m = -INFINITY, l = 0.f;                          // running maximum and denominator
   f32x16 o[DT];
 #pragma unroll
   for (int dt = 0; dt < DT; ++dt) o[dt] = splat16(0.f);
@@ -263,7 +263,6 @@ attn_fwd_mfma_kernel(const AttnArgs a, int slots) {
 #pragma unroll
     for (int i = 2; i < 16; ++i) x = fmaxf(x, s[i]);
     const float mn = fmaxf(m, half_max(x) * c);
-    if (LONG) m_before = m;
     ms = mn == -INFINITY ? 0.f : mn;                     // fully masked so far: keep exp2 finite
     corr = exp2_raw(m - ms);
     m = mn;
@@ -320,6 +319,8 @@ attn_fwd_mfma_kernel(const AttnArgs a, int slots) {
   // iterations whose two steps only meet whole units of keys that every query of the wavefront attends to
   const int whole = a.causal ? min(w_end, q_first) >> 5 : w_end >> 5;
   const int fast = LONG && whole > 2 ? (whole - 1) >> 1 : 0;
+  // first unit behind that loop, whose denominator is rounded once more: the other form does the same
+  const int hand_over = !LONG && a.Sk > 128 && whole > 2 ? (whole - 1) & ~1 : -1;
   int slot = 0, it = 0;
   if (LONG) ring_turn<2 * Stager<NW, DH>::N>(n_blk > 1);           // set 0
   if (LONG && fast > 0) {
@@ -339,7 +340,9 @@ attn_fwd_mfma_kernel(const AttnArgs a, int slots) {
       step(std::integral_constant<int, 1>{}, sb, sa);
       slot = next;
     }
-    m = m_before;                                        // the next unit is formed once more below
+    l *= corr;                                           // the next unit is formed once more below
+#pragma unroll
+    for (int dt = 0; dt < DT; ++dt) o[dt] *= corr;
   }
   for (; it < n_blk; ++it) {
     const int next = slot == (LONG ? RING : slots) - 1 ? 0 : slot + 1;
@@ -370,7 +373,11 @@ attn_fwd_mfma_kernel(const AttnArgs a, int slots) {
         s[i] = exp2_raw(fmaf(s[i], c, -ms));
         t[i & 1] += s[i];
       }
-      l = fmaf(l, corr, t[0] + t[1]);
+      const float lu = t[0] + t[1];
+      float two = l * corr;
+      if (!LONG) pin(two);                               // (a product of its own)
+      l = fmaf(l, corr, lu);
+      if (!LONG && 2 * it + rt == hand_over) l = two + lu;
 #pragma unroll
       for (int dt = 0; dt < DT; ++dt) o[dt] *= corr;
 #pragma unroll
