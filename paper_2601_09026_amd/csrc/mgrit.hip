@@ -1426,9 +1426,9 @@ int layer_step_on(const mgrit_model_desc* desc, int adjoint, int n_groups, const
   if (adjoint) STCHK(check_ptr_array(lin_state, n_groups));
   if (desc->arch == MGRIT_ARCH_CROSS && !memory) return MGRIT_INVALID_ARG;
   bool few = second_lane;
-  if (few && workspace_bytes < layer_step_bytes(desc, adjoint, n_groups, second_lane, true)) few = false;
-  const size_t need = layer_step_bytes(desc, adjoint, n_groups, second_lane, few);
+  size_t need = layer_step_bytes(desc, adjoint, n_groups, second_lane, few);
   if (need == 0) return MGRIT_INVALID_ARG;
+  if (few && workspace_bytes < need) need = layer_step_bytes(desc, adjoint, n_groups, second_lane, few = false);
   if (workspace_bytes < need) return MGRIT_WORKSPACE_TOO_SMALL;
   hipStream_t st = static_cast<hipStream_t>(stream);
 
