@@ -18,16 +18,17 @@
 // dKV pass:  S = Q K^T, dP = dO V^T, P, dA;  dV^T += dO^T P,  dK^T += Q^T dA
 // No atomics: dQ and dK/dV are separate passes, so results are bit-reproducible.
 //
-// What bounds them: the chain of a wavefront, scores - exponentials - products, with three wavefronts per SIMD at most.  In
-// a step of 8 x 512 tokens, heads of 64, the vector unit issues for 56 % of the forward kernel (a 32 x 32 unit of scores
-// is 16 exponentials of 8 clocks and about 130 other instructions of 4) and the matrix cores work for 20 %; in the backward
-// passes 24-28 % and 20-23 %; with one head of 128 the matrix cores work for 42 / 52 / 38 % (forward, dQ, dK/dV).  Sequences
-// of 128 tokens and fewer wait for memory instead.  Hence tiles straight from memory to LDS in one
-// layout that serves the plain and the transposing reads (no transposed copy, no registers in between), and no scores for
-// halves of a tile that no pair is in.  Microseconds per launch, with tiles staged through registers and
-// transposed in LDS -> now, forward / whole backward: 5 layers of 8 x 512 causal, 12 heads of 64: 47 -> 45 / 142 -> 119;
-// 5 of 64 x 197, 6 of 64: 69 -> 63 / 230 -> 177; 5 of 32 x 128, 12 of 64: 29 -> 28 / 88 -> 70; 6 of 64 x 64, 8 of 64:
-// 25 -> 24 / 70 -> 48; 4 of 8 x 2048, one of 128: 95 -> 90 / 265 -> 256.
+// What bounds them: the chain of a wavefront, scores - exponentials - products, with three wavefronts per SIMD (d_head 64;
+// the plain forward loop four) or two (128).  In a step of 8 x 512 tokens, heads of 64, the vector unit issues for 60 % of
+// the forward kernel's cycles (a 32 x 32 unit of scores is 16 exponentials of 8 clocks and about 130 other instructions
+// of 4) and the matrix cores work for 21 %; in the backward passes 26-29 % and 20-24 %; with one head of 128 the matrix
+// cores work for 42 / 51 / 53 % (forward, dQ, dK/dV).  (Counter summaries of the two shapes under profiles/, where
+// the counter of issue cycles counts in fours.)  Sequences of 128 tokens and fewer wait for memory instead.  Hence tiles
+// straight from memory to LDS in one layout that serves the plain and the transposing reads (no transposed copy, no
+// registers in between), and no scores for halves of a tile that no pair is in.  Microseconds per launch, with tiles
+// staged through registers and transposed in LDS -> now, forward / whole backward: 5 layers of 8 x 512 causal, 12 heads of
+// 64: 40 -> 39 / 137 -> 116; 5 of 64 x 197, 6 of 64: 57 -> 49 / 228 -> 170; 5 of 32 x 128, 12 of 64: 27.5 -> 26 / 82 -> 63;
+// 6 of 64 x 64, 8 of 64: 23 -> 23 / 64 -> 45; 4 of 8 x 2048, one of 128: 82 -> 78 / 262 -> 221.
 #include <type_traits>
 
 #include "common.h"

@@ -308,8 +308,8 @@ __device__ __forceinline__ void tile_epilogue(
 //  * RAGGED: N no multiple of BN or K no multiple of BK (both multiples of 8): weight rows are clamped,
 //    columns guarded, and the chunks of the last k-tile that lie past K come from a zero chunk.
 // What bounds it: large launches the matrix cores and then the epilogue, which moves 4 to 16 bytes per output
-// element with the matrix cores idle (in the step at the GPT-2 shape they are busy for 56 % of a 256x256 launch
-// with the plain store and for 37-47 % with the other epilogues: profiles/gpt2_small_fwd_adjoint_pmc_summary.txt);
+// element with the matrix cores idle (in the step at the GPT-2 shape they are busy for 55 % of a 256x256 launch
+// with the plain store and for 37-46 % with the other epilogues: profiles/gpt2_small_fwd_adjoint_pmc_summary.txt);
 // launches of up to one tile per CU the latency of first touches past the L2, which the deep ring covers.
 // ---------------------------------------------------------------------------
 // LDS has 64 four-byte banks (256 bytes per clock); a 16-byte read is served 16 lanes at a
