@@ -59,7 +59,7 @@ template <typename T> __device__ __forceinline__ void pin(T& v) { asm volatile("
 // AGAIN: the lane's offsets are formed at each use instead of kept in 3 registers per load, for the dK/dV pass at d_head
 // 128: its accumulators and own rows take 192 of 256 registers, and with the offsets kept 13 or 20 went to scratch (whole
 // backward, 4 layers of 8 x 2048, one head: 246 -> 221 us, causal 209 -> 183; 5 of 16 x 300, 6 heads: 178 -> 150).
-template <int NW, int DH, bool AGAIN = false> struct Stager {
+template <int NW, int DH, bool AGAIN = false, bool STREAM = false> struct Stager {
   using L = Lay<DH>;
   static constexpr int N = L::TILE / 1024 / NW;          // load instructions per wavefront and tile
   static_assert(N >= 1, "one load or more per wavefront");
@@ -74,7 +74,7 @@ template <int NW, int DH, bool AGAIN = false> struct Stager {
     if constexpr (AGAIN) pin(l);
     auto load = [&](int j, bool whole) {
       const int r = (wave * N + j) * L::RPI + l / L::CPR, chunk = ((l % L::CPR) ^ L::swz(r)) * 16;
-      load_to_lds(base, dst + (wave * N + j) * 1024, (whole || r < left ? r : left) * rs + chunk, 0);
+      load_to_lds<STREAM>(base, dst + (wave * N + j) * 1024, (whole || r < left ? r : left) * rs + chunk, 0);
     };
     if (left >= 63) {                                    // block-uniform
 #pragma unroll
@@ -206,7 +206,8 @@ template <int DH, int NW> constexpr int fa_waves() { return DH == 64 && NW == 4 
 // one or two sets do (`slots`).  Same operations on the same numbers in the same order: which of the two runs may
 // follow from the launch (attn_fwd_mfma_dh()).  The running maximum is exact: rescaling only when it grew by more than a
 // threshold is faster and loses 4 % of the output's precision.
-template <int NW, int DH, bool LONG>
+// STREAM: keys and values with the non-temporal hint.
+template <int NW, int DH, bool LONG, bool STREAM = false>
 __global__ void __launch_bounds__(NW * 64, (DH == 64 && !LONG ? 4 : fa_waves<DH, NW>()))
 attn_fwd_mfma_kernel(const AttnArgs a, int slots) {
   using L = Lay<DH>;
@@ -223,7 +224,7 @@ attn_fwd_mfma_kernel(const AttnArgs a, int slots) {
   const int k_end = a.causal ? min(a.Sk, min(q0 + NW * 32, a.Sq)) : a.Sk;        // keys the block needs
   const int w_end = q_first >= a.Sq ? 0 : a.causal ? min(a.Sk, q_first + 32) : a.Sk;   // ... and the wavefront
   const int n_blk = (k_end + 63) >> 6;
-  const Stager<NW, DH> sk(a.k_row_stride, wave, lane), sv(a.v_row_stride, wave, lane);
+  const Stager<NW, DH, false, STREAM> sk(a.k_row_stride, wave, lane), sv(a.v_row_stride, wave, lane);
   auto stage = [&](int slot, int it) {
     sk.issue(smem + slot * 2 * L::TILE, P.K, it * 64, a.Sk);
     sv.issue(smem + slot * 2 * L::TILE + L::TILE, P.V, it * 64, a.Sk);
@@ -762,6 +763,12 @@ static hipError_t attn_fwd_mfma_dh(const AttnArgs& a, hipStream_t st) {
   else if (at_once(RING) || (DH == 64 && rows == 128 && (a.causal ? (a.Sk + 128) / 2 : a.Sk) > 448)) sets = RING;
   else sets = DH == 128 && (at_once(2) || (rows == 128 && a.Sk >= 512)) ? 2 : 1;
   const bool pipelined = sets == RING;
+  // One block of queries per head reads its keys and values once.  Where they exceed the memory-side cache (256 MB) by far,
+  // such launches are bound by HBM and faster if nothing is kept: 2048 heads of 64, 64 queries on 2048 keys (1.07 GB) 226 -> 201
+  // us, 16 on 800 (0.42 GB) 85 -> 76; d_head 128, 1024 heads, 64 on 2048 213 -> 183.  At 0.27 GB 49 -> 50, below up to 30 % slower.
+  const double kv_bytes = 4.0 * a.Sk * DH * a.B * a.H * a.n_groups;
+  if (rows == 64 && !pipelined && kv_bytes > 300e6)
+    return launch_ring<DH>(attn_fwd_mfma_kernel<2, DH, false, true>, 64, a.Sq, a.Sk, a, st, sets);
   if (rows == 64)
     return launch_ring<DH>(pipelined ? attn_fwd_mfma_kernel<2, DH, true> : attn_fwd_mfma_kernel<2, DH, false>, 64, a.Sq, a.Sk,
                            a, st, sets);

@@ -142,10 +142,11 @@ __device__ __forceinline__ __amdgpu_buffer_rsrc_t lds_source(const void* base) {
   const unsigned lo = __builtin_amdgcn_readfirstlane((unsigned)p), hi = __builtin_amdgcn_readfirstlane((unsigned)(p >> 32));
   return __builtin_amdgcn_make_buffer_rsrc((void*)((unsigned long)hi << 32 | lo), 0, 0xffffffffu, 0x00020000);
 }
+template <bool STREAM = false>                             // non-temporal: read once, not to be kept in the caches
 __device__ __forceinline__ void load_to_lds(__amdgpu_buffer_rsrc_t src, unsigned char* dst, int lane_offset,
                                             int scalar_offset) {
   __builtin_amdgcn_raw_ptr_buffer_load_lds(src, (__attribute__((address_space(3))) void*)dst, 16, lane_offset,
-                                           scalar_offset, 0, 0);
+                                           scalar_offset, 0, STREAM ? 2 : 0);
 }
 
 template <int N> __device__ __forceinline__ void wait_vmcnt() {

@@ -73,9 +73,11 @@ def test_attention_edges_bf16(arch, dh, S, Sm):
     (64, wls.ARCH_CROSS, 16, 40, 200, (1, 6, 7)),        # 128 blocks of 64 queries
     (128, wls.ARCH_CROSS, 16, 64, 330, (4, 5, 9)),       # 64 blocks: three sets up to 256, two up to 512, then one
     (128, wls.ARCH_CROSS, 16, 100, 190, (4, 8, 9)),
+    (64, wls.ARCH_CROSS, 16, 24, 1030, (1, 9)), (128, wls.ARCH_CROSS, 16, 24, 1030, (1, 9)),  # 304 MB of keys and values
 ])
 def test_attention_ring_bits(dh, arch, B, S, Sm, counts):
-    """How many tile sets a block of attention gets follows from the launch and must not show in the result."""
+    """How many tile sets a block of attention gets, and with which hint it loads, follows from the launch and must not
+    show in the result."""
     wl = make(arch, wls.DTYPE_BF16, d=512, H=512 // dh, f=64, B=B, S=S, Sm=Sm)
     print(f"[case] attention rings dh={dh} arch={arch} B={B} S={S} Sm={Sm}", flush=True)
     G = max(counts)
