@@ -428,7 +428,7 @@ void mgrit_set_adjoint_cache(int on);
  * 5 other elementwise, 8+e MFMA grouped GEMM with epilogue e launched over
  * several groups (relaxation sweeps), 16+e the same over a single group (the serial coarse
  * chain); e: 0 store, 1 bias+GELU, 2 sublayer sum, 3 Euler update, 4 multiply by GELU',
- * 5 fp32 store, 6 GELU' of the cache pass.
+ * 5 fp32 store, 6 GELU' of the cache pass; 24 the row-local chains of narrow layers.
  * Returns 0, -1 for a bad class, -3 if the pool overflowed. */
 int  mgrit_profile_enable(int max_records);
 void mgrit_profile_reset(void);

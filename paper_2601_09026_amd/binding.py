@@ -280,6 +280,7 @@ PROFILE_CLASSES = {0: "gemm_generic", 1: "attn_fwd", 2: "attn_bwd", 3: "ln_fwd",
 # the same epilogues launched over a single group (the serial coarse chain)
 PROFILE_CLASSES.update({c + 8: n.replace("gemm_mfma_", "gemm_mfma_single_") for c, n in list(PROFILE_CLASSES.items())
                         if c >= 8})
+PROFILE_CLASSES[24] = "chain"
 
 
 def mgrit_profile_enable(max_records: int) -> None:

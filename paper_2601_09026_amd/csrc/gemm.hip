@@ -1243,6 +1243,7 @@ static int g_tile_cfg = 0;                 // 0 = choose by shape
 static int g_grad_slices = 0;              // the same
 void gemm_force_simple(int on) { g_force_simple = on; }
 void gemm_set_tile_config(int cfg) { g_tile_cfg = cfg; }
+bool gemm_forced() { return g_force_simple || g_tile_cfg; }
 void gemm_set_grad_slices(int n) { g_grad_slices = n > 0 ? n : 0; }
 
 // Compute units of the current device (256 if the query fails).

@@ -11,6 +11,7 @@ size_t gemm_tn_partial_floats(int n_groups, int M, int N, int K, bool is_bf16); 
 void gemm_force_simple(int on);
 void gemm_set_tile_config(int cfg);
 void gemm_set_grad_slices(int n);
+bool gemm_forced();                                         // a test hook chooses the products' kernels
 double gemm_model_cost(int n_groups, int M, int N, int K);
 int compute_units();                                        // of the current device
 void attn_set_wide_blocks(int mask);
@@ -74,6 +75,43 @@ hipError_t upload_tables(void** tab, const PtrSource* src, int n_src, int n, hip
 // out_g[c, r] = in_g[r, c] for every group and every matrix of the list (at most 7 per block: byte offset, shape)
 struct TransposeList { int n; int rows[7], cols[7], tiles[7]; long off[7]; };
 hipError_t launch_transpose(int n_groups, Params in, Params out, const TransposeList& l, int elem_bytes, hipStream_t st);
+
+// ---- chain.hip (bf16, d = 64 or 128) -------------------------------------------
+struct ChainHeadArgs {
+  int n_groups, T;
+  Rows X;
+  Params P; long g_off, be_off, w_off, b_off;
+  void* out; Slots out_slots;                             // [slot, T, 3d]
+  Slots cs; void* xhat; float* rstd; void* u;             // optional: cache entries (slots cs)
+  float eps;
+};
+struct ChainTailArgs {
+  int n_groups, T, f;
+  const void* o; long o_slot_stride; Slots o_slots;       // attention output
+  Rows X, OUT, RHS;
+  const float* base; long base_slot_stride; Slots base_slots;   // optional fp32 addend of ybar
+  Params P; long wo_off, bo_off, g_off, be_off, w1_off, b1_off, w2_off, b2_off;
+  float hstep, rhs_sign, eps;
+  Slots cs; void *xhat, *dact; float* rstd;               // modes 1, 2: cache entries (slots cs) ...
+  float* ybar; void *u, *act;                             // ... and those that parameter gradients need, or null
+};
+// mode 0: the step; 1: the cache entries alone; 2: both
+hipError_t launch_chain_tail(const ChainTailArgs& a, int d, int mode, hipStream_t st);
+hipError_t launch_chain_head(const ChainHeadArgs& a, int d, hipStream_t st);
+struct ChainAdjointArgs {
+  int n_groups, T, f;
+  const void* c; Slots c_slots;                           // tail: operand-type copy of IN, or null: formed here ...
+  void* c_out;                                            // ... and left in slots loc
+  Rows IN, OUT, RHS;                                      // head: without OUT du alone
+  Params P, PT; long g_off, w1_off, w2_off, wo_off, wqkv_off;   // PT: matrices stored transposed
+  Slots cs; const void *dact, *xhat; const float* rstd;   // cache entries
+  Slots loc; void *dz, *du, *ds, *da; float* dx; const void* dqkv;   // work buffers; dz, du, ds may be null in the tail, du in the head
+  void* out_cast; Slots oc_slots;
+  float hstep, rhs_sign;
+};
+hipError_t launch_chain_adjoint_tail(const ChainAdjointArgs& a, int d, hipStream_t st);
+hipError_t launch_chain_adjoint_head(const ChainAdjointArgs& a, int d, hipStream_t st);
+bool chain_ok(int d, int f, int T, bool is_bf16);
 
 // ---- grads.hip ---------------------------------------------------------------
 // LayerNorm gain / shift gradients of up to three LayerNorms of the same layers: sums over tokens of

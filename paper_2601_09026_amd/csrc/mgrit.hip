@@ -196,6 +196,7 @@ struct Engine {
   bool bf16;
   int T, Tm, d, f, H, dh;
   size_t esz;                      // operand element size
+  bool chain;                      // narrow layers: what is local to a row runs as one launch on either side of attention
   hipStream_t st;
   int Gc;                          // groups per launch chunk
   // forward work buffers, Gc slots each
@@ -240,6 +241,7 @@ struct Engine {
     bf16 = m->dtype == MGRIT_DTYPE_BF16;
     T = m->batch * m->seq; Tm = m->batch * m->mem_seq; d = m->d_model; f = m->d_ff; H = m->n_heads;
     dh = d / H; esz = bf16 ? 2 : 4; st = s;
+    chain = !gemm_forced() && chain_ok(d, f, T, bf16);
     mgrit_model_desc m32 = *m;
     m32.dtype = MGRIT_DTYPE_F32;
     compute_layout(&m32, &glay);
@@ -457,12 +459,23 @@ int forward_chunk(Engine& E, int n, Rows IN, Rows OUT, Rows RHS, Params TH, floa
   ln.gamma_off = L.offset[MGRIT_P_LN1_G]; ln.beta_off = L.offset[MGRIT_P_LN1_B];
   ln.out = u1; ln.out_slot_stride = E.Td(); ln.out_slots = us; ln.eps = E.md.ln_eps;
   if (cache) { ln.xhat = E.c_xh1; ln.xhat_slot_stride = E.Td(); ln.xhat_slots = cs; ln.rstd = E.c_rs1; }
-  HIPCHK(launch_ln_fwd(ln, E.bf16, E.st));
+  GemmArgs g;
+  if (E.chain) {
+    ChainHeadArgs h;
+    memset(&h, 0, sizeof(h));
+    h.n_groups = n; h.T = T; h.X = IN; h.P = TH; h.g_off = ln.gamma_off; h.be_off = ln.beta_off; h.eps = ln.eps;
+    h.w_off = L.offset[MGRIT_P_WQKV]; h.b_off = L.offset[MGRIT_P_BQKV];
+    h.out = qkv; h.out_slots = cs; h.cs = cs;
+    if (cache) { h.xhat = E.c_xh1; h.rstd = E.c_rs1; }
+    if (keep) h.u = E.c_u1;
+    HIPCHK(launch_chain_head(h, d, E.st));
+  } else {
+    HIPCHK(launch_ln_fwd(ln, E.bf16, E.st));
+    g = gemm_base(n, T, 3 * d, d, u1, E.Td(), us, TH, L.offset[MGRIT_P_WQKV], L.offset[MGRIT_P_BQKV]);
+    g.out = qkv; g.out_slot_stride = (long)T * 3 * d; g.out_slots = cs;
+    HIPCHK(launch_gemm(g, EPI_STORE, E.bf16, E.st));
+  }
   ln.xhat = nullptr; ln.rstd = nullptr;
-
-  GemmArgs g = gemm_base(n, T, 3 * d, d, u1, E.Td(), us, TH, L.offset[MGRIT_P_WQKV], L.offset[MGRIT_P_BQKV]);
-  g.out = qkv; g.out_slot_stride = (long)T * 3 * d; g.out_slots = cs;
-  HIPCHK(launch_gemm(g, EPI_STORE, E.bf16, E.st));
 
   AttnArgs at;
   memset(&at, 0, sizeof(at));
@@ -478,6 +491,22 @@ int forward_chunk(Engine& E, int n, Rows IN, Rows OUT, Rows RHS, Params TH, floa
 
   const bool cross = E.md.arch == MGRIT_ARCH_CROSS;
   float* x3 = cache ? E.c_x3 : E.x3;
+  auto tail = [&](const void* o, int w_id, int b_id, const float* base) -> int {
+    ChainTailArgs t;
+    memset(&t, 0, sizeof(t));
+    t.n_groups = n; t.T = T; t.f = f; t.o = o; t.o_slot_stride = E.Td(); t.o_slots = cs;
+    t.base = base; t.base_slot_stride = E.Td(); t.base_slots = cs;
+    t.X = IN; t.OUT = OUT; t.RHS = RHS; t.hstep = hstep; t.rhs_sign = E.rhs_sign; t.eps = E.md.ln_eps; t.P = TH;
+    t.wo_off = L.offset[w_id]; t.bo_off = L.offset[b_id];
+    t.g_off = L.offset[MGRIT_P_LN2_G]; t.be_off = L.offset[MGRIT_P_LN2_B];
+    t.w1_off = L.offset[MGRIT_P_W1]; t.b1_off = L.offset[MGRIT_P_B1]; t.w2_off = L.offset[MGRIT_P_W2]; t.b2_off = L.offset[MGRIT_P_B2];
+    t.cs = cs;
+    if (cache) { t.xhat = E.c_xh2; t.rstd = E.c_rs2; t.dact = E.c_z; }
+    if (keep) { t.ybar = E.c_xin; t.u = E.c_u2; t.act = E.c_act; }
+    HIPCHK(launch_chain_tail(t, d, cache, E.st));
+    return MGRIT_OK;
+  };
+  if (E.chain && !cross) return tail(ob, MGRIT_P_WO, MGRIT_P_BO, nullptr);
   // s = SA(LN1(X)) kept in fp32 (never X + s: the Euler sum must not lose the small increment)
   g = gemm_base(n, T, d, d, ob, E.Td(), cs, TH, L.offset[MGRIT_P_WO], L.offset[MGRIT_P_BO]);
   g.out = cross ? x3 : xin; g.out_slot_stride = E.Td(); g.out_slots = cs;
@@ -506,6 +535,7 @@ int forward_chunk(Engine& E, int n, Rows IN, Rows OUT, Rows RHS, Params TH, floa
     at.o = oc; at.o_row_stride = d; at.o_slot_stride = E.Td(); at.o_slots = cs;
     if (cache) { at.lse = E.c_lsec; at.lse_slot_stride = (long)E.md.batch * E.H * E.md.seq; at.lse_slots = cs; }
     HIPCHK(launch_attn_fwd(at, E.bf16, E.st));
+    if (E.chain) return tail(oc, MGRIT_P_WO_C, MGRIT_P_BO_C, x3);
     g = gemm_base(n, T, d, d, oc, E.Td(), cs, TH, L.offset[MGRIT_P_WO_C], L.offset[MGRIT_P_BO_C]);
     g.base = x3; g.base_slot_stride = E.Td(); g.base_slots = cs;
     g.out = xin; g.out_slot_stride = E.Td(); g.out_slots = cs;
@@ -590,41 +620,57 @@ int adjoint_chunk(Engine& E, int n, Rows IN, Rows OUT, Rows RHS, Params TH, Para
   const auto& L = E.lay;
   const size_t esz = E.esz;
 
+  const bool cross = E.md.arch == MGRIT_ARCH_CROSS;
   const void* cbuf = E.cb;                 // operand-type copy of the inputs
   Slots cbs = loc;
-  if (sh && sh->have_inputs(n)) { cbuf = sh->in; cbs = sh->in_slots; }
-  else HIPCHK(launch_cast_rows(n, E.Td(), IN, E.cb, E.Td(), loc, E.bf16, E.st));
-
-  // dz = (c W2) * gelu'(z)        [T,d] x [d,f]: transposed W2 is [f,d]; gelu'(z) comes from the cache
-  GemmArgs g = gemm_base(n, T, f, d, cbuf, E.Td(), cbs, THT, L.offset[MGRIT_P_W2], -1);
-  g.out = E.dz; g.out_slot_stride = (long)T * f; g.out_slots = loc;
-  g.aux = E.c_z; g.aux_slot_stride = (long)T * f; g.aux_slots = cs;
-  HIPCHK(launch_gemm(g, EPI_DGELU, E.bf16, E.st));
-
-  // du2 = dz W1                   [T,f] x [f,d]: transposed W1 is [d,f]
-  g = gemm_base(n, T, d, f, E.dz, (long)T * f, loc, THT, L.offset[MGRIT_P_W1], -1);
-  g.out = E.du; g.out_slot_stride = E.Td(); g.out_slots = loc;
-  HIPCHK(launch_gemm(g, EPI_STORE, E.bf16, E.st));
-
-  // dX' = LN2^T du2 ;  ds = c + dX'
+  const bool have = sh && sh->have_inputs(n);
+  if (have) { cbuf = sh->in; cbs = sh->in_slots; }
+  GemmArgs g;
   LnBwdArgs lb;
-  memset(&lb, 0, sizeof(lb));
-  lb.n_groups = n; lb.T = T; lb.d = d; lb.eps = E.md.ln_eps;
-  lb.dy = E.du; lb.dy_slot_stride = E.Td(); lb.dy_slots = loc;
-  lb.xhat = E.c_xh2; lb.xhat_slot_stride = E.Td(); lb.xhat_slots = cs; lb.rstd = E.c_rs2;   // LN2 input X + ybar
-  lb.P = TH; lb.gamma_off = L.offset[MGRIT_P_LN2_G];
-  lb.out_f32 = E.dxin; lb.of_slot_stride = E.Td(); lb.of_slots = loc;
-  lb.cop = cbuf; lb.cop_slot_stride = E.Td(); lb.cop_slots = cbs;
-  const bool cross = E.md.arch == MGRIT_ARCH_CROSS;
-  lb.out_op = cross ? E.dsc : E.ds; lb.oo_slot_stride = E.Td(); lb.oo_slots = loc;
-  HIPCHK(launch_ln_bwd(lb, E.bf16, E.st));
+  ChainAdjointArgs ch;
+  if (E.chain) {
+    memset(&ch, 0, sizeof(ch));
+    ch.n_groups = n; ch.T = T; ch.f = f; ch.IN = IN; ch.P = TH; ch.PT = THT; ch.g_off = L.offset[MGRIT_P_LN2_G];
+    if (have) { ch.c = cbuf; ch.c_slots = cbs; }
+    ch.w1_off = L.offset[MGRIT_P_W1]; ch.w2_off = L.offset[MGRIT_P_W2]; ch.wqkv_off = L.offset[MGRIT_P_WQKV];
+    ch.wo_off = L.offset[cross ? MGRIT_P_WO_C : MGRIT_P_WO];
+    ch.cs = cs; ch.dact = E.c_z; ch.xhat = E.c_xh2; ch.rstd = E.c_rs2;
+    ch.loc = loc; ch.da = E.da; ch.dx = E.dxin;
+    if (gp) { ch.c_out = E.cb; ch.dz = E.dz; ch.du = E.du; ch.ds = cross ? E.dsc : E.ds; }
+    HIPCHK(launch_chain_adjoint_tail(ch, d, E.st));
+  } else {
+    if (!have) HIPCHK(launch_cast_rows(n, E.Td(), IN, E.cb, E.Td(), loc, E.bf16, E.st));
+    // dz = (c W2) * gelu'(z)        [T,d] x [d,f]: transposed W2 is [f,d]; gelu'(z) comes from the cache
+    g = gemm_base(n, T, f, d, cbuf, E.Td(), cbs, THT, L.offset[MGRIT_P_W2], -1);
+    g.out = E.dz; g.out_slot_stride = (long)T * f; g.out_slots = loc;
+    g.aux = E.c_z; g.aux_slot_stride = (long)T * f; g.aux_slots = cs;
+    HIPCHK(launch_gemm(g, EPI_DGELU, E.bf16, E.st));
+
+    // du2 = dz W1                   [T,f] x [f,d]: transposed W1 is [d,f]
+    g = gemm_base(n, T, d, f, E.dz, (long)T * f, loc, THT, L.offset[MGRIT_P_W1], -1);
+    g.out = E.du; g.out_slot_stride = E.Td(); g.out_slots = loc;
+    HIPCHK(launch_gemm(g, EPI_STORE, E.bf16, E.st));
+
+    // dX' = LN2^T du2 ;  ds = c + dX'
+    memset(&lb, 0, sizeof(lb));
+    lb.n_groups = n; lb.T = T; lb.d = d; lb.eps = E.md.ln_eps;
+    lb.dy = E.du; lb.dy_slot_stride = E.Td(); lb.dy_slots = loc;
+    lb.xhat = E.c_xh2; lb.xhat_slot_stride = E.Td(); lb.xhat_slots = cs; lb.rstd = E.c_rs2;   // LN2 input X + ybar
+    lb.P = TH; lb.gamma_off = L.offset[MGRIT_P_LN2_G];
+    lb.out_f32 = E.dxin; lb.of_slot_stride = E.Td(); lb.of_slots = loc;
+    lb.cop = cbuf; lb.cop_slot_stride = E.Td(); lb.cop_slots = cbs;
+    lb.out_op = cross ? E.dsc : E.ds; lb.oo_slot_stride = E.Td(); lb.oo_slots = loc;
+    HIPCHK(launch_ln_bwd(lb, E.bf16, E.st));
+  }
 
   if (cross) {
     // Here dsc = c + dx2 is the cotangent of ybar = s + CA(LN3(Y + s), E); dxin = dx2.
     // do_c = dsc Wo_c
-    g = gemm_base(n, T, d, d, E.dsc, E.Td(), loc, THT, L.offset[MGRIT_P_WO_C], -1);
-    g.out = E.da; g.out_slot_stride = E.Td(); g.out_slots = loc;
-    HIPCHK(launch_gemm(g, EPI_STORE, E.bf16, E.st));
+    if (!E.chain) {
+      g = gemm_base(n, T, d, d, E.dsc, E.Td(), loc, THT, L.offset[MGRIT_P_WO_C], -1);
+      g.out = E.da; g.out_slot_stride = E.Td(); g.out_slots = loc;
+      HIPCHK(launch_gemm(g, EPI_STORE, E.bf16, E.st));
+    }
     // cross-attention backward: lambda needs dQ only; dK, dV feed the gradients of Wkv_c and of the memory
     AttnArgs ac;
     memset(&ac, 0, sizeof(ac));
@@ -668,9 +714,11 @@ int adjoint_chunk(Engine& E, int n, Rows IN, Rows OUT, Rows RHS, Params TH, Para
   }
 
   // da = ds Wo
-  g = gemm_base(n, T, d, d, E.ds, E.Td(), loc, THT, L.offset[MGRIT_P_WO], -1);
-  g.out = E.da; g.out_slot_stride = E.Td(); g.out_slots = loc;
-  HIPCHK(launch_gemm(g, EPI_STORE, E.bf16, E.st));
+  if (!E.chain || cross) {
+    g = gemm_base(n, T, d, d, E.ds, E.Td(), loc, THT, L.offset[MGRIT_P_WO], -1);
+    g.out = E.da; g.out_slot_stride = E.Td(); g.out_slots = loc;
+    HIPCHK(launch_gemm(g, EPI_STORE, E.bf16, E.st));
+  }
 
   // attention backward
   AttnArgs at;
@@ -688,6 +736,16 @@ int adjoint_chunk(Engine& E, int n, Rows IN, Rows OUT, Rows RHS, Params TH, Para
   at.dqkv_row_stride = 3 * d; at.dqkv_slot_stride = (long)T * 3 * d; at.dqkv_slots = loc;
   at.D = E.Dbuf; at.D_slot_stride = (long)E.md.batch * E.H * E.md.seq; at.D_slots = loc;
   HIPCHK(launch_attn_bwd(at, E.bf16, E.st));
+
+  if (E.chain) {
+    const bool write = !gp || gp->write_state;
+    ch.g_off = L.offset[MGRIT_P_LN1_G]; ch.xhat = E.c_xh1; ch.rstd = E.c_rs1; ch.dqkv = E.dqkv;
+    ch.du = gp ? E.du1 : nullptr;
+    if (write) { ch.OUT = OUT; ch.RHS = RHS; ch.hstep = hstep; ch.rhs_sign = E.rhs_sign; }
+    if (write && sh && sh->out) { ch.out_cast = sh->out; ch.oc_slots = sh->out_slots; }
+    HIPCHK(launch_chain_adjoint_head(ch, d, E.st));
+    return MGRIT_OK;
+  }
 
   // du1 = dqkv Wqkv               [T,3d] x [3d,d]: transposed Wqkv is [d,3d]
   g = gemm_base(n, T, d, 3 * d, E.dqkv, (long)T * 3 * d, loc, THT, L.offset[MGRIT_P_WQKV], -1);

@@ -10,7 +10,8 @@ enum ProfClass : int {
   PC_LN_FWD_SINGLE = 6, PC_LN_BWD_SINGLE = 7,   // LayerNorm launches over a single group (coarse chain)
   PC_GEMM_MFMA = 8,          // + epilogue id (0..6): launches over several groups (relaxation sweeps)
   PC_GEMM_MFMA_SINGLE = 16,  // + epilogue id: one group per launch (the serial coarse chain)
-  PC_COUNT = 24
+  PC_CHAIN = 24,             // row-local chains of a narrow layer
+  PC_COUNT = 25
 };
 
 bool prof_enabled();

@@ -1,0 +1,152 @@
+"""Layers 64 and 128 wide in bf16 run what is local to a token row as one launch on either side of attention.  These
+launches against the general path (one launch per operator, chosen by the hook that fixes the products' tiles) at the
+edges of their tiles: 32 rows a wavefront, 64 or 128 a block, chunks of 64 hidden features, ring of eight weight tiles.
+
+Bound: both paths round the same intermediates to bf16 and differ in the order of fp32 sums, so an operand differs by at most
+one rounding step, 2^-8 of its value, and so does an increment normwise (measured for one step: 1e-6 to 1e-4).  In a training
+step such differences come in once more with each solve: one step for Z, two for lambda, whose operands differ and which is
+linearised at states that do, three for the gradients formed from both.  (The general path alone moves lambda by 3.7e-3
+when 1e-5 is added to every Z; the paths differ by 4.0e-3 there.)"""
+import pytest
+import torch
+
+from paper_2601_09026_amd import binding as mb
+from paper_2601_09026_amd import workloads as wls
+
+from gpu_util import DeviceModel, dev
+from test_gpu_layer_step import make
+from test_gpu_param_grads import grad_blocks
+
+pytestmark = pytest.mark.gpu
+STEP = 2.0 ** -8
+
+
+def both_paths(run):
+    out = []
+    for cfg in (0, 4):
+        mb.lib().mgrit_debug_gemm_tile_config(cfg)
+        try:
+            out.append(run())
+        finally:
+            mb.lib().mgrit_debug_gemm_tile_config(0)
+    return out
+
+
+def close(a, b, base, what, roundings=1):
+    a, b, base = a.double(), b.double(), base.double()
+    assert torch.isfinite(a).all(), what
+    assert (a - b).norm() <= roundings * STEP * (b - base).norm(), f"{what}: {(a - b).norm() / (b - base).norm():.2e}"
+
+
+def states(wl, G, seed):
+    gen = torch.Generator(device="cuda")
+    gen.manual_seed(seed)
+    return [list(torch.randn((G, wl.tokens, wl.d_model), generator=gen, device="cuda")) for _ in range(3)]
+
+
+def steps(dm, wl, adjoint, ins, lin, rhs):
+    mem = wls.cross_memory(wl)
+    outs = [torch.full_like(x, float("nan")) for x in ins]
+    mb.layer_step_batched(dm.desc, adjoint, ins, outs, dm.blocks, 0.5, lin_state=lin if adjoint else None, rhs=rhs,
+                          memory=None if mem is None else dev(mem))
+    torch.cuda.synchronize()
+    return outs
+
+
+@pytest.mark.parametrize("adjoint", [False, True])
+@pytest.mark.parametrize("arch,d,H,f,B,S,Sm,G,rhs", [
+    (wls.ARCH_ENCODER, 64, 1, 64, 1, 1, 0, 1, False),         # one token, one chunk: fewer tiles than the ring has slots
+    (wls.ARCH_CAUSAL, 64, 4, 128, 1, 31, 0, 2, True),
+    (wls.ARCH_ENCODER, 64, 1, 192, 1, 33, 0, 3, False),
+    (wls.ARCH_CROSS, 64, 2, 256, 3, 43, 7, 2, True),          # 129 rows
+    (wls.ARCH_ENCODER, 64, 1, 512, 2, 64, 0, 1, False),
+    (wls.ARCH_ENCODER, 64, 2, 2048, 16, 129, 0, 1, True),     # 2064 tokens, the widest hidden layer
+    (wls.ARCH_CAUSAL, 128, 1, 64, 1, 32, 0, 1, True),
+    (wls.ARCH_ENCODER, 128, 2, 128, 1, 63, 0, 3, False),
+    (wls.ARCH_CROSS, 128, 2, 192, 1, 127, 33, 2, True),
+    (wls.ARCH_CAUSAL, 128, 4, 256, 1, 128, 0, 2, False),
+    (wls.ARCH_ENCODER, 128, 1, 128, 4, 4096, 0, 2, True),     # 256 blocks of 128 rows
+    (wls.ARCH_CAUSAL, 128, 2, 512, 8, 257, 0, 5, True),       # 2056 tokens: wide hidden layers from 2048 on
+])
+def test_steps_match_general_path(arch, d, H, f, B, S, Sm, G, rhs, adjoint):
+    wl = make(arch, wls.DTYPE_BF16, d=d, H=H, f=f, B=B, S=S, Sm=Sm)
+    print(f"[case] chain steps arch={arch} d={d} f={f} B={B} S={S} Sm={Sm} G={G} adjoint={adjoint}", flush=True)
+    dm = DeviceModel(wl, n_layers=G, weight_std=0.08, keep_host=False)
+    ins, lin, r = states(wl, G, 5)
+    chain, general = both_paths(lambda: steps(dm, wl, adjoint, ins, lin, r if rhs else None))
+    for g in range(G):
+        close(chain[g], general[g], ins[g] + r[g] if rhs else ins[g], f"group {g}")
+
+
+@pytest.mark.parametrize("arch,d,H,f,S,Sm,N,cf,levels", [
+    (wls.ARCH_ENCODER, 64, 1, 128, 36, 0, 16, 4, 2),
+    (wls.ARCH_CAUSAL, 128, 2, 256, 68, 0, 8, 2, 3),
+    (wls.ARCH_CROSS, 128, 1, 64, 20, 44, 8, 4, 2),
+    (wls.ARCH_CAUSAL, 64, 2, 64, 132, 0, 5, 1, 1),            # serial: gradients beside the chain of steps
+])
+@pytest.mark.parametrize("cache", [True, False])
+def test_training_matches_general_path(arch, d, H, f, S, Sm, N, cf, levels, cache):
+    """Both solves with every gradient, from the linearisation cache and with the internals recomputed."""
+    iters = 2 if levels > 1 else 0
+    wl = wls.Workload("t", arch, d, H, f, 2, S, Sm, N, 0.5, cf, levels, iters, wls.DTYPE_BF16, 17)
+    print(f"[case] chain training arch={arch} d={d} f={f} S={S} N={N} cf={cf} L={levels} cache={cache}", flush=True)
+    dm = DeviceModel(wl, weight_std=0.08, keep_host=False)
+    opts = mb.mgrit_opts(N, wl.h, cf, levels, iters)
+    mem = wls.cross_memory(wl)
+    mem = None if mem is None else dev(mem)
+    Z0, lamN = dev(wls.initial_state(wl)), dev(wls.terminal_adjoint(wl))
+
+    def run():
+        Z, _ = mb.mgrit_forward(dm.desc, opts, Z0, dm.blocks, memory=mem)
+        gb, dE = grad_blocks(dm.desc, N), None if mem is None else torch.full_like(mem, float("nan"))
+        lam, _ = mb.mgrit_adjoint(dm.desc, opts, Z, dm.blocks, lamN, memory=mem, dtheta=gb, dmemory=dE)
+        torch.cuda.synchronize()
+        return [Z, lam] + [b.view(torch.float32) for b in gb] + ([] if dE is None else [dE])
+
+    mb.mgrit_set_adjoint_cache(cache)
+    try:
+        chain, general = both_paths(run)
+    finally:
+        mb.mgrit_set_adjoint_cache(True)
+    close(chain[0][1:], general[0][1:], Z0.expand_as(chain[0][1:]), "Z")
+    close(chain[1][:-1], general[1][:-1], lamN.expand_as(chain[1][:-1]), "lambda", 2)
+    for i, (x, y) in enumerate(zip(chain[2:], general[2:])):
+        written = torch.isfinite(y)                           # (padding between the parameters is not)
+        close(x[written], y[written], torch.zeros_like(y[written]), f"gradient {i}", 3)
+
+
+@pytest.mark.parametrize("adjoint", [False, True])
+@pytest.mark.parametrize("d,f,B,S,G", [(64, 256, 8, 512, 5), (128, 128, 8, 512, 5)])
+def test_block_size_does_not_show(d, f, B, S, G, adjoint):
+    """One layer a launch runs on blocks of 64 rows, five on blocks of 128."""
+    wl = make(wls.ARCH_CAUSAL, wls.DTYPE_BF16, d=d, H=1, f=f, B=B, S=S)
+    print(f"[case] chain block size d={d} f={f} B={B} S={S} G={G} adjoint={adjoint}", flush=True)
+    dm = DeviceModel(wl, n_layers=G, weight_std=0.08, keep_host=False)
+    ins, lin, rhs = states(wl, G, 6)
+    out = []
+    mb.mgrit_set_lanes(1)
+    try:
+        for n in (1, G):
+            mb.mgrit_set_max_groups_per_launch(n)
+            out.append(steps(dm, wl, adjoint, ins, lin, rhs))
+    finally:
+        mb.mgrit_set_max_groups_per_launch(0)
+        mb.mgrit_set_lanes(2)
+    for x, y in zip(*out):
+        assert torch.isfinite(x).all() and torch.equal(x, y)
+
+
+@pytest.mark.parametrize("d,f", [(64, 128), (128, 128)])
+def test_non_finite_rows_stay_where_they_are(d, f):
+    """Single-token sequences: what is not finite in one row shows in that row, as on the general path, and nowhere else."""
+    wl = make(wls.ARCH_ENCODER, wls.DTYPE_BF16, d=d, H=1, f=f, B=70, S=1)
+    print(f"[case] chain non-finite d={d}", flush=True)
+    dm = DeviceModel(wl, n_layers=1, weight_std=0.08, keep_host=False)
+    ins, lin, _ = states(wl, 1, 7)
+    for t, v in ((ins, float("nan")), (lin, float("inf"))):
+        t[0][3, 5] = v
+        t[0][69, d - 1] = -float("inf")
+    for adjoint in (False, True):
+        chain, general = both_paths(lambda: steps(dm, wl, adjoint, ins, lin, None)[0])
+        assert torch.equal(torch.isfinite(chain), torch.isfinite(general))
+        assert torch.isfinite(chain).all(dim=1).sum() == 68
