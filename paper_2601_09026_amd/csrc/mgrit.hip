@@ -822,29 +822,30 @@ int param_grads_chunk(Engine& E, int n, Params THT, Rows LIN, Slots cs, float hs
   return MGRIT_OK;
 }
 
-// A sweep that fits one launch chunk and whose products take less than the host needs to enqueue a second chain of
-// launches (about 8 kernels and the events of the fork and join, 3-4 us each) stays in one piece.  The measure is the
-// four products of an encoder's forward step alone, whatever the sweep runs (bf16 from the tile model, fp32 at 100 TFLOP/s
-// and 3 us a launch): attention, cross attention and the transposed products add to both sides alike.
-// Whole calls, split and in one piece (with the larger chunks above): four layers of 64 tokens, fp32, 111 -> 37 us;
-// transposed steps of 6 layers of 462 tokens, 320 wide, 235 -> 103 us; training step of 16 layers of 64 tokens
-// 3.41 -> 2.42 ms.
-// Over 284 layer steps of 2 to 8 layers, 64 to 1024 wide, 64 to 16384 tokens, both directions and types, cross attention
-// and sequences of 2048 tokens among them, no sweep below the line is faster split (attention of 2048 tokens, 128 wide, 29 us
-// by this measure: four layers of 8 sequences 204 split, 187 in one piece; transposed 558, 528).  Above it both happen: 42
-// to 60 us mostly still in one piece (768 wide, four layers of 512 tokens 125 -> 85), but five layers of 8 x 2048 tokens,
-// 128 wide (48 us), split: 260 -> 280, a training step of such sweeps 22.8 -> 24.9 ms; and from about 400 us on the
-// overlap wins (768 wide, six layers of 4096 tokens 564 -> 576, transposed 1133 -> 1215).
-constexpr double SMALL_SWEEP_US = 40.0;
+// A sweep that fits one launch chunk stays in one piece unless it is long.  Split, it is two chains of launches over half the
+// layers each: the host enqueues twice as many (about 8 kernels and the events of the fork and join, 3-4 us each), every
+// launch fills half as much of the chip, and what is gained, one chain's traffic under the other's products, weighs more than
+// that only in long launches.  The measure is the four products of an encoder's forward step and its attention, whatever the
+// sweep runs: bf16 products from the tile model and attention at 800 TFLOP/s, fp32 at 100 TFLOP/s, 3 us a launch and 50 TFLOP/s.
+// Split -> in one piece, over 252 bf16 layer steps of 2, 4 and 5 layers (128 to 1024 wide, 64 to 4096 tokens, both directions,
+// cross attention) and 250 training steps whose sweeps have 3 to 5 layers (d_head 64 and 128, up to 8 x 2048 tokens):
+//   bf16 below 40 us: 10 to 120 % faster;  40 to 110 us: layer steps 10 to 60 % faster (768 wide, 4 x 64 tokens 105 -> 60 us;
+//   512 wide, 4 x 1024 tokens 109 -> 84), training steps 0 to 12 % (512 wide, 2048 tokens, 9.2 -> 8.3 ms); 110 to 220 us: layer
+//   steps 0 to 20 % faster, training steps between 7 % faster and 9 % slower (128 wide, 5 layers of 8 x 2048 tokens, 156 us,
+//   16.5 -> 18.0 ms); above: within 6 % either way, long attention slower.
+//   fp32 (95 steps of both kinds) below 400 us: 0 to 50 % faster (512 wide, 2 x 256 tokens 129 -> 90 us; 4 x 512 tokens,
+//   141 us, 381 -> 360); above: 9 % faster to 2 % slower.
+// (Products below 40 us were never faster split, whatever the attention beside them: four layers of 8 x 2048 tokens, 128
+// wide, 204 split, 187 in one piece; transposed 558, 528.)
+constexpr double SMALL_SWEEP_US = 110.0, SMALL_PRODUCTS_US = 40.0, SMALL_SWEEP_F32_US = 400.0;
 inline bool small_sweep(const Engine& E, int G) {
   if (G > E.Gc) return false;
-  double us;
-  if (E.bf16)
-    us = gemm_model_cost(G, E.T, 3 * E.d, E.d) + gemm_model_cost(G, E.T, E.d, E.d) + gemm_model_cost(G, E.T, E.f, E.d) +
-         gemm_model_cost(G, E.T, E.d, E.f);
-  else
-    us = 12.0 + (double)G * E.T * (8.0 * E.d * E.d + 4.0 * E.d * E.f) / 1e8;
-  return us < SMALL_SWEEP_US;
+  const double keys = E.md.arch == MGRIT_ARCH_ENCODER ? E.md.seq : 0.5 * E.md.seq + E.md.mem_seq;
+  const double attn = 4.0 * keys * E.d * E.T * G;            // flops
+  if (!E.bf16) return 12.0 + (double)G * E.T * (8.0 * E.d * E.d + 4.0 * E.d * E.f) / 1e8 + attn / 5e7 < SMALL_SWEEP_F32_US;
+  const double us = gemm_model_cost(G, E.T, 3 * E.d, E.d) + gemm_model_cost(G, E.T, E.d, E.d) +
+                    gemm_model_cost(G, E.T, E.f, E.d) + gemm_model_cost(G, E.T, E.d, E.f);
+  return us < SMALL_PRODUCTS_US || us + attn / 8e8 < SMALL_SWEEP_US;
 }
 
 // Runs `fn(lane engine, first group, count)` over chunks of a sweep; with a second lane the

@@ -155,6 +155,25 @@ def test_sweeps_in_one_piece_and_split(arch, dtype, G, adjoint):
         assert torch.isfinite(x).all() and torch.equal(x, y)
 
 
+@pytest.mark.parametrize("adjoint", [False, True])
+@pytest.mark.parametrize("dtype,d,B,S,G", [
+    (wls.DTYPE_BF16, 512, 4, 512, 5), (wls.DTYPE_BF16, 768, 4, 512, 4),          # 108 and 163 us: the line is at 110
+    (wls.DTYPE_F32, 512, 4, 256, 4), (wls.DTYPE_F32, 512, 8, 256, 4)])           # 291 and 570 us: at 400
+def test_sweeps_around_the_line_of_two_lanes(dtype, d, B, S, G, adjoint):
+    wl = make(wls.ARCH_CAUSAL, dtype, d=d, H=d // 64, f=4 * d, B=B, S=S)
+    print(f"[case] two lanes or one dtype={dtype} d={d} B={B} S={S} G={G} adjoint={adjoint}", flush=True)
+    dm = DeviceModel(wl, n_layers=G, weight_std=0.05, keep_host=False)
+    out = {}
+    try:
+        for lanes in (2, 1):
+            mb.mgrit_set_lanes(lanes)
+            out[lanes] = step(dm, wl, adjoint, G)
+    finally:
+        mb.mgrit_set_lanes(2)
+    for x, y in zip(out[1], out[2]):
+        assert torch.isfinite(x).all() and torch.equal(x, y)
+
+
 @pytest.mark.parametrize("dtype,d,S,Sm,N,cf,levels,relax,lanes,mg", [
     (wls.DTYPE_BF16, 128, 40, 24, 16, 4, 2, 1, 2, 0),
     (wls.DTYPE_BF16, 128, 17, 65, 8, 2, 3, 0, 1, 0),
