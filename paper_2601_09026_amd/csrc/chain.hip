@@ -930,33 +930,37 @@ template <int D> hipError_t tail_of(const ChainTailArgs& a, int mode, hipStream_
 }
 }  // namespace
 
-hipError_t launch_chain_tail(const ChainTailArgs& a, int d, int mode, hipStream_t st) {
+hipError_t launch_chain_tail(const ChainTailArgs& a, int d, int mode, bool is_bf16, hipStream_t st) {
   if (a.n_groups <= 0) return hipSuccess;
   const double n = (double)a.n_groups * a.T;
   ProfScope ps(PC_CHAIN, n * (2.0 * d * d + (mode == 1 ? 2.0 : 4.0) * d * a.f),
                n * (d * (mode == 1 ? 6.0 : 10.0) + (a.RHS.present() ? 4.0 * d : 0.0) + (mode ? 2.0 * (d + a.f) : 0.0)), st);
+  if (!is_bf16) return launch_chain_f32_tail(a, mode, st);
   return d == 64 ? tail_of<64>(a, mode, st) : tail_of<128>(a, mode, st);
 }
-hipError_t launch_chain_head(const ChainHeadArgs& a, int d, hipStream_t st) {
+hipError_t launch_chain_head(const ChainHeadArgs& a, int d, bool is_bf16, hipStream_t st) {
   if (a.n_groups <= 0) return hipSuccess;
   const double rows = (double)a.n_groups * a.T;
   ProfScope ps(PC_CHAIN, rows * 6.0 * d * d, rows * d * (10.0 + (a.xhat ? 2.0 : 0.0)), st);
+  if (!is_bf16) return launch_chain_f32_head(a, st);
   const bool n = narrow(a.n_groups, a.T);
   if (d == 64) return n ? launch(chain_head_kernel<64, 2>, a, 2, 2 * vec_bytes(d) + vec_bytes(3 * d), st) : launch(chain_head_kernel<64, 4>, a, 4, 2 * vec_bytes(d) + vec_bytes(3 * d), st);
   return n ? launch(chain_head_kernel<128, 2>, a, 2, 2 * vec_bytes(d) + vec_bytes(3 * d), st) : launch(chain_head_kernel<128, 4>, a, 4, 2 * vec_bytes(d) + vec_bytes(3 * d), st);
 }
-hipError_t launch_chain_adjoint_tail(const ChainAdjointArgs& a, int d, hipStream_t st) {
+hipError_t launch_chain_adjoint_tail(const ChainAdjointArgs& a, int d, bool is_bf16, hipStream_t st) {
   if (a.n_groups <= 0) return hipSuccess;
   const double rows = (double)a.n_groups * a.T;
   ProfScope ps(PC_CHAIN, rows * (2.0 * d * d + 4.0 * d * a.f), rows * (10.0 * d + 2.0 * a.f), st);
+  if (!is_bf16) return launch_chain_f32_adjoint_tail(a, st);
   const bool n = narrow(a.n_groups, a.T);
   if (d == 64) return n ? launch(chain_adjoint_tail_kernel<64, 2>, a, 2, vec_bytes(d), st) : launch(chain_adjoint_tail_kernel<64, 4>, a, 4, vec_bytes(d), st);
   return n ? launch(chain_adjoint_tail_kernel<128, 2>, a, 2, vec_bytes(d), st) : launch(chain_adjoint_tail_kernel<128, 4>, a, 4, vec_bytes(d), st);
 }
-hipError_t launch_chain_adjoint_head(const ChainAdjointArgs& a, int d, hipStream_t st) {
+hipError_t launch_chain_adjoint_head(const ChainAdjointArgs& a, int d, bool is_bf16, hipStream_t st) {
   if (a.n_groups <= 0) return hipSuccess;
   const double rows = (double)a.n_groups * a.T;
   ProfScope ps(PC_CHAIN, rows * 6.0 * d * d, rows * d * (20.0 + (a.RHS.present() ? 4.0 : 0.0) + (a.out_cast ? 2.0 : 0.0)), st);
+  if (!is_bf16) return launch_chain_f32_adjoint_head(a, st);
   const bool n = narrow(a.n_groups, a.T);
   if (d == 64) return n ? launch(chain_adjoint_head_kernel<64, 2>, a, 2, vec_bytes(d), st) : launch(chain_adjoint_head_kernel<64, 4>, a, 4, vec_bytes(d), st);
   return n ? launch(chain_adjoint_head_kernel<128, 2>, a, 2, vec_bytes(d), st) : launch(chain_adjoint_head_kernel<128, 4>, a, 4, vec_bytes(d), st);
@@ -969,7 +973,8 @@ hipError_t launch_chain_adjoint_head(const ChainAdjointArgs& a, int d, hipStream
 // wide hidden layers need many tokens.  The rule follows from the model alone: how many layers share a launch cannot show in
 // a result.
 bool chain_ok(int d, int f, int T, bool is_bf16) {
-  if (!is_bf16 || (d != 64 && d != 128) || f % 64 != 0 || f > 2048 || 2.0 * T * (f > 3 * d ? f : 3 * d) >= 2e9) return false;
+  if (!is_bf16) return chain_f32_ok(d, f);
+  if ((d != 64 && d != 128) || f % 64 != 0 || f > 2048 || 2.0 * T * (f > 3 * d ? f : 3 * d) >= 2e9) return false;
   return d == 64 ? f <= 512 || T >= 2048 : f <= 256 || T >= 2048;
 }
 

@@ -76,7 +76,7 @@ hipError_t upload_tables(void** tab, const PtrSource* src, int n_src, int n, hip
 struct TransposeList { int n; int rows[7], cols[7], tiles[7]; long off[7]; };
 hipError_t launch_transpose(int n_groups, Params in, Params out, const TransposeList& l, int elem_bytes, hipStream_t st);
 
-// ---- chain.hip (bf16, d = 64 or 128) -------------------------------------------
+// ---- chain.hip (bf16, d = 64 or 128), chain_f32.hip (d = 64) --------------------
 struct ChainHeadArgs {
   int n_groups, T;
   Rows X;
@@ -96,8 +96,8 @@ struct ChainTailArgs {
   float* ybar; void *u, *act;                             // ... and those that parameter gradients need, or null
 };
 // mode 0: the step; 1: the cache entries alone; 2: both
-hipError_t launch_chain_tail(const ChainTailArgs& a, int d, int mode, hipStream_t st);
-hipError_t launch_chain_head(const ChainHeadArgs& a, int d, hipStream_t st);
+hipError_t launch_chain_tail(const ChainTailArgs& a, int d, int mode, bool is_bf16, hipStream_t st);
+hipError_t launch_chain_head(const ChainHeadArgs& a, int d, bool is_bf16, hipStream_t st);
 struct ChainAdjointArgs {
   int n_groups, T, f;
   const void* c; Slots c_slots;                           // tail: operand-type copy of IN, or null: formed here ...
@@ -109,9 +109,14 @@ struct ChainAdjointArgs {
   void* out_cast; Slots oc_slots;
   float hstep, rhs_sign;
 };
-hipError_t launch_chain_adjoint_tail(const ChainAdjointArgs& a, int d, hipStream_t st);
-hipError_t launch_chain_adjoint_head(const ChainAdjointArgs& a, int d, hipStream_t st);
+hipError_t launch_chain_adjoint_tail(const ChainAdjointArgs& a, int d, bool is_bf16, hipStream_t st);
+hipError_t launch_chain_adjoint_head(const ChainAdjointArgs& a, int d, bool is_bf16, hipStream_t st);
 bool chain_ok(int d, int f, int T, bool is_bf16);
+hipError_t launch_chain_f32_tail(const ChainTailArgs& a, int mode, hipStream_t st);      // (through the above)
+hipError_t launch_chain_f32_head(const ChainHeadArgs& a, hipStream_t st);
+hipError_t launch_chain_f32_adjoint_tail(const ChainAdjointArgs& a, hipStream_t st);
+hipError_t launch_chain_f32_adjoint_head(const ChainAdjointArgs& a, hipStream_t st);
+bool chain_f32_ok(int d, int f);
 
 // ---- grads.hip ---------------------------------------------------------------
 // LayerNorm gain / shift gradients of up to three LayerNorms of the same layers: sums over tokens of

@@ -468,7 +468,7 @@ int forward_chunk(Engine& E, int n, Rows IN, Rows OUT, Rows RHS, Params TH, floa
     h.out = qkv; h.out_slots = cs; h.cs = cs;
     if (cache) { h.xhat = E.c_xh1; h.rstd = E.c_rs1; }
     if (keep) h.u = E.c_u1;
-    HIPCHK(launch_chain_head(h, d, E.st));
+    HIPCHK(launch_chain_head(h, d, E.bf16, E.st));
   } else {
     HIPCHK(launch_ln_fwd(ln, E.bf16, E.st));
     g = gemm_base(n, T, 3 * d, d, u1, E.Td(), us, TH, L.offset[MGRIT_P_WQKV], L.offset[MGRIT_P_BQKV]);
@@ -503,7 +503,7 @@ int forward_chunk(Engine& E, int n, Rows IN, Rows OUT, Rows RHS, Params TH, floa
     t.cs = cs;
     if (cache) { t.xhat = E.c_xh2; t.rstd = E.c_rs2; t.dact = E.c_z; }
     if (keep) { t.ybar = E.c_xin; t.u = E.c_u2; t.act = E.c_act; }
-    HIPCHK(launch_chain_tail(t, d, cache, E.st));
+    HIPCHK(launch_chain_tail(t, d, cache, E.bf16, E.st));
     return MGRIT_OK;
   };
   if (E.chain && !cross) return tail(ob, MGRIT_P_WO, MGRIT_P_BO, nullptr);
@@ -637,7 +637,7 @@ int adjoint_chunk(Engine& E, int n, Rows IN, Rows OUT, Rows RHS, Params TH, Para
     ch.cs = cs; ch.dact = E.c_z; ch.xhat = E.c_xh2; ch.rstd = E.c_rs2;
     ch.loc = loc; ch.da = E.da; ch.dx = E.dxin;
     if (gp) { ch.c_out = E.cb; ch.dz = E.dz; ch.du = E.du; ch.ds = cross ? E.dsc : E.ds; }
-    HIPCHK(launch_chain_adjoint_tail(ch, d, E.st));
+    HIPCHK(launch_chain_adjoint_tail(ch, d, E.bf16, E.st));
   } else {
     if (!have) HIPCHK(launch_cast_rows(n, E.Td(), IN, E.cb, E.Td(), loc, E.bf16, E.st));
     // dz = (c W2) * gelu'(z)        [T,d] x [d,f]: transposed W2 is [f,d]; gelu'(z) comes from the cache
@@ -743,7 +743,7 @@ int adjoint_chunk(Engine& E, int n, Rows IN, Rows OUT, Rows RHS, Params TH, Para
     ch.du = gp ? E.du1 : nullptr;
     if (write) { ch.OUT = OUT; ch.RHS = RHS; ch.hstep = hstep; ch.rhs_sign = E.rhs_sign; }
     if (write && sh && sh->out) { ch.out_cast = sh->out; ch.oc_slots = sh->out_slots; }
-    HIPCHK(launch_chain_adjoint_head(ch, d, E.st));
+    HIPCHK(launch_chain_adjoint_head(ch, d, E.bf16, E.st));
     return MGRIT_OK;
   }
 

@@ -1,4 +1,4 @@
-"""Layers 64 and 128 wide in bf16 run what is local to a token row as one launch on either side of attention.  These
+"""Layers 64 and 128 wide in bf16, and 64 wide in fp32, run what is local to a token row as one launch on either side of attention.  These
 launches against the general path (one launch per operator, chosen by the hook that fixes the products' tiles) at the
 edges of their tiles: 32 rows a wavefront, 64 or 128 a block, chunks of 64 hidden features, ring of eight weight tiles.
 
@@ -6,7 +6,9 @@ Bound: both paths round the same intermediates to bf16 and differ in the order o
 one rounding step, 2^-8 of its value, and so does an increment normwise (measured for one step: 1e-6 to 1e-4).  In a training
 step such differences come in once more with each solve: one step for Z, two for lambda, whose operands differ and which is
 linearised at states that do, three for the gradients formed from both.  (The general path alone moves lambda by 3.7e-3
-when 1e-5 is added to every Z; the paths differ by 4.0e-3 there.)"""
+when 1e-5 is added to every Z; the paths differ by 4.0e-3 there.)
+fp32: sums of up to 256 products in another order, 2^-24 times a random walk of 16 steps and as much again for each of the four
+products on the way: 64 roundings of the increment; and the rounding of the state itself on either side."""
 import pytest
 import torch
 
@@ -30,6 +32,12 @@ def both_paths(run):
         finally:
             mb.lib().mgrit_debug_gemm_tile_config(0)
     return out
+
+
+def close_f32(a, b, base, what):
+    a, b, base = a.double(), b.double(), base.double()
+    assert torch.isfinite(a).all(), what
+    assert (a - b).norm() <= 2.0 ** -24 * (64 * (b - base).norm() + 4 * b.norm()), f"{what}: {(a - b).norm() / (b - base).norm():.2e}"
 
 
 def close(a, b, base, what, roundings=1):
@@ -78,6 +86,26 @@ def test_steps_match_general_path(arch, d, H, f, B, S, Sm, G, rhs, adjoint):
         close(chain[g], general[g], ins[g] + r[g] if rhs else ins[g], f"group {g}")
 
 
+@pytest.mark.parametrize("adjoint", [False, True])
+@pytest.mark.parametrize("arch,H,f,B,S,Sm,G,rhs", [
+    (wls.ARCH_ENCODER, 1, 64, 1, 1, 0, 1, True),
+    (wls.ARCH_CAUSAL, 4, 128, 1, 15, 0, 2, False),
+    (wls.ARCH_ENCODER, 4, 256, 1, 17, 0, 3, True),
+    (wls.ARCH_CROSS, 2, 256, 3, 11, 5, 2, True),              # 33 rows
+    (wls.ARCH_ENCODER, 1, 256, 5, 205, 0, 16, True),          # 1025 rows: 65 tiles of 16, 1040 of them: two a block
+    (wls.ARCH_CAUSAL, 2, 64, 16, 64, 0, 16, False),           # 1024 tiles, two a block
+    (wls.ARCH_CAUSAL, 2, 128, 1, 1008, 0, 16, False),         # 1008, one a block
+])
+def test_fp32_steps_match_general_path(arch, H, f, B, S, Sm, G, rhs, adjoint):
+    wl = make(arch, wls.DTYPE_F32, d=64, H=H, f=f, B=B, S=S, Sm=Sm)
+    print(f"[case] fp32 chain steps arch={arch} f={f} B={B} S={S} Sm={Sm} G={G} adjoint={adjoint}", flush=True)
+    dm = DeviceModel(wl, n_layers=G, weight_std=0.08, keep_host=False)
+    ins, lin, r = states(wl, G, 8)
+    chain, general = both_paths(lambda: steps(dm, wl, adjoint, ins, lin, r if rhs else None))
+    for g in range(G):
+        close_f32(chain[g], general[g], ins[g] + r[g] if rhs else ins[g], f"group {g}")
+
+
 @pytest.mark.parametrize("arch,d,H,f,S,Sm,N,cf,levels", [
     (wls.ARCH_ENCODER, 64, 1, 128, 36, 0, 16, 4, 2),
     (wls.ARCH_CAUSAL, 128, 2, 256, 68, 0, 8, 2, 3),
@@ -116,10 +144,12 @@ def test_training_matches_general_path(arch, d, H, f, S, Sm, N, cf, levels, cach
 
 
 @pytest.mark.parametrize("adjoint", [False, True])
-@pytest.mark.parametrize("d,f,B,S,G", [(64, 256, 8, 512, 5), (128, 128, 8, 512, 5)])
-def test_block_size_does_not_show(d, f, B, S, G, adjoint):
-    """One layer a launch runs on blocks of 64 rows, five on blocks of 128."""
-    wl = make(wls.ARCH_CAUSAL, wls.DTYPE_BF16, d=d, H=1, f=f, B=B, S=S)
+@pytest.mark.parametrize("dtype,d,f,B,S,G", [
+    (wls.DTYPE_BF16, 64, 256, 8, 512, 5), (wls.DTYPE_BF16, 128, 128, 8, 512, 5),   # blocks of 64 rows alone, of 128 together
+    (wls.DTYPE_F32, 64, 256, 8, 512, 5), (wls.DTYPE_F32, 64, 64, 8, 512, 4)])      # 16 and 32
+def test_block_size_does_not_show(dtype, d, f, B, S, G, adjoint):
+    """How many rows a block takes follows from how many layers share the launch."""
+    wl = make(wls.ARCH_CAUSAL, dtype, d=d, H=1, f=f, B=B, S=S)
     print(f"[case] chain block size d={d} f={f} B={B} S={S} G={G} adjoint={adjoint}", flush=True)
     dm = DeviceModel(wl, n_layers=G, weight_std=0.08, keep_host=False)
     ins, lin, rhs = states(wl, G, 6)
@@ -136,10 +166,10 @@ def test_block_size_does_not_show(d, f, B, S, G, adjoint):
         assert torch.isfinite(x).all() and torch.equal(x, y)
 
 
-@pytest.mark.parametrize("d,f", [(64, 128), (128, 128)])
-def test_non_finite_rows_stay_where_they_are(d, f):
+@pytest.mark.parametrize("dtype,d,f", [(wls.DTYPE_BF16, 64, 128), (wls.DTYPE_BF16, 128, 128), (wls.DTYPE_F32, 64, 128)])
+def test_non_finite_rows_stay_where_they_are(dtype, d, f):
     """Single-token sequences: what is not finite in one row shows in that row, as on the general path, and nowhere else."""
-    wl = make(wls.ARCH_ENCODER, wls.DTYPE_BF16, d=d, H=1, f=f, B=70, S=1)
+    wl = make(wls.ARCH_ENCODER, dtype, d=d, H=1, f=f, B=70, S=1)
     print(f"[case] chain non-finite d={d}", flush=True)
     dm = DeviceModel(wl, n_layers=1, weight_std=0.08, keep_host=False)
     ins, lin, _ = states(wl, 1, 7)
