@@ -313,8 +313,19 @@ def main():
                                       "launches_per_step": sum(v["launches"] for v in sel) / args.steps,
                                       "ms_per_step": sum(v["ms"] for v in sel) / args.steps}
         else:
-            gen = totals.get("gemm_generic")
-            if gen:
+            gen, chain = totals.get("gemm_generic"), totals.get("chain")
+            if chain and not (gen and gen["ms"] > chain["ms"]):
+                # narrow layers: the products run inside the row-local chains, which bf16 rows pass through at the
+                # memory's rate and few fp32 rows as one block's chain of products
+                rate, per = (chain["bytes"], 1e9) if wl.dtype == wls.DTYPE_BF16 else (chain["flops"], 1e12)
+                peak, unit = (PEAK_HBM_GBS, "GB/s") if wl.dtype == wls.DTYPE_BF16 else (157.3, "TFLOP/s")
+                ach = rate / (chain["ms"] * 1e-3) / per
+                roofline = {"bound": "hbm" if wl.dtype == wls.DTYPE_BF16 else "alu",
+                            "kernel": "chain_*_kernel (row-local chains of narrow layers)", "achieved": ach, "peak": peak,
+                            "unit": unit, "frac": ach / peak, "traffic": None,
+                            "launches_per_step": chain["launches"] / args.steps,
+                            "avg_launch_us": chain["ms"] * 1e3 / chain["launches"]}
+            elif gen:
                 ach = gen["flops"] / (gen["ms"] * 1e-3) / 1e12
                 roofline = {"bound": "alu", "kernel": "gemm_f32_mfma_kernel (fp32 MFMA 32x32x2; small and ragged launches: gemm_f32_small_kernel, 16x16x4)", "achieved": ach,
                             "peak": 157.3, "unit": "TFLOP/s", "frac": ach / 157.3, "traffic": None,
@@ -323,9 +334,9 @@ def main():
         # outweigh the GEMMs and are the dominant kernel instead (algorithmic flops: 2 products
         # forward, 5 backward; the two-pass backward recomputes two of them)
         att = [totals[k] for k in ("attn_fwd", "attn_bwd") if k in totals]
-        if att and roofline is not None and roofline["bound"] == "mfma" and wl.d_model // wl.n_heads in (64, 128):
+        if att and roofline is not None and roofline["bound"] in ("mfma", "hbm") and wl.d_model // wl.n_heads in (64, 128):
             a_ms = sum(v["ms"] for v in att)
-            if a_ms > sum(v["ms"] for v in gemm):
+            if a_ms > sum(v["ms"] for v in gemm or [totals["chain"]]):
                 a_fl = sum(v["flops"] for v in att); a_n = sum(v["launches"] for v in att)
                 ach = a_fl / (a_ms * 1e-3) / 1e12
                 roofline = {"bound": "mfma", "kernel": "attn_fwd_mfma_kernel + attn_bwd_*_mfma_kernel (fused softmax attention)",
@@ -336,14 +347,14 @@ def main():
                             "algorithmic_bytes_per_launch": sum(v["bytes"] for v in att) / a_n,
                             "share_of_instrumented_step_time": a_ms / args.steps / events_ms_per_step,
                             "instrumented_ms_per_step": events_ms_per_step,
-                            "grouped_gemm_TFLOPs": roofline["achieved"]}
+                            **({"grouped_gemm_TFLOPs": roofline["achieved"]} if gemm else {})}
         hbm = {}
         # an event pair adds a few microseconds to the launch it brackets (reported, not subtracted: the
         # rates below are lower bounds; a kernel trace of the same launches gives the durations proper)
         bracket_us = mb.mgrit_measure_event_bracket(stream)
         # LayerNorm: the launches over several groups (relaxation sweeps: tens of MB, beyond the caches
         # between producer and consumer) and the single-group ones of the coarse chain apart
-        for k in ("ln_fwd", "ln_vjp", "ln_fwd_single", "ln_vjp_single", "elementwise"):
+        for k in ("ln_fwd", "ln_vjp", "ln_fwd_single", "ln_vjp_single", "elementwise", "chain"):
             if k in totals and totals[k]["ms"] > 0:
                 gbs = totals[k]["bytes"] / (totals[k]["ms"] * 1e-3) / 1e9
                 hbm[k] = {"achieved_GBs": gbs, "frac_of_8TBs": gbs / PEAK_HBM_GBS,
