@@ -15,43 +15,28 @@ constexpr int WAVE = 64;
 
 // ---------------------------------------------------------------------------
 // Per-group addressing.  A batched launch works on `n` independent groups
-// (coarse intervals).  Everything a group touches is found through lists of
-// device pointers indexed affinely by the group number, so that one launch can
+// (coarse intervals).  Everything a group touches is found through device
+// pointer tables indexed affinely by the group number, so that one launch can
 // serve any sweep of the MGRIT driver without re-uploading pointers:
-//   group g has entry i0 + g*is
+//   table entry of group g = tab[i0 + g*is]
 // Packed intermediate buffers are indexed by "slot" = slot0 + g*slot_s.
-//
-// Evenly spaced pointers (states of one array, blocks of one array, any one or two pointers) are computed; only other
-// lists are read from device memory.  A small launch is bound by its chain of dependent loads, of which the list was one
-// (kernel arguments, list, operands), behind a launch that wrote the list: without both, one step of 4 layers of 64 tokens,
-// d = 64, fp32 takes 19.6 instead of 22.9 us, of one layer of 197 tokens, d = 384, bf16 42.7 instead of 44.0.
 // ---------------------------------------------------------------------------
-struct Table {
-  const void* p;                    // step == 0: device array of device pointers (may be null); else entry 0 itself
-  long step;                        // bytes from one entry to the next
-  // A list does not change while a kernel runs: read as constant memory, i.e. by scalar loads also behind stores (a vector
-  // load would be waited for together with every store before it).  What it points to is global memory.
-  __device__ __forceinline__ char* at(long i) const {
-    typedef const void* const __attribute__((address_space(4)))* list;
-    typedef char __attribute__((address_space(1)))* global;
-    return (char*)(global)(step ? (char*)p + i * step : (char*)((list)p)[i]);
-  }
-};
-
-struct Rows {                       // fp32 [T,d] states
-  Table tab;
+struct Rows {                       // fp32 [T,d] states reached through a table
+  const void* const* tab;           // device array of device pointers (may be null)
   int i0, is;
   long off;                         // element offset inside every state (a row range of a stacked state)
   __device__ __forceinline__ float* at(int g) const {
-    return reinterpret_cast<float*>(tab.at(i0 + (long)g * is)) + off;
+    return (float*)const_cast<void*>(tab[i0 + (long)g * is]) + off;
   }
-  __host__ __device__ bool present() const { return tab.p != nullptr; }
+  __host__ __device__ bool present() const { return tab != nullptr; }
 };
 
-struct Params {                     // packed parameter blocks
-  Table tab;
+struct Params {                     // packed parameter blocks reached through a table
+  const void* const* tab;
   int i0, is;
-  __device__ __forceinline__ const char* at(int g) const { return tab.at(i0 + (long)g * is); }
+  __device__ __forceinline__ const char* at(int g) const {
+    return (const char*)tab[i0 + (long)g * is];
+  }
 };
 
 struct Slots {

@@ -504,6 +504,13 @@ gemm_mfma_kernel(const GemmArgs a, int tiles_m, int tiles_n, int total_tiles, in
                                          M, m0 + wm0, n0 + wn0, lane);
 }
 
+// Pointer tables do not change while a kernel runs: read as constant memory, i.e. by scalar loads also behind stores
+// (a vector load would be waited for together with every store before it).
+__device__ __forceinline__ const char* table_entry(const void* const* tab, long i) {
+  typedef const void* const __attribute__((address_space(4)))* cptr;
+  return (const char*)((cptr)tab)[i];
+}
+
 typedef __attribute__((__vector_size__(16))) unsigned u32x4;
 typedef __attribute__((address_space(3))) f32x4 lds_f32x4;
 
@@ -606,7 +613,7 @@ gemm_mfma_dgelu_walk_kernel(const GemmArgs a, int tiles_m, int tiles_n, int tota
     p.m0 = __builtin_amdgcn_readfirstlane(tm) * BM;
     p.n0 = __builtin_amdgcn_readfirstlane(tn) * BN;
     p.A = lds_source(reinterpret_cast<const bf16*>(a.A) + a.a_slots.of(p.g) * a.a_slot_stride + (long)p.m0 * K);
-    p.B = lds_source(a.B.at(p.g) + a.b_off + 2 * (long)p.n0 * K);
+    p.B = lds_source(table_entry(a.B.tab, a.B.i0 + (long)p.g * a.B.is) + a.b_off + 2 * (long)p.n0 * K);
 #pragma unroll
     for (int j = 0; j < LD_; ++j) {
       const int row = (wave * LD_ + j) * RPL + lrow;

@@ -65,14 +65,13 @@ hipError_t launch_add_rows(int n_groups, long elems, Rows A, Rows B, Rows D, hip
 // partial[block] = sum over the block's elements of (a-b)^2 in double; then out[0] = sqrt(sum partial)
 hipError_t launch_resnorm(int n_groups, long elems, Rows A, Rows B, double* partial, int max_partial,
                           float* out, hipStream_t st);
-// entries base + i*step (step != 0), computed where they are used
-inline Table spaced(const void* base, long step) { return {base, step}; }
-// space[i] = base + i*stride_bytes, i < n
-hipError_t launch_fill_table(void** space, char* base, long stride_bytes, int n, hipStream_t st);
-// A table for each of n_lists host lists of n pointers (null list: null table).  Lists that are not evenly spaced are
-// copied to `space` (n_lists * n entries): pointers travel as kernel arguments, 128 a launch (safe for any host memory,
-// capturable).
-hipError_t make_tables(Table* out, void** space, const void* const* const* lists, int n_lists, int n, hipStream_t st);
+// tab[i] = base + i*stride_bytes, i < n
+hipError_t launch_fill_table(void** tab, char* base, long stride_bytes, int n, hipStream_t st);
+// tab[i] = ptrs[i]: pointers travel as kernel arguments, 128 a launch (safe for any host memory, capturable)
+hipError_t upload_pointers(void** tab, const void* const* host_ptrs, int n, hipStream_t st);
+// n_src tables of n entries, one behind the other: a host list each, or (list = null) base + i*stride
+struct PtrSource { const void* const* list; const char* base; long stride; };
+hipError_t upload_tables(void** tab, const PtrSource* src, int n_src, int n, hipStream_t st);
 // out_g[c, r] = in_g[r, c] for every group and every matrix of the list (at most 7 per block: byte offset, shape)
 struct TransposeList { int n; int rows[7], cols[7], tiles[7]; long off[7]; };
 hipError_t launch_transpose(int n_groups, Params in, Params out, const TransposeList& l, int elem_bytes, hipStream_t st);

@@ -402,11 +402,10 @@ inline bool make_lane(Engine& E2, const Engine& E, Bump& b, bool adjoint, bool m
   return true;
 }
 
-inline Rows shift(Rows r, int c0) { if (r.present()) r.i0 += c0 * r.is; return r; }
+inline Rows shift(Rows r, int c0) { if (r.tab) r.i0 += c0 * r.is; return r; }
 inline Params shift(Params p, int c0) { p.i0 += c0 * p.is; return p; }
 inline Slots shift(Slots s, int c0) { s.s0 += c0 * s.ss; return s; }
-const Table NO_TABLE = {nullptr, 0};
-const Rows NO_ROWS = {NO_TABLE, 0, 0};
+const Rows NO_ROWS = {nullptr, 0, 0};
 
 GemmArgs gemm_base(int n, int M, int N, int K, const void* A, long a_stride, Slots a_slots, Params B, long b_off,
                    long bias_off) {
@@ -893,7 +892,7 @@ int adjoint_groups(Engine& E, Engine* E2, int G, Rows IN, Rows OUT, Rows RHS, Pa
     if (sd) s = shift(*sd, c0);
     CastShadow shc;
     if (sh) shc = shift(*sh, c0);
-    Params dt = {NO_TABLE, 0, 0};
+    Params dt = {nullptr, 0, 0};
     GradPass gp;
     if (emit) {
       if (DT) { dt = shift(*DT, c0); gp.DT = &dt; }
@@ -920,7 +919,7 @@ int adjoint_groups(Engine& E, Engine* E2, int G, Rows IN, Rows OUT, Rows RHS, Pa
 int gradient_groups(Engine& E, Engine* E2, int G, Rows IN, Params TH, Params THT, Rows LIN, Slots cs,
                     const Params* DT, float* dE_all, float hstep, const StackedDec* sd = nullptr) {
   return run_chunks(E, E2, G, [&](Engine& L, int c0, int n) {
-    Params dt = {NO_TABLE, 0, 0};
+    Params dt = {nullptr, 0, 0};
     GradPass gp;
     if (DT) { dt = shift(*DT, c0); gp.DT = &dt; }
     gp.dE_all = dE_all;
@@ -962,12 +961,13 @@ struct Driver {
   bool adjoint = false;
   int N = 0, cf = 1, L = 1, relax = MGRIT_RELAX_FCF;
   float h = 0.f;
-  Table tabW = NO_TABLE;           // level-0 point m -> state row (forward: m, adjoint: N-m)
-  Table tabZ = NO_TABLE;           // adjoint: forward state n (linearisation)
-  Table tabTh = NO_TABLE;          // layer n -> parameter block
-  Table tabThT = NO_TABLE;         // layer n -> transposed block (adjoint)
-  std::vector<Table> tabG;         // level l >= 1: point j -> right-hand side g^l_j
-  Table tabR = NO_TABLE;           // k -> scratch state R_k
+  // device pointer tables
+  void** tabW = nullptr;           // level-0 point m -> state row (forward: m, adjoint: N-m)
+  void** tabZ = nullptr;           // adjoint: forward state n (linearisation)
+  void** tabTh = nullptr;          // layer n -> parameter block
+  void** tabThT = nullptr;         // layer n -> transposed block (adjoint)
+  std::vector<void**> tabG;        // level l >= 1: point j -> right-hand side g^l_j
+  void** tabR = nullptr;           // k -> scratch state R_k
   double* partial = nullptr;
   int max_partial = 0;
   float* resnorm = nullptr;
@@ -983,7 +983,7 @@ struct Driver {
   long state_elems() const { return Ed ? x_elems + y_elems : E->Td(); }
 
   static int ipow(int b, int e) { int r = 1; while (e-- > 0) r *= b; return r; }
-  static Rows part(Rows r, long off) { if (r.present()) r.off += off; return r; }
+  static Rows part(Rows r, long off) { if (r.tab) r.off += off; return r; }
 
   // Stacked grid: the groups of a sweep start at increasing (forward) or decreasing (adjoint)
   // layers, so they split into one run of encoder steps and one run of decoder steps.  An
@@ -1018,7 +1018,7 @@ struct Driver {
       const Rows in = shift(IN, c0), out = shift(OUT, c0), rhs = shift(RHS, c0);
       const Rows inx = in, outx = out, rhsx = rhs;
       const Rows iny = part(in, x_elems), outy = part(out, x_elems), rhsy = part(rhs, x_elems);
-      Params TH = {tabTh, nl, ns};
+      Params TH = {(const void* const*)tabTh, nl, ns};
       if (!adjoint) {
         // fill: these level-0 steps read final states and leave their layers' cache entries (see fill_cache)
         if (enc) {
@@ -1031,10 +1031,10 @@ struct Driver {
         }
         continue;
       }
-      Params THT = {tabThT, nl, ns};
-      Rows LIN = {tabZ, nl, ns};
-      const bool emit = emit_now && tabDT.p != nullptr;         // see step(): these steps read final values
-      const Params DT = {tabDT, nl, ns};
+      Params THT = {(const void* const*)tabThT, nl, ns};
+      Rows LIN = {(const void* const*)tabZ, nl, ns};
+      const bool emit = emit_now && tabDT != nullptr;         // see step(): these steps read final values
+      const Params DT = {(const void* const*)tabDT, nl, ns};
       if (emit) emitted = true;
       if (enc) {
         STCHK(adjoint_groups(Le, Le2, n, inx, outx, rhsx, TH, THT, LIN, Slots{nl, ns}, hstep, nullptr, emit, &DT));
@@ -1053,7 +1053,7 @@ struct Driver {
   // lambda_{n+1}, which is exactly the input of the level-0 steps of the last cycle's closing
   // F-relaxation (and of every step of a serial run): those steps emit their layer's gradients on
   // the way (emit_final), the remaining N / cf layers get a pass of their own afterwards.
-  Table tabDT = NO_TABLE;          // layer n -> gradient block, or null
+  void** tabDT = nullptr;          // layer n -> gradient block, or null
   float* dE_all = nullptr;         // per-layer memory-gradient terms, or null
   bool want_grads = false, last_cycle = false, emit_now = false, emitted = false;
   // Forward solve on behalf of an adjoint that follows: the level-0 steps of the last cycle's closing
@@ -1075,7 +1075,7 @@ struct Driver {
     Engine* L2 = only ? nullptr : E2;
     const int s = ipow(cf, lvl);
     const float hstep = (float)((double)s * (double)h);
-    Rows IN = {tabW, j0 * s, js * s};
+    Rows IN = {(const void* const*)tabW, j0 * s, js * s};
     if (Ed) {
       if (!adjoint) return step_stacked(cnt, j0 * s, js * s, IN, OUT, RHS, hstep, cache_now && lvl == 0);
       const bool keep = emit_now;
@@ -1085,18 +1085,18 @@ struct Driver {
       return st;
     }
     if (!adjoint) {
-      Params TH = {tabTh, j0 * s, js * s};
+      Params TH = {(const void* const*)tabTh, j0 * s, js * s};
       if (cache_now && lvl == 0) return forward_groups(L1, L2, cnt, IN, OUT, RHS, TH, hstep, 2, Slots{j0, js});
       return forward_groups(L1, L2, cnt, IN, OUT, RHS, TH, hstep, 0, Slots{0, 0});
     }
     const int n0 = N - (j0 + 1) * s, ns = -js * s;       // layer the coarse step lands on
-    Params TH = {tabTh, n0, ns};
-    Params THT = {tabThT, n0, ns};
-    Rows LIN = {tabZ, n0, ns};
+    Params TH = {(const void* const*)tabTh, n0, ns};
+    Params THT = {(const void* const*)tabThT, n0, ns};
+    Rows LIN = {(const void* const*)tabZ, n0, ns};
     // operand-type copies of the states (see CastShadow): the inputs' copies exist if every input point was
     // written by a step of this call; the outputs' copies are left when the outputs are grid points
     CastShadow sh;
-    const bool out_is_point = OUT.tab.p == tabW.p;
+    const bool out_is_point = OUT.tab == (const void* const*)tabW;
     if (shadow) {
       sh.in = shadow; sh.in_slots = Slots{j0 * s, js * s}; sh.valid = shadow_valid.data();
       if (out_is_point) { sh.out = shadow; sh.out_slots = Slots{OUT.i0, OUT.is}; }
@@ -1104,9 +1104,9 @@ struct Driver {
     int st;
     if (emit_now && lvl == 0) {
       emitted = true;
-      const Params DT = {tabDT, n0, ns};
+      const Params DT = {(const void* const*)tabDT, n0, ns};
       st = adjoint_groups(L1, L2, cnt, IN, OUT, RHS, TH, THT, LIN, Slots{n0, ns}, hstep, nullptr, true,
-                          tabDT.p ? &DT : nullptr, dE_all, shadow ? &sh : nullptr);
+                          tabDT ? &DT : nullptr, dE_all, shadow ? &sh : nullptr);
     } else {
       st = adjoint_groups(L1, L2, cnt, IN, OUT, RHS, TH, THT, LIN, Slots{n0, ns}, hstep, nullptr, false, nullptr,
                           nullptr, shadow ? &sh : nullptr);
@@ -1218,11 +1218,11 @@ struct Driver {
 
   Rows W(int lvl, int j0, int js) const {
     const int s = ipow(cf, lvl);
-    return Rows{tabW, j0 * s, js * s};
+    return Rows{(const void* const*)tabW, j0 * s, js * s};
   }
   Rows Gr(int lvl, int j0, int js) const {
     if (lvl == 0) return NO_ROWS;
-    return Rows{tabG[lvl], j0, js};
+    return Rows{(const void* const*)tabG[lvl], j0, js};
   }
 
   int f_relax(int lvl, int M) {
@@ -1243,12 +1243,12 @@ struct Driver {
       STCHK(f_relax(lvl, M));
     }
     // R_k = Phi(w_{k cf - 1}) + g_{k cf}
-    Rows R = {tabR, 0, 1};
+    Rows R = {(const void* const*)tabR, 0, 1};
     STCHK(step(lvl, cf - 1, cf, M, R, Gr(lvl, cf, cf)));
     if (E && lvl == 0 && resnorm)
       HIPCHK(launch_resnorm(M, state_elems(), R, W(lvl, cf, cf), partial, max_partial, resnorm + iter, E->st));
     // g'_k = R_k - Phi'(w_{(k-1) cf}),  k = 1..M
-    Rows Gn = {E ? tabG[lvl + 1] : NO_TABLE, 1, 1};
+    Rows Gn = {(const void* const*)(E ? tabG[lvl + 1] : nullptr), 1, 1};
     if (E && E2 && g_pipeline && lvl + 1 == L - 1 && M >= 2 && cf >= 2)
       return coarse_solve_with_relaxation(lvl, M, R, Gn);
     STCHK(coarse_rhs(lvl, 0, M, R, Gn, nullptr));
@@ -1299,20 +1299,20 @@ struct Driver {
         const int j = j0 + i, layer = N - 1 - j;
         ++evals; ++sweeps;
         sh.in_slots = Slots{j, 1}; sh.out_slots = Slots{j + 1, 1};
-        STCHK(adjoint_chunk(chain[b], 1, W(0, j, 1), W(0, j + 1, 1), NO_ROWS, Params{tabTh, layer, -1},
-                            Params{tabThT, layer, -1}, Rows{tabZ, layer, -1},
+        STCHK(adjoint_chunk(chain[b], 1, W(0, j, 1), W(0, j + 1, 1), NO_ROWS, Params{(const void* const*)tabTh, layer, -1},
+                            Params{(const void* const*)tabThT, layer, -1}, Rows{(const void* const*)tabZ, layer, -1},
                             Slots{layer, -1}, hstep, &gp, nullptr, &sh, Slots{i, 1}));
         shadow_valid[(size_t)j + 1] = 1;
       }
       HIPCHK(hipEventRecord(a.pipe[2 + b], E->st));
       HIPCHK(hipStreamWaitEvent(E2->st, a.pipe[2 + b], 0));
       const int layer = N - 1 - j0;
-      const Params DT = {tabDT, layer, -1};
-      gp.DT = tabDT.p ? &DT : nullptr;
+      const Params DT = {(const void* const*)tabDT, layer, -1};
+      gp.DT = tabDT ? &DT : nullptr;
       gp.dE_all = dE_all;
       gp.dE_slots = Slots{layer, -1};
-      STCHK(param_grads_chunk(grads[b], n, Params{tabThT, layer, -1},
-                              Rows{tabZ, layer, -1}, Slots{layer, -1}, hstep, gp, shadow,
+      STCHK(param_grads_chunk(grads[b], n, Params{(const void* const*)tabThT, layer, -1},
+                              Rows{(const void* const*)tabZ, layer, -1}, Slots{layer, -1}, hstep, gp, shadow,
                               Slots{j0, 1}));
       HIPCHK(hipEventRecord(a.pipe[b], E2->st));
     }
@@ -1362,7 +1362,7 @@ struct Plan {                       // workspace of mgrit_forward / mgrit_adjoin
   bool two_lanes = false;
   Driver D;
   void* thT_blocks = nullptr;
-  void **th_list = nullptr, **dt_list = nullptr;   // room for the caller's lists of parameter and gradient blocks
+  void** tabDT = nullptr;           // layer n -> gradient block (adjoint with parameter gradients)
   float* dE_all = nullptr;          // cross-attention decoder: per-layer terms of the memory gradient
   size_t bytes = 0;
 };
@@ -1399,13 +1399,15 @@ int make_plan(Plan& P, const mgrit_model_desc* md, const mgrit_opts* op, int mod
   Driver& D = P.D;
   D.E = &E; D.E2 = P.two_lanes ? &P.E2 : nullptr; D.adjoint = adjoint; D.N = N; D.cf = op->cf; D.L = serial ? 1 : op->levels; D.relax = op->relax;
   D.h = op->h;
-  P.th_list = b.take<void*>(N);
+  D.tabW = b.take<void*>(N + 1);
+  D.tabTh = b.take<void*>(N);
   if (adjoint) {
+    D.tabZ = b.take<void*>(N + 1);
+    D.tabThT = b.take<void*>(N);
     P.thT_blocks = b.take_bytes((size_t)N * E.lay.block_bytes);
-    D.tabThT = spaced(P.thT_blocks, (long)E.lay.block_bytes);
   }
   if (mode == 2) {
-    P.dt_list = b.take<void*>(N);
+    P.tabDT = b.take<void*>(N);
     if (md->arch == MGRIT_ARCH_CROSS) P.dE_all = b.take<float>((size_t)N * E.Tm * E.d);
     for (Engine* L : {&E, P.two_lanes ? &P.E2 : nullptr})
       if (L) L->carve_grad_work(b);
@@ -1414,14 +1416,26 @@ int make_plan(Plan& P, const mgrit_model_desc* md, const mgrit_opts* op, int mod
     D.shadow = b.take_bytes((size_t)(N + 1) * E.T * E.d * E.esz);
     D.shadow_valid.assign((size_t)N + 1, 0);
   }
-  D.tabG.assign(D.L, NO_TABLE);
+  D.tabG.assign(D.L, nullptr);
   if (!serial) {
+    D.tabR = b.take<void*>(M0);
     D.max_partial = M0 * resnorm_partials_per_group();
     D.partial = b.take<double>(D.max_partial);
     const size_t state = (size_t)E.T * E.d * sizeof(float);
-    D.tabR = spaced(b.take_bytes(M0 * state), (long)state);
-    for (int l = 1; l < D.L; ++l)
-      D.tabG[l] = spaced(b.take_bytes((size_t)(N / Driver::ipow(op->cf, l) + 1) * state), (long)state);
+    char* Rbuf = static_cast<char*>(b.take_bytes(M0 * state));
+    std::vector<char*> Gbuf(D.L, nullptr);
+    for (int l = 1; l < D.L; ++l) {
+      const int Nl = N / Driver::ipow(op->cf, l);
+      D.tabG[l] = b.take<void*>(Nl + 1);
+      Gbuf[l] = static_cast<char*>(b.take_bytes((size_t)(Nl + 1) * state));
+    }
+    if (ws) {
+      if (launch_fill_table(D.tabR, Rbuf, (long)state, M0, st) != hipSuccess) return MGRIT_HIP_ERROR;
+      for (int l = 1; l < D.L; ++l) {
+        const int Nl = N / Driver::ipow(op->cf, l);
+        if (launch_fill_table(D.tabG[l], Gbuf[l], (long)state, Nl + 1, st) != hipSuccess) return MGRIT_HIP_ERROR;
+      }
+    }
   }
   P.bytes = (b.off + 255) / 256 * 256;
   return MGRIT_OK;
@@ -1446,7 +1460,7 @@ size_t layer_step_bytes(const mgrit_model_desc* desc, int adjoint, int n_groups,
     E.carve_adjoint(b, gc, n_groups);
     if (second_lane && n_groups >= 2) make_lane(E2, E, b, true, true);
     b.take_bytes((size_t)n_groups * E.lay.block_bytes);
-    b.take<void*>((size_t)n_groups * 5);
+    b.take<void*>((size_t)n_groups * 6);
   } else {
     E.carve_forward(b, gc);
     if (second_lane && n_groups >= 2) make_lane(E2, E, b, false, true);
@@ -1488,11 +1502,16 @@ int layer_step_on(const mgrit_model_desc* desc, int adjoint, int n_groups, const
     E.carve_adjoint(b, gc, G);
     if (second_lane && G >= 2 && make_lane(E2, E, b, true, false)) L2 = &E2;
     char* tblocks = static_cast<char*>(b.take_bytes((size_t)G * E.lay.block_bytes));
-    const void* const* lists[5] = {in, out, theta, lin_state, rhs};
-    Table tabs[5];
-    HIPCHK(make_tables(tabs, b.take<void*>((size_t)G * 5), lists, 5, G, st));
-    Params TH = {tabs[2], 0, 1}, THT = {spaced(tblocks, (long)E.lay.block_bytes), 0, 1};
-    Rows IN = {tabs[0], 0, 1}, OUT = {tabs[1], 0, 1}, LIN = {tabs[3], 0, 1}, RHS = {tabs[4], 0, 1};
+    void** tabs = b.take<void*>((size_t)G * 6);
+    void **tIn = tabs, **tOut = tabs + G, **tTh = tabs + 2 * G, **tLin = tabs + 3 * G, **tRhs = tabs + 4 * G,
+         **tThT = tabs + 5 * G;
+    const PtrSource src[6] = {{in, nullptr, 0}, {out, nullptr, 0}, {theta, nullptr, 0}, {lin_state, nullptr, 0},
+                              {rhs, nullptr, 0}, {nullptr, tblocks, (long)E.lay.block_bytes}};   // as the tables above
+    HIPCHK(upload_tables(tabs, src, 6, G, st));
+    Params TH = {(const void* const*)tTh, 0, 1}, THT = {(const void* const*)tThT, 0, 1};
+    Rows IN = {(const void* const*)tIn, 0, 1}, OUT = {(const void* const*)tOut, 0, 1};
+    Rows LIN = {(const void* const*)tLin, 0, 1};
+    Rows RHS = rhs ? Rows{(const void* const*)tRhs, 0, 1} : NO_ROWS;
     STCHK(transpose_blocks(E, G, TH, THT));
     if (desc->arch == MGRIT_ARCH_CROSS)
       HIPCHK(launch_cast_flat(static_cast<const float*>(memory), E.memb, (long)E.Tm * E.d, E.bf16, st));
@@ -1501,13 +1520,15 @@ int layer_step_on(const mgrit_model_desc* desc, int adjoint, int n_groups, const
   }
   E.carve_forward(b, gc);
   if (second_lane && G >= 2 && make_lane(E2, E, b, false, false)) L2 = &E2;
-  const void* const* lists[4] = {in, out, theta, rhs};
-  Table tabs[4];
-  HIPCHK(make_tables(tabs, b.take<void*>((size_t)G * 4), lists, 4, G, st));
+  void** tabs = b.take<void*>((size_t)G * 4);
+  void **tIn = tabs, **tOut = tabs + G, **tTh = tabs + 2 * G, **tRhs = tabs + 3 * G;
+  const PtrSource src[4] = {{in, nullptr, 0}, {out, nullptr, 0}, {theta, nullptr, 0}, {rhs, nullptr, 0}};
+  HIPCHK(upload_tables(tabs, src, rhs ? 4 : 3, G, st));
   if (desc->arch == MGRIT_ARCH_CROSS)
     HIPCHK(launch_cast_flat(static_cast<const float*>(memory), E.memb, (long)E.Tm * E.d, E.bf16, st));
-  Params TH = {tabs[2], 0, 1};
-  Rows IN = {tabs[0], 0, 1}, OUT = {tabs[1], 0, 1}, RHS = {tabs[3], 0, 1};
+  Params TH = {(const void* const*)tTh, 0, 1};
+  Rows IN = {(const void* const*)tIn, 0, 1}, OUT = {(const void* const*)tOut, 0, 1};
+  Rows RHS = rhs ? Rows{(const void* const*)tRhs, 0, 1} : NO_ROWS;
   return forward_groups(E, L2, G, IN, OUT, RHS, TH, hstep, 0, Slots{0, 0});
 }
 
@@ -1569,7 +1590,7 @@ int64_t mgrit_step_evaluations(const mgrit_opts* opts) {
   if (validate_opts(opts) != MGRIT_OK) return -1;
   Driver D;
   D.N = opts->N; D.cf = opts->cf; D.L = serial_run(opts) ? 1 : opts->levels; D.relax = opts->relax;
-  D.tabG.assign(D.L, NO_TABLE);
+  D.tabG.assign(D.L, nullptr);
   D.run(opts->iters);
   return D.evals;
 }
@@ -1578,7 +1599,7 @@ int64_t mgrit_step_depth(const mgrit_opts* opts) {
   if (validate_opts(opts) != MGRIT_OK) return -1;
   Driver D;
   D.N = opts->N; D.cf = opts->cf; D.L = serial_run(opts) ? 1 : opts->levels; D.relax = opts->relax;
-  D.tabG.assign(D.L, NO_TABLE);
+  D.tabG.assign(D.L, nullptr);
   D.run(opts->iters);
   return D.sweeps;
 }
@@ -1633,12 +1654,12 @@ int forward_impl(const mgrit_model_desc* desc, const mgrit_opts* opts, const voi
   Driver& D = P.D;
   const int N = opts->N;
   const size_t state = (size_t)E.T * E.d * sizeof(float);
-  D.tabW = spaced(Z_all, (long)state);
-  HIPCHK(make_tables(&D.tabTh, P.th_list, &theta, 1, N, st));
+  HIPCHK(launch_fill_table(D.tabW, static_cast<char*>(Z_all), (long)state, N + 1, st));
+  HIPCHK(upload_pointers(D.tabTh, theta, N, st));
   if (desc->arch == MGRIT_ARCH_CROSS)
     HIPCHK(launch_cast_flat(static_cast<const float*>(memory), E.memb, (long)E.Tm * E.d, E.bf16, st));
   if (E.kv_all)
-    STCHK(memory_kv(E, N, NO_ROWS, Params{D.tabTh, 0, 1}, E.kv_all, Slots{0, 1}));
+    STCHK(memory_kv(E, N, NO_ROWS, Params{(const void* const*)D.tabTh, 0, 1}, E.kv_all, Slots{0, 1}));
   // initial values (Z0 may be row 0 of Z_all itself)
   if (Z0 != Z_all) HIPCHK(hipMemcpyAsync(Z_all, Z0, state, hipMemcpyDeviceToDevice, st));
   if (!serial_run(opts) && opts->init_guess == 0) {
@@ -1676,15 +1697,16 @@ int adjoint_impl(const mgrit_model_desc* desc, const mgrit_opts* opts, const voi
   const int N = opts->N;
   const size_t state = (size_t)E.T * E.d * sizeof(float);
   // reversed index: point m lives in row N-m
-  D.tabW = spaced(static_cast<char*>(lambda_all) + (size_t)N * state, -(long)state);
-  D.tabZ = spaced(Z_all, (long)state);
-  HIPCHK(make_tables(&D.tabTh, P.th_list, &theta, 1, N, st));
-  Params TH = {D.tabTh, 0, 1};
-  Params THT = {D.tabThT, 0, 1};
+  HIPCHK(launch_fill_table(D.tabW, static_cast<char*>(lambda_all) + (size_t)N * state, -(long)state, N + 1, st));
+  HIPCHK(launch_fill_table(D.tabZ, static_cast<char*>(const_cast<void*>(Z_all)), (long)state, N + 1, st));
+  HIPCHK(upload_pointers(D.tabTh, theta, N, st));
+  HIPCHK(launch_fill_table(D.tabThT, static_cast<char*>(P.thT_blocks), (long)E.lay.block_bytes, N, st));
+  Params TH = {(const void* const*)D.tabTh, 0, 1};
+  Params THT = {(const void* const*)D.tabThT, 0, 1};
   if (desc->arch == MGRIT_ARCH_CROSS)
     HIPCHK(launch_cast_flat(static_cast<const float*>(memory), E.memb, (long)E.Tm * E.d, E.bf16, st));
   // linearisation cache for all N layers, batched over layers (unless every chunk recomputes its own)
-  Rows Zrows = {D.tabZ, 0, 1};
+  Rows Zrows = {(const void* const*)D.tabZ, 0, 1};
   if (prefilled && D.E2 && !serial_run(opts)) {
     // The forward solve's closing relaxation has left every layer it stepped through: all but the last
     // layer of each interval (n = cf-1, 2cf-1, ..).  That short pass does not touch the transposed weights,
@@ -1695,8 +1717,8 @@ int adjoint_impl(const mgrit_model_desc* desc, const mgrit_opts* opts, const voi
     HIPCHK(hipStreamWaitEvent(D.E2->st, a.fork, 0));
     int status = transpose_blocks(*D.E2, N, TH, THT);
     if (status == MGRIT_OK)
-      status = forward_groups(E, nullptr, N / cf, Rows{D.tabZ, cf - 1, cf}, NO_ROWS, NO_ROWS,
-                              Params{D.tabTh, cf - 1, cf}, 0.f, 1, Slots{cf - 1, cf});
+      status = forward_groups(E, nullptr, N / cf, Rows{(const void* const*)D.tabZ, cf - 1, cf}, NO_ROWS, NO_ROWS,
+                              Params{(const void* const*)D.tabTh, cf - 1, cf}, 0.f, 1, Slots{cf - 1, cf});
     // the helper lane is joined back whatever happened
     const hipError_t e1 = hipEventRecord(a.join, D.E2->st);
     const hipError_t e2 = e1 == hipSuccess ? hipStreamWaitEvent(st, a.join, 0) : e1;
@@ -1708,8 +1730,8 @@ int adjoint_impl(const mgrit_model_desc* desc, const mgrit_opts* opts, const voi
       // a serial run's forward solve has left all layers; with one lane the few missing ones follow here
       const int cf = opts->cf;
       if (!serial_run(opts))
-        STCHK(forward_groups(E, D.E2, N / cf, Rows{D.tabZ, cf - 1, cf}, NO_ROWS, NO_ROWS,
-                             Params{D.tabTh, cf - 1, cf}, 0.f, 1, Slots{cf - 1, cf}));
+        STCHK(forward_groups(E, D.E2, N / cf, Rows{(const void* const*)D.tabZ, cf - 1, cf}, NO_ROWS, NO_ROWS,
+                             Params{(const void* const*)D.tabTh, cf - 1, cf}, 0.f, 1, Slots{cf - 1, cf}));
     } else if (!E.recompute) {
       STCHK(forward_groups(E, D.E2, N, Zrows, NO_ROWS, NO_ROWS, TH, 0.f, 1, Slots{0, 1}));
     }
@@ -1725,7 +1747,7 @@ int adjoint_impl(const mgrit_model_desc* desc, const mgrit_opts* opts, const voi
   }
   if (D.shadow) {
     // operand-type copies of the initial values: point 0 (lambda_N) and the C-points that were set to it
-    const Rows first = {D.tabW, 0, 1};
+    const Rows first = {(const void* const*)D.tabW, 0, 1};
     HIPCHK(launch_cast_rows(1, E.Td(), first, D.shadow, E.Td(), Slots{0, 1}, E.bf16, st));
     D.shadow_valid[0] = 1;
     if (!serial_run(opts) && opts->init_guess == 0) {
@@ -1738,8 +1760,8 @@ int adjoint_impl(const mgrit_model_desc* desc, const mgrit_opts* opts, const voi
     }
   }
   D.resnorm = resnorm;
-  const void* const* grads = dtheta;
-  HIPCHK(make_tables(&D.tabDT, P.dt_list, &grads, 1, N, st));
+  if (dtheta) HIPCHK(upload_pointers(P.tabDT, (const void* const*)dtheta, N, st));
+  D.tabDT = dtheta ? P.tabDT : nullptr;
   D.dE_all = dmemory ? P.dE_all : nullptr;
   D.want_grads = dtheta || dmemory;
   STCHK(D.run(opts->iters));
@@ -1751,10 +1773,10 @@ int adjoint_impl(const mgrit_model_desc* desc, const mgrit_opts* opts, const voi
     const bool emitted = D.emitted;
     const int stride = emitted ? opts->cf : 1;
     const int count = emitted ? (D.serial() ? 0 : N / opts->cf) : N;
-    Rows LamNext = {D.tabW, N - 1, -stride};
-    Params DT = {D.tabDT, 0, stride};
-    const Params THs = {D.tabTh, 0, stride}, THTs = {D.tabThT, 0, stride};
-    const Rows Zs = {D.tabZ, 0, stride};
+    Rows LamNext = {(const void* const*)D.tabW, N - 1, -stride};
+    Params DT = {(const void* const*)P.tabDT, 0, stride};
+    const Params THs = {(const void* const*)D.tabTh, 0, stride}, THTs = {(const void* const*)D.tabThT, 0, stride};
+    const Rows Zs = {(const void* const*)D.tabZ, 0, stride};
     if (count > 0)
       STCHK(gradient_groups(E, D.E2, count, LamNext, THs, THTs, Zs, Slots{0, stride}, dtheta ? &DT : nullptr,
                             dmemory ? P.dE_all : nullptr, opts->h));
@@ -1812,7 +1834,7 @@ struct StackedPlan {
   bool two_lanes = false;
   Driver D;
   void* thT_blocks = nullptr;
-  void **th_list = nullptr, **thT_list = nullptr, **dt_list = nullptr;
+  void** tabDT = nullptr;
   size_t enc_block = 0, dec_block = 0;
   size_t bytes = 0;
 };
@@ -1882,24 +1904,38 @@ int make_stacked_plan(StackedPlan& P, const mgrit_model_desc* md, const mgrit_op
   D.Ed = &P.Ed; D.Ed2 = P.two_lanes ? &P.Ed2 : nullptr;
   D.n_enc = n_enc; D.x_elems = P.Ee.Td(); D.y_elems = P.Ed.Td();
   D.adjoint = adjoint; D.N = N; D.cf = op->cf; D.L = serial ? 1 : op->levels; D.relax = op->relax; D.h = op->h;
-  P.th_list = b.take<void*>(N);
+  D.tabW = b.take<void*>(N + 1);
+  D.tabTh = b.take<void*>(N);
   if (adjoint) {
-    P.thT_list = b.take<void*>(N);
+    D.tabZ = b.take<void*>(N + 1);
+    D.tabThT = b.take<void*>(N);
     P.thT_blocks = b.take_bytes((size_t)n_enc * P.enc_block + (size_t)n_dec * P.dec_block);
   }
   if (mode == 2) {
-    P.dt_list = b.take<void*>(N);
+    P.tabDT = b.take<void*>(N);
     for (Engine* L : {&P.Ee, &P.Ed, P.two_lanes ? &P.Ee2 : nullptr, P.two_lanes ? &P.Ed2 : nullptr})
       if (L) L->carve_grad_work(b);
   }
-  D.tabG.assign(D.L, NO_TABLE);
+  D.tabG.assign(D.L, nullptr);
   if (!serial) {
+    D.tabR = b.take<void*>(M0);
     D.max_partial = M0 * resnorm_partials_per_group();
     D.partial = b.take<double>(D.max_partial);
     const size_t state = (size_t)D.state_elems() * sizeof(float);
-    D.tabR = spaced(b.take_bytes(M0 * state), (long)state);
-    for (int l = 1; l < D.L; ++l)
-      D.tabG[l] = spaced(b.take_bytes((size_t)(N / Driver::ipow(op->cf, l) + 1) * state), (long)state);
+    char* Rbuf = static_cast<char*>(b.take_bytes(M0 * state));
+    std::vector<char*> Gbuf(D.L, nullptr);
+    for (int l = 1; l < D.L; ++l) {
+      const int Nl = N / Driver::ipow(op->cf, l);
+      D.tabG[l] = b.take<void*>(Nl + 1);
+      Gbuf[l] = static_cast<char*>(b.take_bytes((size_t)(Nl + 1) * state));
+    }
+    if (ws) {
+      if (launch_fill_table(D.tabR, Rbuf, (long)state, M0, st) != hipSuccess) return MGRIT_HIP_ERROR;
+      for (int l = 1; l < D.L; ++l) {
+        const int Nl = N / Driver::ipow(op->cf, l);
+        if (launch_fill_table(D.tabG[l], Gbuf[l], (long)state, Nl + 1, st) != hipSuccess) return MGRIT_HIP_ERROR;
+      }
+    }
   }
   P.bytes = (b.off + 255) / 256 * 256;
   return MGRIT_OK;
@@ -1949,8 +1985,8 @@ int forward_stacked_impl(const mgrit_model_desc* desc, const mgrit_opts* opts, i
   Driver& D = P.D;
   const int N = opts->N;
   const size_t state = (size_t)D.state_elems() * sizeof(float);
-  D.tabW = spaced(Z_all, (long)state);
-  HIPCHK(make_tables(&D.tabTh, P.th_list, &theta, 1, N, st));
+  HIPCHK(launch_fill_table(D.tabW, static_cast<char*>(Z_all), (long)state, N + 1, st));
+  HIPCHK(upload_pointers(D.tabTh, theta, N, st));
   if (Z0 != Z_all) HIPCHK(hipMemcpyAsync(Z_all, Z0, state, hipMemcpyDeviceToDevice, st));
   if (!serial_run(opts) && opts->init_guess == 0) {
     for (int k = 1; k <= N / opts->cf; ++k)
@@ -1980,20 +2016,19 @@ int adjoint_stacked_impl(const mgrit_model_desc* desc, const mgrit_opts* opts, i
   Driver& D = P.D;
   const int N = opts->N, n_dec = N - n_enc;
   const size_t state = (size_t)D.state_elems() * sizeof(float);
-  D.tabW = spaced(static_cast<char*>(lambda_all) + (size_t)N * state, -(long)state);
-  D.tabZ = spaced(Z_all, (long)state);
-  HIPCHK(make_tables(&D.tabTh, P.th_list, &theta, 1, N, st));
+  HIPCHK(launch_fill_table(D.tabW, static_cast<char*>(lambda_all) + (size_t)N * state, -(long)state, N + 1, st));
+  HIPCHK(launch_fill_table(D.tabZ, static_cast<char*>(const_cast<void*>(Z_all)), (long)state, N + 1, st));
+  HIPCHK(upload_pointers(D.tabTh, theta, N, st));
   char* tblocks = static_cast<char*>(P.thT_blocks);
-  HIPCHK(launch_fill_table(P.thT_list, tblocks, (long)P.enc_block, n_enc, st));
-  HIPCHK(launch_fill_table(P.thT_list + n_enc, tblocks + (size_t)n_enc * P.enc_block, (long)P.dec_block, n_dec, st));
-  D.tabThT = {P.thT_list, 0};
-  const Params TH = {D.tabTh, 0, 1};
-  const Params THT = {D.tabThT, 0, 1};
+  HIPCHK(launch_fill_table(D.tabThT, tblocks, (long)P.enc_block, n_enc, st));
+  HIPCHK(launch_fill_table(D.tabThT + n_enc, tblocks + (size_t)n_enc * P.enc_block, (long)P.dec_block, n_dec, st));
+  const Params TH = {(const void* const*)D.tabTh, 0, 1};
+  const Params THT = {(const void* const*)D.tabThT, 0, 1};
   STCHK(transpose_blocks(P.Ee, n_enc, TH, THT));
   STCHK(transpose_blocks(P.Ed, n_dec, shift(TH, n_enc), shift(THT, n_enc)));
   // linearisation cache, batched over layers: encoder layers at the X rows of Z_n, decoder layers at
   // the Y rows with the X rows of the same state as memory
-  const Rows Zrows = {D.tabZ, 0, 1};
+  const Rows Zrows = {(const void* const*)D.tabZ, 0, 1};
   const Rows ZdecX = shift(Zrows, n_enc), ZdecY = Driver::part(ZdecX, D.x_elems);
   if (prefilled) {
     // the forward solve has left every layer but the last of each interval (n = cf-1, 2cf-1, ..): the
@@ -2002,13 +2037,13 @@ int adjoint_stacked_impl(const mgrit_model_desc* desc, const mgrit_opts* opts, i
     int left_e = n_enc >= cf ? (n_enc - cf) / cf + 1 : 0;           // layers cf-1 + k cf below n_enc
     if (left_e > left) left_e = left;
     if (left_e > 0)
-      STCHK(forward_groups(P.Ee, D.E2, left_e, Rows{D.tabZ, cf - 1, cf}, NO_ROWS, NO_ROWS,
-                           Params{D.tabTh, cf - 1, cf}, 0.f, 1, Slots{cf - 1, cf}));
+      STCHK(forward_groups(P.Ee, D.E2, left_e, Rows{(const void* const*)D.tabZ, cf - 1, cf}, NO_ROWS, NO_ROWS,
+                           Params{(const void* const*)D.tabTh, cf - 1, cf}, 0.f, 1, Slots{cf - 1, cf}));
     if (left - left_e > 0) {
       const int n0 = cf - 1 + left_e * cf;                           // first of them in the decoder
-      const Rows ZX = {D.tabZ, n0, cf};
+      const Rows ZX = {(const void* const*)D.tabZ, n0, cf};
       STCHK(forward_groups(P.Ed, D.Ed2, left - left_e, Driver::part(ZX, D.x_elems), NO_ROWS, NO_ROWS,
-                           Params{D.tabTh, n0, cf}, 0.f, 1, Slots{n0 - n_enc, cf}, ZX));
+                           Params{(const void* const*)D.tabTh, n0, cf}, 0.f, 1, Slots{n0 - n_enc, cf}, ZX));
     }
   } else if (!P.Ee.recompute) {
     STCHK(forward_groups(P.Ee, D.E2, n_enc, Zrows, NO_ROWS, NO_ROWS, TH, 0.f, 1, Slots{0, 1}));
@@ -2022,8 +2057,8 @@ int adjoint_stacked_impl(const mgrit_model_desc* desc, const mgrit_opts* opts, i
                             hipMemcpyDeviceToDevice, st));
   }
   D.resnorm = resnorm;
-  const void* const* grads = dtheta;
-  HIPCHK(make_tables(&D.tabDT, P.dt_list, &grads, 1, N, st));
+  if (dtheta) HIPCHK(upload_pointers(P.tabDT, (const void* const*)dtheta, N, st));
+  D.tabDT = dtheta ? P.tabDT : nullptr;
   D.want_grads = dtheta != nullptr;
   STCHK(D.run(opts->iters));
   if (dtheta) {
@@ -2035,10 +2070,10 @@ int adjoint_stacked_impl(const mgrit_model_desc* desc, const mgrit_opts* opts, i
     const int count = emitted ? (D.serial() ? 0 : N / opts->cf) : N;
     int count_e = (n_enc + stride - 1) / stride;           // groups g with g * stride < n_enc
     if (count_e > count) count_e = count;
-    const Rows LamNext = {D.tabW, N - 1, -stride};
-    const Params DT = {D.tabDT, 0, stride};
-    const Params THs = {D.tabTh, 0, stride}, THTs = {D.tabThT, 0, stride};
-    const Rows Zs = {D.tabZ, 0, stride};
+    const Rows LamNext = {(const void* const*)D.tabW, N - 1, -stride};
+    const Params DT = {(const void* const*)P.tabDT, 0, stride};
+    const Params THs = {(const void* const*)D.tabTh, 0, stride}, THTs = {(const void* const*)D.tabThT, 0, stride};
+    const Rows Zs = {(const void* const*)D.tabZ, 0, stride};
     if (count_e > 0)
       STCHK(gradient_groups(P.Ee, D.E2, count_e, LamNext, THs, THTs, Zs, Slots{0, stride}, &DT, nullptr, opts->h));
     if (count - count_e > 0) {

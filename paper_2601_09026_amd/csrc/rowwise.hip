@@ -441,52 +441,40 @@ int resnorm_partials_per_group() { return RN_BLOCKS; }
 // ---------------------------------------------------------------------------
 // pointer tables
 // ---------------------------------------------------------------------------
-__global__ void fill_table_kernel(void** space, char* base, long stride_bytes, int n) {
+__global__ void fill_table_kernel(void** tab, char* base, long stride_bytes, int n) {
   const int i = blockIdx.x * blockDim.x + threadIdx.x;
-  if (i < n) space[i] = base + (long)i * stride_bytes;
+  if (i < n) tab[i] = base + (long)i * stride_bytes;
 }
 
-hipError_t launch_fill_table(void** space, char* base, long stride_bytes, int n, hipStream_t st) {
+hipError_t launch_fill_table(void** tab, char* base, long stride_bytes, int n, hipStream_t st) {
   if (n <= 0) return hipSuccess;
-  hipLaunchKernelGGL(fill_table_kernel, dim3((n + 255) / 256), dim3(256), 0, st, space, base, stride_bytes, n);
+  hipLaunchKernelGGL(fill_table_kernel, dim3((n + 255) / 256), dim3(256), 0, st, tab, base, stride_bytes, n);
   return hipGetLastError();
 }
 
 constexpr int PACK = 128;                  // 1 KB of kernel arguments
 struct PtrPack { const void* p[PACK]; };
-__global__ void __launch_bounds__(PACK) upload_ptrs_kernel(void** space, PtrPack pack, int n) {
+__global__ void __launch_bounds__(PACK) upload_ptrs_kernel(void** tab, PtrPack pack, int n) {
   const int i = threadIdx.x;
-  if (i < n) space[i] = const_cast<void*>(pack.p[i]);
+  if (i < n) tab[i] = const_cast<void*>(pack.p[i]);
 }
 
-hipError_t make_tables(Table* out, void** space, const void* const* const* lists, int n_lists, int n, hipStream_t st) {
+hipError_t upload_tables(void** tab, const PtrSource* src, int n_src, int n, hipStream_t st) {
   PtrPack pack;
   int m = 0;
-  const auto send = [&] {
-    if (m == 0) return;
-    hipLaunchKernelGGL(upload_ptrs_kernel, dim3(1), dim3(PACK), 0, st, space, pack, m);
-    space += m;
-    m = 0;
-  };
-  for (int s = 0; s < n_lists; ++s) {
-    out[s] = {nullptr, 0};
-    if (!lists[s]) continue;
-    const auto entry = [&](int i) { return reinterpret_cast<intptr_t>(lists[s][i]); };
-    const long step = n > 1 ? entry(1) - entry(0) : 1;
-    bool even = step != 0;
-    for (int i = 2; i < n && even; ++i) even = entry(i) - entry(i - 1) == step;
-    if (even) {
-      out[s] = spaced(lists[s][0], step);
-      continue;
-    }
-    out[s].p = space + m;
+  for (int s = 0; s < n_src; ++s)
     for (int i = 0; i < n; ++i) {
-      pack.p[m++] = lists[s][i];
-      if (m == PACK) send();
+      pack.p[m++] = src[s].list ? src[s].list[i] : src[s].base + i * src[s].stride;
+      if (m < PACK && !(s == n_src - 1 && i == n - 1)) continue;
+      hipLaunchKernelGGL(upload_ptrs_kernel, dim3(1), dim3(PACK), 0, st, tab, pack, m);
+      tab += m;
+      m = 0;
     }
-  }
-  send();
   return hipGetLastError();
+}
+hipError_t upload_pointers(void** tab, const void* const* host_ptrs, int n, hipStream_t st) {
+  const PtrSource src = {host_ptrs, nullptr, 0};
+  return upload_tables(tab, &src, 1, n, st);
 }
 
 // ---------------------------------------------------------------------------

@@ -2,7 +2,7 @@
 multiply-by-GELU' products (more than one 256x256 tile per compute unit) against 128x128 tiles, bit for bit; bf16
 attention at the edges of its 32-row units, 64-row tiles and rings of three tiles against the CPU oracle; many layers of
 few tokens in one launch against one layer per launch, bit for bit; keys and values of the decoder's memory formed once
-per layer against formed in every step, bit for bit; evenly spaced lists of pointers against others, bit for bit."""
+per layer against formed in every step, bit for bit."""
 import ctypes as C
 
 import pytest
@@ -214,75 +214,3 @@ def test_kept_memory_projections_bits(dtype, d, S, Sm, N, cf, levels, relax, lan
     assert torch.isfinite(outs[0][0]).all() and torch.isfinite(outs[0][1]).all()
     for Z, r in outs[1:]:
         assert torch.equal(Z, outs[0][0]) and torch.equal(r, outs[0][1])
-
-
-def laid_out(tensors, how):
-    """Copies of equally sized tensors, evenly spaced (up or down) or not."""
-    n, x = len(tensors), tensors[0]
-    room = torch.empty((2 * n + 1, *x.shape), dtype=x.dtype, device=x.device)
-    at = {"even": list(range(n)), "down": [2 * (n - i) for i in range(n)],
-          "odd": [i + (i > 1) for i in range(n)]}[how]        # (any two are evenly spaced)
-    for i, t in zip(at, tensors):
-        room[i] = t
-    return [room[i] for i in at]
-
-
-@pytest.mark.parametrize("adjoint", [False, True])
-@pytest.mark.parametrize("arch,dtype,d,f", [
-    (wls.ARCH_CROSS, wls.DTYPE_BF16, 192, 256), (wls.ARCH_ENCODER, wls.DTYPE_BF16, 128, 256),
-    (wls.ARCH_CROSS, wls.DTYPE_F32, 72, 136), (wls.ARCH_CAUSAL, wls.DTYPE_F32, 64, 128),
-])
-def test_lists_of_pointers_step(arch, dtype, d, f, adjoint):
-    """Evenly spaced lists are computed in the kernels, others are read from memory (at 27 groups their upload is two
-    launches); the same layer everywhere is a list of spacing 0."""
-    wl = make(arch, dtype, d=d, H=d // 64 or 1, f=f, B=2, S=21, Sm=17 if arch == wls.ARCH_CROSS else 0)
-    mem = wls.cross_memory(wl)
-    mem = None if mem is None else dev(mem)
-    for G in (1, 2, 3, 27):
-        print(f"[case] lists of pointers arch={arch} dtype={dtype} d={d} adjoint={adjoint} G={G}", flush=True)
-        dm = DeviceModel(wl, n_layers=G, weight_std=0.05, keep_host=False)
-        gen = torch.Generator(device="cuda")
-        gen.manual_seed(7)
-        ins, lin, rhs = (list(torch.randn((G, wl.tokens, wl.d_model), generator=gen, device="cuda")) for _ in range(3))
-
-        def run(how, blocks):
-            outs = laid_out([torch.full_like(x, float("nan")) for x in ins], how)
-            mb.layer_step_batched(dm.desc, adjoint, laid_out(ins, how), outs, blocks, 0.5,
-                                  lin_state=laid_out(lin, how) if adjoint else None, rhs=laid_out(rhs, how), memory=mem)
-            torch.cuda.synchronize()
-            return torch.stack(outs)
-
-        want = run("odd", laid_out(dm.blocks, "odd"))
-        assert torch.isfinite(want).all()
-        for how in ("even", "down"):
-            assert torch.equal(run(how, laid_out(dm.blocks, how)), want), (G, how)
-        assert torch.equal(run("even", laid_out(dm.blocks, "odd")), want), G
-        one = run("odd", [dm.blocks[0]] * G)                 # layer 0 everywhere, against copies of it
-        assert torch.equal(one, run("even", laid_out([dm.blocks[0]] * G, "even"))), G
-
-
-@pytest.mark.parametrize("arch", [wls.ARCH_ENCODER, wls.ARCH_CROSS])
-def test_lists_of_pointers_solve(arch):
-    """Parameter and gradient blocks of a training step, evenly spaced or not."""
-    wl = make(arch, wls.DTYPE_BF16, d=128, H=2, f=256, B=2, S=20, Sm=16 if arch == wls.ARCH_CROSS else 0)
-    N = 8
-    dm = DeviceModel(wl, n_layers=N, weight_std=0.05, keep_host=False)
-    opts = mb.mgrit_opts(N, 1.0 / N, 2, 2, 2)
-    mem = wls.cross_memory(wl)
-    mem = None if mem is None else dev(mem)
-    gen = torch.Generator(device="cuda")
-    gen.manual_seed(11)
-    Z0, lamN = (torch.randn((wl.tokens, wl.d_model), generator=gen, device="cuda") for _ in range(2))
-    got = {}
-    for how in ("even", "down", "odd"):
-        print(f"[case] lists of pointers, solve arch={arch} {how}", flush=True)
-        blocks = laid_out(dm.blocks, how)
-        grads = laid_out([torch.full((mb.grad_layout(dm.desc).block_bytes // 4,), float("nan"), device="cuda")
-                          .view(torch.uint8) for _ in range(N)], how)
-        Z, _ = mb.mgrit_forward(dm.desc, opts, Z0, blocks, memory=mem)
-        lam, _ = mb.mgrit_adjoint(dm.desc, opts, Z, blocks, lamN, memory=mem, dtheta=grads)
-        torch.cuda.synchronize()
-        got[how] = (Z, lam, torch.stack(grads).view(torch.int32))
-    for how in ("down", "odd"):
-        for a, b in zip(got[how], got["even"]):
-            assert torch.equal(a, b), how
