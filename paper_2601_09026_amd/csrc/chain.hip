@@ -965,17 +965,26 @@ hipError_t launch_chain_adjoint_head(const ChainAdjointArgs& a, int d, bool is_b
   if (d == 64) return n ? launch(chain_adjoint_head_kernel<64, 2>, a, 2, vec_bytes(d), st) : launch(chain_adjoint_head_kernel<64, 4>, a, 4, vec_bytes(d), st);
   return n ? launch(chain_adjoint_head_kernel<128, 2>, a, 2, vec_bytes(d), st) : launch(chain_adjoint_head_kernel<128, 4>, a, 4, vec_bytes(d), st);
 }
-// Whole layer steps launch by launch and on chains, forward / adjoint with the cache pass, in us:
-//   128 wide, 512 hidden: 1 x 64 tokens 33 / 63 and 34 / 72, 2 x 512 tokens 41 / 96 and 42 / 104, 8 x 512 tokens 48 / 108 and
-//   43 / 107, 4 layers of these 64 / 146 and 51 / 122; 256 hidden: 1 x 64 tokens 35 / 65 and 27 / 59; 64 wide, 256 hidden:
-//   1 x 64 tokens 37 / 66 and 20 / 43.
-// A wavefront's way through 512 hidden features takes as long as the launches it replaces while it has its SIMD to itself; so
-// wide hidden layers need many tokens.  The rule follows from the model alone: how many layers share a launch cannot show in
-// a result.
+// Whole layer steps launch by launch and on chains, forward / adjoint with the cache pass, in us (sequences of 64):
+//   128 wide, 256 hidden: 1 x 64 tokens 28 / 62 and 26 / 58, 4 x 2048 tokens 40 / 82 and 32 / 70; 64 wide, 512 hidden: 1 x 64
+//   tokens 29 / 58 and 23 / 53.  Never slower up to there.
+// A wavefront's way through the hidden features takes a time of its own (128 wide, 2048 hidden: 70 us forward, 150 adjoint),
+// which the launches it replaces take only where there are many tokens.  Wide hidden layers of a single layer:
+//   128 wide, 384: 2048 tokens 32 / 66 and 31 / 67;  512: 2048 tokens 33 / 67 and 34 / 73, 3072 tokens 35 / 72 and 34 / 74, 6144
+//   tokens 39 / 81 and 36 / 79;  768: 8192 tokens 45 / 90 and 43 / 95;  1024: 8192 tokens 46 / 93 and 49 / 108, 10240 tokens
+//   57 / 113 and 51 / 110;  2048: 4096 tokens 46 / 89 and 70 / 153, 12288 tokens 75 / 150 and 75 / 161, 16384 tokens 84 / 181 and
+//   76 / 167;
+//   64 wide, 768: 2048 tokens 35 / 65 and 30 / 67;  1024: 4096 tokens 35 / 72 and 35 / 78, 6144 tokens 39 / 80 and 36 / 81;
+//   2048: 4096 tokens 42 / 83 and 54 / 121, 12288 tokens 59 / 121 and 56 / 128, 16384 tokens 67 / 144 and 58 / 130.
+// The lines lie where a training step of single layers (serial propagation, every launch one layer) is no slower on chains:
+// within 1 % there, and a single transposed step alone up to 4 % slower (decoders with cross attention, 384 and 512 hidden: 1
+// to 5 and 4 to 7 %), while launches of two layers gain up to 20 % and of four 10 to 45 %.  The rule follows from the model
+// alone: how many layers share a launch cannot show in a result.
 bool chain_ok(int d, int f, int T, bool is_bf16) {
   if (!is_bf16) return chain_f32_ok(d, f);
   if ((d != 64 && d != 128) || f % 64 != 0 || f > 2048 || 2.0 * T * (f > 3 * d ? f : 3 * d) >= 2e9) return false;
-  return d == 64 ? f <= 512 || T >= 2048 : f <= 256 || T >= 2048;
+  if (d == 64) return f <= 512 || T >= (f <= 768 ? 2048 : f <= 1024 ? 6144 : 16384);
+  return f <= 256 || T >= (f <= 384 ? 2048 : f <= 512 ? 3072 : f <= 1024 ? 10240 : 16384);
 }
 
 }  // namespace mg

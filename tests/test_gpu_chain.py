@@ -68,13 +68,16 @@ def steps(dm, wl, adjoint, ins, lin, rhs):
     (wls.ARCH_ENCODER, 64, 1, 192, 1, 33, 0, 3, False),
     (wls.ARCH_CROSS, 64, 2, 256, 3, 43, 7, 2, True),          # 129 rows
     (wls.ARCH_ENCODER, 64, 1, 512, 2, 64, 0, 1, False),
-    (wls.ARCH_ENCODER, 64, 2, 2048, 16, 129, 0, 1, True),     # 2064 tokens, the widest hidden layer
+    (wls.ARCH_ENCODER, 64, 2, 2048, 16, 129, 0, 1, True),     # 2064 tokens: launch by launch both times
+    (wls.ARCH_ENCODER, 64, 2, 2048, 127, 130, 0, 1, True),    # 16510 tokens, the widest hidden layer
     (wls.ARCH_CAUSAL, 128, 1, 64, 1, 32, 0, 1, True),
     (wls.ARCH_ENCODER, 128, 2, 128, 1, 63, 0, 3, False),
     (wls.ARCH_CROSS, 128, 2, 192, 1, 127, 33, 2, True),
     (wls.ARCH_CAUSAL, 128, 4, 256, 1, 128, 0, 2, False),
     (wls.ARCH_ENCODER, 128, 1, 128, 4, 4096, 0, 2, True),     # 256 blocks of 128 rows
-    (wls.ARCH_CAUSAL, 128, 2, 512, 8, 257, 0, 5, True),       # 2056 tokens: wide hidden layers from 2048 on
+    (wls.ARCH_CAUSAL, 128, 2, 512, 8, 257, 0, 5, True),       # 2056 tokens: launch by launch both times
+    (wls.ARCH_CAUSAL, 128, 2, 512, 12, 257, 0, 5, True),      # 3084 tokens: 512 hidden features from 3072 on
+    (wls.ARCH_CROSS, 128, 1, 448, 13, 239, 21, 1, False),     # 3107 tokens, seven chunks
 ])
 def test_steps_match_general_path(arch, d, H, f, B, S, Sm, G, rhs, adjoint):
     wl = make(arch, wls.DTYPE_BF16, d=d, H=H, f=f, B=B, S=S, Sm=Sm)
@@ -84,6 +87,37 @@ def test_steps_match_general_path(arch, d, H, f, B, S, Sm, G, rhs, adjoint):
     chain, general = both_paths(lambda: steps(dm, wl, adjoint, ins, lin, r if rhs else None))
     for g in range(G):
         close(chain[g], general[g], ins[g] + r[g] if rhs else ins[g], f"group {g}")
+
+
+def chain_launches(dm, wl, adjoint, ins, lin):
+    mb.mgrit_profile_enable(256)
+    try:
+        mb.mgrit_profile_reset()
+        steps(dm, wl, adjoint, ins, lin, None)
+        return mb.mgrit_profile_read().get("chain", {"launches": 0})["launches"]
+    finally:
+        mb.mgrit_profile_enable(0)
+
+
+@pytest.mark.parametrize("dtype,d,f,B,S,chain", [
+    (wls.DTYPE_BF16, 64, 512, 1, 8, True), (wls.DTYPE_BF16, 64, 576, 1, 2047, False), (wls.DTYPE_BF16, 64, 576, 1, 2048, True),
+    (wls.DTYPE_BF16, 64, 768, 1, 2048, True), (wls.DTYPE_BF16, 64, 832, 3, 2047, False), (wls.DTYPE_BF16, 64, 832, 3, 2048, True),
+    (wls.DTYPE_BF16, 64, 1024, 3, 2048, True), (wls.DTYPE_BF16, 64, 1088, 127, 129, False), (wls.DTYPE_BF16, 64, 1088, 128, 128, True),
+    (wls.DTYPE_BF16, 64, 2112, 128, 129, False),
+    (wls.DTYPE_BF16, 128, 256, 1, 8, True), (wls.DTYPE_BF16, 128, 320, 1, 2047, False), (wls.DTYPE_BF16, 128, 384, 1, 2048, True),
+    (wls.DTYPE_BF16, 128, 448, 1, 3071, False), (wls.DTYPE_BF16, 128, 512, 1, 3072, True),
+    (wls.DTYPE_BF16, 128, 576, 5, 2047, False), (wls.DTYPE_BF16, 128, 1024, 5, 2048, True),
+    (wls.DTYPE_BF16, 128, 1088, 127, 129, False), (wls.DTYPE_BF16, 128, 2048, 128, 128, True),
+    (wls.DTYPE_BF16, 64, 96, 1, 64, False), (wls.DTYPE_BF16, 192, 192, 1, 64, False),
+    (wls.DTYPE_F32, 64, 256, 1, 8, True), (wls.DTYPE_F32, 64, 192, 1, 8, False), (wls.DTYPE_F32, 128, 128, 1, 8, False)])
+def test_where_the_lines_lie(dtype, d, f, B, S, chain):
+    """Either side of each line of the rule: widths, hidden widths and the tokens from which wide hidden layers take chains."""
+    wl = make(wls.ARCH_ENCODER, dtype, d=d, H=d // 64, f=f, B=B, S=S)
+    print(f"[case] chain or not dtype={dtype} d={d} f={f} B={B} S={S}", flush=True)
+    dm = DeviceModel(wl, n_layers=1, weight_std=0.08, keep_host=False)
+    ins, lin, _ = states(wl, 1, 9)
+    assert chain_launches(dm, wl, False, ins, lin) == (2 if chain else 0)
+    assert chain_launches(dm, wl, True, ins, lin) == (4 if chain else 0)          # the layer's entries of the cache as well
 
 
 @pytest.mark.parametrize("adjoint", [False, True])
