@@ -19,6 +19,7 @@
 
 #include "common.h"
 #include "kernels.h"
+#include "lds_limit.h"
 #include "prof.h"
 
 namespace mg {
@@ -902,19 +903,12 @@ __global__ void __launch_bounds__(64 * NW, 2) chain_adjoint_head_kernel(const Ch
   }
 }
 
-template <typename K, typename A>
-hipError_t launch(K kern, const A& a, int nw, int vectors, hipStream_t st) {
+template <auto kern, typename A>
+hipError_t launch(const A& a, int nw, int vectors, hipStream_t st) {
   const int tiles_m = (a.T + 32 * nw - 1) / (32 * nw), total = tiles_m * a.n_groups, per_xcd = (total + 7) / 8;
   const int smem = RING_BYTES + vectors + 1024;            // (a bias is read one piece ahead)
-  static const void* raised[32];                           // kernels whose LDS limit has been raised (calls enqueue one at a time)
-  for (const void*& k : raised) {
-    if (k == reinterpret_cast<const void*>(kern)) break;
-    if (k) continue;
-    const hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(kern), hipFuncAttributeMaxDynamicSharedMemorySize, 80 << 10);
-    if (e != hipSuccess) return e;
-    k = reinterpret_cast<const void*>(kern);
-    break;
-  }
+  static unsigned long raised = 0;
+  if (const hipError_t e = raise_lds_limit(reinterpret_cast<const void*>(kern), 80 << 10, raised); e != hipSuccess) return e;
   hipLaunchKernelGGL(kern, dim3(per_xcd * 8), dim3(64 * nw), smem, st, a, tiles_m, total, per_xcd);
   return hipGetLastError();
 }
@@ -922,8 +916,8 @@ hipError_t launch(K kern, const A& a, int nw, int vectors, hipStream_t st) {
 bool narrow(int n_groups, int T) { return (long)n_groups * ((T + 127) / 128) <= compute_units() / 2; }
 
 template <int D, int MODE> hipError_t tail_of(const ChainTailArgs& a, hipStream_t st) {
-  return narrow(a.n_groups, a.T) ? launch(chain_tail_kernel<D, 2, MODE>, a, 2, 4 * vec_bytes(D) + vec_bytes(a.f), st)
-                                 : launch(chain_tail_kernel<D, 4, MODE>, a, 4, 4 * vec_bytes(D) + vec_bytes(a.f), st);
+  return narrow(a.n_groups, a.T) ? launch<chain_tail_kernel<D, 2, MODE>>(a, 2, 4 * vec_bytes(D) + vec_bytes(a.f), st)
+                                 : launch<chain_tail_kernel<D, 4, MODE>>(a, 4, 4 * vec_bytes(D) + vec_bytes(a.f), st);
 }
 template <int D> hipError_t tail_of(const ChainTailArgs& a, int mode, hipStream_t st) {
   return mode == 0 ? tail_of<D, 0>(a, st) : mode == 1 ? tail_of<D, 1>(a, st) : tail_of<D, 2>(a, st);
@@ -944,8 +938,8 @@ hipError_t launch_chain_head(const ChainHeadArgs& a, int d, bool is_bf16, hipStr
   ProfScope ps(PC_CHAIN, rows * 6.0 * d * d, rows * d * (10.0 + (a.xhat ? 2.0 : 0.0)), st);
   if (!is_bf16) return launch_chain_f32_head(a, st);
   const bool n = narrow(a.n_groups, a.T);
-  if (d == 64) return n ? launch(chain_head_kernel<64, 2>, a, 2, 2 * vec_bytes(d) + vec_bytes(3 * d), st) : launch(chain_head_kernel<64, 4>, a, 4, 2 * vec_bytes(d) + vec_bytes(3 * d), st);
-  return n ? launch(chain_head_kernel<128, 2>, a, 2, 2 * vec_bytes(d) + vec_bytes(3 * d), st) : launch(chain_head_kernel<128, 4>, a, 4, 2 * vec_bytes(d) + vec_bytes(3 * d), st);
+  if (d == 64) return n ? launch<chain_head_kernel<64, 2>>(a, 2, 2 * vec_bytes(d) + vec_bytes(3 * d), st) : launch<chain_head_kernel<64, 4>>(a, 4, 2 * vec_bytes(d) + vec_bytes(3 * d), st);
+  return n ? launch<chain_head_kernel<128, 2>>(a, 2, 2 * vec_bytes(d) + vec_bytes(3 * d), st) : launch<chain_head_kernel<128, 4>>(a, 4, 2 * vec_bytes(d) + vec_bytes(3 * d), st);
 }
 hipError_t launch_chain_adjoint_tail(const ChainAdjointArgs& a, int d, bool is_bf16, hipStream_t st) {
   if (a.n_groups <= 0) return hipSuccess;
@@ -953,8 +947,8 @@ hipError_t launch_chain_adjoint_tail(const ChainAdjointArgs& a, int d, bool is_b
   ProfScope ps(PC_CHAIN, rows * (2.0 * d * d + 4.0 * d * a.f), rows * (10.0 * d + 2.0 * a.f), st);
   if (!is_bf16) return launch_chain_f32_adjoint_tail(a, st);
   const bool n = narrow(a.n_groups, a.T);
-  if (d == 64) return n ? launch(chain_adjoint_tail_kernel<64, 2>, a, 2, vec_bytes(d), st) : launch(chain_adjoint_tail_kernel<64, 4>, a, 4, vec_bytes(d), st);
-  return n ? launch(chain_adjoint_tail_kernel<128, 2>, a, 2, vec_bytes(d), st) : launch(chain_adjoint_tail_kernel<128, 4>, a, 4, vec_bytes(d), st);
+  if (d == 64) return n ? launch<chain_adjoint_tail_kernel<64, 2>>(a, 2, vec_bytes(d), st) : launch<chain_adjoint_tail_kernel<64, 4>>(a, 4, vec_bytes(d), st);
+  return n ? launch<chain_adjoint_tail_kernel<128, 2>>(a, 2, vec_bytes(d), st) : launch<chain_adjoint_tail_kernel<128, 4>>(a, 4, vec_bytes(d), st);
 }
 hipError_t launch_chain_adjoint_head(const ChainAdjointArgs& a, int d, bool is_bf16, hipStream_t st) {
   if (a.n_groups <= 0) return hipSuccess;
@@ -962,8 +956,8 @@ hipError_t launch_chain_adjoint_head(const ChainAdjointArgs& a, int d, bool is_b
   ProfScope ps(PC_CHAIN, rows * 6.0 * d * d, rows * d * (20.0 + (a.RHS.present() ? 4.0 : 0.0) + (a.out_cast ? 2.0 : 0.0)), st);
   if (!is_bf16) return launch_chain_f32_adjoint_head(a, st);
   const bool n = narrow(a.n_groups, a.T);
-  if (d == 64) return n ? launch(chain_adjoint_head_kernel<64, 2>, a, 2, vec_bytes(d), st) : launch(chain_adjoint_head_kernel<64, 4>, a, 4, vec_bytes(d), st);
-  return n ? launch(chain_adjoint_head_kernel<128, 2>, a, 2, vec_bytes(d), st) : launch(chain_adjoint_head_kernel<128, 4>, a, 4, vec_bytes(d), st);
+  if (d == 64) return n ? launch<chain_adjoint_head_kernel<64, 2>>(a, 2, vec_bytes(d), st) : launch<chain_adjoint_head_kernel<64, 4>>(a, 4, vec_bytes(d), st);
+  return n ? launch<chain_adjoint_head_kernel<128, 2>>(a, 2, vec_bytes(d), st) : launch<chain_adjoint_head_kernel<128, 4>>(a, 4, vec_bytes(d), st);
 }
 // Whole layer steps launch by launch and on chains, forward / adjoint with the cache pass, in us (sequences of 64):
 //   128 wide, 256 hidden: 1 x 64 tokens 28 / 62 and 26 / 58, 4 x 2048 tokens 40 / 82 and 32 / 70; 64 wide, 512 hidden: 1 x 64

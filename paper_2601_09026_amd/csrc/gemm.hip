@@ -14,6 +14,7 @@
 
 #include "common.h"
 #include "kernels.h"
+#include "lds_limit.h"
 #include "prof.h"
 
 namespace mg {
@@ -1277,13 +1278,8 @@ static hipError_t launch_mfma(const GemmArgs& a, hipStream_t st) {
     pm = resident / 8;
   }
   auto kern = gemm_mfma_kernel<BM, BN, BK, STAGES, OCC, RAGGED, EPI, bf16, WM, WN>;
-  static bool attr_done = false;
-  if (!attr_done) {
-    hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(kern),
-                                       hipFuncAttributeMaxDynamicSharedMemorySize, (int)smem);
-    if (e != hipSuccess) return e;
-    attr_done = true;
-  }
+  static unsigned long raised = 0;
+  if (const hipError_t e = raise_lds_limit(reinterpret_cast<const void*>(kern), (int)smem, raised); e != hipSuccess) return e;
   hipLaunchKernelGGL(kern, dim3(per_xcd * 8), dim3(64 * WM * WN), smem, st, a, tiles_m, tiles_n, total,
                      per_xcd, pm, pn);
   return hipGetLastError();
@@ -1299,13 +1295,8 @@ static hipError_t launch_dgelu_walk(const GemmArgs& a, hipStream_t st) {
   const int smem = 2 * 512 * 128 + 8 * 4096;               // ring and eight staging regions: all of a CU's LDS
   int pm = 0, pn = 0;                                      // as in launch_mfma
   if (tiles_n > 4 && tiles_n % 4 == 0 && compute_units() == 256 && tiles_m % 4 == 0) pm = pn = 4;
-  static bool attr_done = false;
-  if (!attr_done) {
-    const hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(gemm_mfma_dgelu_walk_kernel),
-                                             hipFuncAttributeMaxDynamicSharedMemorySize, smem);
-    if (e != hipSuccess) return e;
-    attr_done = true;
-  }
+  static unsigned long raised = 0;
+  if (const hipError_t e = raise_lds_limit(reinterpret_cast<const void*>(gemm_mfma_dgelu_walk_kernel), smem, raised); e != hipSuccess) return e;
   hipLaunchKernelGGL(gemm_mfma_dgelu_walk_kernel, dim3(compute_units() / 8 * 8), dim3(512), smem, st, a, tiles_m, tiles_n,
                      total, per_xcd, pm, pn);
   return hipGetLastError();
@@ -1443,13 +1434,8 @@ static hipError_t launch_tn_tile(const GemmTnArgs& a, int splits, hipStream_t st
   const size_t staging = (size_t)WM * WN * ((32 * (BN / WN * 4 + 16) + 1023) / 1024 * 1024);
   const size_t smem = ring > staging ? ring : staging;
   auto kern = gemm_tn_mfma_kernel<BM, BN, STAGES, WM, WN, TAIL>;
-  static bool attr_done = false;
-  if (!attr_done) {
-    hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(kern),
-                                       hipFuncAttributeMaxDynamicSharedMemorySize, (int)smem);
-    if (e != hipSuccess) return e;
-    attr_done = true;
-  }
+  static unsigned long raised = 0;
+  if (const hipError_t e = raise_lds_limit(reinterpret_cast<const void*>(kern), (int)smem, raised); e != hipSuccess) return e;
   hipLaunchKernelGGL(kern, dim3(per_xcd * 8), dim3(64 * WM * WN), smem, st, a, tiles_m, tiles_n, splits, total, per_xcd);
   return hipGetLastError();
 }
