@@ -924,18 +924,22 @@ template <int D> hipError_t tail_of(const ChainTailArgs& a, int mode, hipStream_
 }
 }  // namespace
 
+// Bytes reported for a launch: the rows that it reads and writes, of the operands that are there (e: bytes of an operand), the
+// tail's second read of X included.
 hipError_t launch_chain_tail(const ChainTailArgs& a, int d, int mode, bool is_bf16, hipStream_t st) {
   if (a.n_groups <= 0) return hipSuccess;
-  const double n = (double)a.n_groups * a.T;
-  ProfScope ps(PC_CHAIN, n * (2.0 * d * d + (mode == 1 ? 2.0 : 4.0) * d * a.f),
-               n * (d * (mode == 1 ? 6.0 : 10.0) + (a.RHS.present() ? 4.0 * d : 0.0) + (mode ? 2.0 * (d + a.f) : 0.0)), st);
+  const double n = (double)a.n_groups * a.T, e = is_bf16 ? 2 : 4, f = a.f;
+  const double step = mode == 1 ? 0 : (d == 128 ? 8.0 : 4.0) * d + (a.RHS.present() ? 4.0 * d : 0);
+  const double kept = (mode ? e * (d + f) : 0) + (a.ybar ? 4.0 * d : 0) + (a.u ? e * d : 0) + (a.act ? e * f : 0);
+  ProfScope ps(PC_CHAIN, n * (2.0 * d * d + (mode == 1 ? 2.0 : 4.0) * d * f),
+               n * ((e + 4) * d + (a.base ? 4.0 * d : 0) + step + kept), st);
   if (!is_bf16) return launch_chain_f32_tail(a, mode, st);
   return d == 64 ? tail_of<64>(a, mode, st) : tail_of<128>(a, mode, st);
 }
 hipError_t launch_chain_head(const ChainHeadArgs& a, int d, bool is_bf16, hipStream_t st) {
   if (a.n_groups <= 0) return hipSuccess;
-  const double rows = (double)a.n_groups * a.T;
-  ProfScope ps(PC_CHAIN, rows * 6.0 * d * d, rows * d * (10.0 + (a.xhat ? 2.0 : 0.0)), st);
+  const double rows = (double)a.n_groups * a.T, e = is_bf16 ? 2 : 4;
+  ProfScope ps(PC_CHAIN, rows * 6.0 * d * d, rows * d * (4 + 3 * e + (a.xhat ? e : 0) + (a.u ? e : 0)), st);
   if (!is_bf16) return launch_chain_f32_head(a, st);
   const bool n = narrow(a.n_groups, a.T);
   if (d == 64) return n ? launch<chain_head_kernel<64, 2>>(a, 2, 2 * vec_bytes(d) + vec_bytes(3 * d), st) : launch<chain_head_kernel<64, 4>>(a, 4, 2 * vec_bytes(d) + vec_bytes(3 * d), st);
@@ -943,8 +947,9 @@ hipError_t launch_chain_head(const ChainHeadArgs& a, int d, bool is_bf16, hipStr
 }
 hipError_t launch_chain_adjoint_tail(const ChainAdjointArgs& a, int d, bool is_bf16, hipStream_t st) {
   if (a.n_groups <= 0) return hipSuccess;
-  const double rows = (double)a.n_groups * a.T;
-  ProfScope ps(PC_CHAIN, rows * (2.0 * d * d + 4.0 * d * a.f), rows * (10.0 * d + 2.0 * a.f), st);
+  const double rows = (double)a.n_groups * a.T, e = is_bf16 ? 2 : 4, f = a.f;
+  const double kept = (a.c ? 0 : a.c_out ? e * d : 0) + (a.dz ? e * f : 0) + (a.du ? e * d : 0) + (a.ds ? e * d : 0);
+  ProfScope ps(PC_CHAIN, rows * (2.0 * d * d + 4.0 * d * f), rows * ((a.c ? e : 4) * d + (2 * e + 4) * d + e * f + kept), st);
   if (!is_bf16) return launch_chain_f32_adjoint_tail(a, st);
   const bool n = narrow(a.n_groups, a.T);
   if (d == 64) return n ? launch<chain_adjoint_tail_kernel<64, 2>>(a, 2, vec_bytes(d), st) : launch<chain_adjoint_tail_kernel<64, 4>>(a, 4, vec_bytes(d), st);
@@ -952,8 +957,9 @@ hipError_t launch_chain_adjoint_tail(const ChainAdjointArgs& a, int d, bool is_b
 }
 hipError_t launch_chain_adjoint_head(const ChainAdjointArgs& a, int d, bool is_bf16, hipStream_t st) {
   if (a.n_groups <= 0) return hipSuccess;
-  const double rows = (double)a.n_groups * a.T;
-  ProfScope ps(PC_CHAIN, rows * 6.0 * d * d, rows * d * (20.0 + (a.RHS.present() ? 4.0 : 0.0) + (a.out_cast ? 2.0 : 0.0)), st);
+  const double rows = (double)a.n_groups * a.T, e = is_bf16 ? 2 : 4;
+  const double step = a.OUT.present() ? e + 12 + (a.RHS.present() ? 4 : 0) + (a.out_cast ? e : 0) : 0;
+  ProfScope ps(PC_CHAIN, rows * 6.0 * d * d, rows * d * (3 * e + (a.du ? e : 0) + step), st);
   if (!is_bf16) return launch_chain_f32_adjoint_head(a, st);
   const bool n = narrow(a.n_groups, a.T);
   if (d == 64) return n ? launch<chain_adjoint_head_kernel<64, 2>>(a, 2, vec_bytes(d), st) : launch<chain_adjoint_head_kernel<64, 4>>(a, 4, vec_bytes(d), st);

@@ -89,12 +89,15 @@ def test_steps_match_general_path(arch, d, H, f, B, S, Sm, G, rhs, adjoint):
         close(chain[g], general[g], ins[g] + r[g] if rhs else ins[g], f"group {g}")
 
 
-def chain_launches(dm, wl, adjoint, ins, lin):
+def profiled(run):
+    """Launches of chains and the bytes reported for them."""
     mb.mgrit_profile_enable(256)
     try:
         mb.mgrit_profile_reset()
-        steps(dm, wl, adjoint, ins, lin, None)
-        return mb.mgrit_profile_read().get("chain", {"launches": 0})["launches"]
+        run()
+        torch.cuda.synchronize()
+        c = mb.mgrit_profile_read().get("chain", {"launches": 0, "bytes": 0.0})
+        return c["launches"], c["bytes"]
     finally:
         mb.mgrit_profile_enable(0)
 
@@ -116,8 +119,40 @@ def test_where_the_lines_lie(dtype, d, f, B, S, chain):
     print(f"[case] chain or not dtype={dtype} d={d} f={f} B={B} S={S}", flush=True)
     dm = DeviceModel(wl, n_layers=1, weight_std=0.08, keep_host=False)
     ins, lin, _ = states(wl, 1, 9)
-    assert chain_launches(dm, wl, False, ins, lin) == (2 if chain else 0)
-    assert chain_launches(dm, wl, True, ins, lin) == (4 if chain else 0)          # the layer's entries of the cache as well
+    assert profiled(lambda: steps(dm, wl, False, ins, lin, None))[0] == (2 if chain else 0)
+    assert profiled(lambda: steps(dm, wl, True, ins, lin, None))[0] == (4 if chain else 0)    # the layer's cache entries as well
+
+
+@pytest.mark.parametrize("arch", [wls.ARCH_ENCODER, wls.ARCH_CROSS])
+@pytest.mark.parametrize("dtype,d,f,e", [(wls.DTYPE_BF16, 64, 192, 2), (wls.DTYPE_BF16, 128, 192, 2), (wls.DTYPE_F32, 64, 128, 4)])
+def test_reported_bytes(dtype, d, f, e, arch):
+    """What a launch reports as its bytes: every row that it reads or writes, by the width of its type and if it is there."""
+    G, cross = 3, arch == wls.ARCH_CROSS
+    wl = wls.Workload("t", arch, d, 1, f, 1, 40, 24 if cross else 0, G, 0.5, 1, 1, 0, dtype, 23)
+    print(f"[case] chain bytes dtype={dtype} d={d} arch={arch}", flush=True)
+    dm = DeviceModel(wl, weight_std=0.08, keep_host=False)
+    ins, lin, rhs = states(wl, G, 9)
+    n, again = G * wl.tokens, 4 * d if d == 128 else 0                            # (X is read a second time)
+    head, tail = 4 * d + 3 * e * d, (e + 4) * d + (4 * d if cross else 0)
+    out, entries = 4 * d + again, e * d + e * (d + f)                             # the step's; normalised rows and gelu'
+    assert profiled(lambda: steps(dm, wl, False, ins, lin, None))[1] == n * (head + tail + out)
+    assert profiled(lambda: steps(dm, wl, False, ins, lin, rhs))[1] == n * (head + tail + out + 4 * d)
+    adj_tail, adj_head = 4 * d + (2 * e + 4) * d + e * f, 4 * e * d + 12 * d      # from an fp32 cotangent
+    assert profiled(lambda: steps(dm, wl, True, ins, lin, rhs))[1] == n * (head + tail + entries + adj_tail + adj_head + 4 * d)
+
+    opts = mb.mgrit_opts(G, 0.5, 1, 1, 0)
+    mem = dev(wls.cross_memory(wl)) if cross else None
+    ws = torch.empty(mb.mgrit_workspace_bytes(dm.desc, opts, 2), dtype=torch.uint8, device="cuda")
+    lamN, Z = dev(wls.terminal_adjoint(wl)), []
+    kept = 2 * e * d + 4 * d + e * f                                              # both LayerNorms' outputs, ybar, gelu
+    forward = lambda: Z.append(mb.mgrit_forward(dm.desc, opts, ins[0], dm.blocks, memory=mem, adjoint_workspace=ws,
+                                                with_gradients=True)[0])
+    assert profiled(forward)[1] == n * (head + tail + out + entries + kept)
+    dE = torch.empty_like(mem) if cross else None
+    adjoint = lambda: mb.mgrit_adjoint(dm.desc, opts, Z[0], dm.blocks, lamN, memory=mem, dtheta=grad_blocks(dm.desc, G),
+                                       dmemory=dE, workspace=ws, linearised=True)
+    left = e * f + 3 * e * d                                                      # dz, du, ds, du of the projection
+    assert profiled(adjoint)[1] == n * (adj_tail - (4 - e) * d + adj_head + left + e * d)   # copies of the cotangents: read, written
 
 
 @pytest.mark.parametrize("adjoint", [False, True])
