@@ -88,6 +88,8 @@ struct RowBuf {
 // the row pair); a set of eight products takes its fragments block by block, k-step by k-step, six products ahead of
 // their use.  Set i loads tile i + LEAD; every G-th set waits for the tiles of the next G sets, by count, and meets the
 // block's other wavefronts, after which nobody reads the tiles before set i any more.
+// Those counts (TILES, and LATER: loads and stores of rows behind the tiles) hold only while the compiler keeps every
+// instruction that they count; tests/test_chain_waits.py reads the built kernels for it.
 // ---------------------------------------------------------------------------
 constexpr int RING_G = 2, RING_LEAD = 6, RING_R = RING_LEAD + RING_G, RING_BYTES = RING_R * 8192;
 constexpr int RING_BEHIND = RING_LEAD - RING_G - 1;          // tiles asked for behind those waited for
