@@ -203,7 +203,7 @@ template <int NW> __device__ __forceinline__ Place place(int tiles_m, int total,
 // Activations between the two products: 32 hidden features of the wavefront's rows, two values at a time, in ITEMS
 // parts of about four instructions that run beside the products; a fragment of 16 features is done after each half.
 // ---------------------------------------------------------------------------
-// GELU (gelu_fast of common.h); BOTH: its derivative (gelu_prime_fast) as well
+// GELU (gelu_fast of common.h, taken apart with its constants); BOTH: its derivative (gelu_prime_fast) as well
 template <bool BOTH> struct Gelu {
   static constexpr int ST = BOTH ? 9 : 7, ITEMS = 8 * ST;
   static constexpr bool LAG = true;
@@ -223,18 +223,18 @@ template <bool BOTH> struct Gelu {
     if constexpr (st == 0) {
       if constexpr (e == 0) { b = bn; if constexpr (q < 3) bn = lds_read4f(bias + (q + 1) * 32); }
       z0 = acc[4 * q + e] + b[e]; z1 = acc[4 * q + e + 1] + b[e + 1];
-      x0 = z0 * 0.70710678118654752440f; x1 = z1 * 0.70710678118654752440f;
+      x0 = z0 * SQRT_HALF; x1 = z1 * SQRT_HALF;
     } else if constexpr (st == 1) {
-      x0 = __builtin_amdgcn_fmed3f(x0, -2.8f, 2.8f); x1 = __builtin_amdgcn_fmed3f(x1, -2.8f, 2.8f);
+      x0 = __builtin_amdgcn_fmed3f(x0, -PHI_CLAMP, PHI_CLAMP); x1 = __builtin_amdgcn_fmed3f(x1, -PHI_CLAMP, PHI_CLAMP);
       t0 = x0 * x0; t1 = x1 * x1;
     } else if constexpr (st == 2) {
-      two(0.5f * -5.83171111e-07f, 0.5f * 2.22840511e-05f, 0.5f * -3.73322994e-04f, true);
+      two(PHI_POLY[0], PHI_POLY[1], PHI_POLY[2], true);
     } else if constexpr (st == 3) {
-      two(0.f, 0.5f * 3.65856420e-03f, 0.5f * -2.37276428e-02f, false);
+      two(0.f, PHI_POLY[3], PHI_POLY[4], false);
     } else if constexpr (st == 4) {
-      two(0.f, 0.5f * 1.09334266e-01f, 0.5f * -3.74316462e-01f, false);
+      two(0.f, PHI_POLY[5], PHI_POLY[6], false);
     } else if constexpr (st == 5) {
-      p0 = fmaf(p0, t0, 0.5f * 1.12810103e+00f); p1 = fmaf(p1, t1, 0.5f * 1.12810103e+00f);
+      p0 = fmaf(p0, t0, PHI_POLY[7]); p1 = fmaf(p1, t1, PHI_POLY[7]);
       p0 = fmaf(x0, p0, 0.5f); p1 = fmaf(x1, p1, 0.5f);
     } else if constexpr (st == 6) {
       w[i & 3] = pack2(z0 * p0, z1 * p1);
@@ -243,9 +243,9 @@ template <bool BOTH> struct Gelu {
         if (BOTH && keep) act.store(rowoff + col + (i >> 2) * 32, out[i >> 2]);
       }
     } else if constexpr (st == 7) {
-      e0 = __builtin_amdgcn_exp2f(z0 * z0 * -0.72134752044448170f); e1 = __builtin_amdgcn_exp2f(z1 * z1 * -0.72134752044448170f);
+      e0 = __builtin_amdgcn_exp2f(z0 * z0 * PDF_EXP2); e1 = __builtin_amdgcn_exp2f(z1 * z1 * PDF_EXP2);
     } else {
-      d[i & 3] = pack2(fmaf(z0, 0.39894228040143267794f * e0, p0), fmaf(z1, 0.39894228040143267794f * e1, p1));
+      d[i & 3] = pack2(fmaf(z0, PDF_SCALE * e0, p0), fmaf(z1, PDF_SCALE * e1, p1));
       if constexpr ((i & 3) == 3) dact.store(rowoff + col + (i >> 2) * 32, __builtin_bit_cast(bf16x8, swap_halves(d[0], d[1], d[2], d[3])));
     }
   }

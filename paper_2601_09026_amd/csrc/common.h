@@ -81,24 +81,22 @@ __device__ __forceinline__ float gelu_prime_f(float z) {
 // transcendental instruction.  The vector unit is what the bias+GELU epilogues wait for: the half is folded into the
 // coefficients, which is exact, and the clamp is one instruction, 12 per GELU.  Folding 1 / sqrt(2) as well saves one
 // more, but rounds differently where the terms cancel at the clamp (error 5.39e-5).
+constexpr float SQRT_HALF = 0.70710678118654752440f, PHI_CLAMP = 2.8f;
+constexpr float PHI_POLY[8] = {0.5f * -5.83171111e-07f, 0.5f * 2.22840511e-05f, 0.5f * -3.73322994e-04f, 0.5f * 3.65856420e-03f,
+                               0.5f * -2.37276428e-02f, 0.5f * 1.09334266e-01f, 0.5f * -3.74316462e-01f, 0.5f * 1.12810103e+00f};
+constexpr float PDF_SCALE = 0.39894228040143267794f, PDF_EXP2 = -0.72134752044448170f;   // pdf(z) = 1 / sqrt(2 pi) * 2^(-z^2 log2(e) / 2)
 __device__ __forceinline__ float phi_fast(float z) {
-  const float x = __builtin_amdgcn_fmed3f(z * 0.70710678118654752440f, -2.8f, 2.8f);
+  const float x = __builtin_amdgcn_fmed3f(z * SQRT_HALF, -PHI_CLAMP, PHI_CLAMP);
   const float t = x * x;
-  float p = 0.5f * -5.83171111e-07f;
-  p = fmaf(p, t, 0.5f * 2.22840511e-05f);
-  p = fmaf(p, t, 0.5f * -3.73322994e-04f);
-  p = fmaf(p, t, 0.5f * 3.65856420e-03f);
-  p = fmaf(p, t, 0.5f * -2.37276428e-02f);
-  p = fmaf(p, t, 0.5f * 1.09334266e-01f);
-  p = fmaf(p, t, 0.5f * -3.74316462e-01f);
-  p = fmaf(p, t, 0.5f * 1.12810103e+00f);
+  float p = PHI_POLY[0];
+#pragma unroll
+  for (int i = 1; i < 8; ++i) p = fmaf(p, t, PHI_POLY[i]);
   return fmaf(x, p, 0.5f);
 }
 __device__ __forceinline__ float gelu_fast(float z) { return z * phi_fast(z); }
 __device__ __forceinline__ float gelu_prime_fast(float z) {
-  // pdf(z) = 1 / sqrt(2 pi) * 2^(-z^2 log2(e) / 2), with the bare exponential instruction
-  const float e = __builtin_amdgcn_exp2f(z * z * -0.72134752044448170f);
-  return fmaf(z, 0.39894228040143267794f * e, phi_fast(z));
+  const float e = __builtin_amdgcn_exp2f(z * z * PDF_EXP2);   // the bare exponential instruction
+  return fmaf(z, PDF_SCALE * e, phi_fast(z));
 }
 template <typename T> __device__ __forceinline__ float gelu_t(float z);
 template <> __device__ __forceinline__ float gelu_t<float>(float z) { return gelu_f(z); }
