@@ -452,8 +452,9 @@ int mgrit_measure_copy_ceiling(const void* src, void* dst, size_t bytes, double*
 int mgrit_measure_event_bracket(double* us, void* stream);
 
 /* Test hook.  First flag: the products x W^T of the steps run on the FMA kernel (the token-major products
- * of the parameter gradients have no other form).  Second flag: bf16 attention of 64- and 128-wide heads
- * runs on the kernels of all other heads, which take its products in fp32. */
+ * of the parameter gradients have no other form), and narrow layers take them too: what the row-local chains would do
+ * runs launch by launch.  Second flag: bf16 attention of 64- and 128-wide heads runs on the kernels of all other heads,
+ * which take its products in fp32. */
 void mgrit_debug_force_simple_kernels(int gemm, int attn);
 
 /* Tuning hook: tile configuration of the matrix-core products (0 = chosen by shape, the default; k-tiles
@@ -461,7 +462,8 @@ void mgrit_debug_force_simple_kernels(int gemm, int attn);
  * stages, one block per CU; 8 and 9 = 64x64 with four and two stages, two and four blocks per CU).
  * 3 falls back to 4 where the shape is no multiple of it.  The token-major products of the parameter gradients
  * come as 1, 6 (also for 3 and 4) and 8 (also for 9).  fp32: 8 and 9 take the 32x32 tiles, the others the 64x64
- * ones where the shape is a multiple of them. */
+ * ones where the shape is a multiple of them.  Any value but 0 also switches off the row-local chains of narrow layers (bf16
+ * 64 and 128 wide, fp32 64 wide), whose products have tiles of their own; a linearising pair has to run under one setting. */
 void mgrit_debug_gemm_tile_config(int cfg);
 
 /* Tuning hook: slices of the token sums in the parameter gradients (0 = chosen by shape, the default; at most
