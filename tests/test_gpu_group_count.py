@@ -58,7 +58,8 @@ def test_layer_step_bits(dtype, d, f, B, S, adjoint):
 @pytest.mark.parametrize("norms", [True, False])
 @pytest.mark.parametrize("arch,dtype,d,f,B,S,Sm", [
     (wls.ARCH_ENCODER, wls.DTYPE_BF16, 256, 1024, 4, 509, 0),    # token slices would pay for one or two layers only
-    (wls.ARCH_CROSS, wls.DTYPE_BF16, 128, 256, 4, 515, 260),
+    (wls.ARCH_CROSS, wls.DTYPE_BF16, 128, 256, 4, 515, 260),     # the row-local chains
+    (wls.ARCH_CROSS, wls.DTYPE_BF16, 256, 512, 4, 515, 260),
     (wls.ARCH_ENCODER, wls.DTYPE_F32, 256, 512, 4, 509, 0)])
 def test_gradient_bits(arch, dtype, d, f, B, S, Sm, norms):
     wl = wls.Workload("t", arch, d, 2, f, B, S, Sm, 4, 0.25, 1, 1, 1, dtype, 91)

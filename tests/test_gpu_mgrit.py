@@ -110,9 +110,10 @@ def tiny(arch=wls.ARCH_ENCODER, dtype=wls.DTYPE_F32, N=32, cf=4, levels=2, iters
 # ----------------------------------------------------------------- genuine iterates, fp32
 @pytest.mark.parametrize("relax", ["F", "FCF"])
 @pytest.mark.parametrize("iters", [1, 2])
-def test_two_level_inexact_iterates_fp32(relax, iters):
+@pytest.mark.parametrize("f", [128, 192])                # the row-local chains and launch by launch
+def test_two_level_inexact_iterates_fp32(relax, iters, f):
     # h = 1 (the paper's setting) and stronger weights: iterates differ visibly from serial
-    wl = tiny(iters=iters)
+    wl = tiny(iters=iters, f=f)
     Zg, Zr, rr = run_case(wl, weight_std=0.08, relax=relax, adjoint=True)
     ser = omgrit.serial_forward(wls.initial_state(wl), DeviceModel(wl, weight_std=0.08).host, wl.h,
                                 shape_of(wl))
@@ -171,13 +172,14 @@ def test_run_to_run_bit_identical():
     assert torch.equal(a, b) and torch.equal(ra, rb)
 
 
+@pytest.mark.parametrize("d", [128, 192])                 # bf16: the row-local chains and launch by launch
 @pytest.mark.parametrize("levels,cf,N", [(2, 4, 32), (3, 2, 16), (2, 4, 12)])
-def test_overlapped_coarse_solve_is_bit_identical_to_the_sequential_order(levels, cf, N):
+def test_overlapped_coarse_solve_is_bit_identical_to_the_sequential_order(levels, cf, N, d):
     """The serial coarse solve hands finished intervals to the helper lane, which F-relaxes them while
     the remaining coarse steps run: the same kernels on the same data as one after the other, so every
     state, adjoint state and residual norm must agree bit for bit (M = 8, 4 and 3 intervals on the level
     above the coarsest; 3 is not a multiple of the launch chunk)."""
-    wl = tiny(arch=wls.ARCH_CAUSAL, dtype=wls.DTYPE_BF16, N=N, cf=cf, levels=levels, iters=2, d=128, f=256)
+    wl = tiny(arch=wls.ARCH_CAUSAL, dtype=wls.DTYPE_BF16, N=N, cf=cf, levels=levels, iters=2, d=d, f=2 * d)
     dm = DeviceModel(wl, weight_std=0.05)
     Z0, lamN = dev(wls.initial_state(wl)), dev(wls.terminal_adjoint(wl))
     opts = mb.mgrit_opts(N, 1.0, cf, levels, 2)
@@ -196,15 +198,16 @@ def test_overlapped_coarse_solve_is_bit_identical_to_the_sequential_order(levels
             assert torch.equal(x, y)
 
 
+@pytest.mark.parametrize("d", [128, 192])                 # bf16: the row-local chains and launch by launch
 @pytest.mark.parametrize("chunk", [1, 3])
-def test_overlapped_coarse_solve_with_many_hand_overs_is_bit_identical(chunk):
+def test_overlapped_coarse_solve_with_many_hand_overs_is_bit_identical(chunk, d):
     """40 intervals handed over one at a time: 39 hand-overs go through the pool of 16 events, which
     wraps around, and with more than 16 chunks the right-hand sides are formed in one sweep instead of
     chunk by chunk; 3 at a time gives 14 chunks with a ragged last one (right-hand sides chunk by
     chunk).  Forward and adjoint against the sequential order, bit for bit."""
     N, cf = 160, 4
-    wl = tiny(arch=wls.ARCH_CAUSAL, dtype=wls.DTYPE_BF16, N=N, cf=cf, levels=2, iters=2, d=128, f=256, B=1, S=40)
-    print(f"[case] many hand-overs: N={N} cf={cf} chunk={chunk}", flush=True)
+    wl = tiny(arch=wls.ARCH_CAUSAL, dtype=wls.DTYPE_BF16, N=N, cf=cf, levels=2, iters=2, d=d, f=2 * d, B=1, S=40)
+    print(f"[case] many hand-overs: d={d} N={N} cf={cf} chunk={chunk}", flush=True)
     dm = DeviceModel(wl, weight_std=0.05, keep_host=False)
     Z0, lamN = dev(wls.initial_state(wl)), dev(wls.terminal_adjoint(wl))
     opts = mb.mgrit_opts(N, 0.1, cf, 2, 2)

@@ -15,8 +15,8 @@ pytestmark = pytest.mark.gpu
 N = 32
 
 
-def model(arch, dtype):
-    wl = wls.Workload("t", arch, 64, 2, 128, 2, 24, 16 if arch == wls.ARCH_CROSS else 0, N, 0.5, 2, 2, 2, dtype, 97)
+def model(arch, dtype, d):
+    wl = wls.Workload("t", arch, d, 2 if d == 64 else 3, 2 * d, 2, 24, 16 if arch == wls.ARCH_CROSS else 0, N, 0.5, 2, 2, 2, dtype, 97)
     return wl, DeviceModel(wl, weight_std=0.05, keep_host=False), mb.mgrit_opts(N, wl.h, 2, 2, 2)
 
 
@@ -44,11 +44,12 @@ def refused(call):
     assert e.value.status == mb.MGRIT_WORKSPACE_TOO_SMALL
 
 
+@pytest.mark.parametrize("d", [64, 192])                  # the row-local chains and launch by launch
 @pytest.mark.parametrize("arch,dtype", [(wls.ARCH_ENCODER, wls.DTYPE_F32), (wls.ARCH_CROSS, wls.DTYPE_F32),
                                         (wls.ARCH_CAUSAL, wls.DTYPE_BF16), (wls.ARCH_CROSS, wls.DTYPE_BF16)])
-def test_solves(arch, dtype):
-    wl, dm, opts = model(arch, dtype)
-    print(f"[case] small workspaces arch={arch} dtype={dtype}", flush=True)
+def test_solves(arch, dtype, d):
+    wl, dm, opts = model(arch, dtype, d)
+    print(f"[case] small workspaces arch={arch} dtype={dtype} d={d}", flush=True)
     mem = wls.cross_memory(wl)
     mem = None if mem is None else dev(mem)
     Z0, lamN = dev(wls.initial_state(wl)), dev(wls.terminal_adjoint(wl))
@@ -74,10 +75,11 @@ def test_solves(arch, dtype):
         refused(lambda: pair(full[0], former[1] - 256, True))
 
 
+@pytest.mark.parametrize("d", [64, 192])                  # the row-local chains and launch by launch
 @pytest.mark.parametrize("dtype", [wls.DTYPE_F32, wls.DTYPE_BF16])
-def test_buffered_and_stacked(dtype):
-    print(f"[case] small workspaces, buffered and stacked dtype={dtype}", flush=True)
-    wl, _, opts = model(wls.ARCH_ENCODER, dtype)
+def test_buffered_and_stacked(dtype, d):
+    print(f"[case] small workspaces, buffered and stacked dtype={dtype} d={d}", flush=True)
+    wl, _, opts = model(wls.ARCH_ENCODER, dtype, d)
     buf = mb.BufferOpts(3, 2, 1.0)
     dm = DeviceModel(wl, n_layers=N + 5, weight_std=0.05, keep_host=False)
     full, former = sizes(lambda: [mb.mgrit_buffered_linearised_workspace_bytes(dm.desc, opts, buf, True),
@@ -100,10 +102,10 @@ def test_buffered_and_stacked(dtype):
         refused(lambda: buffered(former[0] - 256, 0))
         refused(lambda: buffered(0, former[1] - 256))
 
-    dec, _, _ = model(wls.ARCH_CROSS, dtype)
+    dec, _, _ = model(wls.ARCH_CROSS, dtype, d)
     desc = mb.model_desc(dec)
-    sw = wls.StackedWorkload("s", wls.Workload("e", wls.ARCH_ENCODER, 64, 2, 128, 2, 16, 0, 14, 0.5, 2, 2, 2, dtype, 98),
-                             wls.Workload("d", wls.ARCH_CROSS, 64, 2, 128, 2, 24, 16, N - 14, 0.5, 2, 2, 2, dtype, 99))
+    sw = wls.StackedWorkload("s", wls.Workload("e", wls.ARCH_ENCODER, d, dec.n_heads, 2 * d, 2, 16, 0, 14, 0.5, 2, 2, 2, dtype, 98),
+                             wls.Workload("d", wls.ARCH_CROSS, d, dec.n_heads, 2 * d, 2, 24, 16, N - 14, 0.5, 2, 2, 2, dtype, 99))
     descs = [mb.encoder_desc(desc)] * 14 + [desc] * (N - 14)
     blocks = [mb.pack_theta(x, wls.stacked_layer_params(sw, n, 0.05)) for n, x in enumerate(descs)]
     Z0, lamN = dev(wls.stacked_initial_state(sw)), dev(wls.stacked_terminal_adjoint(sw))
@@ -126,17 +128,18 @@ def test_buffered_and_stacked(dtype):
         refused(lambda: stacked(full[0], former[1] - 256, True))
 
 
+@pytest.mark.parametrize("d", [64, 192])                  # the row-local chains and launch by launch
 @pytest.mark.parametrize("adjoint", [False, True])
 @pytest.mark.parametrize("dtype", [wls.DTYPE_F32, wls.DTYPE_BF16])
-def test_layer_step(dtype, adjoint):
-    wl, _, _ = model(wls.ARCH_CAUSAL, dtype)
+def test_layer_step(dtype, adjoint, d):
+    wl, _, _ = model(wls.ARCH_CAUSAL, dtype, d)
     G = 20
-    print(f"[case] small workspaces, layer step dtype={dtype} adjoint={adjoint}", flush=True)
+    print(f"[case] small workspaces, layer step dtype={dtype} d={d} adjoint={adjoint}", flush=True)
     dm = DeviceModel(wl, n_layers=G, weight_std=0.05, keep_host=False)
     full, former = sizes(lambda: [mb.mgrit_layer_step_workspace_bytes(dm.desc, adjoint, G)], dtype)
     gen = torch.Generator(device="cuda")
     gen.manual_seed(5)
-    ins, lin = (list(torch.randn((G, wl.tokens, 64), generator=gen, device="cuda")) for _ in range(2))
+    ins, lin = (list(torch.randn((G, wl.tokens, d), generator=gen, device="cuda")) for _ in range(2))
 
     def run(size):
         outs = [torch.full_like(x, float("nan")) for x in ins]
