@@ -248,7 +248,8 @@ def test_full_gpt2_small_forward_and_adjoint_against_the_stored_oracle_sequence(
 def test_full_mc_deep_narrow_against_the_stored_oracle_sequence():
     """The deep-narrow configuration at its full size (8 sequences of 2048 tokens, one head of 128, 256
     layers, 3 levels, F-relaxation), as bench.py launches it (this is where the 256-row attention blocks and
-    the 2-rows-per-wavefront LayerNorm run at full length).  Z_0 and lambda_N are copied exactly; Z and
+    the row-local chains run at full length; the 2-rows-per-wavefront LayerNorm of rows this short runs at the same length
+    in test_gpu_chain.py's comparisons, launch by launch).  Z_0 and lambda_N are copied exactly; Z and
     lambda at every C-point against the oracle's complete iterate of one sequence, computed offline (a
     quarter of an hour): see check_against_stored_sequence; the full-batch residual norms against the
     oracle's, stored by tests/golden/make_resnorm_golden.py (an hour and a half); and after the closing
@@ -269,6 +270,13 @@ def test_full_mc_deep_narrow_against_the_stored_oracle_sequence():
     for norms in (rg.cpu().numpy(), ag.cpu().numpy()):
         assert np.isfinite(norms).all() and norms[1] < norms[0], norms
     einc = check_against_stored_sequence(wl, stored_sequence("mc_deep_narrow", 5), Zg, lg, tol)
+    # the pair of calls that bench.py times: the same results, bit for bit, at this size too
+    ws = torch.empty(mb.mgrit_workspace_bytes(dm.desc, opts, 1), dtype=torch.uint8, device="cuda")
+    Z2, r2 = mb.mgrit_forward(dm.desc, opts, dev(Z0), dm.blocks, adjoint_workspace=ws)
+    l2, a2 = mb.mgrit_adjoint(dm.desc, opts, Z2, dm.blocks, dev(lamN), workspace=ws, linearised=True)
+    torch.cuda.synchronize()
+    assert torch.equal(Z2, Zg) and torch.equal(r2, rg) and torch.equal(l2, lg) and torch.equal(a2, ag)
+    del Z2, l2, ws
     gold = golden("mc_deep_narrow")
     check_norms("forward", rg.cpu().numpy(), gold["forward"], tol, gold["increment_norm"], einc["Z"])
     check_norms("adjoint", ag.cpu().numpy(), gold["adjoint"], tol, gold["adjoint_increment_norm"], einc["lambda"])
