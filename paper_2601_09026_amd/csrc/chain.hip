@@ -11,10 +11,12 @@
 // between the wavefront's halves, and a result becomes the next product's operand by packing and two half exchanges per
 // 16 features.  The weights pass through a ring of 8 KB tiles in LDS that the wavefronts of a block share.
 //
-// 4 layers of 16384 tokens, 128 wide, 128 hidden, launch by launch -> chain: head 34 -> 19 us (84 MB, 4.4 TB/s), tail
-// 65 -> 28 us (117 MB, 4.2 TB/s), adjoint_tail 63 -> 32 us (101 MB), adjoint_head 53 -> 39 us (168 MB, 4.3 TB/s): all bound by
-// their rows' traffic; the blocks of a launch start and end together, so that loads, products and stores hardly overlap.
-// With 512 hidden features the GELU (14 vector instructions a value) takes as long as the traffic.
+// 4 layers of 16384 tokens, 128 wide, 128 hidden, launch by launch -> chain: head 34 -> 22 us (84 MB, 3.8 TB/s), tail
+// 65 -> 29 us (117 MB, 4.1 TB/s), adjoint_tail from fp32 cotangents 63 -> 28 us (117 MB, 4.1 TB/s), adjoint_head 53 -> 37 us
+// (168 MB, 4.5 TB/s), where a copy reaches 5.8 TB/s.  What bounds them are their rows' traffic and its waits: the blocks of a
+// launch start and end together, so that loads, products and stores hardly overlap, and two wavefronts a SIMD wait to issue
+// for 39 to 73 % of their cycles with the matrix cores 7 to 13 % busy.
+// With 512 hidden features (tail 48, adjoint_tail 43 us) the GELU, 14 vector instructions a value, takes as long as the traffic.
 #include <type_traits>
 
 #include "common.h"

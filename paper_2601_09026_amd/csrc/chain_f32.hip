@@ -5,9 +5,9 @@
 // and asks for all its weights (144 registers a lane for 256 hidden features) before it does anything else, so that a
 // launch waits for memory once.  The rows pass from one product to the next through LDS, where LayerNorm takes 16 lanes a row.
 // Whole layer steps launch by launch -> on chains, forward / adjoint with the cache pass, 256 hidden: 4 layers of 2 x 32
-// tokens 39 / 68 -> 28 / 48 us, 4 x 512 tokens 67 / 160 -> 51 / 131, 16 layers of 16 x 512 tokens 557 / 1449 -> 401 / 1220.
-// What is left of the smallest: a launch takes 5 to 8 us of which the products are 1 to 2, the rest its start, one trip to memory
-// and its end.
+// tokens 31 / 59 -> 21 / 43 us, of 4 x 512 tokens 64 / 156 -> 48 / 128, 16 layers of 16 x 512 tokens 546 / 1460 -> 400 / 1230.
+// What is left of the smallest: head and adjoint_head take 5 to 6 us, tail and adjoint_tail 10 to 11, of which the products are
+// 1 to 2, the rest a launch's start, one trip to memory, the steps between the products and its end.
 #include <type_traits>
 
 #include "common.h"
