@@ -1304,12 +1304,20 @@ static hipError_t launch_dgelu_walk(const GemmArgs& a, hipStream_t st) {
 
 // Two 64x64 tiles per CU are where the larger tile takes over: whole steps of small launches are up to twice as fast
 // on 32x32 tiles (1024 wide, 2 layers of 128 tokens: 171 us against 325), large ones lose up to 13 % to fetching each
-// operand twice as often (1024 wide, 4 layers of 1024 tokens: 1191 us against 1052), and near the line the two differ
-// by 2-8 % either way.  Ragged shapes have no other matrix-core kernel.
+// operand twice as often (1024 wide, 4 layers of 1024 tokens: 1191 us against 1052).  Between two and four tiles per CU
+// the larger one takes as long as a whole number of them: a launch whose last round is at most a quarter full is faster on
+// the smaller (large -> small, us: reduction 1280, 2.03 tiles per CU 90 -> 78 and, transposed, 83 -> 71; reduction 2048, 2.25:
+// 154 -> 134, 140 -> 121; 4096, 3.12: 390 -> 343, 344 -> 304; 640, 3.05: 73 -> 63, 60 -> 54; of 320 and less, 17 to 35 us,
+// within 8 % either way), one that fills it by half or more is not (2.62: 156 -> 164, 2.00: 107 -> 128).  Ragged shapes have
+// no other matrix-core kernel.
+inline bool large_f32_tile(long tiles, long cus) {
+  const long rounds = tiles / cus, rest = tiles % cus;
+  return rounds >= 4 || (rounds >= 2 && (rest == 0 || 4 * rest > cus));
+}
 template <int EPI>
 static hipError_t launch_f32_mfma(const GemmArgs& a, hipStream_t st) {
   const int tiles_m = (a.M + 63) / 64, tiles_n = (a.N + 63) / 64;
-  const bool large = g_tile_cfg ? g_tile_cfg < 8 : (long)tiles_m * tiles_n * a.n_groups >= 2 * compute_units();
+  const bool large = g_tile_cfg ? g_tile_cfg < 8 : large_f32_tile((long)tiles_m * tiles_n * a.n_groups, compute_units());
   if (a.N % 64 == 0 && a.K % 16 == 0 && large) {
     hipLaunchKernelGGL((gemm_f32_mfma_kernel<EPI>), dim3(tiles_m * tiles_n, 1, a.n_groups), dim3(256), 0, st, a,
                        tiles_m, tiles_n);

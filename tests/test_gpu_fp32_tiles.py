@@ -4,10 +4,12 @@ and one row past a tile; attention (all fp32 heads, bf16 heads that are not 64 o
 sequences of one row, around 16-row parts, around 64-row tiles, over several tiles, and key counts unlike the query
 counts.  The attention cases run forward and adjoint; sequences up to 64 take the one-launch backward."""
 import pytest
+import torch
 
 from paper_2601_09026_amd import binding as mb
 from paper_2601_09026_amd import workloads as wls
 
+from gpu_util import DeviceModel
 from test_gpu_layer_step import make, run_adjoint_case, run_forward_case
 
 pytestmark = pytest.mark.gpu
@@ -43,6 +45,36 @@ def test_projection_on_64x64_tiles_fp32(d, H, f, B, S):
         run_adjoint_case(wl, G=2, hstep=0.5, with_rhs=True, weight_std=0.05, force_simple=0)
     finally:
         mb.lib().mgrit_debug_gemm_tile_config(0)
+
+
+@pytest.mark.parametrize("adjoint", [False, True])
+@pytest.mark.parametrize("d,T,G", [                # tiles of 64 x 64 of the products 256 wide (their reduction 256 and 512):
+    (256, 8128, 1), (256, 8192, 1), (256, 8193, 1),            # 508, 512, 516: two rounds on 256 CUs, less, and a third begun
+    (256, 4608, 2), (256, 4672, 2),                # 576, 584: the third round filled by a quarter, and by more
+    (256, 4096, 3), (256, 4400, 3),                # 768, 828: three rounds, and a fourth filled by a quarter
+    (256, 4097, 4)])                               # 1040: four
+def test_lines_between_the_tiles_fp32(d, T, G, adjoint):
+    """Either side of the lines of the rule that chooses a launch's tile, against both tiles: the same bits."""
+    print(f"[case] fp32 tiles T={T} G={G} adjoint={adjoint}", flush=True)
+    wl = make(wls.ARCH_ENCODER, wls.DTYPE_F32, d=d, H=4, f=512, B=T, S=1)
+    dm = DeviceModel(wl, n_layers=G, weight_std=0.05, keep_host=False)
+    gen = torch.Generator(device="cuda")
+    gen.manual_seed(3)
+    ins, lin = (list(torch.randn((G, T, d), generator=gen, device="cuda")) for _ in range(2))
+    out = []
+    mb.mgrit_set_lanes(1)
+    try:
+        for cfg in (0, 1, 8):
+            mb.lib().mgrit_debug_gemm_tile_config(cfg)
+            out.append([torch.full_like(x, float("nan")) for x in ins])
+            mb.layer_step_batched(dm.desc, adjoint, ins, out[-1], dm.blocks, 0.5, lin_state=lin if adjoint else None)
+            torch.cuda.synchronize()
+    finally:
+        mb.lib().mgrit_debug_gemm_tile_config(0)
+        mb.mgrit_set_lanes(2)
+    for other in out[1:]:
+        for x, y in zip(out[0], other):
+            assert torch.isfinite(x).all() and torch.equal(x, y)
 
 
 @pytest.mark.parametrize("dtype", [wls.DTYPE_F32, wls.DTYPE_BF16])
