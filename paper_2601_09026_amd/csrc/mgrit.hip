@@ -829,15 +829,17 @@ int param_grads_chunk(Engine& E, int n, Params THT, Rows LIN, Slots cs, float hs
 // sweep runs: bf16 products from the tile model and attention at 800 TFLOP/s, fp32 at 100 TFLOP/s, 3 us a launch and 50 TFLOP/s.
 // Split -> in one piece, over 252 bf16 layer steps of 2, 4 and 5 layers (128 to 1024 wide, 64 to 4096 tokens, both directions,
 // cross attention) and 250 training steps whose sweeps have 3 to 5 layers (d_head 64 and 128, up to 8 x 2048 tokens):
-//   bf16 below 40 us: 10 to 120 % faster;  40 to 110 us: layer steps 10 to 60 % faster (768 wide, 4 x 64 tokens 105 -> 60 us;
-//   512 wide, 4 x 1024 tokens 109 -> 84), training steps 0 to 12 % (512 wide, 2048 tokens, 9.2 -> 8.3 ms); 110 to 220 us: layer
-//   steps 0 to 20 % faster, training steps between 7 % faster and 9 % slower (128 wide, 5 layers of 8 x 2048 tokens, 156 us,
-//   16.5 -> 18.0 ms); above: within 6 % either way, long attention slower.
-//   fp32 (95 steps of both kinds) below 400 us: 0 to 50 % faster (512 wide, 2 x 256 tokens 129 -> 90 us; 4 x 512 tokens,
-//   141 us, 381 -> 360); above: 9 % faster to 2 % slower.
+//   bf16 below 40 us: 10 to 120 % faster;  40 to 110 us: layer steps between 60 % faster and, near 110, 4 % slower (768 wide,
+//   4 x 64 tokens 105 -> 60 us; 512 wide, 4 x 1024 tokens 109 -> 84), training steps 0 to 12 % faster (512 wide, 2048 tokens,
+//   9.2 -> 8.3 ms);  110 to 220 us: layer steps 0 to 20 % faster, training steps between 7 % faster and 9 % slower (128 wide,
+//   5 layers of 8 x 2048 tokens, 156 us, 16.5 -> 18.0 ms);  above: within 6 % either way, long attention slower.
+//   fp32 (190 steps and solves whose sweeps have 2 to 16 layers, 64 to 1024 wide) below 80 us: 0 to 50 % faster (512 wide,
+//   2 x 256 tokens 129 -> 90 us);  80 to 300 us: between 25 % faster and 4 % slower, 3 % faster on average (512 wide, 4 x 512
+//   tokens, 141 us, 381 -> 360; training step, 832 wide, 256 tokens, cross attention, 145 us, 22.3 -> 23.1 ms);  above: within
+//   6 % either way, 0.5 % slower on average.
 // (Products below 40 us were never faster split, whatever the attention beside them: four layers of 8 x 2048 tokens, 128
 // wide, 204 split, 187 in one piece; transposed 558, 528.)
-constexpr double SMALL_SWEEP_US = 110.0, SMALL_PRODUCTS_US = 40.0, SMALL_SWEEP_F32_US = 400.0;
+constexpr double SMALL_SWEEP_US = 110.0, SMALL_PRODUCTS_US = 40.0, SMALL_SWEEP_F32_US = 300.0;
 inline bool small_sweep(const Engine& E, int G) {
   if (G > E.Gc) return false;
   const double keys = E.md.arch == MGRIT_ARCH_ENCODER ? E.md.seq : 0.5 * E.md.seq + E.md.mem_seq;

@@ -158,7 +158,7 @@ def test_sweeps_in_one_piece_and_split(arch, dtype, G, adjoint):
 @pytest.mark.parametrize("adjoint", [False, True])
 @pytest.mark.parametrize("dtype,d,B,S,G", [
     (wls.DTYPE_BF16, 512, 4, 512, 5), (wls.DTYPE_BF16, 768, 4, 512, 4),          # 108 and 163 us: the line is at 110
-    (wls.DTYPE_F32, 512, 4, 256, 4), (wls.DTYPE_F32, 512, 8, 256, 4)])           # 291 and 570 us: at 400
+    (wls.DTYPE_F32, 512, 4, 256, 4), (wls.DTYPE_F32, 512, 8, 256, 4)])           # 291 and 570 us: at 300
 def test_sweeps_around_the_line_of_two_lanes(dtype, d, B, S, G, adjoint):
     wl = make(wls.ARCH_CAUSAL, dtype, d=d, H=d // 64, f=4 * d, B=B, S=S)
     print(f"[case] two lanes or one dtype={dtype} d={d} B={B} S={S} G={G} adjoint={adjoint}", flush=True)
