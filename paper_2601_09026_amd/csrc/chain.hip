@@ -981,14 +981,20 @@ hipError_t launch_chain_adjoint_head(const ChainAdjointArgs& a, int d, bool is_b
 //   64 wide, 768: 2048 tokens 35 / 65 and 30 / 67;  1024: 4096 tokens 35 / 72 and 35 / 78, 6144 tokens 39 / 80 and 36 / 81;
 //   2048: 4096 tokens 42 / 83 and 54 / 121, 12288 tokens 59 / 121 and 56 / 128, 16384 tokens 67 / 144 and 58 / 130.
 // The lines lie where a training step of single layers (serial propagation, every launch one layer) is no slower on chains:
-// within 1 % there, and a single transposed step alone up to 4 % slower (decoders with cross attention, 384 and 512 hidden: 1
-// to 5 and 4 to 7 %), while launches of two layers gain up to 20 % and of four 10 to 45 %.  The rule follows from the model
+// within 1 % there, and a single transposed step alone up to 4 % slower, while launches of two layers gain up to 20 % and of
+// four 10 to 45 %.  Cross attention adds as many launches on either path, so that decoders 128 wide gain less and need more
+// tokens: 256 hidden, training steps of 16 layers on 2 levels, 64
+// tokens 3.20 -> 3.55 ms, 256 tokens 3.33 -> 3.51, 1024 tokens 3.83 -> 3.76;  384: 2048 tokens,
+// step 56 / 109 -> 55 / 114 us, serial training step 2.30 -> 2.35 ms, 3072 tokens 57 / 115 -> 56 / 118, 2.41 both;  512: 4096
+// tokens 60 / 119 -> 60 / 127, 2.55 -> 2.62, 6144 tokens 66 / 130 -> 65 / 131, 2.78 -> 2.75.  The rule follows from the model
 // alone: how many layers share a launch cannot show in a result.
-bool chain_ok(int d, int f, int T, bool is_bf16) {
+bool chain_ok(int d, int f, int T, bool cross, bool is_bf16) {
   if (!is_bf16) return chain_f32_ok(d, f);
   if ((d != 64 && d != 128) || f % 64 != 0 || f > 2048 || 2.0 * T * (f > 3 * d ? f : 3 * d) >= 2e9) return false;
   if (d == 64) return f <= 512 || T >= (f <= 768 ? 2048 : f <= 1024 ? 6144 : 16384);
-  return f <= 256 || T >= (f <= 384 ? 2048 : f <= 512 ? 3072 : f <= 1024 ? 10240 : 16384);
+  if (f > 512) return T >= (f <= 1024 ? 10240 : 16384);
+  if (cross) return f <= 128 || T >= (f <= 256 ? 1024 : f <= 384 ? 3072 : 6144);
+  return f <= 256 || T >= (f <= 384 ? 2048 : 3072);
 }
 
 }  // namespace mg

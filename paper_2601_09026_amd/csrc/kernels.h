@@ -111,7 +111,7 @@ struct ChainAdjointArgs {
 };
 hipError_t launch_chain_adjoint_tail(const ChainAdjointArgs& a, int d, bool is_bf16, hipStream_t st);
 hipError_t launch_chain_adjoint_head(const ChainAdjointArgs& a, int d, bool is_bf16, hipStream_t st);
-bool chain_ok(int d, int f, int T, bool is_bf16);
+bool chain_ok(int d, int f, int T, bool cross, bool is_bf16);
 hipError_t launch_chain_f32_tail(const ChainTailArgs& a, int mode, hipStream_t st);      // (through the above)
 hipError_t launch_chain_f32_head(const ChainHeadArgs& a, hipStream_t st);
 hipError_t launch_chain_f32_adjoint_tail(const ChainAdjointArgs& a, hipStream_t st);

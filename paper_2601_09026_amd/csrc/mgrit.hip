@@ -241,7 +241,7 @@ struct Engine {
     bf16 = m->dtype == MGRIT_DTYPE_BF16;
     T = m->batch * m->seq; Tm = m->batch * m->mem_seq; d = m->d_model; f = m->d_ff; H = m->n_heads;
     dh = d / H; esz = bf16 ? 2 : 4; st = s;
-    chain = !gemm_forced() && chain_ok(d, f, T, bf16);
+    chain = !gemm_forced() && chain_ok(d, f, T, m->arch == MGRIT_ARCH_CROSS, bf16);
     mgrit_model_desc m32 = *m;
     m32.dtype = MGRIT_DTYPE_F32;
     compute_layout(&m32, &glay);

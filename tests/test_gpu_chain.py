@@ -97,12 +97,14 @@ def steps(dm, wl, adjoint, ins, lin, rhs):
     (wls.ARCH_ENCODER, 64, 2, 2048, 127, 130, 0, 1, True),    # 16510 tokens, the widest hidden layer
     (wls.ARCH_CAUSAL, 128, 1, 64, 1, 32, 0, 1, True),
     (wls.ARCH_ENCODER, 128, 2, 128, 1, 63, 0, 3, False),
-    (wls.ARCH_CROSS, 128, 2, 192, 1, 127, 33, 2, True),
+    (wls.ARCH_CROSS, 128, 2, 192, 1, 127, 33, 2, True),       # (decoders of few tokens: launch by launch both times)
+    (wls.ARCH_CROSS, 128, 2, 192, 9, 115, 33, 2, True),       # 1035 tokens
+    (wls.ARCH_CROSS, 128, 2, 128, 1, 127, 33, 2, True),
     (wls.ARCH_CAUSAL, 128, 4, 256, 1, 128, 0, 2, False),
     (wls.ARCH_ENCODER, 128, 1, 128, 4, 4096, 0, 2, True),     # 256 blocks of 128 rows
     (wls.ARCH_CAUSAL, 128, 2, 512, 8, 257, 0, 5, True),       # 2056 tokens: launch by launch both times
     (wls.ARCH_CAUSAL, 128, 2, 512, 12, 257, 0, 5, True),      # 3084 tokens: 512 hidden features from 3072 on
-    (wls.ARCH_CROSS, 128, 1, 448, 13, 239, 21, 1, False),     # 3107 tokens, seven chunks
+    (wls.ARCH_CROSS, 128, 1, 448, 26, 239, 21, 1, False),     # 6214 tokens, seven chunks
 ])
 def test_steps_match_general_path(arch, d, H, f, B, S, Sm, G, rhs, adjoint):
     wl = make(arch, wls.DTYPE_BF16, d=d, H=H, f=f, B=B, S=S, Sm=Sm)
@@ -140,8 +142,21 @@ def profiled(run):
     (wls.DTYPE_F32, 64, 256, 1, 8, True), (wls.DTYPE_F32, 64, 192, 1, 8, False), (wls.DTYPE_F32, 128, 128, 1, 8, False)])
 def test_where_the_lines_lie(dtype, d, f, B, S, chain):
     """Either side of each line of the rule: widths, hidden widths and the tokens from which wide hidden layers take chains."""
-    wl = make(wls.ARCH_ENCODER, dtype, d=d, H=d // 64, f=f, B=B, S=S)
-    print(f"[case] chain or not dtype={dtype} d={d} f={f} B={B} S={S}", flush=True)
+    check_path(wls.ARCH_ENCODER, dtype, d, f, B, S, chain)
+
+
+@pytest.mark.parametrize("dtype,d,f,B,S,chain", [
+    (wls.DTYPE_BF16, 64, 512, 1, 8, True), (wls.DTYPE_BF16, 64, 1024, 3, 2048, True), (wls.DTYPE_F32, 64, 256, 1, 8, True),
+    (wls.DTYPE_BF16, 128, 128, 1, 8, True), (wls.DTYPE_BF16, 128, 192, 1, 1023, False), (wls.DTYPE_BF16, 128, 256, 1, 1024, True),
+    (wls.DTYPE_BF16, 128, 320, 3, 1023, False), (wls.DTYPE_BF16, 128, 384, 3, 1024, True),
+    (wls.DTYPE_BF16, 128, 448, 3, 2047, False), (wls.DTYPE_BF16, 128, 512, 3, 2048, True), (wls.DTYPE_BF16, 128, 576, 3, 2048, False)])
+def test_where_the_lines_of_decoders_lie(dtype, d, f, B, S, chain):
+    check_path(wls.ARCH_CROSS, dtype, d, f, B, S, chain)
+
+
+def check_path(arch, dtype, d, f, B, S, chain):
+    wl = make(arch, dtype, d=d, H=d // 64, f=f, B=B, S=S, Sm=16)
+    print(f"[case] chain or not arch={arch} dtype={dtype} d={d} f={f} B={B} S={S}", flush=True)
     dm = DeviceModel(wl, n_layers=1, weight_std=0.08, keep_host=False)
     ins, lin, _ = states(wl, 1, 9)
     assert profiled(lambda: steps(dm, wl, False, ins, lin, None))[0] == (2 if chain else 0)
@@ -149,7 +164,7 @@ def test_where_the_lines_lie(dtype, d, f, B, S, chain):
 
 
 @pytest.mark.parametrize("arch", [wls.ARCH_ENCODER, wls.ARCH_CROSS])
-@pytest.mark.parametrize("dtype,d,f,e", [(wls.DTYPE_BF16, 64, 192, 2), (wls.DTYPE_BF16, 128, 192, 2), (wls.DTYPE_F32, 64, 128, 4)])
+@pytest.mark.parametrize("dtype,d,f,e", [(wls.DTYPE_BF16, 64, 192, 2), (wls.DTYPE_BF16, 128, 128, 2), (wls.DTYPE_F32, 64, 128, 4)])
 def test_reported_bytes(dtype, d, f, e, arch):
     """What a launch reports as its bytes: every row that it reads or writes, by the width of its type and if it is there."""
     G, cross = 3, arch == wls.ARCH_CROSS

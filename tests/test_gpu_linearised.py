@@ -29,7 +29,7 @@ def poisoned(nbytes):
     return torch.full(((max(nbytes, 256) + 3) // 4,), float("nan"), dtype=torch.float32, device="cuda").view(torch.uint8)
 
 
-@pytest.mark.parametrize("d", [128, 192])                 # bf16: the row-local chains and launch by launch
+@pytest.mark.parametrize("d,f", [(128, 256), (128, 128), (192, 384)])   # bf16: chains (decoders the second alone), launch by launch
 @pytest.mark.parametrize("arch,dtype,levels,cf,N,relax,lanes,mg,grads", [
     (wls.ARCH_ENCODER, wls.DTYPE_BF16, 2, 4, 16, 1, 2, 0, False),
     (wls.ARCH_ENCODER, wls.DTYPE_BF16, 2, 4, 16, 1, 2, 0, True),
@@ -41,10 +41,10 @@ def poisoned(nbytes):
     (wls.ARCH_ENCODER, wls.DTYPE_F32, 2, 2, 8, 1, 2, 0, False),
     (wls.ARCH_ENCODER, wls.DTYPE_BF16, 1, 4, 5, 1, 2, 0, True),
     (wls.ARCH_ENCODER, wls.DTYPE_BF16, 2, 4, 40, 1, 2, 1, False)])
-def test_linearising_pair_equals_plain_pair(arch, dtype, levels, cf, N, relax, lanes, mg, grads, d):
-    wl = wls.Workload("t", arch, d, d // 64, 2 * d, 2, 40, 24 if arch == wls.ARCH_CROSS else 0, N, 0.5, cf, levels, 2,
+def test_linearising_pair_equals_plain_pair(arch, dtype, levels, cf, N, relax, lanes, mg, grads, d, f):
+    wl = wls.Workload("t", arch, d, d // 64, f, 2, 40, 24 if arch == wls.ARCH_CROSS else 0, N, 0.5, cf, levels, 2,
                       dtype, 91, relax=relax)
-    print(f"[case] linearising arch={arch} dtype={dtype} d={d} L={levels} cf={cf} N={N} relax={relax} lanes={lanes} "
+    print(f"[case] linearising arch={arch} dtype={dtype} d={d} f={f} L={levels} cf={cf} N={N} relax={relax} lanes={lanes} "
           f"mg={mg} grads={grads}", flush=True)
     dm = DeviceModel(wl, weight_std=0.05, keep_host=False)
     opts = mb.mgrit_opts(N, wl.h, cf, levels, 2, relax)
@@ -80,15 +80,15 @@ def test_linearising_pair_equals_plain_pair(arch, dtype, levels, cf, N, relax, l
         mb.mgrit_set_max_groups_per_launch(0)
 
 
-@pytest.mark.parametrize("d", [128, 192])                 # bf16: the row-local chains and launch by launch
+@pytest.mark.parametrize("d,f", [(128, 256), (128, 128), (192, 384)])   # bf16: chains (decoders the second alone), launch by launch
 @pytest.mark.parametrize("buffered", [False, True])
 @pytest.mark.parametrize("dtype,Sm,grads", [(wls.DTYPE_BF16, 24, True), (wls.DTYPE_BF16, 200, False),
                                             (wls.DTYPE_F32, 33, True)])
-def test_linearising_decoder_in_the_least_workspace(dtype, Sm, grads, buffered, d):
+def test_linearising_decoder_in_the_least_workspace(dtype, Sm, grads, buffered, d, f):
     """The keys and values of the memory go to the adjoint's cache whatever the size of the forward workspace."""
     N = 8
-    wl = wls.Workload("t", wls.ARCH_CROSS, d, d // 64, 2 * d, 2, 40, Sm, N, 0.5, 4, 2, 2, dtype, 95)
-    print(f"[case] linearising decoder, least workspace dtype={dtype} d={d} Sm={Sm} grads={grads} buffered={buffered}", flush=True)
+    wl = wls.Workload("t", wls.ARCH_CROSS, d, d // 64, f, 2, 40, Sm, N, 0.5, 4, 2, 2, dtype, 95)
+    print(f"[case] linearising decoder, least workspace dtype={dtype} d={d} f={f} Sm={Sm} grads={grads} buffered={buffered}", flush=True)
     dm = DeviceModel(wl, weight_std=0.05, keep_host=False)
     opts, buf = mb.mgrit_opts(N, wl.h, 4, 2, 2), mb.BufferOpts(0, 0, 0.0)
     mem, Z0 = dev(wls.cross_memory(wl)), dev(wls.initial_state(wl))
@@ -147,7 +147,7 @@ def test_linearising_entry_points_check_their_arguments():
     torch.cuda.synchronize()
 
 
-@pytest.mark.parametrize("d", [128, 192])                 # bf16: the row-local chains and launch by launch
+@pytest.mark.parametrize("d,f", [(128, 256), (128, 128), (192, 384)])   # bf16: chains (decoders the second alone), launch by launch
 @pytest.mark.parametrize("n_enc,n_dec,cf,levels,relax,dtype,lanes,mg,grads", [
     (8, 8, 4, 2, 1, wls.DTYPE_BF16, 2, 0, False),
     (6, 10, 4, 2, 1, wls.DTYPE_BF16, 2, 0, True),           # the decoder starts inside a coarse interval
@@ -155,14 +155,14 @@ def test_linearising_entry_points_check_their_arguments():
     (10, 6, 2, 2, 1, wls.DTYPE_F32, 1, 3, False),
     (5, 4, 4, 1, 1, wls.DTYPE_BF16, 2, 0, True)])           # serial run: the forward solve leaves every layer
 def test_linearising_pair_equals_plain_pair_on_the_stacked_grid(n_enc, n_dec, cf, levels, relax, dtype, lanes, mg,
-                                                                grads, d):
-    enc = wls.Workload("enc", wls.ARCH_ENCODER, d, d // 64, 2 * d, 2, 24, 0, n_enc, 0.5, cf, levels, 2, dtype, 93,
+                                                                grads, d, f):
+    enc = wls.Workload("enc", wls.ARCH_ENCODER, d, d // 64, f, 2, 24, 0, n_enc, 0.5, cf, levels, 2, dtype, 93,
                        relax=relax)
-    dec = wls.Workload("dec", wls.ARCH_CROSS, d, d // 64, 2 * d, 2, 20, 24, n_dec, 0.5, cf, levels, 2, dtype, 94,
+    dec = wls.Workload("dec", wls.ARCH_CROSS, d, d // 64, f, 2, 20, 24, n_dec, 0.5, cf, levels, 2, dtype, 94,
                        relax=relax)
     sw = wls.StackedWorkload("stacked", enc, dec)
     print(f"[case] linearising, stacked grid n_enc={n_enc} n_dec={n_dec} cf={cf} L={levels} relax={relax} "
-          f"dtype={dtype} d={d} lanes={lanes} mg={mg} grads={grads}", flush=True)
+          f"dtype={dtype} d={d} f={f} lanes={lanes} mg={mg} grads={grads}", flush=True)
     desc_d = mb.model_desc(dec)
     desc_e = mb.encoder_desc(desc_d)
     blocks = [mb.pack_theta(desc_e if n < sw.n_enc else desc_d, wls.stacked_layer_params(sw, n, 0.05))
@@ -199,13 +199,13 @@ def test_linearising_pair_equals_plain_pair_on_the_stacked_grid(n_enc, n_dec, cf
         mb.mgrit_set_max_groups_per_launch(0)
 
 
-@pytest.mark.parametrize("d", [128, 192])                 # bf16: the row-local chains and launch by launch
+@pytest.mark.parametrize("d,f", [(128, 256), (128, 128), (192, 384)])   # bf16: chains (decoders the second alone), launch by launch
 @pytest.mark.parametrize("arch,n_open,n_close,grads", [(wls.ARCH_CAUSAL, 2, 2, True), (wls.ARCH_ENCODER, 0, 3, False),
                                                        (wls.ARCH_CROSS, 1, 0, False)])
-def test_linearising_pair_equals_plain_pair_with_buffer_layers(arch, n_open, n_close, grads, d):
-    wl = wls.Workload("t", arch, d, d // 64, 2 * d, 2, 40, 24 if arch == wls.ARCH_CROSS else 0, 8, 0.25, 4, 2, 2,
+def test_linearising_pair_equals_plain_pair_with_buffer_layers(arch, n_open, n_close, grads, d, f):
+    wl = wls.Workload("t", arch, d, d // 64, f, 2, 40, 24 if arch == wls.ARCH_CROSS else 0, 8, 0.25, 4, 2, 2,
                       wls.DTYPE_BF16, 95)
-    print(f"[case] linearising, buffer layers arch={arch} d={d} open={n_open} close={n_close} grads={grads}", flush=True)
+    print(f"[case] linearising, buffer layers arch={arch} d={d} f={f} open={n_open} close={n_close} grads={grads}", flush=True)
     n = n_open + 8 + n_close
     dm = DeviceModel(wl, n_layers=n, weight_std=0.05, keep_host=False)
     opts = mb.mgrit_opts(8, wl.h, 4, 2, 2)

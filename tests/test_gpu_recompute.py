@@ -36,15 +36,15 @@ def both_modes(run):
         assert torch.isfinite(x.float() if x.dtype != torch.uint8 else x.view(torch.float32)).all()
 
 
-@pytest.mark.parametrize("d", [128, 192])                 # bf16: the row-local chains and launch by launch
+@pytest.mark.parametrize("d,f", [(128, 256), (128, 128), (192, 384)])   # bf16: chains (decoders the second alone), launch by launch
 @pytest.mark.parametrize("arch,dtype,levels,cf,N,lanes,mg", [
     (wls.ARCH_ENCODER, wls.DTYPE_BF16, 2, 4, 16, 2, 0), (wls.ARCH_CAUSAL, wls.DTYPE_BF16, 3, 2, 16, 2, 3),
     (wls.ARCH_CROSS, wls.DTYPE_BF16, 2, 4, 16, 2, 0), (wls.ARCH_CAUSAL, wls.DTYPE_F32, 2, 4, 8, 1, 0),
     (wls.ARCH_ENCODER, wls.DTYPE_BF16, 1, 4, 5, 2, 0)])
-def test_recompute_equals_cached(arch, dtype, levels, cf, N, lanes, mg, d):
-    wl = wls.Workload("t", arch, d, d // 64, 2 * d, 2, 40, 24 if arch == wls.ARCH_CROSS else 0, N, 0.5, cf, levels, 2,
+def test_recompute_equals_cached(arch, dtype, levels, cf, N, lanes, mg, d, f):
+    wl = wls.Workload("t", arch, d, d // 64, f, 2, 40, 24 if arch == wls.ARCH_CROSS else 0, N, 0.5, cf, levels, 2,
                       dtype, 83)
-    print(f"[case] recompute arch={arch} dtype={dtype} d={d} L={levels} cf={cf} N={N} lanes={lanes} mg={mg}", flush=True)
+    print(f"[case] recompute arch={arch} dtype={dtype} d={d} f={f} L={levels} cf={cf} N={N} lanes={lanes} mg={mg}", flush=True)
     dm = DeviceModel(wl, weight_std=0.05, keep_host=False)
     opts = mb.mgrit_opts(N, wl.h, cf, levels, 2)
     mem = wls.cross_memory(wl)
@@ -74,12 +74,12 @@ def test_recompute_equals_cached(arch, dtype, levels, cf, N, lanes, mg, d):
         mb.mgrit_set_max_groups_per_launch(0)
 
 
-@pytest.mark.parametrize("d", [128, 192])                 # bf16: the row-local chains and launch by launch
-def test_recompute_equals_cached_on_the_stacked_grid(d):
-    enc = wls.Workload("enc", wls.ARCH_ENCODER, d, d // 64, 2 * d, 2, 24, 0, 6, 0.5, 4, 2, 2, wls.DTYPE_BF16, 84)
-    dec = wls.Workload("dec", wls.ARCH_CROSS, d, d // 64, 2 * d, 2, 20, 24, 10, 0.5, 4, 2, 2, wls.DTYPE_BF16, 85)
+@pytest.mark.parametrize("d,f", [(128, 256), (128, 128), (192, 384)])   # bf16: chains (decoders the second alone), launch by launch
+def test_recompute_equals_cached_on_the_stacked_grid(d, f):
+    enc = wls.Workload("enc", wls.ARCH_ENCODER, d, d // 64, f, 2, 24, 0, 6, 0.5, 4, 2, 2, wls.DTYPE_BF16, 84)
+    dec = wls.Workload("dec", wls.ARCH_CROSS, d, d // 64, f, 2, 20, 24, 10, 0.5, 4, 2, 2, wls.DTYPE_BF16, 85)
     sw = wls.StackedWorkload("stacked", enc, dec)
-    print(f"[case] recompute, stacked grid d={d} N={sw.N} n_enc={sw.n_enc}", flush=True)
+    print(f"[case] recompute, stacked grid d={d} f={f} N={sw.N} n_enc={sw.n_enc}", flush=True)
     desc_d = mb.model_desc(dec)
     desc_e = mb.encoder_desc(desc_d)
     blocks = [mb.pack_theta(desc_e if n < sw.n_enc else desc_d, wls.stacked_layer_params(sw, n, 0.05))
@@ -96,10 +96,10 @@ def test_recompute_equals_cached_on_the_stacked_grid(d):
     both_modes(run)
 
 
-@pytest.mark.parametrize("d", [128, 192])                 # bf16: the row-local chains and launch by launch
-def test_recompute_equals_cached_with_buffer_layers(d):
-    wl = wls.Workload("t", wls.ARCH_CAUSAL, d, d // 64, 2 * d, 2, 40, 0, 8, 0.25, 4, 2, 2, wls.DTYPE_BF16, 86)
-    print(f"[case] recompute, buffer layers d={d}", flush=True)
+@pytest.mark.parametrize("d,f", [(128, 256), (128, 128), (192, 384)])   # bf16: chains (decoders the second alone), launch by launch
+def test_recompute_equals_cached_with_buffer_layers(d, f):
+    wl = wls.Workload("t", wls.ARCH_CAUSAL, d, d // 64, f, 2, 40, 0, 8, 0.25, 4, 2, 2, wls.DTYPE_BF16, 86)
+    print(f"[case] recompute, buffer layers d={d} f={f}", flush=True)
     dm = DeviceModel(wl, n_layers=12, weight_std=0.05, keep_host=False)
     opts = mb.mgrit_opts(8, wl.h, 4, 2, 2)
     buf = mb.BufferOpts(2, 2, 1.0)

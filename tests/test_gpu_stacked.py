@@ -186,11 +186,11 @@ def test_full_size_mt_stacked_sampled_sentence_pairs():
     check_norms("adjoint", ag.cpu().numpy(), gold["adjoint"], tol, gold["adjoint_increment_norm"], einc["lambda"])
 
 
-@pytest.mark.parametrize("width", [128, 192])             # bf16: the row-local chains and launch by launch
-def test_overlapped_coarse_solve_is_bit_identical_on_the_stacked_grid(width):
+@pytest.mark.parametrize("width,f", [(128, 256), (128, 128), (192, 384)])   # chains (decoders the second alone), launch by launch
+def test_overlapped_coarse_solve_is_bit_identical_on_the_stacked_grid(width, f):
     """Coarse steps of both kinds (encoder, then decoder) hand finished intervals to the helper lane:
     same states, adjoint states and norms as the sequential order, bit for bit."""
-    sw = stacked(dtype=wls.DTYPE_BF16, d=width, H=width // 64, f=2 * width, n_enc=12, n_dec=20, cf=4, levels=2, h=0.5)
+    sw = stacked(dtype=wls.DTYPE_BF16, d=width, H=width // 64, f=f, n_enc=12, n_dec=20, cf=4, levels=2, h=0.5)
     d = sw.dec
     desc_d = mb.model_desc(d)
     desc_e = mb.encoder_desc(desc_d)
@@ -212,11 +212,11 @@ def test_overlapped_coarse_solve_is_bit_identical_on_the_stacked_grid(width):
         assert torch.equal(x, y)
 
 
-@pytest.mark.parametrize("width", [128, 192])             # bf16: the row-local chains and launch by launch
-def test_overlapped_coarse_solve_with_many_hand_overs_on_the_stacked_grid(width):
+@pytest.mark.parametrize("width,f", [(128, 256), (128, 128), (192, 384)])   # chains (decoders the second alone), launch by launch
+def test_overlapped_coarse_solve_with_many_hand_overs_on_the_stacked_grid(width, f):
     """36 intervals handed over one at a time (the pool of 16 hand-over events wraps around; the
     right-hand sides are formed in one sweep): bit-identical to the sequential order."""
-    sw = stacked(dtype=wls.DTYPE_BF16, d=width, H=width // 64, f=2 * width, B=1, Sx=24, Sy=20, n_enc=60, n_dec=84, cf=4, levels=2, h=0.1)
+    sw = stacked(dtype=wls.DTYPE_BF16, d=width, H=width // 64, f=f, B=1, Sx=24, Sy=20, n_enc=60, n_dec=84, cf=4, levels=2, h=0.1)
     d = sw.dec
     print(f"[case] stacked, many hand-overs: N={sw.N} n_enc={sw.n_enc}", flush=True)
     desc_d = mb.model_desc(d)
