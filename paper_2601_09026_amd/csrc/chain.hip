@@ -983,11 +983,10 @@ hipError_t launch_chain_adjoint_head(const ChainAdjointArgs& a, int d, bool is_b
 // The lines lie where a training step of single layers (serial propagation, every launch one layer) is no slower on chains:
 // within 1 % there, and a single transposed step alone up to 4 % slower, while launches of two layers gain up to 20 % and of
 // four 10 to 45 %.  Cross attention adds as many launches on either path, so that decoders 128 wide gain less and need more
-// tokens: 256 hidden, training steps of 16 layers on 2 levels, 64
-// tokens 3.20 -> 3.55 ms, 256 tokens 3.33 -> 3.51, 1024 tokens 3.83 -> 3.76;  384: 2048 tokens,
-// step 56 / 109 -> 55 / 114 us, serial training step 2.30 -> 2.35 ms, 3072 tokens 57 / 115 -> 56 / 118, 2.41 both;  512: 4096
-// tokens 60 / 119 -> 60 / 127, 2.55 -> 2.62, 6144 tokens 66 / 130 -> 65 / 131, 2.78 -> 2.75.  The rule follows from the model
-// alone: how many layers share a launch cannot show in a result.
+// tokens: 256 hidden, training steps of 16 layers on 2 levels, 64 tokens 3.20 -> 3.55 ms, 256 tokens 3.33 -> 3.51, 1024 tokens
+// 3.83 -> 3.76;  384: 2048 tokens, step 56 / 109 -> 55 / 114 us, serial training step 2.30 -> 2.35 ms, 3072 tokens 57 / 115 ->
+// 56 / 118, 2.41 both;  512: 4096 tokens 60 / 119 -> 60 / 127, 2.55 -> 2.62, 6144 tokens 66 / 130 -> 65 / 131, 2.78 -> 2.75.
+// The rule follows from the model alone: how many layers share a launch cannot show in a result.
 bool chain_ok(int d, int f, int T, bool cross, bool is_bf16) {
   if (!is_bf16) return chain_f32_ok(d, f);
   if ((d != 64 && d != 128) || f % 64 != 0 || f > 2048 || 2.0 * T * (f > 3 * d ? f : 3 * d) >= 2e9) return false;
